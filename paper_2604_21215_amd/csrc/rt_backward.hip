@@ -781,16 +781,45 @@ __global__ __launch_bounds__(256) void bw_dx_kernel(const float *__restrict__ dn
     }
 }
 
-// out[col] (+)= sum_r A[r lda + col] Bm[r ldb + col]  (gain gradients: column sums of gradient times normalised value).
-// grid ceil(ncol / 64), block 256 (four row phases per column, joined in LDS in a fixed order).
+// Column sums of a product, sum_r A[r lda + col] Bm[r ldb + col] (gain gradients: gradient times normalised value), in two
+// launches: slices of the rows side by side, then the slices of a column in a fixed order.  Bound: the two tensors read once.
+// With one workgroup per 64 columns walking all rows (16 workgroups at d = 1024) the chip was idle: M = 16384 took 1790 us
+// per gain (75 GB/s); 64 slices of 256 rows take 27 us + 4 us to join them (4.9 TB/s).
+// part[slice][col]; grid (ceil(ncol / 64), slices), block 256 (four row phases per column, eight rows of each in flight).
+constexpr int kColsumSlices = 64;
 __global__ __launch_bounds__(256) void bw_colsum_kernel(const float *__restrict__ A, size_t lda, const float *__restrict__ Bm,
-                                                        size_t ldb, int M, int ncol, float *__restrict__ out, int accumulate)
+                                                        size_t ldb, int M, int ncol, int rows_per_slice, float *__restrict__ slices)
+{
+    __shared__ float part[4][64];
+    const int cx = threadIdx.x & 63, ry = threadIdx.x >> 6, col = blockIdx.x * 64 + cx;
+    const int r0 = blockIdx.y * rows_per_slice, r1 = min(M, r0 + rows_per_slice);
+    float s = 0.f;
+    if (col < ncol) {
+        int r = r0 + ry;
+        for (; r + 28 < r1; r += 32) {
+            float a[8], b[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) { a[e] = A[(size_t)(r + 4 * e) * lda + col]; b[e] = Bm[(size_t)(r + 4 * e) * ldb + col]; }
+#pragma unroll
+            for (int e = 0; e < 8; ++e) s = fmaf(a[e], b[e], s);
+        }
+        for (; r < r1; r += 4) s = fmaf(A[(size_t)r * lda + col], Bm[(size_t)r * ldb + col], s);
+    }
+    part[ry][cx] = s;
+    __syncthreads();
+    if (ry == 0 && col < ncol) slices[(size_t)blockIdx.y * ncol + col] = (part[0][cx] + part[1][cx]) + (part[2][cx] + part[3][cx]);
+}
+// out[col] (+)= the slices' sums; grid ceil(ncol / 64), block 256 (four phases of slices per column)
+__global__ __launch_bounds__(256) void bw_colsum_join_kernel(const float *__restrict__ slices, int n_slices, int ncol,
+                                                             float *__restrict__ out, int accumulate)
 {
     __shared__ float part[4][64];
     const int cx = threadIdx.x & 63, ry = threadIdx.x >> 6, col = blockIdx.x * 64 + cx;
     float s = 0.f;
-    if (col < ncol)
-        for (int r = ry; r < M; r += 4) s = fmaf(A[(size_t)r * lda + col], Bm[(size_t)r * ldb + col], s);
+    if (col < ncol) {
+#pragma unroll 16
+        for (int j = ry; j < n_slices; j += 4) s += slices[(size_t)j * ncol + col];
+    }
     part[ry][cx] = s;
     __syncthreads();
     if (ry == 0 && col < ncol) {
@@ -827,6 +856,7 @@ struct BwBufs {
     bf16_t *WqkvT_b;         // [d][3d]
     bf16_t *tA, *tB;         // transposed operands of the parameter sums, [rows][Mp]
     float *part;             // contraction slices of a parameter sum
+    float *csum;             // [kColsumSlices][d] row slices of a gain gradient
     // single-launch reverse loop: the loop-independent halves of its products (rt_backward_persistent.hip) and its
     // exchange words
     bf16_t *gy_pf;           // [M][d] gy with position-first rows
@@ -871,6 +901,7 @@ size_t carve_bufs(BwBufs &Bf, char *base, size_t B, size_t N, size_t d, size_t F
     Bf.G3_b = cv.take<bf16_t>(M * 3 * d); Bf.WqkvT_b = cv.take<bf16_t>(3 * d * d);
     Bf.tA = cv.take<bf16_t>(wide * Mp); Bf.tB = cv.take<bf16_t>((F > d ? F : d) * Mp);
     Bf.part = cv.take<float>(16 * d * d > 4 * F * d ? 16 * d * d : 4 * F * d);
+    Bf.csum = cv.take<float>((size_t)kColsumSlices * d);
     if (E == 2) {
         Bf.gy_pf = cv.take<bf16_t>(M * d);
         Bf.A_gy = cv.take<float>(M * F); Bf.A_uz = cv.take<float>(M * F);
@@ -1116,7 +1147,10 @@ hipError_t backward_layer(const LayerDims &D, const Weights &W, const void *x_, 
     }
     // gain gradients that need the normalised values (before anything is overwritten)
     auto colsum = [&](const float *A, size_t lda, const float *Bm, size_t ldb, float *out, bool acc) {
-        hipLaunchKernelGGL(bw_colsum_kernel, dim3((unsigned)((d + 63) / 64)), blk, 0, st, A, lda, Bm, ldb, M, d, out, acc ? 1 : 0);
+        // slices of 32 rows (one unrolled trip of every row phase) and more
+        const int per = ((M + kColsumSlices - 1) / kColsumSlices + 31) / 32 * 32, n = (M + per - 1) / per;
+        hipLaunchKernelGGL(bw_colsum_kernel, dim3((unsigned)((d + 63) / 64), (unsigned)n), blk, 0, st, A, lda, Bm, ldb, M, d, per, Bf.csum);
+        hipLaunchKernelGGL(bw_colsum_join_kernel, dim3((unsigned)((d + 63) / 64)), blk, 0, st, Bf.csum, n, d, out, acc ? 1 : 0);
     };
     const size_t ld3 = 3 * (size_t)d;
     hipLaunchKernelGGL(bw_head_norm_bw_kernel<T>, dim3(M, H), dim3(64), 0, st, Bf.dq, Bf.qkv, 3 * d, 0, Bf.rq, g_q, Bf.G3, 3 * d, 0, H, nf);
