@@ -2,7 +2,7 @@
 // that produces the first layer's input, and the final RMS normalisation followed by the untied
 // output projection ("LM head").  Neither is part of the layer recurrence (Sec. 6.1 leaves embedding
 // and unembedding out of its cost model); both are bandwidth-bound single passes.
-#include "rt_common.h"
+#include "rt_mfma_device.h"
 
 namespace rt {
 
@@ -85,6 +85,96 @@ __global__ __launch_bounds__(256) void lm_head_kernel(const T *__restrict__ W, c
     }
 }
 
+// The same on the matrix cores (bf16 storage): D[16 vocabulary rows][16 batch columns] += W[16][32] z^T[32][16].  The
+// normalised rows are not rounded: each element is staged as three bf16 parts whose sum holds all 24 bits of the fp32 value,
+// and every weight fragment feeds three instructions (the chip has ten times the matrix rate that this needs at the memory
+// rate).  Bound: the matrix, read once per 16 batch rows.  The plain-ALU form above reads 32 KB of LDS and issues 8192 adds
+// per weight row at 8 batch rows: 153 us for 67 MB (d = 1024, 32768 rows, 8 batch rows) = 0.44 TB/s; here 22 us = 3.0 TB/s.
+// A wavefront takes 16 vocabulary rows at a time; the contraction index of a step pair is assigned so that a lane's two
+// loads are 32 contiguous bytes (four lanes cover a row's 128), kHeadAhead pairs are in flight, the first of them requested
+// before the rows are normalised.
+// grid (<= row tiles / 8, batch tiles of bt), block 512, LDS 3 bt (d + 8) bf16.  d a multiple of 256.
+constexpr int kHeadAhead = 4;
+__global__ __launch_bounds__(512) void lm_head_mfma_kernel(const bf16_t *__restrict__ W, const bf16_t *__restrict__ g,
+                                                           const bf16_t *__restrict__ z, long long z_stride,
+                                                           float *__restrict__ logits, int B, int d, int vocab, float eps,
+                                                           int norm_free, int bt, int wide_stores)
+{
+    extern __shared__ __align__(16) unsigned char head_smem[];
+    bf16_t *zs = reinterpret_cast<bf16_t *>(head_smem);   // [3][bt][d + 8]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int col = lane & 15, gk = lane >> 4;
+    const int b0 = blockIdx.y * bt, nb = min(bt, B - b0), ld = d + 8;
+    const int tiles = (vocab + 15) / 16, tstep = gridDim.x * 8;
+    int tile = blockIdx.x * 8 + wave;
+    uint4 w[2 * kHeadAhead];
+    const bf16_t *wr = W + (size_t)min(tile * 16 + col, vocab - 1) * d + 16 * gk;
+#pragma unroll
+    for (int j = 0; j < kHeadAhead; ++j) {
+        w[2 * j] = *reinterpret_cast<const uint4 *>(wr + 64 * j);
+        w[2 * j + 1] = *reinterpret_cast<const uint4 *>(wr + 64 * j + 8);
+    }
+    for (int b = wave; b < nb; b += 8) {
+        const bf16_t *zr = z + (long long)(b0 + b) * z_stride;
+        float ss = 0.f;
+#pragma unroll 4
+        for (int k = lane; k < d; k += 64) { const float v = bf16_to_f32(zr[k]); ss = fmaf(v, v, ss); }
+        ss = wave_sum(ss);
+        const float rinv = norm_free ? 1.f : rsqrtf(ss / (float)d + eps);
+#pragma unroll 4
+        for (int k = lane; k < d; k += 64) {
+            const float v = bf16_to_f32(zr[k]) * (rinv * ((g && !norm_free) ? bf16_to_f32(g[k]) : 1.f));
+            const bf16_t p0 = f32_to_bf16(v);
+            const float r1 = (p0 & 0x7F80u) == 0x7F80u ? 0.f : v - bf16_to_f32(p0);   // an infinity has no remainder
+            const bf16_t p1 = f32_to_bf16(r1);
+            zs[(size_t)b * ld + k] = p0;
+            zs[(size_t)(bt + b) * ld + k] = p1;
+            zs[(size_t)(2 * bt + b) * ld + k] = f32_to_bf16(r1 - bf16_to_f32(p1));
+        }
+    }
+    __syncthreads();
+    const int cb = min(col, nb - 1);   // columns beyond the batch repeat its last row (their results are dropped)
+    const bf16_t *zh = zs + (size_t)cb * ld + 16 * gk, *zm = zh + (size_t)bt * ld, *zl = zm + (size_t)bt * ld;
+    for (; tile < tiles; tile += tstep) {   // no barrier below
+        const bf16_t *wn = W + (size_t)min((tile + tstep) * 16 + col, vocab - 1) * d + 16 * gk;   // the next tile's rows
+        f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int k0 = 0; k0 < d; k0 += 64 * kHeadAhead) {
+            const bool last = k0 + 64 * kHeadAhead >= d;
+            const bf16_t *src = last ? wn : wr + k0 + 64 * kHeadAhead;
+#pragma unroll
+            for (int j = 0; j < kHeadAhead; ++j) {
+                Frag a0, a1, x;
+                a0.u = w[2 * j];
+                a1.u = w[2 * j + 1];
+                if (!last || tile + tstep < tiles) {
+                    w[2 * j] = *reinterpret_cast<const uint4 *>(src + 64 * j);
+                    w[2 * j + 1] = *reinterpret_cast<const uint4 *>(src + 64 * j + 8);
+                }
+                const int k = k0 + 64 * j;
+                x.u = *reinterpret_cast<const uint4 *>(zl + k); acc = mfma16(a0, x, acc);
+                x.u = *reinterpret_cast<const uint4 *>(zl + k + 8); acc = mfma16(a1, x, acc);
+                x.u = *reinterpret_cast<const uint4 *>(zm + k); acc = mfma16(a0, x, acc);
+                x.u = *reinterpret_cast<const uint4 *>(zm + k + 8); acc = mfma16(a1, x, acc);
+                x.u = *reinterpret_cast<const uint4 *>(zh + k); acc = mfma16(a0, x, acc);
+                x.u = *reinterpret_cast<const uint4 *>(zh + k + 8); acc = mfma16(a1, x, acc);
+            }
+        }
+        wr = wn;
+        if (col < nb) {   // lane: four consecutive vocabulary rows of batch row b0 + col
+            const int v0 = tile * 16 + 4 * gk;
+            float *out = logits + (size_t)(b0 + col) * vocab + v0;
+            if (wide_stores) {
+                if (v0 < vocab) *reinterpret_cast<float4 *>(out) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+            } else {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                    if (v0 + r < vocab) out[r] = acc[r];
+            }
+        }
+    }
+}
+constexpr size_t kHeadMfmaMaxLds = 152 * 1024;
+
 template <typename T>
 hipError_t embed_rows_launch(const void *table, const int32_t *ids, void *x, int B, int N, int d, int vocab,
                              long long ids_stride, int first, hipStream_t st)
@@ -99,6 +189,22 @@ template <typename T>
 hipError_t lm_head_launch(const void *W, const void *g, const void *z, long long z_stride, float *logits, int B, int d,
                           int vocab, float eps, int norm_free, hipStream_t st)
 {
+    // bf16 rows of whole 256-index blocks: the matrix-core kernel (head of 32768 rows, d = 1024, B = 8: 22 us against 153 of the plain-ALU form, which keeps the other types and widths)
+    if (sizeof(T) == 2 && d % (64 * kHeadAhead) == 0 && (size_t)3 * (d + 8) * 2 <= kHeadMfmaMaxLds) {
+        int bt = (int)(kHeadMfmaMaxLds / ((size_t)3 * (d + 8) * 2));
+        bt = bt > 16 ? 16 : bt;
+        bt = bt > B ? B : bt;
+        const size_t lds = (size_t)3 * bt * (d + 8) * 2;
+        hipError_t e = hipFuncSetAttribute((const void *)lm_head_mfma_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kHeadMfmaMaxLds);
+        if (e != hipSuccess) return e;
+        const int tiles = (vocab + 15) / 16, want = (tiles + 7) / 8;
+        const int fit = (int)((size_t)160 * 1024 / lds), resident = 256 * (fit > 3 ? 3 : fit);   // workgroups on the chip at once
+        const int wide = vocab % 4 == 0 && ((uintptr_t)logits & 15) == 0;
+        hipLaunchKernelGGL(lm_head_mfma_kernel, dim3(want < resident ? want : resident, (B + bt - 1) / bt), dim3(512), lds, st,
+                           (const bf16_t *)W, (const bf16_t *)g, (const bf16_t *)z, z_stride, logits, B, d, vocab, eps, norm_free, bt,
+                           wide);
+        return hipGetLastError();
+    }
     int bt = kHeadLdsFloats / d;
     if (bt > 8) bt = 8;
     int blocks = (vocab + 3) / 4;

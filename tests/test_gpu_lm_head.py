@@ -1,0 +1,40 @@
+"""rt_lm_head on the matrix cores at the edges of its tiles: vocabulary rows in tiles of 16 (remainders, rows that allow no
+16-byte stores), batch tiles of up to 16 (fewer, full, one more; fewer rows where wide rows fill the LDS), row widths of one,
+several and many blocks of 256, strided rows."""
+import numpy as np
+import pytest
+
+from paper_2604_21215_amd import inputs as gen
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("d,vocab,B,norm_free", [(256, 1, 1, False), (256, 15, 16, False), (512, 4097, 17, False), (1024, 2064, 8, False),
+                                                 (768, 33000, 5, False), (2048, 130, 33, False), (12288, 50, 3, False), (1024, 62, 9, True)])
+def test_lm_head_tiles(oracle, d, vocab, B, norm_free):
+    from paper_2604_21215_amd import binding, torch_io as tio
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    rng = np.random.default_rng(d + vocab)
+    W = gen.round_to_bf16((rng.standard_normal((vocab, d)) * 0.05).astype(np.float32))
+    g = gen.round_to_bf16(rng.uniform(0.5, 1.5, d).astype(np.float32))
+    z = gen.round_to_bf16(rng.standard_normal((B, 3, d)).astype(np.float32))
+    ctx = binding.RTContext(d, d // 64, 4 * d, B, 8, "bf16", rms_eps=1e-6, flags=binding.RT_FLAG_NORM_FREE if norm_free else 0,
+                            stream=torch.cuda.current_stream().cuda_stream)
+    try:
+        zd = tio.to_device(z, "bf16")
+        out = torch.full((B + 1, vocab), float("nan"), dtype=torch.float32, device="cuda:0")   # one guard row behind
+        ctx.rt_lm_head(tio.to_device(W, "bf16"), tio.to_device(g, "bf16"), zd[:, 1], zd.stride(0), B, out[:B])
+        torch.cuda.synchronize()
+        got = out.cpu().numpy().astype(np.float64)
+    finally:
+        ctx.rt_destroy()
+    W64, z64, g64 = W.astype(np.float64), z[:, 1].astype(np.float64), g.astype(np.float64)
+    ref = oracle.lm_head(W64, z64, g64, norm_free=True) if norm_free else oracle.lm_head(W64, z64, g64, eps=1e-6)
+    n = z64 if norm_free else z64 / np.sqrt((z64 ** 2).mean(-1, keepdims=True) + 1e-6) * g64
+    # fp32 operands and sums: rounding errors of 2^-24 of the partial sums, which grow like the root of the d terms; rows
+    # rounded to bf16 would be off by 2^-9 / sqrt(3 d) of the sum of magnitudes, three times this bound at d = 1024
+    bound = 8 * np.sqrt(d) * 2.0 ** -24 * (np.abs(n) @ np.abs(W64).T)
+    assert np.all(np.abs(got[:B] - ref) <= bound)
+    assert np.all(np.isnan(got[B]))
