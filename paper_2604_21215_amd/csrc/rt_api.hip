@@ -705,7 +705,7 @@ static rt_status decode_impl(rt_ctx *c, const LayerDims &D, const rt_layer_weigh
     const int nsplit = (t + chunk - 1) / chunk;
     if (nsplit > 0) RT_TRY(Launch<T>::decode_split(D, c->S, K, V, t, chunk, nsplit, st), "decode_split");
     if (!mm) return enqueue_position<T>(c, D, W, x_t, (size_t)D.d, y_t, (size_t)D.d, K, V, t, 0, nsplit, false);
-    RT_TRY(Launch<T>::merge(D, c->S, K, V, t, 0, nsplit, st, true), "merge");
+    RT_TRY(Launch<T>::merge(D, c->S, K, V, t, 0, nsplit, st, step_uses_wide(D) ? 2 : 1), "merge");
     const size_t row = (size_t)t * D.B * D.d * sizeof(T);
     RT_TRY(step_base_case_mm(D, W, c->S, x_t, y_t, (char *)K + row, (char *)V + row, st), "step_base_case_mm");
     return RT_OK;

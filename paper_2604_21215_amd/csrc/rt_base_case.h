@@ -15,7 +15,7 @@ namespace rt {
 //   far_rel >= 0 (chunked schedule of the layer-wavefront engine): `levels` covers the blocks inside the
 //   position's chunk of 2^log2_chunk positions only; all keys before the chunk were folded into one more
 //   partial state, stored at slot t of relative level far_rel.
-//   op_a: if not null, a is also written as a bf16 head row and a bf16 remainder row (rows 2b, 2b + 1 of [2B][d]).
+//   op_a: if not null, a is also written as operand rows (operand_offsets; op_fragments: in fragment order).
 //   alibi > 0: linear positional bias; the temporary pair is at distance 0 and every stored partial state was
 //   written with its maximum already expressed relative to this query's position, so only the window needs it.
 //   HP: the query and the temporary key come unrounded from Qf / Ktf and the window keys are head K plus
@@ -31,7 +31,7 @@ __device__ __forceinline__ float merge_body(const T *__restrict__ Q, const float
                                            const float *__restrict__ po, float *__restrict__ attn_cat, int BH, int H,
                                            int bh, int t, int q_row, int p_min, int log2_pmin, int levels, int slots,
                                            int n_splits, float scale, int far_rel = -1, int log2_chunk = 0,
-                                           bf16_t *__restrict__ op_a = nullptr, float alibi = 0.f)
+                                           bf16_t *__restrict__ op_a = nullptr, float alibi = 0.f, bool op_fragments = false)
 {
     const int lane = threadIdx.x & 63;
     const size_t rs = (size_t)BH * kHeadDim;
@@ -108,11 +108,11 @@ __device__ __forceinline__ float merge_body(const T *__restrict__ Q, const float
     const int b = bh / H, h = bh % H;
     const float a = o / l;
     if (attn_cat) attn_cat[(size_t)b * H * kHeadDim + h * kHeadDim + lane] = a;
-    if (op_a) {   // the same value as bf16 head + remainder rows (2b, 2b + 1) for the matrix-core products
-        const size_t d = (size_t)H * kHeadDim;
+    if (op_a) {   // the same value as bf16 head + remainder for the matrix-core products
         const bf16_t hi = f32_to_bf16(a);
-        op_a[(size_t)(2 * b) * d + h * kHeadDim + lane] = hi;
-        op_a[(size_t)(2 * b + 1) * d + h * kHeadDim + lane] = f32_to_bf16(a - bf16_to_f32(hi));
+        const ulonglong2 oo = operand_offsets(op_fragments, BH / H, H * kHeadDim, b, h * kHeadDim + lane);
+        op_a[oo.x] = hi;
+        op_a[oo.y] = f32_to_bf16(a - bf16_to_f32(hi));
     }
     return a;
 }

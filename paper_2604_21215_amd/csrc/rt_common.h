@@ -49,6 +49,18 @@ __device__ __forceinline__ void load8(const bf16_t *p, float *o)
     o[6] = __uint_as_float(a.w << 16); o[7] = __uint_as_float(a.w & 0xFFFF0000u);
 }
 
+// Operand rows of the matrix-core products of one position: element k of batch row b as a bf16 head (offset .x) and its bf16
+// remainder (.y), 2 B K elements in all.  Plain: rows 2b and 2b + 1 of [2B][K].  Fragment order: tiles of 16 batch rows
+// (the last one of as many as there are), per 32 indices the 16-byte pieces in the order in which the lanes of a matrix
+// instruction take them, heads before remainders: a wavefront's load is one contiguous run.
+__device__ __forceinline__ ulonglong2 operand_offsets(bool fragment_order, int B, int K, int b, int k)
+{
+    if (!fragment_order) return make_ulonglong2((size_t)(2 * b) * K + k, (size_t)(2 * b + 1) * K + k);
+    const int tile = b >> 4, nbt = min(16, B - 16 * tile);
+    const size_t hi = (size_t)tile * 32 * K + (size_t)(k >> 5) * (64 * nbt) + ((((k >> 3) & 3) * nbt + (b & 15)) * 8 + (k & 7));
+    return make_ulonglong2(hi, hi + 32 * nbt);
+}
+
 // ---------------------------------------------------------------- wavefront (64 lanes) reductions
 __device__ __forceinline__ float wave_sum(float v)
 {
@@ -216,9 +228,9 @@ template <typename T> struct Launch {
     // one position's q, k_tmp, v_tmp (decoding step): rows b of Q, Kt, Vt
     static hipError_t prepass_one(const LayerDims &D, const Weights &W, const Scratch &S, const void *x_t, size_t x_stride,
                                   hipStream_t st, bool matrix_cores = false);
-    // split_out: a is also written as operand rows (bf16 head + remainder) into S.op_a
+    // split_out: a is also written as operand rows (1: plain, 2: fragment order) into S.op_a
     static hipError_t merge(const LayerDims &D, const Scratch &S, const void *K, const void *V, int t, int q_row,
-                            int n_decode_splits, hipStream_t st, bool split_out = false);
+                            int n_decode_splits, hipStream_t st, int split_out = 0);
     static hipError_t gemv_wo(const LayerDims &D, const Weights &W, const Scratch &S, const void *x_t, size_t x_stride_b,
                               hipStream_t st);
     static hipError_t gemv_w1(const LayerDims &D, const Weights &W, const Scratch &S, hipStream_t st);
@@ -274,6 +286,8 @@ bool wavefront_uses_matrix_cores(int d, int F, bool mfma_bf16);
 // One position of one layer with the same products from the caller's row-major weights (decoding, bf16): x_t, y_t
 // rows d apart ([B][d]); K_row, V_row the cache rows to write ([B][H][64]).
 bool step_mm_supported(const LayerDims &D, bool mfma_bf16);
+bool step_uses_wide(const LayerDims &D);
+hipError_t step_qkv_wide(const LayerDims &D, const Weights &W, const Scratch &S, const void *x_t, size_t x_stride, hipStream_t st);
 hipError_t step_qkv_mm(const LayerDims &D, const Weights &W, const Scratch &S, const void *x_t, size_t x_stride, hipStream_t st);
 hipError_t step_base_case_mm(const LayerDims &D, const Weights &W, const Scratch &S, const void *x_t, void *y_t, void *K_row,
                              void *V_row, hipStream_t st);

@@ -189,7 +189,8 @@ template <typename T>
 hipError_t lm_head_launch(const void *W, const void *g, const void *z, long long z_stride, float *logits, int B, int d,
                           int vocab, float eps, int norm_free, hipStream_t st)
 {
-    // bf16 rows of whole 256-index blocks: the matrix-core kernel (head of 32768 rows, d = 1024, B = 8: 22 us against 153 of the plain-ALU form, which keeps the other types and widths)
+    // bf16 rows of whole 256-index blocks: the matrix-core kernel (32768 rows, d = 1024, B = 8: 22 us against 153 of the
+    // plain-ALU form, which keeps the other types and widths)
     if (sizeof(T) == 2 && d % (64 * kHeadAhead) == 0 && (size_t)3 * (d + 8) * 2 <= kHeadMfmaMaxLds) {
         int bt = (int)(kHeadMfmaMaxLds / ((size_t)3 * (d + 8) * 2));
         bt = bt > 16 ? 16 : bt;

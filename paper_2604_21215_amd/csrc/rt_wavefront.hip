@@ -38,7 +38,7 @@ __device__ __forceinline__ int layer_pos(int t0, int l, int chunk) { return t0 -
 template <typename T, bool HP>
 __global__ __launch_bounds__(64) void wf_merge_kernel(const WaveLayer *__restrict__ layers, int l_first, int s, int chunk,
                                                       int log2_chunk, int BH, int H, int p_min, int log2_pmin, float scale,
-                                                      float alibi)
+                                                      float alibi, bool op_fragments)
 {
     const int l = l_first + blockIdx.y, t = layer_pos(s, l, chunk);
     const WaveLayer &Y = layers[l];
@@ -52,13 +52,14 @@ __global__ __launch_bounds__(64) void wf_merge_kernel(const WaveLayer *__restric
         const size_t d = (size_t)H * kHeadDim;
         Y.S.attn_cat[(size_t)b * d + h * kHeadDim + lane] = a;
         const bf16_t hi = f32_to_bf16(a);
-        Y.S.op_a[(size_t)(2 * b) * d + h * kHeadDim + lane] = hi;
-        Y.S.op_a[(size_t)(2 * b + 1) * d + h * kHeadDim + lane] = f32_to_bf16(a - bf16_to_f32(hi));
+        const ulonglong2 oo = operand_offsets(op_fragments, BH / H, (int)d, b, h * kHeadDim + lane);
+        Y.S.op_a[oo.x] = hi;
+        Y.S.op_a[oo.y] = f32_to_bf16(a - bf16_to_f32(hi));
         return;
     }
     merge_body<T, HP>((const T *)Y.S.Q, Y.S.Qf, (const T *)Y.S.Kt, Y.S.Ktf, (const T *)Y.S.Vt, (const T *)Y.K, Y.S.Klo,
                       (const T *)Y.V, Y.S.pm, Y.S.pl, Y.S.po, Y.S.attn_cat, BH, H, blockIdx.x, t, t, p_min, log2_pmin, tree_levels,
-                      Y.S.slots, -1, scale, tree_levels, log2_chunk, HP ? Y.S.op_a : nullptr, alibi);
+                      Y.S.slots, -1, scale, tree_levels, log2_chunk, HP ? Y.S.op_a : nullptr, alibi, op_fragments);
 }
 
 template <typename T> struct StackedRows {   // rows o < n_first from Wa, the rest from Wb
@@ -132,11 +133,138 @@ __device__ __forceinline__ void split_store4(bf16_t *__restrict__ op, size_t hi_
 __device__ __forceinline__ float rms_scale_from_parts(const float *__restrict__ ssq, int col, int g, int ng, int K, float eps)
 {
     float tot = 0.f;
-    const int per = (ng + 3) / 4;
-    for (int j = g * per; j < min(ng, (g + 1) * per); ++j) tot += ssq[(size_t)col * ng + j];
+    const int n4 = ng / 16;   // 16-byte pieces per lane (K is a multiple of 256)
+    const float4 *p = reinterpret_cast<const float4 *>(ssq + (size_t)col * ng) + g * n4;
+    for (int j = 0; j < n4; j += 4) {   // four pieces in flight: all of them up to K = 1024
+        float4 q[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q[e] = p[min(j + e, n4 - 1)];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (j + e < n4) tot += (q[e].x + q[e].y) + (q[e].z + q[e].w);
+    }
     tot += __shfl_xor(tot, 16, 64);
     tot += __shfl_xor(tot, 32, 64);
     return rsqrtf(tot / (float)K + eps);
+}
+
+constexpr int EPI_QKV = 4;
+// 1 / rms of a head whose 64 values lie in the four row groups of the workgroup (hss [4][ncol]); a barrier for every wavefront
+__device__ __forceinline__ float head_scale(const float *v, bool owner, bool live, int g, int rg, int col, int ncol, float *hss, float eps)
+{
+    float ss = live ? (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]) : 0.f;
+    ss += __shfl_xor(ss, 16, 64);
+    ss += __shfl_xor(ss, 32, 64);
+    if (owner && g == 0) hss[rg * ncol + col] = ss;
+    __syncthreads();
+    return rsqrtf(((hss[col] + hss[ncol + col]) + (hss[2 * ncol + col] + hss[3 * ncol + col])) / (float)kHeadDim + eps);
+}
+
+// What follows a finished 16 x 16 tile of one of the products: lane = outputs row0 + 4 g .. + 3 (g = lane / 16) of batch row b,
+// acc their sums, rscale the RMS scale of that row's input.  owner: this wavefront holds a tile; live: and b is a batch row.
+// rg, col: the tile's place in the workgroup, row group and batch column of ncol (EPI_KV: a workgroup is the head block_x of
+// [k heads | v heads], its four row groups meet in hss [4][ncol] behind a barrier that every wavefront reaches).
+template <int EPI>
+__device__ __forceinline__ void mm_epilogue(const WaveLayer &Y, int t, const f32x4_t &acc, float rscale, bool owner, bool live, int b,
+                                            int row0, int block_x, int rg, int col, int ncol, int B, int N, int d, int F, int H,
+                                            float eps, int norm_free, float alpha, float *hss)
+{
+    const int g = ((int)threadIdx.x & 63) >> 4, o = row0 + 4 * g;
+    const bool frag = ncol != kMmBatch;   // wide_body reads its operand rows in fragment order
+    float v[4] = {acc[0] * rscale, acc[1] * rscale, acc[2] * rscale, acc[3] * rscale};
+    if (EPI == EPI_WO || EPI == EPI_W2) {
+        if (!owner) return;   // no barrier on this path
+        float gn[4] = {1.f, 1.f, 1.f, 1.f}, ss = 0.f;
+        const bf16_t *gp = (const bf16_t *)(EPI == EPI_WO ? Y.W.g_mlp : Y.W.g_kv);
+        if (gp && !norm_free) {
+            const uint2 gg = *reinterpret_cast<const uint2 *>(gp + o);
+            gn[0] = __uint_as_float(gg.x << 16); gn[1] = __uint_as_float(gg.x & 0xFFFF0000u);
+            gn[2] = __uint_as_float(gg.y << 16); gn[3] = __uint_as_float(gg.y & 0xFFFF0000u);
+        }
+        float res[4];
+        if (EPI == EPI_WO) {
+            const uint2 xr = *reinterpret_cast<const uint2 *>((const bf16_t *)Y.x + ((size_t)b * N + t) * d + o);
+            res[0] = __uint_as_float(xr.x << 16); res[1] = __uint_as_float(xr.x & 0xFFFF0000u);
+            res[2] = __uint_as_float(xr.y << 16); res[3] = __uint_as_float(xr.y & 0xFFFF0000u);
+        } else {
+            const float4 hr = *reinterpret_cast<const float4 *>(Y.S.h + (size_t)b * d + o);
+            res[0] = hr.x; res[1] = hr.y; res[2] = hr.z; res[3] = hr.w;
+        }
+        float gv[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) { v[r] = res[r] + alpha * v[r]; ss = fmaf(v[r], v[r], ss); gv[r] = v[r] * gn[r]; }
+        if (!live) ss = 0.f;
+        ss += __shfl_xor(ss, 16, 64);
+        ss += __shfl_xor(ss, 32, 64);
+        if (live) {
+            const ulonglong2 oo = operand_offsets(frag, B, d, b, o);
+            if (EPI == EPI_WO) {
+                *reinterpret_cast<float4 *>(Y.S.h + (size_t)b * d + o) = make_float4(v[0], v[1], v[2], v[3]);
+                split_store4(Y.S.op_h, oo.x, oo.y, gv);
+                if (g == 0) Y.S.ssq_h[(size_t)b * (d / 16) + row0 / 16] = ss;
+            } else {
+                *reinterpret_cast<uint2 *>((bf16_t *)Y.y + ((size_t)b * N + t) * d + o) =
+                    make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+                split_store4(Y.S.op_z, oo.x, oo.y, gv);
+                if (g == 0) Y.S.ssq_z[(size_t)b * (d / 16) + row0 / 16] = ss;
+            }
+        }
+    } else if (EPI == EPI_W1) {
+        if (live) {
+            float u[4];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) u[r] = gelu_erf(v[r]);
+            const ulonglong2 oo = operand_offsets(frag, B, F, b, o);
+            split_store4(Y.S.op_u, oo.x, oo.y, u);
+        }
+    } else if (EPI == EPI_QKV) {
+        if (!frag) {
+            if (live) *reinterpret_cast<float4 *>(Y.S.qkv_raw + (size_t)b * 3 * d + o) = make_float4(v[0], v[1], v[2], v[3]);
+            return;
+        }
+        // wide_body: the workgroup is one head of [q heads | k_tmp heads | v_tmp heads]; qkRMS and the rows of the step
+        const int which = block_x / H, h = block_x - which * H, hd = 16 * rg + 4 * g;
+        if (which < 2 && !norm_free) {
+            const float sc = head_scale(v, owner, live, g, rg, col, ncol, hss, eps);
+            const bf16_t *gn = (const bf16_t *)(which == 0 ? Y.W.g_q : Y.W.g_k);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] *= sc * (gn ? bf16_to_f32(gn[h * kHeadDim + hd + r]) : 1.f);
+        }
+        if (live)
+            *reinterpret_cast<uint2 *>((bf16_t *)(which == 0 ? Y.S.Q : (which == 1 ? Y.S.Kt : Y.S.Vt)) + ((size_t)b * H + h) * kHeadDim + hd) =
+                make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
+    } else {
+        // the workgroup is head hh of [k heads | v heads]; this wavefront holds head dimensions 16 rg + 4g .. + 3
+        const int hh = block_x;
+        const bool is_k = hh < H;
+        if (is_k && !norm_free) {
+            const float sc = head_scale(v, owner, live, g, rg, col, ncol, hss, eps);
+            const bf16_t *gk = (const bf16_t *)Y.W.g_k;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] *= sc * (gk ? bf16_to_f32(gk[hh * kHeadDim + 16 * rg + 4 * g + r]) : 1.f);
+        }
+        if (live) {
+            const int h = is_k ? hh : hh - H, bh = b * H + h, BH = B * H;
+            const size_t off = ((size_t)t * BH + bh) * kHeadDim + 16 * rg + 4 * g;
+            const uint32_t p01 = pack_bf16(v[0], v[1]), p23 = pack_bf16(v[2], v[3]);
+            if (is_k) {
+                *reinterpret_cast<uint2 *>((bf16_t *)Y.K + off) = make_uint2(p01, p23);
+                const float r0 = v[0] - __uint_as_float(p01 << 16), r1 = v[1] - __uint_as_float(p01 & 0xFFFF0000u);
+                const float r2 = v[2] - __uint_as_float(p23 << 16), r3 = v[3] - __uint_as_float(p23 & 0xFFFF0000u);
+                if (Y.S.Klo) *reinterpret_cast<uint2 *>(Y.S.Klo + off) = make_uint2(pack_bf16(r0, r1), pack_bf16(r2, r3));
+                if (Y.S.Kh) *reinterpret_cast<uint2 *>(Y.S.Kh + off) = make_uint2(pack_f16(v[0], v[1]), pack_f16(v[2], v[3]));
+            } else {
+                *reinterpret_cast<uint2 *>((bf16_t *)Y.V + off) = make_uint2(p01, p23);
+                if (Y.S.VT) {
+                    bf16_t *vt = Y.S.VT + ((size_t)bh * kHeadDim + 16 * rg + 4 * g) * Y.S.vt_stride + t;
+                    vt[0] = (bf16_t)(p01 & 0xFFFFu);
+                    vt[(size_t)Y.S.vt_stride] = (bf16_t)(p01 >> 16);
+                    vt[2 * (size_t)Y.S.vt_stride] = (bf16_t)(p23 & 0xFFFFu);
+                    vt[3 * (size_t)Y.S.vt_stride] = (bf16_t)(p23 >> 16);
+                }
+            }
+        }
+    }
 }
 
 // NW wavefronts per workgroup, KS of them share 16 rows: 16 * NW / KS rows per workgroup.  XL: the operand rows of
@@ -150,7 +278,6 @@ __device__ __forceinline__ float rms_scale_from_parts(const float *__restrict__ 
 // fragments of a step pair are then 64 bytes apart in its row: half a cache line per row and instruction).
 // EPI_QKV: the raw [q | k_tmp | v_tmp] of one position from [Wq; Wk; Wv] and the operand rows op_x (a decoding step).
 // Y: the layer; t: its position (row t of x / y / K / V / V^T); block_x: row block; batch_tile: which 16 batch rows.
-constexpr int EPI_QKV = 4;
 template <int EPI, int KS, int NW, bool XL, bool PACKED>
 __device__ __forceinline__ void mm_body(const WaveLayer &Y, int t, int block_x, int batch_tile, int B, int N, int d, int F, int H,
                                         float eps, int norm_free, float alpha, unsigned char *wf_mm_smem)
@@ -278,92 +405,8 @@ __device__ __forceinline__ void mm_body(const WaveLayer &Y, int t, int block_x, 
         }
     }
     // wavefronts with kw == 0 hold the tile: lane = outputs (rows row0 + 4g .. + 3, batch row b0 + col)
-    const bool live = col < Bn && kw == 0;
-    const int b = b0 + cb, o = row0 + 4 * g;
-    float v[4] = {acc[0] * rscale, acc[1] * rscale, acc[2] * rscale, acc[3] * rscale};
-    if (EPI == EPI_WO || EPI == EPI_W2) {
-        if (kw != 0) return;   // no barrier below on this path
-        float gn[4] = {1.f, 1.f, 1.f, 1.f}, ss = 0.f;
-        const bf16_t *gp = (const bf16_t *)(EPI == EPI_WO ? Y.W.g_mlp : Y.W.g_kv);
-        if (gp && !norm_free) {
-            const uint2 gg = *reinterpret_cast<const uint2 *>(gp + o);
-            gn[0] = __uint_as_float(gg.x << 16); gn[1] = __uint_as_float(gg.x & 0xFFFF0000u);
-            gn[2] = __uint_as_float(gg.y << 16); gn[3] = __uint_as_float(gg.y & 0xFFFF0000u);
-        }
-        float res[4];
-        if (EPI == EPI_WO) {
-            const uint2 xr = *reinterpret_cast<const uint2 *>((const bf16_t *)Y.x + ((size_t)b * N + t) * d + o);
-            res[0] = __uint_as_float(xr.x << 16); res[1] = __uint_as_float(xr.x & 0xFFFF0000u);
-            res[2] = __uint_as_float(xr.y << 16); res[3] = __uint_as_float(xr.y & 0xFFFF0000u);
-        } else {
-            const float4 hr = *reinterpret_cast<const float4 *>(Y.S.h + (size_t)b * d + o);
-            res[0] = hr.x; res[1] = hr.y; res[2] = hr.z; res[3] = hr.w;
-        }
-        float gv[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) { v[r] = res[r] + alpha * v[r]; ss = fmaf(v[r], v[r], ss); gv[r] = v[r] * gn[r]; }
-        if (!live) ss = 0.f;
-        ss += __shfl_xor(ss, 16, 64);
-        ss += __shfl_xor(ss, 32, 64);
-        if (live) {
-            if (EPI == EPI_WO) {
-                *reinterpret_cast<float4 *>(Y.S.h + (size_t)b * d + o) = make_float4(v[0], v[1], v[2], v[3]);
-                split_store4(Y.S.op_h, (size_t)(2 * b) * d + o, (size_t)(2 * b + 1) * d + o, gv);
-                if (g == 0) Y.S.ssq_h[(size_t)b * (d / 16) + row0 / 16] = ss;
-            } else {
-                *reinterpret_cast<uint2 *>((bf16_t *)Y.y + ((size_t)b * N + t) * d + o) =
-                    make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
-                split_store4(Y.S.op_z, (size_t)(2 * b) * d + o, (size_t)(2 * b + 1) * d + o, gv);
-                if (g == 0) Y.S.ssq_z[(size_t)b * (d / 16) + row0 / 16] = ss;
-            }
-        }
-    } else if (EPI == EPI_W1) {
-        if (live) {
-            float u[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) u[r] = gelu_erf(v[r]);
-            split_store4(Y.S.op_u, (size_t)(2 * b) * F + o, (size_t)(2 * b + 1) * F + o, u);
-        }
-    } else if (EPI == EPI_QKV) {
-        if (live) *reinterpret_cast<float4 *>(Y.S.qkv_raw + (size_t)b * 3 * d + o) = make_float4(v[0], v[1], v[2], v[3]);
-    } else {
-        // the workgroup is head hh of [k heads | v heads]; this wavefront holds head dimensions 16 rg + 4g .. + 3
-        const int hh = block_x;
-        const bool is_k = hh < H;
-        if (is_k && !norm_free) {
-            float ss = live ? (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]) : 0.f;
-            ss += __shfl_xor(ss, 16, 64);
-            ss += __shfl_xor(ss, 32, 64);
-            if (kw == 0 && g == 0) hss[rg * 16 + col] = ss;
-            __syncthreads();   // is_k is uniform over the workgroup
-            const float tot = (hss[col] + hss[16 + col]) + (hss[32 + col] + hss[48 + col]);
-            const float sc = rsqrtf(tot / (float)kHeadDim + eps);
-            const bf16_t *gk = (const bf16_t *)Y.W.g_k;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) v[r] *= sc * (gk ? bf16_to_f32(gk[hh * kHeadDim + 16 * rg + 4 * g + r]) : 1.f);
-        }
-        if (live) {
-            const int h = is_k ? hh : hh - H, bh = b * H + h, BH = B * H;
-            const size_t off = ((size_t)t * BH + bh) * kHeadDim + 16 * rg + 4 * g;
-            const uint32_t p01 = pack_bf16(v[0], v[1]), p23 = pack_bf16(v[2], v[3]);
-            if (is_k) {
-                *reinterpret_cast<uint2 *>((bf16_t *)Y.K + off) = make_uint2(p01, p23);
-                const float r0 = v[0] - __uint_as_float(p01 << 16), r1 = v[1] - __uint_as_float(p01 & 0xFFFF0000u);
-                const float r2 = v[2] - __uint_as_float(p23 << 16), r3 = v[3] - __uint_as_float(p23 & 0xFFFF0000u);
-                if (Y.S.Klo) *reinterpret_cast<uint2 *>(Y.S.Klo + off) = make_uint2(pack_bf16(r0, r1), pack_bf16(r2, r3));
-                if (Y.S.Kh) *reinterpret_cast<uint2 *>(Y.S.Kh + off) = make_uint2(pack_f16(v[0], v[1]), pack_f16(v[2], v[3]));
-            } else {
-                *reinterpret_cast<uint2 *>((bf16_t *)Y.V + off) = make_uint2(p01, p23);
-                if (Y.S.VT) {
-                    bf16_t *vt = Y.S.VT + ((size_t)bh * kHeadDim + 16 * rg + 4 * g) * Y.S.vt_stride + t;
-                    vt[0] = (bf16_t)(p01 & 0xFFFFu);
-                    vt[(size_t)Y.S.vt_stride] = (bf16_t)(p01 >> 16);
-                    vt[2 * (size_t)Y.S.vt_stride] = (bf16_t)(p23 & 0xFFFFu);
-                    vt[3 * (size_t)Y.S.vt_stride] = (bf16_t)(p23 >> 16);
-                }
-            }
-        }
-    }
+    mm_epilogue<EPI>(Y, t, acc, rscale, kw == 0, col < Bn && kw == 0, b0 + cb, row0, block_x, rg, col, kMmBatch, B, N, d, F, H, eps,
+                     norm_free, alpha, hss);
 }
 
 // the body over the active layers of a stack (layer-wavefront engine): grid (row blocks, layers, batch tiles of 16)
@@ -388,10 +431,141 @@ __global__ __launch_bounds__(64 * NW) void step_mm_kernel(const WaveLayer Y, int
     mm_body<EPI, KS, NW, XL, false>(Y, 0, (int)blockIdx.x, (int)blockIdx.z, B, 1, d, F, H, eps, norm_free, alpha, wf_mm_smem);
 }
 
+// ---------------------------------------------------------------------------------------------
+// The same products for more batch rows than two tiles of 16 (kWideFrom): there every batch tile reads the matrix again and
+// stages its own operand rows, and the launches are bound by those reads and their dependent trips (W1 at d = 1024, B = 200:
+// 79 us; Wo, W1, W2, [Wk; Wv] at B = 100 in the stack engine: 6.6, 14.5, 18.8, 11.8 us).  Here a workgroup owns 16 NO outputs of
+// 32 batch rows, its eight wavefronts split the contraction, and a wavefront requests all operands of two 32-index steps,
+// two such groups ahead, straight into fragments (no LDS in the loop: the fragments of a wavefront are used by it alone); the
+// eight partial tiles meet in LDS once, and wavefront w finishes tile w (row group w % NO, batch columns 16 (w / NO) ..).
+// 32 columns, because an operand row costs a head and a remainder row: 64 x 32 outputs read as many bytes of W as of x.
+// NO = 2 where n_out is only d: twice the workgroups (B = 100: 128 instead of 64).  Measured
+// at d = 1024: B = 100 in the stack engine 5.3, 8.1, 11.3, 9.1 us; a decoding step at B = 200 QKV 31 (89 before), W1 19, W2 18
+// (44), [Wk; Wv] 11 (21) us.  The operand rows come in fragment order (operand_offsets): as plain rows, whose fragments are
+// 64-byte pieces of sixteen lines, W2 at B = 100 took 19.2 us.
+// grid (n_out / (16 NO), layers, batch tiles of 32), block 512, LDS 14 NO KB + 512 B.  EPI_KV and EPI_QKV need NO = 4: a
+// workgroup is one head, and EPI_QKV writes the normalised rows Q, Kt, Vt of a decoding step (no finalize launch).
+// ---------------------------------------------------------------------------------------------
+constexpr int kWideBatch = 32, kWideWaves = 8;
+template <int EPI, int NO, bool PACKED>
+__device__ __forceinline__ void wide_body(const WaveLayer &Y, int t, int block_x, int batch_tile, int B, int N, int d, int F, int H,
+                                          float eps, int norm_free, float alpha, unsigned char *wide_smem)
+{
+    static_assert(NO == 4 || (NO == 2 && EPI != EPI_KV && EPI != EPI_QKV), "these epilogues own whole heads");
+    f32x4_t *part = reinterpret_cast<f32x4_t *>(wide_smem);                                       // [2 NO][7][64]
+    float *hss = reinterpret_cast<float *>(wide_smem + (size_t)2 * NO * (kWideWaves - 1) * 1024);   // [4][32]
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int c16 = lane & 15, g = lane >> 4;
+    const int row0 = block_x * 16 * NO, b0 = batch_tile * kWideBatch;
+    const int K = EPI == EPI_W2 ? F : d, nk = K / (32 * kWideWaves);   // 32-index steps of this wavefront
+    const bf16_t *Wp, *Wr, *X;   // fragment order / the caller's rows (row0 ..) / operand rows in fragment order
+    if (EPI == EPI_WO) { Wp = Y.S.wp_o; Wr = (const bf16_t *)Y.W.Wo + (size_t)row0 * K; X = Y.S.op_a; }
+    else if (EPI == EPI_W1) { Wp = Y.S.wp_1; Wr = (const bf16_t *)Y.W.W1 + (size_t)row0 * K; X = Y.S.op_h; }
+    else if (EPI == EPI_W2) { Wp = Y.S.wp_2; Wr = (const bf16_t *)Y.W.W2 + (size_t)row0 * K; X = Y.S.op_u; }
+    else if (EPI == EPI_KV) {
+        Wp = Y.S.wp_kv; X = Y.S.op_z;
+        Wr = row0 < d ? (const bf16_t *)Y.W.Wk + (size_t)row0 * K : (const bf16_t *)Y.W.Wv + (size_t)(row0 - d) * K;
+    } else {
+        Wp = nullptr; X = Y.S.op_x;
+        Wr = (const bf16_t *)(row0 < d ? Y.W.Wq : (row0 < 2 * d ? Y.W.Wk : Y.W.Wv)) + (size_t)(row0 % d) * K;
+    }
+    const bf16_t *wr = PACKED ? Wp + ((size_t)(row0 / 16) * (K / 32) + (size_t)wave * nk) * 512 + lane * 8
+                              : Wr + (size_t)c16 * K + (size_t)wave * nk * 32 + 8 * g;
+    constexpr int kStep = PACKED ? 512 : 32;
+    const size_t tile_stride = (size_t)16 * K;   // elements between row tiles, either order
+    const bf16_t *xr[2];
+    int xs[2];   // elements of a 32-index step: heads, then remainders, of the tile's batch rows
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {   // a tile or column past the batch repeats the last one (their results are dropped)
+        const int tile = min(b0 / 16 + c, (B - 1) / 16), nbt = min(16, B - 16 * tile);
+        xs[c] = 64 * nbt;
+        xr[c] = X + (size_t)tile * 32 * K + (size_t)wave * nk * xs[c] + (g * nbt + min(c16, nbt - 1)) * 8;
+    }
+
+    f32x4_t acc[NO][2];
+#pragma unroll
+    for (int j = 0; j < NO; ++j)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) acc[j][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    Frag w[2][2][NO], xh[2][2][2], xl[2][2][2];
+#define RT_WIDE_LOAD(buf, s0)                                                             \
+    _Pragma("unroll") for (int e = 0; e < 2; ++e)                                         \
+    {                                                                                     \
+        const int s_ = min((s0) + e, nk - 1);                                             \
+        _Pragma("unroll") for (int j = 0; j < NO; ++j)                                    \
+            w[buf][e][j].u = global_load16(wr + j * tile_stride + (size_t)s_ * kStep);    \
+        _Pragma("unroll") for (int c = 0; c < 2; ++c)                                     \
+        {                                                                                 \
+            xh[buf][e][c].u = global_load16(xr[c] + s_ * xs[c]);                          \
+            xl[buf][e][c].u = global_load16(xr[c] + s_ * xs[c] + xs[c] / 2);              \
+        }                                                                                 \
+    }
+#define RT_WIDE_COMPUTE(buf, s0)                                                          \
+    _Pragma("unroll") for (int e = 0; e < 2; ++e) if ((s0) + e < nk)                      \
+    {                                                                                     \
+        _Pragma("unroll") for (int c = 0; c < 2; ++c)                                     \
+        {                                                                                 \
+            _Pragma("unroll") for (int j = 0; j < NO; ++j)                                \
+                acc[j][c] = mfma16(w[buf][e][j], xl[buf][e][c], acc[j][c]);               \
+            _Pragma("unroll") for (int j = 0; j < NO; ++j)                                \
+                acc[j][c] = mfma16(w[buf][e][j], xh[buf][e][c], acc[j][c]);               \
+        }                                                                                 \
+    }
+    RT_WIDE_LOAD(0, 0)
+    if (nk > 2) { RT_WIDE_LOAD(1, 2) }
+    // the tile that this wavefront finishes, and the RMS scale of its batch column's input
+    const bool owner = wave < 2 * NO;
+    const int rg = wave % NO, col = 16 * ((wave / NO) & 1) + c16;
+    const int cb = min(b0 + col, B - 1);
+    float rscale = 1.f;
+    if (!norm_free && (EPI == EPI_W1 || EPI == EPI_KV || EPI == EPI_QKV))
+        rscale = rms_scale_from_parts(EPI == EPI_W1 ? Y.S.ssq_h : (EPI == EPI_KV ? Y.S.ssq_z : Y.S.ssq_x), cb, g, d / 16, d, eps);
+    for (int s = 0; s < nk; s += 4) {
+        RT_WIDE_COMPUTE(0, s)
+        if (s + 4 < nk) { RT_WIDE_LOAD(0, s + 4) }
+        RT_WIDE_COMPUTE(1, s + 2)
+        if (s + 6 < nk) { RT_WIDE_LOAD(1, s + 6) }
+    }
+#undef RT_WIDE_LOAD
+#undef RT_WIDE_COMPUTE
+    // tile i is summed by wavefront i: its own part stays in registers, the other seven meet in LDS (56 KB at NO = 4)
+    f32x4_t sum = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 2 * NO; ++i) {
+        if (wave == i) sum = acc[i % NO][i / NO];
+        else part[(i * (kWideWaves - 1) + ((wave - i - 1) & (kWideWaves - 1))) * 64 + lane] = acc[i % NO][i / NO];
+    }
+    __syncthreads();
+    if (owner) {
+#pragma unroll
+        for (int k = 0; k < kWideWaves - 1; ++k) sum += part[(wave * (kWideWaves - 1) + k) * 64 + lane];
+    }
+    mm_epilogue<EPI>(Y, t, sum, rscale, owner, owner && b0 + col < B, cb, row0 + 16 * rg, block_x, rg, col, kWideBatch, B, N, d, F, H,
+                     eps, norm_free, alpha, hss);
+}
+template <int EPI, int NO>
+__global__ __launch_bounds__(64 * kWideWaves) void wf_wide_kernel(const WaveLayer *__restrict__ layers, int l_first, int s, int chunk,
+                                                                  int B, int N, int d, int F, int H, float eps, int norm_free,
+                                                                  float alpha)
+{
+    extern __shared__ __align__(16) unsigned char wide_smem[];
+    const int l = l_first + blockIdx.y;
+    wide_body<EPI, NO, true>(layers[l], layer_pos(s, l, chunk), (int)blockIdx.x, (int)blockIdx.z, B, N, d, F, H, eps, norm_free, alpha,
+                             wide_smem);
+}
+template <int EPI, int NO>
+__global__ __launch_bounds__(64 * kWideWaves) void step_wide_kernel(const WaveLayer Y, int B, int d, int F, int H, float eps,
+                                                                    int norm_free, float alpha)
+{
+    extern __shared__ __align__(16) unsigned char wide_smem[];
+    wide_body<EPI, NO, false>(Y, 0, (int)blockIdx.x, (int)blockIdx.z, B, 1, d, F, H, eps, norm_free, alpha, wide_smem);
+}
+
 // A decoding step's input rows x_t [B][d] as operand rows: head + remainder of x * g_attn, and the sums of squares of
 // x per 16 elements.  grid (ceil(d / 1024), B), block 256: a thread takes 4 elements, 4 adjacent threads one group.
 __global__ __launch_bounds__(256) void step_prep_kernel(const bf16_t *__restrict__ x, size_t x_stride, const bf16_t *__restrict__ g,
-                                                        bf16_t *__restrict__ op_x, float *__restrict__ ssq_x, int d, int norm_free)
+                                                        bf16_t *__restrict__ op_x, float *__restrict__ ssq_x, int d, int norm_free,
+                                                        bool op_fragments)
 {
     const int b = blockIdx.y, e0 = ((int)blockIdx.x * 256 + (int)threadIdx.x) * 4;
     const bool in = e0 < d;   // d is a multiple of 64: a group of 16 is all in or all out
@@ -407,7 +581,8 @@ __global__ __launch_bounds__(256) void step_prep_kernel(const bf16_t *__restrict
 #pragma unroll
     for (int r = 0; r < 4; ++r) gv[r] = v[r] * ((g && !norm_free && in) ? bf16_to_f32(g[e0 + r]) : 1.f);
     if (in) {
-        split_store4(op_x, (size_t)(2 * b) * d + e0, (size_t)(2 * b + 1) * d + e0, gv);
+        const ulonglong2 oo = operand_offsets(op_fragments, gridDim.y, d, b, e0);
+        split_store4(op_x, oo.x, oo.y, gv);
         if ((threadIdx.x & 3) == 0) ssq_x[(size_t)b * (d / 16) + e0 / 16] = ss;
     }
 }
@@ -610,6 +785,26 @@ static hipError_t mm_launch(int n_out, unsigned nl, hipStream_t st, const WaveLa
     return hipSuccess;
 }
 
+// Batches and widths from which the products take 32 sequences per workgroup.  Measured (us, tiles of 16 / these): decoding step at
+// t = 511, d = 1024: B = 49 110 / 82, B = 64 120 / 87, B = 128 206 / 140, B = 256 407 / 225; B = 80: d = 768 99 / 80, d = 512 65 / 63,
+// d = 256 44 / 53; a position of the stack engine with one layer: B = 49 55 / 39, B = 128 64 / 46; B = 60: d = 512 35 / 29.
+// Up to 32 rows there are two tiles of 16 at most, and smaller batches mostly run on the single-launch engines.
+constexpr int kWideFrom = 33, kWideWidth = 512;
+constexpr size_t wide_lds_bytes(int NO) { return (size_t)2 * NO * (kWideWaves - 1) * 1024 + 4 * kWideBatch * 4; }
+template <int EPI, int NO>
+static void wide_launch(int n_out, unsigned nl, hipStream_t st, const WaveLayer *dev_layers, int l0, int s, int chunk, const LayerDims &D)
+{
+    const dim3 grid((unsigned)(n_out / (16 * NO)), nl, (unsigned)((D.B + kWideBatch - 1) / kWideBatch));
+    hipLaunchKernelGGL((wf_wide_kernel<EPI, NO>), grid, dim3(64 * kWideWaves), wide_lds_bytes(NO), st, dev_layers, l0, s, chunk, D.B, D.N,
+                       D.d, D.F, D.H, D.eps, D.norm_free, D.alpha);
+}
+template <int EPI, int NO> static void step_wide_launch(const WaveLayer &Y, int n_out, const LayerDims &D, hipStream_t st)
+{
+    const dim3 grid((unsigned)(n_out / (16 * NO)), 1, (unsigned)((D.B + kWideBatch - 1) / kWideBatch));
+    hipLaunchKernelGGL((step_wide_kernel<EPI, NO>), grid, dim3(64 * kWideWaves), wide_lds_bytes(NO), st, Y, D.B, D.d, D.F, D.H, D.eps,
+                       D.norm_free, D.alpha);
+}
+
 // The steps of one prefill.  The layers are dealt to W.n groups of consecutive layers, each group enqueued on its own
 // stream: a step is a chain of dependent launches, each with a serial start-up and tail, and the chains of different
 // groups fill each other's gaps.  A group's first layer enters a chunk only after the group below has finished it:
@@ -624,7 +819,7 @@ static hipError_t wavefront_steps(const LayerDims &D, const WaveLayer *dev_layer
     const int far_rel = log2_chunk - D.log2_pmin;
     const unsigned bt = (unsigned)((B + kBatchTile - 1) / kBatchTile);
     constexpr int rows_d = (4 / KSd) * kGemvRows, rows_F = (4 / KSF) * kGemvRows;   // output rows per workgroup
-    const bool use_mm = HP && wavefront_uses_matrix_cores(d, F, true);
+    const bool use_mm = HP && wavefront_uses_matrix_cores(d, F, true), wide = use_mm && B >= kWideFrom && d >= kWideWidth;
     const int G = W.n < L ? W.n : L;
     const int per = (L + G - 1) / G;   // layers per group
     hipError_t e;
@@ -667,8 +862,13 @@ static hipError_t wavefront_steps(const LayerDims &D, const WaveLayer *dev_layer
                 }
             }
             hipLaunchKernelGGL((wf_merge_kernel<T, HP>), dim3(BH, nl), dim3(64), 0, st, dev_layers, l0, s, chunk, log2_chunk, BH,
-                               D.H, D.p_min, D.log2_pmin, D.scale, D.alibi);
-            if (HP && use_mm) {
+                               D.H, D.p_min, D.log2_pmin, D.scale, D.alibi, wide);
+            if (HP && wide) {
+                wide_launch<EPI_WO, 2>(d, nl, st, dev_layers, l0, s, chunk, D);
+                wide_launch<EPI_W1, 4>(F, nl, st, dev_layers, l0, s, chunk, D);
+                wide_launch<EPI_W2, 2>(d, nl, st, dev_layers, l0, s, chunk, D);
+                wide_launch<EPI_KV, 4>(2 * d, nl, st, dev_layers, l0, s, chunk, D);
+            } else if (HP && use_mm) {
                 if ((e = mm_launch<EPI_WO, 4, 8>(d, nl, st, dev_layers, l0, s, chunk, D)) != hipSuccess) return e;
                 if ((e = mm_launch<EPI_W1, 1, 4>(F, nl, st, dev_layers, l0, s, chunk, D)) != hipSuccess) return e;
                 if ((e = mm_launch<EPI_W2, 4, 8>(d, nl, st, dev_layers, l0, s, chunk, D)) != hipSuccess) return e;
@@ -799,6 +999,18 @@ static WaveLayer step_layer(const Weights &W, const Scratch &S, const void *x_t,
     return Y;
 }
 
+bool step_uses_wide(const LayerDims &D) { return D.B >= kWideFrom && D.d >= kWideWidth; }
+
+// Q, Kt, Vt of the rows x_t [B][d] (step_uses_wide)
+hipError_t step_qkv_wide(const LayerDims &D, const Weights &W, const Scratch &S, const void *x_t, size_t x_stride, hipStream_t st)
+{
+    if (x_stride != (size_t)D.d) return hipErrorInvalidValue;   // Wo's epilogue addresses the rows of x_t d apart
+    hipLaunchKernelGGL(step_prep_kernel, dim3((unsigned)((D.d + 1023) / 1024), (unsigned)D.B), dim3(256), 0, st, (const bf16_t *)x_t,
+                       x_stride, (const bf16_t *)W.g_attn, S.op_x, S.ssq_x, D.d, D.norm_free, true);
+    step_wide_launch<EPI_QKV, 4>(step_layer(W, S, x_t, nullptr, nullptr, nullptr), 3 * D.d, D, st);
+    return hipGetLastError();
+}
+
 // raw [q | k_tmp | v_tmp] of the rows x_t [B][d] into S.qkv_raw
 hipError_t step_qkv_mm(const LayerDims &D, const Weights &W, const Scratch &S, const void *x_t, size_t x_stride, hipStream_t st)
 {
@@ -806,7 +1018,7 @@ hipError_t step_qkv_mm(const LayerDims &D, const Weights &W, const Scratch &S, c
     // operand rows that fit LDS: the product's workgroups prepare their operand rows themselves
     if (!step_mm_stages<EPI_QKV, 4>(D))
         hipLaunchKernelGGL(step_prep_kernel, dim3((unsigned)((D.d + 1023) / 1024), (unsigned)D.B), dim3(256), 0, st, (const bf16_t *)x_t,
-                           x_stride, (const bf16_t *)W.g_attn, S.op_x, S.ssq_x, D.d, D.norm_free);
+                           x_stride, (const bf16_t *)W.g_attn, S.op_x, S.ssq_x, D.d, D.norm_free, false);
     const WaveLayer Y = step_layer(W, S, x_t, nullptr, nullptr, nullptr);
     return step_mm_launch<EPI_QKV, 4, 4>(Y, 3 * D.d, D, st);
 }
@@ -817,6 +1029,13 @@ hipError_t step_base_case_mm(const LayerDims &D, const Weights &W, const Scratch
 {
     const WaveLayer Y = step_layer(W, S, x_t, y_t, K_row, V_row);
     hipError_t e;
+    if (step_uses_wide(D)) {
+        step_wide_launch<EPI_WO, 2>(Y, D.d, D, st);
+        step_wide_launch<EPI_W1, 4>(Y, D.F, D, st);
+        step_wide_launch<EPI_W2, 2>(Y, D.d, D, st);
+        step_wide_launch<EPI_KV, 4>(Y, 2 * D.d, D, st);
+        return hipGetLastError();
+    }
     // Wo and W2 have d / 16 row groups only: eight wavefronts share each group's contraction (shorter dependent chains)
     // when every wavefront still gets whole 64-index step pairs
     e = D.d % 512 == 0 ? step_mm_launch<EPI_WO, 8, 8>(Y, D.d, D, st) : step_mm_launch<EPI_WO, 4, 4>(Y, D.d, D, st);
