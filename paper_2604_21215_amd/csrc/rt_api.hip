@@ -41,7 +41,7 @@ struct rt_ctx {
     int stack_L = 0, stack_chunk = 0;
     std::vector<Scratch> stack_S;
     WaveLayer *stack_dev = nullptr;
-    WaveStreams wave_streams = {};   // st[1..], ev[..] created on first use
+    WaveStreams wave_streams = {};   // ev[..], and st[1..] for captured calls, created on first use
     void *par_slab = nullptr;        // activations of the loop-free evaluations (rt_layer_recompute, rt_transformer_layer)
     size_t par_bytes = 0;
     void *bw_slab = nullptr;         // scratch of rt_layer_backward
@@ -58,6 +58,60 @@ struct rt_ctx {
 };
 
 static const char *kNoCtx = "no context";
+
+// Side streams of the layer-wavefront engine, lent to a call for the time it enqueues its work.  A process has four hardware
+// queues and a stream keeps the one it was given: with two side streams per context the streams of several contexts share
+// queues with each other and with the caller's stream, and groups of layers that should overlap run one after the other
+// (12 layers,
+// B = 4, N = 4096: 285 ms for the only context of a process, 420 - 725 ms for some of several, 284 ms for all of them from here).  Calls that follow one another take
+// the same streams from here; calls on several threads at once take different ones.  A lent stream goes back with work still
+// queued on it: the next call's work on it follows in order, and every wait inside a call is for work enqueued before it, so
+// no two calls can wait for each other.  At most kPooledSets sets stay; the last context of the process gives all of them back.
+// A call that is being captured uses streams of its own context: a pooled stream would stay part of the capture.
+namespace {
+struct SideStreams {
+    int device;
+    hipStream_t st[kMaxWaveStreams - 1];
+};
+constexpr size_t kPooledSets = 4;
+std::mutex g_side_mu;
+SideStreams g_side_free[kPooledSets];
+size_t g_side_count = 0;
+int g_contexts = 0;   // contexts of this process
+
+void destroy_side(SideStreams &s)
+{
+    for (hipStream_t &st : s.st)
+        if (st) (void)hipStreamDestroy(st);
+}
+SideStreams take_side(int device)
+{
+    std::lock_guard<std::mutex> lock(g_side_mu);
+    for (size_t i = g_side_count; i-- > 0;)
+        if (g_side_free[i].device == device) {
+            const SideStreams s = g_side_free[i];
+            for (--g_side_count; i < g_side_count; ++i) g_side_free[i] = g_side_free[i + 1];
+            return s;
+        }
+    return SideStreams{device, {}};
+}
+void give_side(SideStreams s)
+{
+    std::lock_guard<std::mutex> lock(g_side_mu);
+    if (g_side_count < kPooledSets) g_side_free[g_side_count++] = s;
+    else destroy_side(s);
+}
+void count_context(int change)
+{
+    std::lock_guard<std::mutex> lock(g_side_mu);
+    g_contexts += change;
+    if (g_contexts > 0) return;
+    for (; g_side_count > 0; --g_side_count) {
+        (void)hipSetDevice(g_side_free[g_side_count - 1].device);
+        destroy_side(g_side_free[g_side_count - 1]);
+    }
+}
+}  // namespace
 
 static rt_status fail(rt_ctx *c, rt_status s, const char *fmt, const char *detail = "")
 {
@@ -333,6 +387,7 @@ rt_status rt_create(const rt_config *cfg, rt_ctx **out)
 
     rt_ctx *c = new (std::nothrow) rt_ctx();
     if (!c) return RT_ERR_OOM;
+    count_context(1);
     c->cfg = *cfg;
     c->cfg.p_min = p_min;
     c->stream = (hipStream_t)cfg->stream;
@@ -352,6 +407,7 @@ rt_status rt_create(const rt_config *cfg, rt_ctx **out)
     hipError_t e = hipMalloc(&c->slab, c->slab_bytes);
     if (e != hipSuccess) {
         (void)hipGetLastError();
+        count_context(-1);
         delete c;
         return e == hipErrorOutOfMemory ? RT_ERR_OOM : RT_ERR_HIP;
     }
@@ -361,6 +417,7 @@ rt_status rt_create(const rt_config *cfg, rt_ctx **out)
         if (e != hipSuccess) {
             (void)hipGetLastError();
             (void)hipFree(c->slab);
+            count_context(-1);
             delete c;
             return RT_ERR_HIP;
         }
@@ -369,6 +426,7 @@ rt_status rt_create(const rt_config *cfg, rt_ctx **out)
     rt_status ps = persistent_create(c->persist, c->cfg, D);
     if (ps != RT_OK && (cfg->flags & RT_FLAG_ENGINE_PERSISTENT)) {
         (void)hipFree(c->slab);
+        count_context(-1);
         delete c;
         return ps;
     }
@@ -423,7 +481,10 @@ rt_status rt_destroy(rt_ctx *c)
         if (c->wave_streams.ev[g]) (void)hipEventDestroy(c->wave_streams.ev[g]);
     }
     hipError_t e = hipFree(c->slab);
+    const int device = c->cfg.device;
     delete c;
+    count_context(-1);
+    (void)hipSetDevice(device);
     return e == hipSuccess ? RT_OK : RT_ERR_HIP;
 }
 
@@ -994,22 +1055,34 @@ extern "C" rt_status rt_stack_prefill(rt_ctx *c, const rt_layer_weights *layers,
     LayerDims D = c->base;
     D.B = B; D.N = N; D.kv_cap = kv_cap;
     c->engine = "wavefront";
-    // groups of layers on streams of their own (RT_WAVE_STREAMS = 1..4 overrides the default of 3: cfg5, 12 layers, takes 302 ms
-    // with two groups, 294-295 ms with three, twice as long with four - the process has four hardware queues)
-    WaveStreams &WS = c->wave_streams;
+    // groups of layers on streams of their own (RT_WAVE_STREAMS = 1..4 overrides the default of 3: 12 layers, B = 4, N = 4096:
+    // 302 ms with two groups, 294-295 ms with three, twice as long with four - the process has four hardware queues)
+    WaveStreams WS = c->wave_streams;
     int want = 3;
     if (const char *ev = getenv("RT_WAVE_STREAMS")) want = atoi(ev);
     if (want < 1) want = 1;
     if (want > kMaxWaveStreams) want = kMaxWaveStreams;
+    if (want > L) want = L;   // a group has a layer
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (want > 1 && c->stream) RT_TRY(hipStreamIsCapturing(c->stream, &capturing), "hipStreamIsCapturing");
+    const bool pooled = want > 1 && capturing == hipStreamCaptureStatusNone;
+    SideStreams side{c->cfg.device, {}};
+    if (pooled) side = take_side(c->cfg.device);
+    hipError_t e = hipSuccess;
     WS.st[0] = c->stream;
-    for (int g = 0; g < want; ++g) {
-        if (g > 0 && !WS.st[g]) RT_TRY(hipStreamCreateWithFlags(&WS.st[g], hipStreamNonBlocking), "hipStreamCreateWithFlags");
-        if (!WS.ev[g]) RT_TRY(hipEventCreateWithFlags(&WS.ev[g], hipEventDisableTiming), "hipEventCreateWithFlags");
+    for (int g = 0; g < want && e == hipSuccess; ++g) {
+        hipStream_t *own = g == 0 ? &WS.st[0] : (pooled ? &side.st[g - 1] : &c->wave_streams.st[g]);
+        if (g > 0 && !*own) e = hipStreamCreateWithFlags(own, hipStreamNonBlocking);
+        WS.st[g] = *own;
+        if (e == hipSuccess && !c->wave_streams.ev[g]) e = hipEventCreateWithFlags(&c->wave_streams.ev[g], hipEventDisableTiming);
+        WS.ev[g] = c->wave_streams.ev[g];
     }
     WS.n = want;
-    hipError_t e;
-    if (c->cfg.dtype == RT_BF16) e = wavefront_prefill<bf16_t>(D, c->stack_dev, host.data(), L, chunk, c->use_mfma, WS);
-    else e = wavefront_prefill<float>(D, c->stack_dev, host.data(), L, chunk, false, WS);
+    if (e == hipSuccess) {
+        if (c->cfg.dtype == RT_BF16) e = wavefront_prefill<bf16_t>(D, c->stack_dev, host.data(), L, chunk, c->use_mfma, WS);
+        else e = wavefront_prefill<float>(D, c->stack_dev, host.data(), L, chunk, false, WS);
+    }
+    if (pooled) give_side(side);
     if (e != hipSuccess) return fail_hip(c, e, "wavefront_prefill");
     return RT_OK;
 }

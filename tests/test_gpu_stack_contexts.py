@@ -1,0 +1,54 @@
+"""rt_stack_prefill on several contexts of one process, whose calls take their side streams from one pool: calls of different
+contexts queued behind each other, on different streams and from different threads give what one context alone gives."""
+import threading
+
+import pytest
+
+from paper_2604_21215_amd import inputs as gen
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("threads", [False, True])
+def test_contexts_share_side_streams(threads):
+    from paper_2604_21215_amd import binding, torch_io as tio
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    B, N, d, L, n = 2, 150, 256, 4, 6   # more contexts at once than the pool keeps
+    dls = [tio.DeviceLayer(gen.make_layer_weights(91, l, d, 4 * d, "bf16"), None, "bf16") for l in range(L)]
+    x = tio.to_device(gen.make_custom(92, "bf16", B, N, d, 4, 4 * d).x, "bf16")
+    ws = [dl.struct for dl in dls]
+    torch.cuda.synchronize()
+
+    def tensors():
+        return ([torch.empty_like(x) for _ in range(L)], [torch.empty((N, B, 4, 64), dtype=x.dtype, device=x.device) for _ in range(L)],
+                [torch.empty((N, B, 4, 64), dtype=x.dtype, device=x.device) for _ in range(L)])
+
+    streams = [torch.cuda.Stream() for _ in range(n)]
+    ctxs = [binding.RTContext(d, 4, 4 * d, B, N, "bf16", resid_scale=0.5, rms_eps=1e-6, reserve_stack_layers=L, stream=s.cuda_stream)
+            for s in streams]
+    outs = [tensors() for _ in range(n)]
+    torch.cuda.synchronize()
+    try:
+        def go(k):
+            for _ in range(2):
+                ctxs[k].rt_stack_prefill(ws, x, *outs[k])
+
+        if threads:
+            pool = [threading.Thread(target=go, args=(k,)) for k in range(n)]
+            for p in pool:
+                p.start()
+            for p in pool:
+                p.join()
+        else:
+            for k in range(n):
+                go(k)
+        torch.cuda.synchronize()
+        for k in range(1, n):
+            for a, b in zip(outs[0], outs[k]):
+                assert all(torch.equal(p, q) for p, q in zip(a, b))
+        assert all(bool(torch.isfinite(t).all()) for t in outs[0][0])
+    finally:
+        for c in ctxs:
+            c.rt_destroy()
