@@ -14,7 +14,8 @@
 //       visited; blocks below kBwPmin keys are handled directly by each query (its "window");
 //   (C) after the loop, batched: dq over all (query, key) pairs, the gradients of the temporary pairs, x through the
 //       three projections and RMS, and every parameter sum as one product over all B N rows.
-// Everything outside the batched products is fp32 on the vector ALUs; the storage type T decides how x, z, gy, gK, gV and
+// Everything outside the batched products is fp32 on the vector ALUs, except the loop's products with bf16 weights, which take the
+// fp32 input as three exact bf16 parts on the matrix cores; the storage type T decides how x, z, gy, gK, gV and
 // the weights are read.  The batched products are fp32 LDS-tiled kernels for fp32 storage; for bf16 storage (the
 // configurations' "bf16 compute with fp32 accumulation") they run on the matrix cores from bf16 copies of their
 // operands - the recompute's activations as bf16 head + bf16 remainder (two products: no rounding of q, k, h or the
@@ -24,6 +25,7 @@
 #include "rt_gemm_tiled.h"
 #include "rt_backward.h"
 #include <cstdlib>
+#include <type_traits>
 
 namespace rt {
 
@@ -349,6 +351,139 @@ static void gemv(hipStream_t st, const T *W, int n_out, int n_in, const float *i
             hipLaunchKernelGGL((bw_gemv_kernel<T, EPI, 4>), dim3((n_out + kGemvRows - 1) / kGemvRows), dim3(256), 0, st, W, n_out,
                                n_in, in + (size_t)b0 * in_stride, in_stride, Bn, rf, out_f + (size_t)b0 * n_out);
     }
+}
+
+// The same products on the matrix cores for bf16 weights: out[b][o] = sum_k W[o][k] in[b][k] with the fp32 input cut into three bf16
+// parts of eight significant bits (head, middle, tail: all 24 bits of it), so that every partial product is exact and the sums are fp32
+// as in the plain-ALU form.  That form is bound by its instructions: with eight batch rows per launch it reads and multiplies the
+// whole matrix once per eight rows and adds every sum across 64 lanes, 7 - 10 us a launch, 24 launches per position at 48 rows.
+// A workgroup owns 16 NT outputs of 16 batch rows; its eight wavefronts take the 64-index pieces of the contraction in turn (a lane's
+// two fragments of a piece are 32 consecutive bytes of a weight row and 64 of an input row) and meet in LDS in a fixed order.
+// Workgroups of the same outputs are a multiple of eight apart, hence on one XCD, whose L2 keeps that share of the matrices (24 d^2
+// bytes / 8 = 2.9 MB at d = 1024) from one position to the next.
+// 48 rows, d = 1024, the four products of a position: 215 -> 40 us, the backward pass of 48 x 512 positions 129 -> 37.8 ms.  grid (n_out / (16 NT), ceil(B / 16)), block 512.
+struct Parts3 {
+    Frag h, m, l;
+};
+__device__ __forceinline__ Parts3 split3(const float (&x)[8])
+{
+    Parts3 s;
+    float r[8], q[8];
+    float big = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        big = fmaxf(big, fabsf(x[e]));
+        r[e] = x[e] - __uint_as_float(__float_as_uint(x[e]) & 0xFFFF0000u);   // exact, at most 16 bits
+    }
+    if (__any(big == INFINITY)) {   // an infinity is its own head: inf - inf is no part of it
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (fabsf(x[e]) == INFINITY) r[e] = 0.f;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) q[e] = r[e] - __uint_as_float(__float_as_uint(r[e]) & 0xFFFF0000u);   // exact, at most 8 bits
+    auto tops = [](float a, float b) { return __builtin_amdgcn_perm(__float_as_uint(b), __float_as_uint(a), 0x07060302u); };
+    s.h.u = make_uint4(tops(x[0], x[1]), tops(x[2], x[3]), tops(x[4], x[5]), tops(x[6], x[7]));
+    s.m.u = make_uint4(tops(r[0], r[1]), tops(r[2], r[3]), tops(r[4], r[5]), tops(r[6], r[7]));
+    s.l.u = make_uint4(tops(q[0], q[1]), tops(q[2], q[3]), tops(q[4], q[5]), tops(q[6], q[7]));
+    return s;
+}
+
+constexpr int kVmLd = 17;
+template <int EPI, int NT>
+__global__ __launch_bounds__(512) void bw_mmv_kernel(const bf16_t *__restrict__ W, int n_out, int n_in, const float *__restrict__ in,
+                                                     int B, const float *__restrict__ res_f, float *__restrict__ out_f)
+{
+    __shared__ float part[8][16 * NT * kVmLd];
+    const int tid = threadIdx.x, lane = tid & 63, kw = tid >> 6, l16 = lane & 15, g = lane >> 4;
+    const int o0 = blockIdx.x * 16 * NT, b0 = blockIdx.y * 16;
+    const bf16_t *wrow = W + (size_t)(o0 + l16) * n_in + 16 * g;
+    const float *irow = in + (size_t)min(b0 + l16, B - 1) * n_in + 16 * g;
+    const int pieces = n_in / 64;
+    const int o = tid % (16 * NT), b = tid / (16 * NT);   // this thread's output
+    const bool writes = b < 16 && b0 + b < B;
+    const size_t at = (size_t)(b0 + b) * n_out + o0 + o;
+    const float factor = EPI == EPI_MUL && writes ? res_f[at] : 1.f;
+    f32x4_t acc[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+
+    // groups of two pieces, loaded one group ahead of their use (groups of four: 37.8 -> 38.6 ms per backward pass of 48 x 512)
+    constexpr int G = 2;
+    uint4 wn[G][NT][2];
+    float xn[G][16];
+    auto fetch = [&](int p0) {
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            const int k = 64 * min(p0 + 8 * j, pieces - 1);
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int s = 0; s < 2; ++s)
+                    wn[j][t][s] = *reinterpret_cast<const uint4 *>(wrow + (size_t)16 * t * n_in + k + 8 * s);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const float4 v = *reinterpret_cast<const float4 *>(irow + k + 4 * s);
+                xn[j][4 * s] = v.x; xn[j][4 * s + 1] = v.y; xn[j][4 * s + 2] = v.z; xn[j][4 * s + 3] = v.w;
+            }
+        }
+    };
+    fetch(kw);
+    for (int p = kw; p < pieces; p += 8 * G) {
+        uint4 wc[G][NT][2];
+        float xc[G][16];
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+#pragma unroll
+            for (int t = 0; t < NT; ++t)
+#pragma unroll
+                for (int s = 0; s < 2; ++s) wc[j][t][s] = wn[j][t][s];
+#pragma unroll
+            for (int e = 0; e < 16; ++e) xc[j][e] = xn[j][e];
+        }
+        if (p + 8 * G < pieces) fetch(p + 8 * G);
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            if (p + 8 * j >= pieces) break;   // wavefront-uniform
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                float x[8];
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x[e] = xc[j][8 * s + e];
+                const Parts3 xs = split3(x);
+#pragma unroll
+                for (int t = 0; t < NT; ++t) {   // small terms first
+                    Frag w;
+                    w.u = wc[j][t][s];
+                    acc[t] = mfma16(w, xs.l, acc[t]);
+                    acc[t] = mfma16(w, xs.m, acc[t]);
+                    acc[t] = mfma16(w, xs.h, acc[t]);
+                }
+            }
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[kw][(16 * t + 4 * g + r) * kVmLd + l16] = acc[t][r];
+    __syncthreads();
+    if (!writes) return;
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) v += part[w][o * kVmLd + b];
+    out_f[at] = EPI == EPI_MUL ? v * factor : v;
+}
+
+// n_out and n_in multiples of 64.  32 outputs per workgroup where 16 would be more than two workgroups per compute unit: the input
+// rows are then read and split half as often (48 x 512, d = 1024: 38.8 -> 37.8 ms per backward pass)
+template <int EPI>
+static void mmv(hipStream_t st, const bf16_t *W, int n_out, int n_in, const float *in, int B, const float *res_f, float *out_f)
+{
+    const unsigned tiles = (unsigned)((B + 15) / 16);
+    if ((size_t)(n_out / 16) * tiles > 512)
+        hipLaunchKernelGGL((bw_mmv_kernel<EPI, 2>), dim3((unsigned)(n_out / 32), tiles), dim3(512), 0, st, W, n_out, n_in, in, B, res_f, out_f);
+    else
+        hipLaunchKernelGGL((bw_mmv_kernel<EPI, 1>), dim3((unsigned)(n_out / 16), tiles), dim3(512), 0, st, W, n_out, n_in, in, B, res_f, out_f);
 }
 
 // ------------------------------------------------------------------------------------------------ (B) reverse loop
@@ -1110,20 +1245,32 @@ hipError_t backward_layer(const LayerDims &D, const Weights &W, const void *x_, 
         }
     }
     if (!single_launch) {
+    const std::integral_constant<int, EPI_KV> plain;
+    const std::integral_constant<int, EPI_MUL> times;
+    auto product = [&](auto epi, const void *Wt, int n_out, int n_in, const float *in, const float *res_f, float *out) {
+        constexpr int EPI = decltype(epi)::value;
+        if constexpr (sizeof(T) == 2) {
+            if (mm) {
+                mmv<EPI>(st, (const bf16_t *)Wt, n_out, n_in, in, B, res_f, out);
+                return;
+            }
+        }
+        gemv<T, EPI>(st, (const T *)Wt, n_out, n_in, in, (size_t)n_in, B, res_f, out);
+    };
     bool pair_done = false;   // [dkraw | dV] of position i was already prepared by the query after it
     for (int i = N - 1; i >= 0; --i) {
         const size_t ro = (size_t)i * B;
         if (!pair_done)
             hipLaunchKernelGGL(bw_pair_grad_kernel<T>, dim3(BH), dim3(64), 0, st, Bf.dK, Bf.dV, Bf.kv, Bf.rk, g_k, Bf.dkraw, Bf.in_kv, i, B,
                                H, nf);
-        gemv<T, EPI_KV>(st, (const T *)Bf.WkvT, d, 2 * d, Bf.in_kv, 2 * (size_t)d, B, nullptr, Bf.d_rz + ro * d);
+        product(plain, Bf.WkvT, d, 2 * d, Bf.in_kv, nullptr, Bf.d_rz + ro * d);
         hipLaunchKernelGGL((bw_norm_bw_row_kernel<T, T>), dim3(B), blk, 0, st, Bf.d_rz, Bf.unit_z, Bf.rinv_z, g_kv, gy + (size_t)i * d,
                            (size_t)N * d, Bf.Gz, Bf.dmo, D.alpha, i, B, d, nf);
-        gemv<T, EPI_MUL>(st, (const T *)Bf.W2T, F, d, Bf.dmo, (size_t)d, B, Bf.gp + ro * F, Bf.dpre + ro * F);
-        gemv<T, EPI_KV>(st, (const T *)Bf.W1T, d, F, Bf.dpre + ro * F, (size_t)F, B, nullptr, Bf.t1 + ro * d);
+        product(times, Bf.W2T, F, d, Bf.dmo, Bf.gp + ro * F, Bf.dpre + ro * F);
+        product(plain, Bf.W1T, d, F, Bf.dpre + ro * F, nullptr, Bf.t1 + ro * d);
         hipLaunchKernelGGL((bw_norm_bw_row_kernel<T, float>), dim3(B), blk, 0, st, Bf.t1, Bf.unit_h, Bf.rinv_h, g_mlp, Bf.Gz + ro * d,
                            (size_t)d, Bf.d_h, Bf.da, D.alpha, i, B, d, nf);
-        gemv<T, EPI_KV>(st, (const T *)Bf.WoT, d, d, Bf.da, (size_t)d, B, nullptr, Bf.dc + ro * d);
+        product(plain, Bf.WoT, d, d, Bf.da, nullptr, Bf.dc + ro * d);
         // position i - 1 lies in this query's window unless i opens a block of kBwPmin positions (then a tile follows below,
         // or i = 0): its pair gradient is complete after this query's update and is finished by the same wavefront
         const int fuse = (i & (kBwPmin - 1)) != 0 ? 1 : 0;
