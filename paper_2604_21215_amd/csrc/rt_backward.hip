@@ -237,26 +237,30 @@ __global__ __launch_bounds__(256) void bw_mm_kernel(const bf16_t *__restrict__ A
                                                     float *__restrict__ C, size_t ldc, float *__restrict__ part, int M, int Nn, int Ks,
                                                     float alpha, int accumulate)
 {
-    __shared__ __align__(16) bf16_t As[kGtRows * kGtLd];
-    __shared__ __align__(16) bf16_t Bs[kGtCols * kGtLd];
+    __shared__ __align__(16) unsigned char ring[TileMany::kLds];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int l32 = lane & 31, hi = lane >> 5;
     const int m0 = blockIdx.x * kGtRows, nb0 = blockIdx.y * kGtCols;
     const size_t k0 = (size_t)blockIdx.z * Ks;
-    const int prow = tid >> 3, pc = tid & 7;
-    const bf16_t *ga[8], *gb[4];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) ga[i] = A + (size_t)min(m0 + prow + 32 * i, M - 1) * lda + k0 + pc * 8;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) gb[i] = W + (size_t)min(nb0 + prow + 32 * i, Nn - 1) * ldb + k0 + pc * 8;
     f32x16_t acc[4][2];
-    tiled_mainloop(ga, gb, nullptr, Ks, As, Bs, acc);
+    tiled_mainloop<TileMany>([&](int r) { return A + (size_t)min(m0 + r, M - 1) * lda + k0; },
+                             [&](int r) { return W + (size_t)min(nb0 + r, Nn - 1) * ldb + k0; }, Ks, ring, acc);
     const bool split = gridDim.z > 1;
     float *out = split ? part + (size_t)blockIdx.z * M * Nn : C;
     const size_t ldo = split ? (size_t)Nn : ldc;
+    const bool adds = !split && accumulate;
 #pragma unroll
-    for (int mt = 0; mt < 4; ++mt)
+    for (int mt = 0; mt < 4; ++mt) {
+        float old[2][16];   // read for 16 rows at once, not row by row
+        if (adds) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt)
+                    old[nt][i] = out[(size_t)min(m0 + wm * 128 + mt * 32 + 8 * (i / 4) + 4 * hi + (i % 4), M - 1) * ldo +
+                                     min(nb0 + wn * 64 + nt * 32 + l32, Nn - 1)];
+        }
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const int m = m0 + wm * 128 + mt * 32 + 8 * (i / 4) + 4 * hi + (i % 4);
@@ -265,11 +269,11 @@ __global__ __launch_bounds__(256) void bw_mm_kernel(const bf16_t *__restrict__ A
             for (int nt = 0; nt < 2; ++nt) {
                 const int n = nb0 + wn * 64 + nt * 32 + l32;
                 if (n >= Nn) continue;
-                float *p = out + (size_t)m * ldo + n;
-                if (split) *p = acc[mt][nt][i];
-                else *p = accumulate ? *p + alpha * acc[mt][nt][i] : alpha * acc[mt][nt][i];
+                const float v = split ? acc[mt][nt][i] : alpha * acc[mt][nt][i];
+                out[(size_t)m * ldo + n] = adds ? old[nt][i] + v : v;
             }
         }
+    }
 }
 
 // C[m][n] (+)= alpha sum_z part[z][m][n]  (fixed order: runs are bit-reproducible)
@@ -1135,6 +1139,15 @@ hipError_t backward_layer(const LayerDims &D, const Weights &W, const void *x_, 
         hipLaunchKernelGGL(bw_to_f32_kernel<T>, grid1(dF), blk, 0, st, (const T *)W.W1, Bf.W1_f, dF);
         hipLaunchKernelGGL(bw_to_f32_kernel<T>, grid1(dF), blk, 0, st, (const T *)W.W2, Bf.W2_f, dF);
     }
+    // a matrix as an operand of the products: in place where its rows are aligned to 16 bytes, else from a copy (in the space of its
+    // fp32 copy, which the matrix-core path does not use)
+    auto operand = [&](const void *Wt, float *space, size_t n) -> const void * {
+        if (!mm || aligned16(Wt)) return Wt;
+        hipLaunchKernelGGL(bw_rows_pf_kernel, grid1(n), blk, 0, st, (const bf16_t *)Wt, (bf16_t *)space, 1, 1, (int)n);
+        return space;
+    };
+    const void *Wq = operand(W.Wq, Bf.Wqkv_f, dd), *Wk = operand(W.Wk, Bf.Wqkv_f + dd, dd), *Wv = operand(W.Wv, Bf.Wqkv_f + 2 * dd, dd);
+    const void *Wo = operand(W.Wo, Bf.Wo_f, dd), *W1 = operand(W.W1, Bf.W1_f, dF);
     auto transpose = [&](const void *in, void *out, int rows, int cols, size_t ldo, int col0) {
         hipLaunchKernelGGL(bw_transpose_kernel<T>, dim3((unsigned)((cols + 31) / 32), (unsigned)((rows + 31) / 32)), blk, 0, st,
                            (const T *)in, (T *)out, rows, cols, ldo, col0);
@@ -1155,7 +1168,7 @@ hipError_t backward_layer(const LayerDims &D, const Weights &W, const void *x_, 
                        B, N, d, D.eps, nf);
     if (mm) {
         hipLaunchKernelGGL(bw_split_rows_kernel, grid1((size_t)M * d), blk, 0, st, Bf.nxg, (size_t)d, Bf.op_hi, Bf.op_lo, (size_t)d, M, d);
-        const void *w3[3] = {W.Wq, W.Wk, W.Wv};
+        const void *w3[3] = {Wq, Wk, Wv};
         for (int j = 0; j < 3; ++j) {
             mm_nt(Bf.op_lo, d, (const bf16_t *)w3[j], d, Bf.qkv + (size_t)j * d, 3 * (size_t)d, M, d, d, 1.f, false, 1);
             mm_nt(Bf.op_hi, d, (const bf16_t *)w3[j], d, Bf.qkv + (size_t)j * d, 3 * (size_t)d, M, d, d, 1.f, true, 1);
@@ -1171,7 +1184,7 @@ hipError_t backward_layer(const LayerDims &D, const Weights &W, const void *x_, 
                        B, N, d, D.eps, nf);
     if (mm) {
         hipLaunchKernelGGL(bw_split_rows_kernel, grid1((size_t)M * d), blk, 0, st, Bf.nzg, (size_t)d, Bf.op_hi, Bf.op_lo, (size_t)d, M, d);
-        const void *w2[2] = {W.Wk, W.Wv};
+        const void *w2[2] = {Wk, Wv};
         for (int j = 0; j < 2; ++j) {
             mm_nt(Bf.op_lo, d, (const bf16_t *)w2[j], d, Bf.kv + (size_t)j * d, 2 * (size_t)d, M, d, d, 1.f, false, 1);
             mm_nt(Bf.op_hi, d, (const bf16_t *)w2[j], d, Bf.kv + (size_t)j * d, 2 * (size_t)d, M, d, d, 1.f, true, 1);
@@ -1198,10 +1211,10 @@ hipError_t backward_layer(const LayerDims &D, const Weights &W, const void *x_, 
         hipLaunchKernelGGL(bw_attn_fwd_kernel, dim3(BH, N), dim3(64), 0, st, Bf.Qn, Bf.Ktn, Bf.Vt, Bf.Kp, Bf.Vp, Bf.c, Bf.lse, B, H, D.scale,
                            D.alibi);
     }
-    act_times_w(Bf.c, W.Wo, Bf.Wo_f, Bf.a, (size_t)d, d);
+    act_times_w(Bf.c, Wo, Bf.Wo_f, Bf.a, (size_t)d, d);
     hipLaunchKernelGGL(bw_rows_norm_kernel<T>, dim3(M), blk, 0, st, x, Bf.a, D.alpha, g_mlp, Bf.unit_h, Bf.hg, Bf.rinv_h, B, N, d, D.eps,
                        nf);
-    act_times_w(Bf.hg, W.W1, Bf.W1_f, Bf.gp, (size_t)F, F);
+    act_times_w(Bf.hg, W1, Bf.W1_f, Bf.gp, (size_t)F, F);
     hipLaunchKernelGGL(bw_gelu_kernel, grid1((size_t)M * F), blk, 0, st, Bf.gp, Bf.act, Bf.gp, (size_t)M * F);
 
     // ---- (B) the reverse loop

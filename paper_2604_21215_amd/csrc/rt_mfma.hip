@@ -35,15 +35,14 @@ __global__ __launch_bounds__(256) void prepass_mfma_kernel(const bf16_t *__restr
 // tiles and the 32 lanes of its half of the wavefront.  grid (ceil(M / 256), 3 d / 128), block 256.
 __global__ __launch_bounds__(256) void prepass_tiled_kernel(const bf16_t *__restrict__ x, const float *__restrict__ rinv,
                                                             const bf16_t *__restrict__ Wq, const bf16_t *__restrict__ Wk,
-                                                            const bf16_t *__restrict__ Wv, const bf16_t *__restrict__ g_attn,
-                                                            const bf16_t *__restrict__ g_q, const bf16_t *__restrict__ g_k,
+                                                            const bf16_t *__restrict__ Wv, const bf16_t *__restrict__ g_q,
+                                                            const bf16_t *__restrict__ g_k,
                                                             bf16_t *__restrict__ Q, bf16_t *__restrict__ Kt,
                                                             bf16_t *__restrict__ Vt, float *__restrict__ Qf,
                                                             float *__restrict__ Ktf, int Bc, int Nc, size_t x_bstride,
                                                             int n0, int d, int H, float eps, int norm_free)
 {
-    __shared__ __align__(16) bf16_t As[kGtRows * kGtLd];
-    __shared__ __align__(16) bf16_t Bs[kGtCols * kGtLd];
+    __shared__ __align__(16) unsigned char ring[TileMany::kLds];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int l32 = lane & 31, hi = lane >> 5;
@@ -52,18 +51,13 @@ __global__ __launch_bounds__(256) void prepass_tiled_kernel(const bf16_t *__rest
     const int c0 = blockIdx.y * kGtCols;          // first of the block's columns of [q | k_tmp | v_tmp]
     const int bw = c0 / d;                         // d is a multiple of 128: a block lies within one of the three
     const bf16_t *Wb = (bw == 0 ? Wq : (bw == 1 ? Wk : Wv)) + (size_t)(c0 - bw * d) * d;
-    const int prow = tid >> 3, pc = tid & 7;
-    const bf16_t *ga[8], *gb[4];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int mr = min(m0 + prow + 32 * i, M - 1);
-        ga[i] = x + (size_t)(mr / Nc) * x_bstride + (size_t)(n0 + mr % Nc) * d + pc * 8;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) gb[i] = Wb + (size_t)(prow + 32 * i) * d + pc * 8;
-
     f32x16_t acc[4][2];
-    tiled_mainloop(ga, gb, (g_attn != nullptr && !norm_free) ? g_attn : nullptr, d, As, Bs, acc);
+    tiled_mainloop<TileMany>(
+        [&](int r) {
+            const int mr = min(m0 + r, M - 1);
+            return x + (size_t)(mr / Nc) * x_bstride + (size_t)(n0 + mr % Nc) * d;
+        },
+        [&](int r) { return Wb + (size_t)r * d; }, d, ring, acc);
 
     const int hcol = c0 - bw * d + wn * 64;        // first column of this wavefront's head within its output
     const bool normed = bw < 2 && !norm_free;
@@ -77,21 +71,30 @@ __global__ __launch_bounds__(256) void prepass_tiled_kernel(const bf16_t *__rest
     }
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
+        const int mb = m0 + wm * 128 + mt * 32;
+        float rs[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) rs[i] = norm_free ? 1.f : rinv[min(mb + 8 * (i / 4) + 4 * hi + (i % 4), M - 1)];
+        const int bb = mb / Nc, nb = mb % Nc;      // batch row and position of the tile's first row
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const int m = m0 + wm * 128 + mt * 32 + 8 * (i / 4) + 4 * hi + (i % 4);
-            const float rs = norm_free ? 1.f : rinv[min(m, M - 1)];
-            const float v0 = acc[mt][0][i] * rs, v1 = acc[mt][1][i] * rs;
+            const int dm = 8 * (i / 4) + 4 * hi + (i % 4), m = mb + dm;
+            const float v0 = acc[mt][0][i] * rs[i], v1 = acc[mt][1][i] * rs[i];
             float sc = 1.f;
             if (normed) {
-                float ss = fmaf(v0, v0, v1 * v1);
-#pragma unroll
-                for (int o = 16; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);   // the 32 lanes that share hi
+                float ss = sum16(fmaf(v0, v0, v1 * v1));
+                ss += __shfl_xor(ss, 16, 64);   // the 32 lanes that share hi
                 sc = rsqrtf(ss / (float)kHeadDim + eps);
             }
             if (m < M) {
-                const int b = m / Nc, n = n0 + m % Nc;
-                const size_t oo = ((size_t)n * Bc + b) * d + hcol + l32;
+                int b = bb, n = nb + dm;
+                if (Nc >= 32) {                  // at most one batch row ends within the tile's 32 rows
+                    if (n >= Nc) { n -= Nc; ++b; }
+                } else {
+                    b = m / Nc;
+                    n = m % Nc;
+                }
+                const size_t oo = ((size_t)(n0 + n) * Bc + b) * d + hcol + l32;
                 const float o0 = v0 * sc * gc[0], o1 = v1 * sc * gc[1];
                 dst[oo] = f32_to_bf16(o0);
                 dst[oo + 32] = f32_to_bf16(o1);
@@ -128,16 +131,18 @@ hipError_t prepass_mfma_launch(const LayerDims &D, const Weights &W, const Scrat
                                size_t x_bstride, int n0, hipStream_t st)
 {
     const int M = Bc * Nc;
-    if (M >= kTiledMinRows && D.d % 128 == 0) {
-        const bf16_t *wq = (const bf16_t *)W.Wq, *wk = (const bf16_t *)W.Wk, *wv = (const bf16_t *)W.Wv, *ga = (const bf16_t *)W.g_attn;
-        if (ga && !D.norm_free && S.wg_qkv) {   // the gain goes into the matrices' columns
+    const bool gained = W.g_attn && !D.norm_free;   // the tiled kernel wants the gain in the matrices' columns
+    if (M >= kTiledMinRows && D.d % 128 == 0 && (!gained || S.wg_qkv) && aligned16(x) &&
+        (gained || (aligned16(W.Wq) && aligned16(W.Wk) && aligned16(W.Wv)))) {
+        const bf16_t *wq = (const bf16_t *)W.Wq, *wk = (const bf16_t *)W.Wk, *wv = (const bf16_t *)W.Wv;
+        if (gained) {
             const size_t pieces = 3 * (size_t)D.d * D.d / 8;
-            hipLaunchKernelGGL(scale_qkv_columns_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st, wq, wk, wv, ga,
-                               S.wg_qkv, D.d);
-            wq = S.wg_qkv; wk = wq + (size_t)D.d * D.d; wv = wk + (size_t)D.d * D.d; ga = nullptr;
+            hipLaunchKernelGGL(scale_qkv_columns_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st, wq, wk, wv,
+                               (const bf16_t *)W.g_attn, S.wg_qkv, D.d);
+            wq = S.wg_qkv; wk = wq + (size_t)D.d * D.d; wv = wk + (size_t)D.d * D.d;
         }
         hipLaunchKernelGGL(prepass_tiled_kernel, dim3((M + kGtRows - 1) / kGtRows, 3 * D.d / kGtCols), dim3(256), 0, st,
-                           (const bf16_t *)x, S.rinv, wq, wk, wv, ga, (const bf16_t *)W.g_q, (const bf16_t *)W.g_k, (bf16_t *)S.Q,
+                           (const bf16_t *)x, S.rinv, wq, wk, wv, (const bf16_t *)W.g_q, (const bf16_t *)W.g_k, (bf16_t *)S.Q,
                            (bf16_t *)S.Kt, (bf16_t *)S.Vt, S.Qf, S.Ktf, Bc, Nc, x_bstride, n0, D.d, D.H, D.eps, D.norm_free);
         return hipGetLastError();
     }

@@ -139,51 +139,61 @@ __global__ __launch_bounds__(256) void tiled_gemm_kernel(const bf16_t *__restric
                                                          const bf16_t *__restrict__ res_b, const float *__restrict__ res_f,
                                                          float *__restrict__ out_f, bf16_t *__restrict__ out_b)
 {
-    __shared__ __align__(16) bf16_t As[kGtRows * kGtLd];
-    __shared__ __align__(16) bf16_t Bs[kGtCols * kGtLd];
+    __shared__ __align__(16) unsigned char ring[TileMany::kLds];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int l32 = lane & 31, hi = lane >> 5;
     const int m0 = blockIdx.x * kGtRows, nb0 = blockIdx.y * kGtCols;
-    const int prow = tid >> 3, pc = tid & 7;
-    const bf16_t *ga[8], *gb[4];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int mr = min(m0 + prow + 32 * i, M - 1);
-        ga[i] = A + ((size_t)(mr / Nc) * N + n0 + mr % Nc) * K + pc * 8;
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) gb[i] = W + (size_t)(nb0 + prow + 32 * i) * K + pc * 8;
-
     f32x16_t acc[4][2];
-    tiled_mainloop(ga, gb, nullptr, K, As, Bs, acc);
+    tiled_mainloop<TileMany>(
+        [&](int r) {
+            const int mr = min(m0 + r, M - 1);
+            return A + ((size_t)(mr / Nc) * N + n0 + mr % Nc) * K;
+        },
+        [&](int r) { return W + (size_t)(nb0 + r) * K; }, K, ring, acc);
 
     float gcol[2] = {1.f, 1.f};
     if (EPI == PG_WO && gain != nullptr && !norm_free) {
 #pragma unroll
         for (int nt = 0; nt < 2; ++nt) gcol[nt] = bf16_to_f32(gain[nb0 + wn * 64 + nt * 32 + l32]);
     }
+    const bool whole = Nc == N;   // rows follow each other (n0 = 0)
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) {
+        // everything 16 rows read first, then their outputs: one wait per 16 rows (read and used row by row, the epilogue of
+        // W2 took a quarter of the kernel)
+        size_t at[16];
+        float r0[16], r1[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
-            const int m = m0 + wm * 128 + mt * 32 + 8 * (i / 4) + 4 * hi + (i % 4);
-            if (m < M) {
-                const size_t row = (size_t)(m / Nc) * N + n0 + m % Nc;
-                const float rs = (EPI == PG_W1 && !norm_free) ? rinv[m] : 1.f;
+            const int m = min(m0 + wm * 128 + mt * 32 + 8 * (i / 4) + 4 * hi + (i % 4), M - 1);
+            const size_t row = whole ? (size_t)m : (size_t)(m / Nc) * N + n0 + m % Nc;
+            at[i] = row * Nn + nb0 + wn * 64 + l32;
+            if (EPI == PG_WO) {
+                r0[i] = bf16_to_f32(res_b[at[i]]);
+                r1[i] = bf16_to_f32(res_b[at[i] + 32]);
+            } else if (EPI == PG_W1) {
+                r0[i] = norm_free ? 1.f : rinv[m];
+            } else {
+                r0[i] = res_f[at[i]];
+                r1[i] = res_f[at[i] + 32];
+            }
+        }
 #pragma unroll
-                for (int nt = 0; nt < 2; ++nt) {
-                    const size_t o = row * Nn + nb0 + wn * 64 + nt * 32 + l32;
-                    const float c = acc[mt][nt][i];
-                    if (EPI == PG_WO) {
-                        const float h = bf16_to_f32(res_b[o]) + alpha * c;
-                        out_f[o] = h;
-                        out_b[o] = f32_to_bf16(h * gcol[nt]);
-                    } else if (EPI == PG_W1) {
-                        out_b[o] = f32_to_bf16(gelu_bf16_out(c * rs));
-                    } else {
-                        out_b[o] = f32_to_bf16(res_f[o] + alpha * c);
-                    }
+        for (int i = 0; i < 16; ++i) {
+            if (m0 + wm * 128 + mt * 32 + 8 * (i / 4) + 4 * hi + (i % 4) >= M) continue;
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt) {
+                const size_t o = at[i] + 32 * nt;
+                const float c = acc[mt][nt][i];
+                if (EPI == PG_WO) {
+                    const float h = (nt == 0 ? r0[i] : r1[i]) + alpha * c;
+                    out_f[o] = h;
+                    out_b[o] = f32_to_bf16(h * gcol[nt]);
+                } else if (EPI == PG_W1) {
+                    out_b[o] = f32_to_bf16(gelu_bf16_out(c * r0[i]));
+                } else {
+                    out_b[o] = f32_to_bf16((nt == 0 ? r0[i] : r1[i]) + alpha * c);
                 }
             }
         }
@@ -905,7 +915,7 @@ static void block_gemms(const LayerDims &D, const Weights &W, const void *x, voi
                                      D.norm_free, D.alpha, nullptr, h_f, nullptr, (bf16_t *)y, none);
         return;
     }
-    if (d % 128 == 0 && F % 128 == 0) {   // both operands through LDS
+    if (d % 128 == 0 && F % 128 == 0 && aligned16(W.Wo) && aligned16(W.W1) && aligned16(W.W2)) {   // both operands through LDS
         const unsigned gt = (unsigned)((M + 255) / 256);
         hipLaunchKernelGGL(tiled_gemm_kernel<PG_WO>, dim3(gt, (unsigned)(d / 128)), dim3(256), 0, st, a_b, (const bf16_t *)W.Wo, M, d, d,
                            Nc, D.N, n0, (const bf16_t *)W.g_mlp, (const float *)nullptr, D.norm_free, D.alpha, (const bf16_t *)x,
