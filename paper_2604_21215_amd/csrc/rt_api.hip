@@ -62,9 +62,8 @@ static const char *kNoCtx = "no context";
 // Side streams of the layer-wavefront engine, lent to a call for the time it enqueues its work.  A process has four hardware
 // queues and a stream keeps the one it was given: with two side streams per context the streams of several contexts share
 // queues with each other and with the caller's stream, and groups of layers that should overlap run one after the other
-// (12 layers,
-// B = 4, N = 4096: 285 ms for the only context of a process, 420 - 725 ms for some of several, 284 ms for all of them from here).  Calls that follow one another take
-// the same streams from here; calls on several threads at once take different ones.  A lent stream goes back with work still
+// (12 layers, B = 4, N = 4096: 285 ms for the only context of a process, 420 - 725 ms for some of several, 284 ms for all of them
+// from here).  Calls that follow one another take the same streams from here; calls on several threads at once take different ones.  A lent stream goes back with work still
 // queued on it: the next call's work on it follows in order, and every wait inside a call is for work enqueued before it, so
 // no two calls can wait for each other.  At most kPooledSets sets stay; the last context of the process gives all of them back.
 // A call that is being captured uses streams of its own context: a pooled stream would stay part of the capture.
@@ -246,7 +245,7 @@ static rt_status stack_workspace(rt_ctx *c, int L, int chunk);
 // the batched steps 40.8 ms at B = 80, 41.3 at B = 96, 42.4 at B = 128)
 constexpr int kBatchedFrom = 81;
 // ... and between these batch sizes the layer-wavefront engine with a single layer (its small-M products on the matrix cores, a
-// batch tile of 16 rows per workgroup) is faster than both (same shapes, ms per call at B = 48 / 56 / 64 / 80 / 128 / 160: chunks
+// batch tile of 16 rows per workgroup then) is faster than both (same shapes, ms per call at B = 48 / 56 / 64 / 80 / 128 / 160: chunks
 // 23.6 / 30.7 / 31.4 / 39.3 / - / -, batched steps 35.4 / 37.5 / 39.8 / 40.5 / 41.7 / 48.4, this engine 28.5 / 28.3 / 29.2 / 30.9 /
 // 33.2 / 49.2)
 constexpr int kWaveFrom = 49, kWaveTo = 128;

@@ -574,7 +574,7 @@ __global__ __launch_bounds__(256) void par_export_tile_kernel(const bf16_t *__re
     *reinterpret_cast<uint4 *>(dst + 8) = make_uint4(w[4], w[5], w[6], w[7]);
 }
 
-// a_t of positions t0 .. t0 + gridDim.y - 1 (merge_body) as bf16 rows of [B][N][d].  grid (B*H, positions), block 64.
+// a_t of positions t0 .. t0 + gridDim.y - 1 (merge_body) as bf16 rows t - row0 of [B][N][d].  grid (B*H, positions), block 64.
 __global__ __launch_bounds__(64) void par_merge_kernel(const bf16_t *__restrict__ Q, const float *__restrict__ Qf,
                                                        const bf16_t *__restrict__ Kt, const float *__restrict__ Ktf,
                                                        const bf16_t *__restrict__ Vt, const bf16_t *__restrict__ K,
@@ -582,13 +582,13 @@ __global__ __launch_bounds__(64) void par_merge_kernel(const bf16_t *__restrict_
                                                        const float *__restrict__ pm, const float *__restrict__ pl,
                                                        const float *__restrict__ po, bf16_t *__restrict__ a_out, int BH, int H,
                                                        int N, int p_min, int log2_pmin, int levels, int slots, float scale,
-                                                       float alibi, int t0)
+                                                       float alibi, int t0, int row0)
 {
     const int bh = blockIdx.x, t = t0 + blockIdx.y;
     const float a = merge_body<bf16_t, true>(Q, Qf, Kt, Ktf, Vt, K, Klo, V, pm, pl, po, nullptr, BH, H, bh, t, t, p_min, log2_pmin,
                                              levels, slots, -1, scale, -1, 0, nullptr, alibi);
     const int b = bh / H, h = bh % H;
-    a_out[((size_t)b * N + t) * ((size_t)H * kHeadDim) + h * kHeadDim + threadIdx.x] = f32_to_bf16(a);
+    a_out[((size_t)b * N + t - row0) * ((size_t)H * kHeadDim) + h * kHeadDim + threadIdx.x] = f32_to_bf16(a);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -1085,6 +1085,180 @@ hipError_t parallel_layer(const LayerDims &D, const Weights &W, const Scratch &S
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------------------------
+// The four products of ONE position of many sequences (blocked_layer with blocks of one position): B rows of compact operands,
+// k-tiles loaded straight into LDS.  The untiled kernels read their fragments from global memory, rows 2 or 8 KB apart, in the middle
+// of the contraction's dependent steps: 54 (W1), 38 (W2), 34 (pairs) and 17 us (Wo) at 1024 rows, d = 1024, for products whose
+// operands pass through a compute unit's LDS in 3 - 8 us.  Two groups of wavefronts share a k-tile: one wavefront per SIMD
+// would wait for every fragment.  Now 19, 20, 13 and 10 us; 256 positions of 1024 sequences 54.4 -> 32.7 ms.
+//   SG_WO: h = x + alpha C (fp32), its row times the MLP's gain in bf16, partial sums of squares of h per 32 columns
+//   SG_W1: u = gelu(C / rms(h)), the statistic from those partial sums
+//   SG_W2: y = z = h + alpha C, its row times the pairs' gain in bf16 (from the unrounded z), partial sums of squares of z
+//   SG_KV: k (normalised per head) and v = C / rms(z) into the cache rows and their copies; a wavefront owns one head of its rows
+// grid (Nn / kCols, ceil(B / kRows)): the column tiles of an XCD are the same at every position, its L2 keeps their share of W.
+// ---------------------------------------------------------------------------------------------
+enum { SG_WO = 0, SG_W1 = 1, SG_W2 = 2, SG_KV = 3 };
+using StepTile64 = GemmTile<1, 1, 2, 128, 4>;     // 64 x 64 outputs
+using StepTile128 = GemmTile<2, 2, 2, 64, 4>;     // 128 x 128
+using StepTileHeads = GemmTile<1, 2, 2, 64, 4>;   // 64 x 128: two heads
+
+struct StepArgs {
+    const bf16_t *A, *W, *W2nd;   // A [B][K]; W2nd: Wv (SG_KV)
+    int B, Nn, K, N, t, H, norm_free;
+    float alpha, eps;
+    const bf16_t *gain;           // of the next product's input (SG_WO, SG_W2), g_k (SG_KV); may be null
+    const bf16_t *x;              // SG_WO: residual rows of [B][N][d]
+    const float *ssq_in;          // SG_W1, SG_KV: [B][K / 32]
+    float *h, *ssq_out;           // h [B][d]: written by SG_WO, read by SG_W2
+    bf16_t *out_b, *y;            // the next product's input [B][Nn]; SG_W2: rows of [B][N][d]
+    bf16_t *K_, *V_, *Klo;        // SG_KV: position-major cache rows
+    uint16_t *Kh;
+};
+
+template <int EPI, class T>
+__global__ __launch_bounds__(T::kThreads) void step_gemm_kernel(StepArgs P)
+{
+    __shared__ __align__(16) unsigned char ring[T::kLds];
+    __shared__ float rs_s[T::kRows];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = (wave >> 1) & 1, wn = wave & 1, kg = wave >> 2;
+    const int l32 = lane & 31, hi = lane >> 5;
+    const int nb0 = blockIdx.x * T::kCols, m0 = blockIdx.y * T::kRows;
+    const bool second = EPI == SG_KV && nb0 >= P.K;   // the values (square projection: K = d)
+    const bf16_t *W = second ? P.W2nd - (size_t)P.K * P.K : P.W;
+    f32x16_t acc[T::MT][T::NT];
+    tiled_mainloop<T>([&](int r) { return P.A + (size_t)min(m0 + r, P.B - 1) * P.K; }, [&](int r) { return W + (size_t)(nb0 + r) * P.K; },
+                      P.K, ring, acc, [&] {
+                          if (EPI != SG_W1 && EPI != SG_KV) return;
+                          constexpr int PER = T::kThreads / T::kRows;   // threads per row: neighbouring lanes (parts is a multiple of 4)
+                          const int r = tid / PER, parts = P.K / 32;
+                          const float *in = P.ssq_in + (size_t)min(m0 + r, P.B - 1) * parts;
+                          float s = 0.f;
+                          for (int j = 4 * (tid % PER); j < parts; j += 4 * PER) {
+                              const float4 q = *reinterpret_cast<const float4 *>(in + j);
+                              s += (q.x + q.y) + (q.z + q.w);
+                          }
+#pragma unroll
+                          for (int o = 1; o < PER; o *= 2) s += __shfl_xor(s, o, 64);
+                          if (tid % PER == 0) rs_s[r] = P.norm_free ? 1.f : rsqrtf(s / (float)P.K + P.eps);
+                      });
+    static_assert(T::KG == 2, "a wavefront finishes eight registers of every tile");
+    const int colw = nb0 + 32 * T::NT * wn + l32;
+    float gcol[T::NT];
+#pragma unroll
+    for (int nt = 0; nt < T::NT; ++nt) {
+        const int c = EPI == SG_KV ? (colw + 32 * nt) % P.K : colw + 32 * nt;
+        gcol[nt] = EPI != SG_W1 && P.gain != nullptr && !P.norm_free && !second ? bf16_to_f32(P.gain[c]) : 1.f;
+    }
+#pragma unroll
+    for (int mt = 0; mt < T::MT; ++mt) {
+        float c[T::NT][8], res[T::NT][8];
+        int b[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            // register i = 8 kg + e: row 8 (i / 4) + 4 hi + i % 4 of the tile
+            const int r = 32 * T::MT * wm + 32 * mt + 16 * kg + 8 * (e / 4) + 4 * hi + e % 4;
+            b[e] = m0 + r;
+            const int bl = min(b[e], P.B - 1);
+            const float rs = EPI == SG_W1 || EPI == SG_KV ? rs_s[r] : 1.f;
+#pragma unroll
+            for (int nt = 0; nt < T::NT; ++nt) {
+                c[nt][e] = acc[mt][nt][e] * rs;
+                if (EPI == SG_WO) res[nt][e] = bf16_to_f32(P.x[((size_t)bl * P.N + P.t) * P.Nn + colw + 32 * nt]);
+                if (EPI == SG_W2) res[nt][e] = P.h[(size_t)bl * P.Nn + colw + 32 * nt];
+            }
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const bool live = b[e] < P.B;
+            if constexpr (EPI == SG_WO || EPI == SG_W2) {
+#pragma unroll
+                for (int nt = 0; nt < T::NT; ++nt) {
+                    const int col = colw + 32 * nt;
+                    const size_t o = (size_t)b[e] * P.Nn + col;
+                    const float v = res[nt][e] + P.alpha * c[nt][e];
+                    if (live) {
+                        if (EPI == SG_WO) P.h[o] = v;
+                        else P.y[((size_t)b[e] * P.N + P.t) * P.Nn + col] = f32_to_bf16(v);
+                        P.out_b[o] = f32_to_bf16(v * gcol[nt]);
+                    }
+                    float ss = sum16(v * v);
+                    ss += __shfl_xor(ss, 16, 64);
+                    if (l32 == 0 && live) P.ssq_out[(size_t)b[e] * (P.Nn / 32) + col / 32] = ss;
+                }
+            } else if constexpr (EPI == SG_W1) {
+#pragma unroll
+                for (int nt = 0; nt < T::NT; ++nt)
+                    if (live) P.out_b[(size_t)b[e] * P.Nn + colw + 32 * nt] = f32_to_bf16(gelu_erf(c[nt][e]));
+            } else {
+                static_assert(EPI != SG_KV || T::NT == 2, "a wavefront's columns are one head");
+                float sc = 1.f;
+                if (!second && !P.norm_free) {
+                    float ss = sum16(fmaf(c[0][e], c[0][e], c[1][e] * c[1][e]));
+                    ss += __shfl_xor(ss, 16, 64);
+                    sc = rsqrtf(ss / (float)kHeadDim + P.eps);
+                }
+                if (!live) continue;
+                const size_t o = ((size_t)P.t * P.B + b[e]) * P.K + (colw - (second ? P.K : 0));
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt) {
+                    const float v = c[nt][e] * sc * gcol[nt];
+                    const bf16_t hb = f32_to_bf16(v);
+                    if (second) {
+                        P.V_[o + 32 * nt] = hb;
+                    } else {
+                        P.K_[o + 32 * nt] = hb;
+                        P.Klo[o + 32 * nt] = f32_to_bf16(v - bf16_to_f32(hb));
+                        P.Kh[o + 32 * nt] = f32_to_f16_bits(v);
+                    }
+                }
+            }
+        }
+    }
+}
+
+template <int EPI, class T> static void step_gemm(const StepArgs &P, hipStream_t st)
+{
+    hipLaunchKernelGGL((step_gemm_kernel<EPI, T>), dim3((unsigned)(P.Nn / T::kCols), (unsigned)((P.B + T::kRows - 1) / T::kRows)),
+                       dim3(T::kThreads), 0, st, P);
+}
+
+// From 129 sequences on (fewer reach this engine only at widths the layer-wavefront engine does not take), where the split-contraction
+// kernels are slower throughout: 512 positions of 160 / 256 / 512 sequences, d = 1024: 45.7 / 49.0 / 68.2 -> 29.8 / 32.9 / 44.3 ms.
+// Both widths multiples of 128: whole k-tiles and column tiles.
+static bool step_products(const LayerDims &D, const Weights &W)
+{
+    return D.B >= 129 && D.d % 128 == 0 && D.F % 128 == 0 && aligned16(W.Wo) && aligned16(W.W1) && aligned16(W.W2) && aligned16(W.Wk) &&
+           aligned16(W.Wv);
+}
+
+// position t from the merged attention rows a [B][d] to the cache row: operands in the scratch of one position
+static void step_position(const LayerDims &D, const Weights &W, const Scratch &S, const void *x, void *y, void *K, void *V, int t,
+                          hipStream_t st)
+{
+    const int d = D.d, F = D.F;
+    StepArgs P = {};
+    P.B = D.B; P.N = D.N; P.t = t; P.H = D.H; P.norm_free = D.norm_free; P.alpha = D.alpha; P.eps = D.eps;
+    P.h = S.h;
+    // h = x + alpha Wo a
+    P.A = S.op_a; P.W = (const bf16_t *)W.Wo; P.Nn = d; P.K = d; P.gain = (const bf16_t *)W.g_mlp; P.x = (const bf16_t *)x;
+    P.out_b = S.op_h; P.ssq_out = S.ssq_h;
+    step_gemm<SG_WO, StepTile64>(P, st);
+    // u = gelu(W1 RMS(h))
+    P.A = S.op_h; P.W = (const bf16_t *)W.W1; P.Nn = F; P.ssq_in = S.ssq_h; P.out_b = S.op_u;
+    // 128 x 128 tiles move half the operand bytes of the 64 x 64 ones, where there are enough of them for three quarters of the chip
+    if ((size_t)(F / 128) * ((D.B + 127) / 128) >= 192) step_gemm<SG_W1, StepTile128>(P, st);
+    else step_gemm<SG_W1, StepTile64>(P, st);
+    // y = h + alpha W2 u
+    P.A = S.op_u; P.W = (const bf16_t *)W.W2; P.Nn = d; P.K = F; P.gain = (const bf16_t *)W.g_kv; P.out_b = S.op_z; P.ssq_out = S.ssq_z;
+    P.y = (bf16_t *)y;
+    step_gemm<SG_W2, StepTile64>(P, st);
+    // k, v = [Wk; Wv] RMS(z)
+    P.A = S.op_z; P.W = (const bf16_t *)W.Wk; P.W2nd = (const bf16_t *)W.Wv; P.Nn = 2 * d; P.K = d; P.gain = (const bf16_t *)W.g_k;
+    P.ssq_in = S.ssq_z; P.K_ = (bf16_t *)K; P.V_ = (bf16_t *)V; P.Klo = S.Klo; P.Kh = S.Kh;
+    step_gemm<SG_KV, StepTileHeads>(P, st);
+}
+
 // Blocked recurrence (Sec. 8, Discussion; the reading is stated at rt_layer_prefill_blocked in rt.h): blocks of Sblk
 // positions, a power of two that divides p_min, so that every event of Algorithm 1 falls on a block boundary.  While
 // a block is evaluated its rows of K, V hold the TEMPORARY pairs (the direct window of merge_body then reads
@@ -1133,19 +1307,22 @@ hipError_t blocked_layer(const LayerDims &D, const Weights &W, const Scratch &S,
     // rows receive the persistent pairs when it is done
     hipLaunchKernelGGL(par_export_tile_kernel, dim3(BH, (N + 63) / 64), dim3(256), 0, st, (const bf16_t *)S.Kt, S.Ktf,
                        (const bf16_t *)S.Vt, (bf16_t *)K, (bf16_t *)V, S.Klo, S.Kh, S.VT, S.vt_stride, BH, N);
+    const bool by_steps = D.p_min % 32 == 0 && step_products(D, W);
     for (int t0 = 0; t0 < N; t0 += Sblk) {
         const int nr = Sblk < N - t0 ? Sblk : N - t0;
+        const bool step = Sblk == 1 && by_steps;
         hipLaunchKernelGGL(par_merge_kernel, dim3(BH, nr), dim3(64), 0, st, (const bf16_t *)S.Q, S.Qf, (const bf16_t *)S.Kt, S.Ktf,
-                           (const bf16_t *)S.Vt, (const bf16_t *)K, S.Klo, (const bf16_t *)V, S.pm, S.pl, S.po, a_b, BH, D.H, N,
-                           D.p_min, D.log2_pmin, S.levels, S.slots, D.scale, D.alibi, t0);
-        block_gemms(D, W, x, y, a_b, h_f, h_b, u_b, S.rinv, t0, nr, st);
+                           (const bf16_t *)S.Vt, (const bf16_t *)K, S.Klo, (const bf16_t *)V, S.pm, S.pl, S.po, step ? S.op_a : a_b, BH,
+                           D.H, step ? 1 : N, D.p_min, D.log2_pmin, S.levels, S.slots, D.scale, D.alibi, t0, step ? t0 : 0);
+        if (step) step_position(D, Wp, S, x, y, K, V, t0, st);
+        else block_gemms(D, W, x, y, a_b, h_f, h_b, u_b, S.rinv, t0, nr, st);
         // persistent pairs of the block from its outputs (rows t0.. of the pre-pass buffers are free again)
         // the tiles of Algorithm 1 are the only readers of the transposed values: with p_min a multiple of 32 it is written
         // in runs of p_min positions right before the tile that closes them
         const bool lazy_vt = D.p_min % 32 == 0;
-        if (B * nr <= kSmallM && d % 128 == 0) {
-            e = small_prepass(D, Wp, S, y, t0, nr, st, K, V, !lazy_vt);   // pairs only, written into the cache by the product's epilogue
-            if (e != hipSuccess) return e;
+        if (step || (B * nr <= kSmallM && d % 128 == 0)) {
+            // pairs only, written into the cache by the product's epilogue
+            if (!step && (e = small_prepass(D, Wp, S, y, t0, nr, st, K, V, !lazy_vt)) != hipSuccess) return e;
             if (lazy_vt && (t0 + nr) % D.p_min == 0)
                 hipLaunchKernelGGL(vt_from_rows_kernel, dim3(BH, (unsigned)(D.p_min / 32)), dim3(256), 0, st, (const bf16_t *)V, S.VT,
                                    S.vt_stride, BH, t0 + nr - D.p_min);
