@@ -38,3 +38,28 @@ def test_lm_head_tiles(oracle, d, vocab, B, norm_free):
     bound = 8 * np.sqrt(d) * 2.0 ** -24 * (np.abs(n) @ np.abs(W64).T)
     assert np.all(np.abs(got[:B] - ref) <= bound)
     assert np.all(np.isnan(got[B]))
+
+
+@pytest.mark.parametrize("d,vocab,B", [(256, 4096, 8), (512, 4096, 17), (1024, 4096, 8), (2048, 4096, 12)])
+def test_lm_head_distance_from_fp64(d, vocab, B):
+    """fp32 sums: the normalised rows carry up to 2^-24 of 1 / rms and two products' roundings (2^-24 / sqrt(3) of the norm each);
+    the sums' own roundings add about as much.  2^-23 in all, where one accumulator per logit that rounds at every matrix
+    instruction is off by 1.6e-7 (d = 256) to 4.8e-7 (d = 2048)."""
+    from paper_2604_21215_amd import binding
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(d)
+    W = (torch.randn(vocab, d, generator=g, device="cuda:0") * 0.02).bfloat16()
+    gain = (torch.randn(d, generator=g, device="cuda:0") * 0.1 + 1).bfloat16()
+    z = torch.randn(B, d, generator=g, device="cuda:0").bfloat16()
+    ctx = binding.RTContext(d, d // 64, 4 * d, B, 8, "bf16", rms_eps=1e-6, stream=torch.cuda.current_stream().cuda_stream)
+    try:
+        out = torch.empty((B, vocab), dtype=torch.float32, device="cuda:0")
+        ctx.rt_lm_head(W, gain, z, d, B, out)
+        torch.cuda.synchronize()
+    finally:
+        ctx.rt_destroy()
+    z64 = z.double().cpu()
+    ref = z64 / (z64.square().mean(-1, keepdim=True) + 1e-6).sqrt() * gain.double().cpu() @ W.double().cpu().T
+    assert float((out.double().cpu() - ref).norm() / ref.norm()) <= 2.0 ** -23
