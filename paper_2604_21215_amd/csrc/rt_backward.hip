@@ -361,6 +361,8 @@ static void gemv(hipStream_t st, const T *W, int n_out, int n_in, const float *i
 // parts of eight significant bits (head, middle, tail: all 24 bits of it), so that every partial product is exact and the sums are fp32
 // as in the plain-ALU form.  That form is bound by its instructions: with eight batch rows per launch it reads and multiplies the
 // whole matrix once per eight rows and adds every sum across 64 lanes, 7 - 10 us a launch, 24 launches per position at 48 rows.
+// The heads' sums of 32 products are added up on the vector ALUs: an accumulator that runs through all three instructions of every
+// 32 indices rounds at each (2.4e-7 of the norm from fp64 at 4096 indices; 1.0e-7 this way, as the plain-ALU form; times equal).
 // A workgroup owns 16 NT outputs of 16 batch rows; its eight wavefronts take the 64-index pieces of the contraction in turn (a lane's
 // two fragments of a piece are 32 consecutive bytes of a weight row and 64 of an input row) and meet in LDS in a fixed order.
 // Workgroups of the same outputs are a multiple of eight apart, hence on one XCD, whose L2 keeps that share of the matrices (24 d^2
@@ -408,9 +410,10 @@ __global__ __launch_bounds__(512) void bw_mmv_kernel(const bf16_t *__restrict__ 
     const bool writes = b < 16 && b0 + b < B;
     const size_t at = (size_t)(b0 + b) * n_out + o0 + o;
     const float factor = EPI == EPI_MUL && writes ? res_f[at] : 1.f;
-    f32x4_t acc[NT];
+    constexpr f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+    f32x4_t head[NT], low[NT];
 #pragma unroll
-    for (int t = 0; t < NT; ++t) acc[t] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < NT; ++t) head[t] = low[t] = zero;
 
     // groups of two pieces, loaded one group ahead of their use (groups of four: 37.8 -> 38.6 ms per backward pass of 48 x 512)
     constexpr int G = 2;
@@ -456,12 +459,12 @@ __global__ __launch_bounds__(512) void bw_mmv_kernel(const bf16_t *__restrict__ 
                 for (int e = 0; e < 8; ++e) x[e] = xc[j][8 * s + e];
                 const Parts3 xs = split3(x);
 #pragma unroll
-                for (int t = 0; t < NT; ++t) {   // small terms first
+                for (int t = 0; t < NT; ++t) {
                     Frag w;
                     w.u = wc[j][t][s];
-                    acc[t] = mfma16(w, xs.l, acc[t]);
-                    acc[t] = mfma16(w, xs.m, acc[t]);
-                    acc[t] = mfma16(w, xs.h, acc[t]);
+                    low[t] = mfma16(w, xs.l, low[t]);
+                    low[t] = mfma16(w, xs.m, low[t]);
+                    head[t] += mfma16(w, xs.h, zero);
                 }
             }
         }
@@ -469,7 +472,7 @@ __global__ __launch_bounds__(512) void bw_mmv_kernel(const bf16_t *__restrict__ 
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) part[kw][(16 * t + 4 * g + r) * kVmLd + l16] = acc[t][r];
+        for (int r = 0; r < 4; ++r) part[kw][(16 * t + 4 * g + r) * kVmLd + l16] = head[t][r] + low[t][r];
     __syncthreads();
     if (!writes) return;
     float v = 0.f;
