@@ -126,12 +126,14 @@ __global__ __launch_bounds__(512) void lm_head_mfma_kernel(const bf16_t *__restr
 #pragma unroll 4
         for (int k = lane; k < d; k += 64) {
             const float v = bf16_to_f32(zr[k]) * (rinv * ((g && !norm_free) ? bf16_to_f32(g[k]) : 1.f));
-            const bf16_t p0 = f32_to_bf16(v);
-            const float r1 = (p0 & 0x7F80u) == 0x7F80u ? 0.f : v - bf16_to_f32(p0);   // an infinity has no remainder
-            const bf16_t p1 = f32_to_bf16(r1);
-            zs[(size_t)b * ld + k] = p0;
-            zs[(size_t)(bt + b) * ld + k] = p1;
-            zs[(size_t)(2 * bt + b) * ld + k] = f32_to_bf16(r1 - bf16_to_f32(p1));
+            // by truncation, as a value beyond the largest bf16 has a finite head then; every difference is exact
+            const uint32_t p0 = __float_as_uint(v) & 0xFFFF0000u;
+            const float r1 = (p0 & 0x7F800000u) == 0x7F800000u ? 0.f : v - __uint_as_float(p0);   // an infinity has no remainder
+            const uint32_t p1 = __float_as_uint(r1) & 0xFFFF0000u;
+            const uint32_t p2 = __float_as_uint(r1 - __uint_as_float(p1));
+            zs[(size_t)b * ld + k] = (bf16_t)(p0 >> 16);
+            zs[(size_t)(bt + b) * ld + k] = (bf16_t)(p1 >> 16);
+            zs[(size_t)(2 * bt + b) * ld + k] = (bf16_t)(p2 >> 16);
         }
     }
     __syncthreads();
@@ -165,7 +167,11 @@ __global__ __launch_bounds__(512) void lm_head_mfma_kernel(const bf16_t *__restr
             }
         }
         static_assert(kHeadAhead == 4, "eight partial sums");
-        const f32x4_t acc = (((head[0] + head[1]) + (head[2] + head[3])) + ((head[4] + head[5]) + (head[6] + head[7]))) + low;
+        const f32x4_t top = ((head[0] + head[1]) + (head[2] + head[3])) + ((head[4] + head[5]) + (head[6] + head[7]));
+        f32x4_t acc = top + low;
+        // an infinite weight times the other parts, zero or of the other sign, is no part of the sum: the head's product stands
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[r] = acc[r] == acc[r] ? acc[r] : top[r];
         wr = wn;
         if (col < nb) {   // lane: four consecutive vocabulary rows of batch row b0 + col
             const int v0 = tile * 16 + 4 * gk;

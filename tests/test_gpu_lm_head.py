@@ -63,3 +63,44 @@ def test_lm_head_distance_from_fp64(d, vocab, B):
     z64 = z.double().cpu()
     ref = z64 / (z64.square().mean(-1, keepdim=True) + 1e-6).sqrt() * gain.double().cpu() @ W.double().cpu().T
     assert float((out.double().cpu() - ref).norm() / ref.norm()) <= 2.0 ** -23
+
+
+@pytest.mark.parametrize("B", [2, 17])
+def test_lm_head_infinite_weights(B):
+    """one infinite weight in a row gives a signed infinity (the normalised values are cut into three parts, some of them zero or of
+    the other sign), opposite ones or a zero value under one NaN; a normalised value beyond the largest bf16 stays finite"""
+    from paper_2604_21215_amd import binding, torch_io as tio
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    d, vocab = 256, 30000
+    rng = np.random.default_rng(5)
+    z = np.zeros((B, d), np.float32)
+    z[:, :254], z[:, 254] = rng.choice((-1.0, 1.0), (B, 254)), 0.5          # 1 / rms = 1.0034...
+    g = np.ones(d, np.float32)
+    g[7:20] = gen.round_to_bf16(rng.uniform(0.5, 1.5, 13).astype(np.float32))
+    g[5] = np.float32(2.0 ** 128 - 2.0 ** 120)                              # the largest bf16
+    W = gen.round_to_bf16((rng.standard_normal((vocab, d)) * 0.05).astype(np.float32))
+    W[:, 5] = 0.0
+    for v in range(256):                                                     # every place of an infinite weight
+        W[v, v] = np.inf if v % 3 else -np.inf
+    W[5, 5] = 2.0 ** -100
+    W[300, 3], W[300, 90], W[301, 3], W[301, 90] = np.inf, -np.inf, np.inf, np.inf
+    W[302, 5] = 0.125
+    ctx = binding.RTContext(d, d // 64, 4 * d, B, 8, "bf16", rms_eps=1e-6, stream=torch.cuda.current_stream().cuda_stream)
+    try:
+        out = torch.empty((B, vocab), dtype=torch.float32, device="cuda:0")
+        ctx.rt_lm_head(tio.to_device(W, "bf16"), tio.to_device(g, "bf16"), tio.to_device(z, "bf16"), d, B, out)
+        torch.cuda.synchronize()
+        got = out.cpu().numpy().astype(np.float64)
+    finally:
+        ctx.rt_destroy()
+    z64 = z.astype(np.float64)
+    n = z64 / np.sqrt((z64 ** 2).mean(-1, keepdims=True) + 1e-6) * g.astype(np.float64)
+    assert 2.0 ** 128 - 2.0 ** 119 < np.abs(n).max() < 2.0 ** 128 - 2.0 ** 103   # fp32 holds it, rounding to bf16 does not
+    with np.errstate(invalid="ignore", over="ignore"):
+        ref = np.stack([(W.astype(np.float64) * n[b]).sum(-1) for b in range(B)])
+    assert np.isinf(ref[:, :255]).sum() >= 254 * B and np.isnan(ref[:, 255]).all() and np.isfinite(ref[:, 303:]).all()
+    assert np.array_equal(np.isnan(got), np.isnan(ref))
+    assert np.array_equal(np.where(np.isinf(got), np.sign(got), 0), np.where(np.isinf(ref), np.sign(ref), 0))
+    ok = np.isfinite(ref)
+    assert np.allclose(got[ok], ref[ok], rtol=1e-5, atol=1e-5)
