@@ -472,7 +472,11 @@ __global__ __launch_bounds__(512) void bw_mmv_kernel(const bf16_t *__restrict__ 
 #pragma unroll
     for (int t = 0; t < NT; ++t)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) part[kw][(16 * t + 4 * g + r) * kVmLd + l16] = head[t][r] + low[t][r];
+        for (int r = 0; r < 4; ++r) {
+            // an infinite weight times the other parts, zero or of the other sign, is no part of the sum: the head's product stands
+            const float v = head[t][r] + low[t][r];
+            part[kw][(16 * t + 4 * g + r) * kVmLd + l16] = v == v ? v : head[t][r];
+        }
     __syncthreads();
     if (!writes) return;
     float v = 0.f;

@@ -26,7 +26,7 @@ def test_backward_wide_batches(oracle, B, N, d, F, kw):
     _run(oracle, "bf16", B, N, d, d // 64, F, alpha=0.7, tol=TOL, **dict(dict(scale=0.25), **kw))
 
 
-def _mlp_dx(B, N, d, F, seed, flags=0, edit=None):
+def _mlp_dx(B, N, d, F, seed, edit=None, grads=None):
     """dx where only the loop's products reach it: Wv = Wo = 0 (nothing through the attention), inputs of +-1 (RMS statistics of
     exactly 1), W1 of small multiples of 1/8 (pre-activations are exact sums).  Returns dx and the same from numpy in fp64."""
     from math import erf, pi, sqrt
@@ -42,12 +42,12 @@ def _mlp_dx(B, N, d, F, seed, flags=0, edit=None):
     x = rng.choice((-1.0, 1.0), (B, N, d)).astype(np.float32)
     z, gy = r16(rng.standard_normal((B, N, d))), r16(rng.standard_normal((B, N, d)))
     if edit:
-        edit(w)
-    ctx = binding.RTContext(d, d // 64, F, B, N, "bf16", rms_eps=0.0, flags=flags, stream=torch.cuda.current_stream().cuda_stream)
+        edit(w, x, gy)
+    ctx = binding.RTContext(d, d // 64, F, B, N, "bf16", rms_eps=0.0, stream=torch.cuda.current_stream().cuda_stream)
     try:
         dl = tio.DeviceLayer(w, None, "bf16")
         dx = torch.empty((B, N, d), dtype=torch.float32, device="cuda:0")
-        ctx.rt_layer_backward(dl.struct, tio.to_device(x, "bf16"), tio.to_device(z, "bf16"), tio.to_device(gy, "bf16"), None, None, dx, {})
+        ctx.rt_layer_backward(dl.struct, tio.to_device(x, "bf16"), tio.to_device(z, "bf16"), tio.to_device(gy, "bf16"), None, None, dx, grads or {})
         torch.cuda.synchronize()
         got = dx.cpu().numpy().astype(np.float64)
     finally:
@@ -65,3 +65,19 @@ def test_loop_products_distance_from_fp64():
     t = ((gy @ W2) * gelu_d) @ W1
     ref = gy + t - x * (x * t).mean(-1, keepdims=True)
     assert np.linalg.norm(got - ref) / np.linalg.norm(ref) <= 2.0 ** -22.25   # 2e-7
+
+
+def test_loop_products_infinite_weight():
+    """an infinite element of W2 gives signed infinities in the gradient of its unit's pre-activation, hence of its row of W1: the
+    parts of a gradient below its head are zero here"""
+    def edit(w, x, gy):
+        w["W2"][3, 10] = np.inf
+        w["W1"][10] *= 0.0625   # gelu' of that unit positive
+        x[:] = x[0, 0]
+        gy[..., 3] = -np.abs(gy[..., 3])
+    gW1 = torch.empty((512, 256), dtype=torch.float32, device="cuda:0")
+    _, x, gy, _, _, gelu_d = _mlp_dx(9, 1, 256, 512, 72, edit=edit, grads=dict(W1=gW1))
+    assert (gelu_d[..., 10] > 1e-3).all() and (gy[..., 3] != 0).all()
+    got = gW1.cpu().numpy()
+    assert np.array_equal(got[10], -np.sign(x[0, 0]) * np.inf)
+    assert np.isfinite(np.delete(got, 10, 0)).all()
