@@ -88,9 +88,11 @@ __global__ __launch_bounds__(256) void lm_head_kernel(const T *__restrict__ W, c
 // The same on the matrix cores (bf16 storage): D[16 vocabulary rows][16 batch columns] += W[16][32] z^T[32][16].  The
 // normalised rows are not rounded: each element is staged as three bf16 parts whose sum holds all 24 bits of the fp32 value,
 // and every weight fragment feeds three instructions (the chip has ten times the matrix rate that this needs at the memory
-// rate).  The heads' sums of 32 products are added up in eight partial sums on the vector ALUs: one accumulator that runs through
+// rate).  The heads' sums of 32 products are added up in four partial sums on the vector ALUs: one accumulator that runs through
 // all 3 d / 32 instructions rounds at every one of them (distance from fp64 at d = 1024 / 4096: 3.4e-7 / 6.9e-7 of the norm; this
-// form 0.9e-7 / 1.2e-7, the plain-ALU form 1.2e-7 / 1.7e-7; the times are the same).  Bound: the matrix, read once per 16 batch rows.  The plain-ALU form above reads 32 KB of LDS and issues 8192 adds
+// form 0.9e-7 / 1.3e-7, the plain-ALU form 1.2e-7 / 1.7e-7; the times are the same, while with eight partial sums a second workgroup
+// of a compute unit no longer has registers: 256 batch rows, d = 512: 104 -> 161 us).
+// Bound: the matrix, read once per 16 batch rows.  The plain-ALU form above reads 32 KB of LDS and issues 8192 adds
 // per weight row at 8 batch rows: 153 us for 67 MB (d = 1024, 32768 rows, 8 batch rows) = 0.44 TB/s; here 22 us = 3.0 TB/s.
 // A wavefront takes 16 vocabulary rows at a time; the contraction index of a step pair is assigned so that a lane's two
 // loads are 32 contiguous bytes (four lanes cover a row's 128), kHeadAhead pairs are in flight, the first of them requested
@@ -142,9 +144,9 @@ __global__ __launch_bounds__(512) void lm_head_mfma_kernel(const bf16_t *__restr
     for (; tile < tiles; tile += tstep) {   // no barrier below
         const bf16_t *wn = W + (size_t)min((tile + tstep) * 16 + col, vocab - 1) * d + 16 * gk;   // the next tile's rows
         constexpr f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
-        f32x4_t low = zero, head[2 * kHeadAhead];   // middle and tail parts: 2^-8 of the sum, in one chain
+        f32x4_t low = zero, head[kHeadAhead];   // middle and tail parts: 2^-8 of the sum, in one chain
 #pragma unroll
-        for (int j = 0; j < 2 * kHeadAhead; ++j) head[j] = zero;
+        for (int j = 0; j < kHeadAhead; ++j) head[j] = zero;
         for (int k0 = 0; k0 < d; k0 += 64 * kHeadAhead) {
             const bool last = k0 + 64 * kHeadAhead >= d;
             const bf16_t *src = last ? wn : wr + k0 + 64 * kHeadAhead;
@@ -162,12 +164,12 @@ __global__ __launch_bounds__(512) void lm_head_mfma_kernel(const bf16_t *__restr
                 x.u = *reinterpret_cast<const uint4 *>(zl + k + 8); low = mfma16(a1, x, low);
                 x.u = *reinterpret_cast<const uint4 *>(zm + k); low = mfma16(a0, x, low);
                 x.u = *reinterpret_cast<const uint4 *>(zm + k + 8); low = mfma16(a1, x, low);
-                x.u = *reinterpret_cast<const uint4 *>(zh + k); head[2 * j] += mfma16(a0, x, zero);
-                x.u = *reinterpret_cast<const uint4 *>(zh + k + 8); head[2 * j + 1] += mfma16(a1, x, zero);
+                x.u = *reinterpret_cast<const uint4 *>(zh + k); head[j] += mfma16(a0, x, zero);
+                x.u = *reinterpret_cast<const uint4 *>(zh + k + 8); head[j] += mfma16(a1, x, zero);
             }
         }
-        static_assert(kHeadAhead == 4, "eight partial sums");
-        const f32x4_t top = ((head[0] + head[1]) + (head[2] + head[3])) + ((head[4] + head[5]) + (head[6] + head[7]));
+        static_assert(kHeadAhead == 4, "four partial sums");
+        const f32x4_t top = (head[0] + head[1]) + (head[2] + head[3]);
         f32x4_t acc = top + low;
         // an infinite weight times the other parts, zero or of the other sign, is no part of the sum: the head's product stands
 #pragma unroll
