@@ -190,6 +190,21 @@ __global__ __launch_bounds__(512) void lm_head_mfma_kernel(const bf16_t *__restr
 }
 constexpr size_t kHeadMfmaMaxLds = 152 * 1024;
 
+// Up to how many batch rows the plain-ALU form is the faster one: few vocabulary rows leave the other with a handful of wavefronts,
+// each with the whole contraction as one chain of loads, where this one has a wavefront per vocabulary row; its time grows with the
+// batch rows, the other's does not.  us, plain / matrix cores, at d = 1024: 2000 rows, B = 1: 4.6 / 12.7, 5: 12.5 / 13.2, 6: 15.1 / 13.1;
+// 4000 rows, B = 2: 11.9 / 12.9, 3: 16.0 / 13.1; 8000, B = 1: 10.0 / 12.8, 2: 17.8 / 12.9; 16000, B = 1: 13.6 / 15.6; 20000, B = 1:
+// 17.3 / 16.5.  d = 256, 1000 rows, B = 2: 4.6 / 5.2, 3: 5.2 / 5.0; d = 512, B = 4: 7.2 / 7.9, 5: 8.3 / 8.0; d = 4096, B = 6: 36.7 / 44.4,
+// 8: 49 / 45 (8000 rows, B = 2: 48.8 / 57.3, 3: 68.8 / 58.2).
+static int head_plain_rows(int d, int vocab)
+{
+    const int wide = d >= 2048 && d <= 8192 ? 1 : 0;
+    if (vocab <= 2048) return d < 512 ? 2 : (d < 1024 ? 4 : 5 + wide);
+    if (vocab <= 4096) return d < 512 ? 1 : 2 + wide;
+    if (vocab <= 8192) return d < 512 ? 0 : 1 + wide;
+    return vocab <= 16384 && d >= 1024 ? 1 : 0;
+}
+
 template <typename T>
 hipError_t embed_rows_launch(const void *table, const int32_t *ids, void *x, int B, int N, int d, int vocab,
                              long long ids_stride, int first, hipStream_t st)
@@ -205,8 +220,8 @@ hipError_t lm_head_launch(const void *W, const void *g, const void *z, long long
                           int vocab, float eps, int norm_free, hipStream_t st)
 {
     // bf16 rows of whole 256-index blocks: the matrix-core kernel (32768 rows, d = 1024, B = 8: 22 us against 153 of the
-    // plain-ALU form, which keeps the other types and widths)
-    if (sizeof(T) == 2 && d % (64 * kHeadAhead) == 0 && (size_t)3 * (d + 8) * 2 <= kHeadMfmaMaxLds) {
+    // plain-ALU form, which keeps the other types and widths, and few rows of both kinds)
+    if (sizeof(T) == 2 && d % (64 * kHeadAhead) == 0 && B > head_plain_rows(d, vocab) && (size_t)3 * (d + 8) * 2 <= kHeadMfmaMaxLds) {
         int bt = (int)(kHeadMfmaMaxLds / ((size_t)3 * (d + 8) * 2));
         bt = bt > 16 ? 16 : bt;
         bt = bt > B ? B : bt;

@@ -1,6 +1,7 @@
 """rt_lm_head on the matrix cores at the edges of its tiles: vocabulary rows in tiles of 16 (remainders, rows that allow no
 16-byte stores), batch tiles of up to 16 (fewer, full, one more; fewer rows where wide rows fill the LDS), row widths of one,
-several and many blocks of 256, strided rows."""
+several and many blocks of 256, strided rows; and the plain-ALU form on both sides of the rule that takes it for few rows of both
+kinds."""
 import numpy as np
 import pytest
 
@@ -11,7 +12,9 @@ torch = pytest.importorskip("torch")
 
 
 @pytest.mark.parametrize("d,vocab,B,norm_free", [(256, 1, 1, False), (256, 15, 16, False), (512, 4097, 17, False), (1024, 2064, 8, False),
-                                                 (768, 33000, 5, False), (2048, 130, 33, False), (12288, 50, 3, False), (1024, 62, 9, True)])
+                                                 (768, 33000, 5, False), (2048, 130, 33, False), (12288, 50, 3, False), (1024, 62, 9, True),
+                                                 (1024, 2048, 5, False), (1024, 2048, 6, False), (512, 4096, 2, True), (512, 4097, 2, False),
+                                                 (2048, 8192, 2, False)])
 def test_lm_head_tiles(oracle, d, vocab, B, norm_free):
     from paper_2604_21215_amd import binding, torch_io as tio
     if not torch.cuda.is_available():
