@@ -36,9 +36,7 @@ template <int MT_, int NT_, int KG_, int KT_, int STAGES_> struct GemmTile {
     // piece of row r in slot c: c ^ swz(r).  A row of 64 bytes shares its 128 bytes of banks with its neighbour.
     __device__ static int swz(int r) { return kPieces == 4 ? (r >> 1) & 3 : r & 7; }
 };
-// Many rows: two workgroups per compute unit (72 KB each).  The form before this one staged the next k-tile through registers
-// (48 KB, one tile ahead, two barriers per k-tile) and read the operands of its epilogues row by row; d = 1024, 16384 rows:
-// pre-pass 220 -> 176, Wo 94 -> 66, W2 189 -> 168, W1 259 -> 257 us (bound by its 67 M GELUs and stores).
+// Many rows: two workgroups per compute unit (72 KB each).
 using TileMany = GemmTile<4, 2, 1, 32, 3>;
 constexpr int kGtRows = TileMany::kRows, kGtCols = TileMany::kCols;
 
@@ -52,7 +50,7 @@ __device__ __forceinline__ float sum16(float v)
     return v;
 }
 
-// what a caller hands in need not be aligned to the 16 bytes of a load into LDS: the kernels that load into registers take it then
+// what a caller hands in need not be aligned to the 16 bytes of a load into LDS: such rows are loaded into registers
 inline bool aligned16(const void *p) { return ((uintptr_t)p & 15) == 0; }
 
 #pragma clang diagnostic push
@@ -166,6 +164,77 @@ template <class T, class RowA, class RowB>
 __device__ __forceinline__ void tiled_mainloop(RowA row_a, RowB row_b, int K, unsigned char *ring, f32x16_t (&acc)[T::MT][T::NT])
 {
     tiled_mainloop<T>(row_a, row_b, K, ring, acc, [] {});
+}
+
+// The same tile with the next k-tile (64 indices) staged through registers, one tile ahead and two barriers per k-tile, for rows that
+// are not aligned to 16 bytes; the sums run in the same order.  Rows of the LDS tiles are 72 elements apart (fragment reads of
+// consecutive rows hit distinct banks).
+constexpr int kStagedLd = 72;
+template <class RowA, class RowB>
+__device__ __forceinline__ void staged_mainloop(RowA row_a, RowB row_b, int K, unsigned char *lds, f32x16_t (&acc)[4][2])
+{
+    bf16_t *As = reinterpret_cast<bf16_t *>(lds), *Bs = As + kGtRows * kStagedLd;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave >> 1, wn = wave & 1;
+    const int l32 = lane & 31, hi = lane >> 5;
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[mt][nt][i] = 0.f;
+    const int prow = tid >> 3, pc = tid & 7;   // piece pc of rows prow + 32 i
+    const bf16_t *ga[8], *gb[4];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) ga[i] = row_a(prow + 32 * i) + 8 * pc;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) gb[i] = row_b(prow + 32 * i) + 8 * pc;
+    u32x4_t ra[8], rb[4];
+    auto fetch = [&](int k0) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) ra[i] = *reinterpret_cast<const u32x4_t *>(ga[i] + k0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) rb[i] = *reinterpret_cast<const u32x4_t *>(gb[i] + k0);
+    };
+    auto stage = [&]() {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4_t *>(As + (prow + 32 * i) * kStagedLd + 8 * pc) = ra[i];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) *reinterpret_cast<u32x4_t *>(Bs + (prow + 32 * i) * kStagedLd + 8 * pc) = rb[i];
+        __syncthreads();
+    };
+    fetch(0);
+    stage();
+    for (int k0 = 0; k0 < K; k0 += 64) {
+        const bool more = k0 + 64 < K;
+        if (more) fetch(k0 + 64);
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+            uint4 fa[4], fb[2];
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt)
+                fa[mt] = *reinterpret_cast<const uint4 *>(As + (wm * 128 + mt * 32 + l32) * kStagedLd + ks * 16 + 8 * hi);
+#pragma unroll
+            for (int nt = 0; nt < 2; ++nt)
+                fb[nt] = *reinterpret_cast<const uint4 *>(Bs + (wn * 64 + nt * 32 + l32) * kStagedLd + ks * 16 + 8 * hi);
+#pragma unroll
+            for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = mfma32u(fa[mt], fb[nt], acc[mt][nt]);
+        }
+        __syncthreads();   // everyone is done reading the tiles
+        if (more) stage();
+    }
+}
+
+// Many rows, either form.  The ring is the faster one mostly where the row tiles leave a ragged last round of workgroups (rt_layer_recompute,
+// us, registers / ring: 3 x 683 rows, d = 768: 254 / 227; 8 x 1000, d = 1024: 536 / 522; 8 x 2048: 991 / 993).
+template <bool ALIGNED> constexpr int kManyLds = ALIGNED ? TileMany::kLds : (kGtRows + kGtCols) * kStagedLd * 2;
+template <bool ALIGNED, class RowA, class RowB>
+__device__ __forceinline__ void many_mainloop(RowA row_a, RowB row_b, int K, unsigned char *lds, f32x16_t (&acc)[4][2])
+{
+    if constexpr (ALIGNED) tiled_mainloop<TileMany>(row_a, row_b, K, lds, acc);
+    else staged_mainloop(row_a, row_b, K, lds, acc);
 }
 
 }  // namespace rt

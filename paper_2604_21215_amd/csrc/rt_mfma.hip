@@ -32,7 +32,9 @@ __global__ __launch_bounds__(256) void prepass_mfma_kernel(const bf16_t *__restr
 
 // The same projection with both operands staged in LDS (tiled_mainloop), for many rows and d a multiple of 128: a
 // wavefront's 64 columns are one head of q, k_tmp or v_tmp, so the qkRMS of a row is a sum over its two column
-// tiles and the 32 lanes of its half of the wavefront.  grid (ceil(M / 256), 3 d / 128), block 256.
+// tiles and the 32 lanes of its half of the wavefront.  ALIGNED: x and the matrices are (16 bytes).  grid (ceil(M / 256), 3 d / 128),
+// block 256.
+template <bool ALIGNED>
 __global__ __launch_bounds__(256) void prepass_tiled_kernel(const bf16_t *__restrict__ x, const float *__restrict__ rinv,
                                                             const bf16_t *__restrict__ Wq, const bf16_t *__restrict__ Wk,
                                                             const bf16_t *__restrict__ Wv, const bf16_t *__restrict__ g_q,
@@ -42,7 +44,7 @@ __global__ __launch_bounds__(256) void prepass_tiled_kernel(const bf16_t *__rest
                                                             float *__restrict__ Ktf, int Bc, int Nc, size_t x_bstride,
                                                             int n0, int d, int H, float eps, int norm_free)
 {
-    __shared__ __align__(16) unsigned char ring[TileMany::kLds];
+    __shared__ __align__(16) unsigned char lds[kManyLds<ALIGNED>];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int l32 = lane & 31, hi = lane >> 5;
@@ -52,12 +54,12 @@ __global__ __launch_bounds__(256) void prepass_tiled_kernel(const bf16_t *__rest
     const int bw = c0 / d;                         // d is a multiple of 128: a block lies within one of the three
     const bf16_t *Wb = (bw == 0 ? Wq : (bw == 1 ? Wk : Wv)) + (size_t)(c0 - bw * d) * d;
     f32x16_t acc[4][2];
-    tiled_mainloop<TileMany>(
+    many_mainloop<ALIGNED>(
         [&](int r) {
             const int mr = min(m0 + r, M - 1);
             return x + (size_t)(mr / Nc) * x_bstride + (size_t)(n0 + mr % Nc) * d;
         },
-        [&](int r) { return Wb + (size_t)r * d; }, d, ring, acc);
+        [&](int r) { return Wb + (size_t)r * d; }, d, lds, acc);
 
     const int hcol = c0 - bw * d + wn * 64;        // first column of this wavefront's head within its output
     const bool normed = bw < 2 && !norm_free;
@@ -132,8 +134,8 @@ hipError_t prepass_mfma_launch(const LayerDims &D, const Weights &W, const Scrat
 {
     const int M = Bc * Nc;
     const bool gained = W.g_attn && !D.norm_free;   // the tiled kernel wants the gain in the matrices' columns
-    if (M >= kTiledMinRows && D.d % 128 == 0 && (!gained || S.wg_qkv) && aligned16(x) &&
-        (gained || (aligned16(W.Wq) && aligned16(W.Wk) && aligned16(W.Wv)))) {
+    if (M >= kTiledMinRows && D.d % 128 == 0 && (!gained || S.wg_qkv)) {
+        const bool aligned = aligned16(x) && (gained || (aligned16(W.Wq) && aligned16(W.Wk) && aligned16(W.Wv)));
         const bf16_t *wq = (const bf16_t *)W.Wq, *wk = (const bf16_t *)W.Wk, *wv = (const bf16_t *)W.Wv;
         if (gained) {
             const size_t pieces = 3 * (size_t)D.d * D.d / 8;
@@ -141,7 +143,8 @@ hipError_t prepass_mfma_launch(const LayerDims &D, const Weights &W, const Scrat
                                (const bf16_t *)W.g_attn, S.wg_qkv, D.d);
             wq = S.wg_qkv; wk = wq + (size_t)D.d * D.d; wv = wk + (size_t)D.d * D.d;
         }
-        hipLaunchKernelGGL(prepass_tiled_kernel, dim3((M + kGtRows - 1) / kGtRows, 3 * D.d / kGtCols), dim3(256), 0, st,
+        const auto kernel = aligned ? prepass_tiled_kernel<true> : prepass_tiled_kernel<false>;
+        hipLaunchKernelGGL(kernel, dim3((M + kGtRows - 1) / kGtRows, 3 * D.d / kGtCols), dim3(256), 0, st,
                            (const bf16_t *)x, S.rinv, wq, wk, wv, (const bf16_t *)W.g_q, (const bf16_t *)W.g_k, (bf16_t *)S.Q,
                            (bf16_t *)S.Kt, (bf16_t *)S.Vt, S.Qf, S.Ktf, Bc, Nc, x_bstride, n0, D.d, D.H, D.eps, D.norm_free);
         return hipGetLastError();

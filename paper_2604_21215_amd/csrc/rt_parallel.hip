@@ -132,25 +132,25 @@ __global__ __launch_bounds__(256) void par_gemm_kernel(const bf16_t *__restrict_
 //   PG_W2: out_b = res_f + alpha C
 // grid (ceil(M / 256), Nn / 128), block 256.
 // ---------------------------------------------------------------------------------------------
-template <int EPI>
+template <int EPI, bool ALIGNED>
 __global__ __launch_bounds__(256) void tiled_gemm_kernel(const bf16_t *__restrict__ A, const bf16_t *__restrict__ W, int M, int Nn,
                                                          int K, int Nc, int N, int n0, const bf16_t *__restrict__ gain,
                                                          const float *__restrict__ rinv, int norm_free, float alpha,
                                                          const bf16_t *__restrict__ res_b, const float *__restrict__ res_f,
                                                          float *__restrict__ out_f, bf16_t *__restrict__ out_b)
 {
-    __shared__ __align__(16) unsigned char ring[TileMany::kLds];
+    __shared__ __align__(16) unsigned char lds[kManyLds<ALIGNED>];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave >> 1, wn = wave & 1;
     const int l32 = lane & 31, hi = lane >> 5;
     const int m0 = blockIdx.x * kGtRows, nb0 = blockIdx.y * kGtCols;
     f32x16_t acc[4][2];
-    tiled_mainloop<TileMany>(
+    many_mainloop<ALIGNED>(
         [&](int r) {
             const int mr = min(m0 + r, M - 1);
             return A + ((size_t)(mr / Nc) * N + n0 + mr % Nc) * K;
         },
-        [&](int r) { return W + (size_t)(nb0 + r) * K; }, K, ring, acc);
+        [&](int r) { return W + (size_t)(nb0 + r) * K; }, K, lds, acc);
 
     float gcol[2] = {1.f, 1.f};
     if (EPI == PG_WO && gain != nullptr && !norm_free) {
@@ -915,17 +915,20 @@ static void block_gemms(const LayerDims &D, const Weights &W, const void *x, voi
                                      D.norm_free, D.alpha, nullptr, h_f, nullptr, (bf16_t *)y, none);
         return;
     }
-    if (d % 128 == 0 && F % 128 == 0 && aligned16(W.Wo) && aligned16(W.W1) && aligned16(W.W2)) {   // both operands through LDS
+    if (d % 128 == 0 && F % 128 == 0) {   // both operands through LDS
         const unsigned gt = (unsigned)((M + 255) / 256);
-        hipLaunchKernelGGL(tiled_gemm_kernel<PG_WO>, dim3(gt, (unsigned)(d / 128)), dim3(256), 0, st, a_b, (const bf16_t *)W.Wo, M, d, d,
+        const auto wo = aligned16(W.Wo) ? tiled_gemm_kernel<PG_WO, true> : tiled_gemm_kernel<PG_WO, false>;
+        const auto w1 = aligned16(W.W1) ? tiled_gemm_kernel<PG_W1, true> : tiled_gemm_kernel<PG_W1, false>;
+        const auto w2 = aligned16(W.W2) ? tiled_gemm_kernel<PG_W2, true> : tiled_gemm_kernel<PG_W2, false>;
+        hipLaunchKernelGGL(wo, dim3(gt, (unsigned)(d / 128)), dim3(256), 0, st, a_b, (const bf16_t *)W.Wo, M, d, d,
                            Nc, D.N, n0, (const bf16_t *)W.g_mlp, (const float *)nullptr, D.norm_free, D.alpha, (const bf16_t *)x,
                            (const float *)nullptr, h_f, h_b);
         if (!D.norm_free)
             hipLaunchKernelGGL(par_rinv_kernel, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, st, h_f, rinv, M, Nc, D.N, n0, d, D.eps);
-        hipLaunchKernelGGL(tiled_gemm_kernel<PG_W1>, dim3(gt, (unsigned)(F / 128)), dim3(256), 0, st, h_b, (const bf16_t *)W.W1, M, F, d,
+        hipLaunchKernelGGL(w1, dim3(gt, (unsigned)(F / 128)), dim3(256), 0, st, h_b, (const bf16_t *)W.W1, M, F, d,
                            Nc, D.N, n0, (const bf16_t *)nullptr, rinv, D.norm_free, D.alpha, (const bf16_t *)nullptr,
                            (const float *)nullptr, (float *)nullptr, u_b);
-        hipLaunchKernelGGL(tiled_gemm_kernel<PG_W2>, dim3(gt, (unsigned)(d / 128)), dim3(256), 0, st, u_b, (const bf16_t *)W.W2, M, d, F,
+        hipLaunchKernelGGL(w2, dim3(gt, (unsigned)(d / 128)), dim3(256), 0, st, u_b, (const bf16_t *)W.W2, M, d, F,
                            Nc, D.N, n0, (const bf16_t *)nullptr, (const float *)nullptr, D.norm_free, D.alpha,
                            (const bf16_t *)nullptr, h_f, (float *)nullptr, (bf16_t *)y);
         return;

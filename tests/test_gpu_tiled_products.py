@@ -1,6 +1,6 @@
 """The products of 2048 rows and more, whose k-tiles are loaded straight into LDS: exact and ragged row tiles, the shortest
-contraction, batch rows shorter than a row tile's 32 rows, and caller's tensors that are not aligned to 16 bytes (which take the
-kernels that load into registers)."""
+contraction, batch rows shorter than a row tile's 32 rows, and caller's tensors that are not aligned to 16 bytes (whose k-tiles are
+staged through registers)."""
 import numpy as np
 import pytest
 
@@ -41,6 +41,28 @@ def test_recompute_many_rows(oracle, B, N, d, F, shift):
         ctx.rt_layer_recompute(struct, xd, zd, y, K, V)
         torch.cuda.synchronize()
         _check("recompute B=%d N=%d d=%d" % (B, N, d), x64, ref, (tio.to_host(y), tio.to_host(K), tio.to_host(V)), TOL["bf16"])
+    finally:
+        ctx.rt_destroy()
+
+
+@pytest.mark.parametrize("gains,d", [("unit", 128), (None, 384)])
+def test_tensors_that_are_not_aligned_give_the_same_bits(gains, d):
+    """staged through registers the tiles are the same ones, summed in the same order"""
+    from paper_2604_21215_amd import binding, torch_io as tio
+    B, N, F = 5, 411, 256
+    li = gen.make_custom(55, "bf16", B, N, d, d // 64, F)
+    ctx, _, dl, xd, y, K, V = _setup(li, B, N, d, d // 64, F, resid_scale=0.7, attn_scale=0.5, rms_eps=1e-6)
+    try:
+        w = {k: tio.to_device(v, "bf16") for k, v in li.weights.items()}
+        g = {k: tio.to_device(v, "bf16") for k, v in li.gains.items()} if gains else {}
+        zd = tio.to_device(gen.round_to_bf16(np.random.default_rng(8).standard_normal((B, N, d)).astype(np.float32)), "bf16")
+        outs = []
+        for sh in (lambda t: t, _shifted):
+            out = [torch.empty_like(t) for t in (y, K, V)]
+            ctx.rt_layer_recompute(binding.make_weights(dict({k: sh(v) for k, v in w.items()}, **g)), sh(xd), sh(zd), *out)
+            torch.cuda.synchronize()
+            outs.append(out)
+        assert all(torch.equal(a, b) for a, b in zip(*outs))
     finally:
         ctx.rt_destroy()
 
