@@ -5,6 +5,7 @@
 #include "rt_persistent.h"
 #include "rt_decode_persistent.h"
 #include "rt_backward.h"
+#include "rt_side_streams.h"
 
 #include <cstdio>
 #include <cstdlib>
@@ -59,57 +60,26 @@ struct rt_ctx {
 
 static const char *kNoCtx = "no context";
 
-// Side streams of the layer-wavefront engine, lent to a call for the time it enqueues its work.  A process has four hardware
-// queues and a stream keeps the one it was given: with two side streams per context the streams of several contexts share
-// queues with each other and with the caller's stream, and groups of layers that should overlap run one after the other
-// (12 layers, B = 4, N = 4096: 285 ms for the only context of a process, 420 - 725 ms for some of several, 284 ms for all of them
-// from here).  Calls that follow one another take the same streams from here; calls on several threads at once take different ones.  A lent stream goes back with work still
-// queued on it: the next call's work on it follows in order, and every wait inside a call is for work enqueued before it, so
-// no two calls can wait for each other.  At most kPooledSets sets stay; the last context of the process gives all of them back.
-// A call that is being captured uses streams of its own context: a pooled stream would stay part of the capture.
+// Side streams of the layer-wavefront engine (rt_side_streams.h).  A call that is being captured uses streams of its own context:
+// a pooled stream would stay part of the capture.
 namespace {
-struct SideStreams {
-    int device;
-    hipStream_t st[kMaxWaveStreams - 1];
-};
-constexpr size_t kPooledSets = 4;
-std::mutex g_side_mu;
-SideStreams g_side_free[kPooledSets];
-size_t g_side_count = 0;
-int g_contexts = 0;   // contexts of this process
-
-void destroy_side(SideStreams &s)
-{
-    for (hipStream_t &st : s.st)
-        if (st) (void)hipStreamDestroy(st);
-}
-SideStreams take_side(int device)
-{
-    std::lock_guard<std::mutex> lock(g_side_mu);
-    for (size_t i = g_side_count; i-- > 0;)
-        if (g_side_free[i].device == device) {
-            const SideStreams s = g_side_free[i];
-            for (--g_side_count; i < g_side_count; ++i) g_side_free[i] = g_side_free[i + 1];
-            return s;
-        }
-    return SideStreams{device, {}};
-}
-void give_side(SideStreams s)
-{
-    std::lock_guard<std::mutex> lock(g_side_mu);
-    if (g_side_count < kPooledSets) g_side_free[g_side_count++] = s;
-    else destroy_side(s);
-}
-void count_context(int change)
-{
-    std::lock_guard<std::mutex> lock(g_side_mu);
-    g_contexts += change;
-    if (g_contexts > 0) return;
-    for (; g_side_count > 0; --g_side_count) {
-        (void)hipSetDevice(g_side_free[g_side_count - 1].device);
-        destroy_side(g_side_free[g_side_count - 1]);
+struct HipStreams {
+    using Stream = hipStream_t;
+    static Stream per_thread() { return hipStreamPerThread; }
+    static bool idle(Stream st)   // also false where the query is refused (another thread is capturing)
+    {
+        if (hipStreamQuery(st) == hipSuccess) return true;
+        (void)hipGetLastError();
+        return false;
     }
-}
+    static void destroy(int device, Stream st)
+    {
+        (void)hipSetDevice(device);
+        (void)hipStreamDestroy(st);
+    }
+};
+using SideStreams = SidePool<HipStreams, kMaxWaveStreams - 1>;
+SideStreams g_side;
 }  // namespace
 
 static rt_status fail(rt_ctx *c, rt_status s, const char *fmt, const char *detail = "")
@@ -386,7 +356,7 @@ rt_status rt_create(const rt_config *cfg, rt_ctx **out)
 
     rt_ctx *c = new (std::nothrow) rt_ctx();
     if (!c) return RT_ERR_OOM;
-    count_context(1);
+    g_side.count_context(1);
     c->cfg = *cfg;
     c->cfg.p_min = p_min;
     c->stream = (hipStream_t)cfg->stream;
@@ -406,7 +376,7 @@ rt_status rt_create(const rt_config *cfg, rt_ctx **out)
     hipError_t e = hipMalloc(&c->slab, c->slab_bytes);
     if (e != hipSuccess) {
         (void)hipGetLastError();
-        count_context(-1);
+        g_side.count_context(-1);
         delete c;
         return e == hipErrorOutOfMemory ? RT_ERR_OOM : RT_ERR_HIP;
     }
@@ -416,7 +386,7 @@ rt_status rt_create(const rt_config *cfg, rt_ctx **out)
         if (e != hipSuccess) {
             (void)hipGetLastError();
             (void)hipFree(c->slab);
-            count_context(-1);
+            g_side.count_context(-1);
             delete c;
             return RT_ERR_HIP;
         }
@@ -425,7 +395,7 @@ rt_status rt_create(const rt_config *cfg, rt_ctx **out)
     rt_status ps = persistent_create(c->persist, c->cfg, D);
     if (ps != RT_OK && (cfg->flags & RT_FLAG_ENGINE_PERSISTENT)) {
         (void)hipFree(c->slab);
-        count_context(-1);
+        g_side.count_context(-1);
         delete c;
         return ps;
     }
@@ -482,7 +452,7 @@ rt_status rt_destroy(rt_ctx *c)
     hipError_t e = hipFree(c->slab);
     const int device = c->cfg.device;
     delete c;
-    count_context(-1);
+    g_side.count_context(-1);
     (void)hipSetDevice(device);
     return e == hipSuccess ? RT_OK : RT_ERR_HIP;
 }
@@ -1065,12 +1035,12 @@ extern "C" rt_status rt_stack_prefill(rt_ctx *c, const rt_layer_weights *layers,
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     if (want > 1 && c->stream) RT_TRY(hipStreamIsCapturing(c->stream, &capturing), "hipStreamIsCapturing");
     const bool pooled = want > 1 && capturing == hipStreamCaptureStatusNone;
-    SideStreams side{c->cfg.device, {}};
-    if (pooled) side = take_side(c->cfg.device);
+    SideStreams::Set *side = pooled ? g_side.take(c->cfg.device, c->stream) : nullptr;
+    if (pooled && !side) return fail(c, RT_ERR_OOM, "side streams%s");
     hipError_t e = hipSuccess;
     WS.st[0] = c->stream;
     for (int g = 0; g < want && e == hipSuccess; ++g) {
-        hipStream_t *own = g == 0 ? &WS.st[0] : (pooled ? &side.st[g - 1] : &c->wave_streams.st[g]);
+        hipStream_t *own = g == 0 ? &WS.st[0] : (pooled ? &side->st[g - 1] : &c->wave_streams.st[g]);
         if (g > 0 && !*own) e = hipStreamCreateWithFlags(own, hipStreamNonBlocking);
         WS.st[g] = *own;
         if (e == hipSuccess && !c->wave_streams.ev[g]) e = hipEventCreateWithFlags(&c->wave_streams.ev[g], hipEventDisableTiming);
@@ -1081,7 +1051,7 @@ extern "C" rt_status rt_stack_prefill(rt_ctx *c, const rt_layer_weights *layers,
         if (c->cfg.dtype == RT_BF16) e = wavefront_prefill<bf16_t>(D, c->stack_dev, host.data(), L, chunk, c->use_mfma, WS);
         else e = wavefront_prefill<float>(D, c->stack_dev, host.data(), L, chunk, false, WS);
     }
-    if (pooled) give_side(side);
+    if (pooled) g_side.give(side);
     if (e != hipSuccess) return fail_hip(c, e, "wavefront_prefill");
     return RT_OK;
 }
