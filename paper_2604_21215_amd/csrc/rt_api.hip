@@ -74,8 +74,11 @@ struct HipStreams {
     }
     static void destroy(int device, Stream st)
     {
+        int current = device;
+        (void)hipGetDevice(&current);
         (void)hipSetDevice(device);
         (void)hipStreamDestroy(st);
+        (void)hipSetDevice(current);
     }
 };
 using SideStreams = SidePool<HipStreams, kMaxWaveStreams - 1>;
@@ -450,10 +453,8 @@ rt_status rt_destroy(rt_ctx *c)
         if (c->wave_streams.ev[g]) (void)hipEventDestroy(c->wave_streams.ev[g]);
     }
     hipError_t e = hipFree(c->slab);
-    const int device = c->cfg.device;
     delete c;
     g_side.count_context(-1);
-    (void)hipSetDevice(device);
     return e == hipSuccess ? RT_OK : RT_ERR_HIP;
 }
 

@@ -6,7 +6,7 @@
 //
 // A set goes back with work still queued on it, and that work waits for the caller's stream it was lent to.  So it is lent again
 // only to a call on the same caller's stream, whose order it shares anyway, or once it has run dry: a call never waits for what another
-// stream has queued.  Calls on several threads at once take different sets.  hipStreamPerThread names a stream per thread and
+// stream has queued.  Calls on several threads at once take different sets; there are no more of them than contexts.  hipStreamPerThread names a stream per thread and
 // counts as a different one every time.
 //
 // Api: Stream, per_thread(), idle(stream), destroy(device, stream).  Plain host code: the rules are checked without a GPU.
@@ -44,20 +44,33 @@ public:
     void give(Set *s)
     {
         std::lock_guard<std::mutex> lock(mu_);
-        if (count_ < 4) { s->next = free_; free_ = s; ++count_; }
-        else destroy(s);
+        s->next = free_;
+        free_ = s;
+        ++count_;
     }
-    // contexts of the process: the last one gives everything back
+    // Contexts of the process.  There is never use for more sets than contexts: when one goes, idle sets beyond that number go too
+    // (work of other contexts may still be queued on the others), with the last one all of them.
     void count_context(int change)
     {
-        std::lock_guard<std::mutex> lock(mu_);
-        contexts_ += change;
-        if (contexts_ > 0) return;
-        while (free_) {
-            Set *s = free_;
-            free_ = s->next;
-            --count_;
-            destroy(s);
+        Set *gone = nullptr;
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            contexts_ += change;
+            for (Set **p = &free_; change < 0 && *p && count_ > contexts_;) {
+                Set *s = *p;
+                if (contexts_ > 0 && !idle(*s)) { p = &s->next; continue; }
+                *p = s->next;
+                --count_;
+                s->next = gone;
+                gone = s;
+            }
+        }
+        while (gone) {   // outside the lock, and never inside a call that has work queued: giving a stream back may wait for it
+            Set *s = gone;
+            gone = s->next;
+            for (Stream &st : s->st)
+                if (st) Api::destroy(s->device, st);
+            delete s;
         }
     }
 
@@ -67,12 +80,6 @@ private:
         for (const Stream &st : s.st)
             if (st && !Api::idle(st)) return false;
         return true;
-    }
-    static void destroy(Set *s)
-    {
-        for (Stream &st : s->st)
-            if (st) Api::destroy(s->device, st);
-        delete s;
     }
     std::mutex mu_;
     Set *free_ = nullptr;

@@ -18,7 +18,7 @@ def program(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("check", ["unrelated_callers"])
+@pytest.mark.parametrize("check", ["unrelated_callers", "many_at_once", "threads"])
 def test_side_streams(program, check):
     r = subprocess.run([program, check], stdout=subprocess.PIPE, text=True, timeout=30)
     assert r.returncode == 0, r.stdout
