@@ -1020,8 +1020,13 @@ extern "C" rt_status rt_stack_prefill(rt_ctx *c, const rt_layer_weights *layers,
         host[l].y = y[l]; host[l].K = K[l]; host[l].V = V[l];
         poison_partials(c, c->stack_S[l]);
     }
-    // pageable source: the copy has been staged when the call returns, `host` may go out of scope
-    RT_TRY(hipMemcpyAsync(c->stack_dev, host.data(), sizeof(WaveLayer) * L, hipMemcpyHostToDevice, c->stream), "descriptor copy");
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (c->stream) RT_TRY(hipStreamIsCapturing(c->stream, &capturing), "hipStreamIsCapturing");
+    const bool eager = capturing == hipStreamCaptureStatusNone;
+    if (eager)   // pageable source: the copy has been staged when the call returns, `host` may go out of scope
+        RT_TRY(hipMemcpyAsync(c->stack_dev, host.data(), sizeof(WaveLayer) * L, hipMemcpyHostToDevice, c->stream), "descriptor copy");
+    else   // a captured copy would read `host` at every replay
+        RT_TRY(wavefront_descriptors(host.data(), c->stack_dev, L, c->stream), "descriptors");
     LayerDims D = c->base;
     D.B = B; D.N = N; D.kv_cap = kv_cap;
     c->engine = "wavefront";
@@ -1033,9 +1038,7 @@ extern "C" rt_status rt_stack_prefill(rt_ctx *c, const rt_layer_weights *layers,
     if (want < 1) want = 1;
     if (want > kMaxWaveStreams) want = kMaxWaveStreams;
     if (want > L) want = L;   // a group has a layer
-    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
-    if (want > 1 && c->stream) RT_TRY(hipStreamIsCapturing(c->stream, &capturing), "hipStreamIsCapturing");
-    const bool pooled = want > 1 && capturing == hipStreamCaptureStatusNone;
+    const bool pooled = want > 1 && eager;
     SideStreams::Set *side = pooled ? g_side.take(c->cfg.device, c->stream) : nullptr;
     if (pooled && !side) return fail(c, RT_ERR_OOM, "side streams%s");
     hipError_t e = hipSuccess;

@@ -265,7 +265,7 @@ struct WaveLayer {
     void *K, *V;      // [kv_cap][B][H][64]
 };
 
-// Streams of the layer-wavefront engine: st[0] is the caller's, the others belong to the context (default
+// Streams of the layer-wavefront engine: st[0] is the caller's, the others are lent to the call (default
 // priority); ev[g] orders group g + 1 after group g (ev[0] also starts the other streams, ev[g >= 1] joins them).
 constexpr int kMaxWaveStreams = 4;
 struct WaveStreams {
@@ -274,6 +274,8 @@ struct WaveStreams {
     hipEvent_t ev[kMaxWaveStreams];
 };
 
+// the descriptors into dev_layers by launches that carry them (a call that is being captured)
+hipError_t wavefront_descriptors(const WaveLayer *host_layers, WaveLayer *dev_layers, int L, hipStream_t st);
 // All layers of a stack, layer l running `chunk` positions behind layer l - 1 (rt_wavefront.hip).
 template <typename T>
 hipError_t wavefront_prefill(const LayerDims &D, const WaveLayer *dev_layers, const WaveLayer *host_layers, int L, int chunk,

@@ -907,6 +907,17 @@ static hipError_t wavefront_steps(const LayerDims &D, const WaveLayer *dev_layer
     return hipSuccess;
 }
 
+// One layer's descriptor from the launch's own arguments: what a captured launch holds on to, unlike a copy from host memory.
+__global__ void wf_descriptor_kernel(const WaveLayer Y, WaveLayer *dst)
+{
+    if (threadIdx.x == 0) *dst = Y;
+}
+hipError_t wavefront_descriptors(const WaveLayer *host_layers, WaveLayer *dev_layers, int L, hipStream_t st)
+{
+    for (int l = 0; l < L; ++l) hipLaunchKernelGGL(wf_descriptor_kernel, dim3(1), dim3(64), 0, st, host_layers[l], dev_layers + l);
+    return hipGetLastError();
+}
+
 template <typename T>
 hipError_t wavefront_prefill(const LayerDims &D, const WaveLayer *dev_layers, const WaveLayer *host_layers, int L, int chunk,
                              bool mfma, const WaveStreams &W)

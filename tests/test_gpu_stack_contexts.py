@@ -52,3 +52,42 @@ def test_contexts_share_side_streams(threads):
     finally:
         for c in ctxs:
             c.rt_destroy()
+
+
+def test_captured_call_replays():
+    """a call recorded in a HIP graph: its replays read the tensors of the recorded call whatever ran on the context since, and give the
+    eager call's bits on the inputs of the moment"""
+    from paper_2604_21215_amd import binding, torch_io as tio
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    B, N, d, L = 2, 150, 256, 4
+    sets = [[tio.DeviceLayer(gen.make_layer_weights(seed, l, d, 4 * d, "bf16"), None, "bf16") for l in range(L)] for seed in (93, 94)]
+    xs = [tio.to_device(gen.make_custom(seed, "bf16", B, N, d, 4, 4 * d).x, "bf16") for seed in (95, 96, 97)]
+    torch.cuda.synchronize()
+
+    def tensors():
+        return ([torch.zeros_like(xs[0]) for _ in range(L)], [torch.zeros((N, B, 4, 64), dtype=xs[0].dtype, device="cuda:0") for _ in range(L)],
+                [torch.zeros((N, B, 4, 64), dtype=xs[0].dtype, device="cuda:0") for _ in range(L)])
+
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ctx = binding.RTContext(d, 4, 4 * d, B, N, "bf16", resid_scale=0.5, rms_eps=1e-6, reserve_stack_layers=L, stream=stream.cuda_stream)
+        try:
+            refs = []
+            for x in xs:
+                refs.append(tensors())
+                ctx.rt_stack_prefill([dl.struct for dl in sets[0]], x, *refs[-1])
+            x, out, other = torch.empty_like(xs[0]), tensors(), tensors()
+            stream.synchronize()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=stream):
+                ctx.rt_stack_prefill([dl.struct for dl in sets[0]], x, *out)
+            for x_new, ref in zip(xs, refs):
+                ctx.rt_stack_prefill([dl.struct for dl in sets[1]], xs[2], *other)   # other descriptors on the same context
+                x.copy_(x_new)
+                graph.replay()
+                stream.synchronize()
+                assert all(torch.equal(p, q) for a, b in zip(out, ref) for p, q in zip(a, b))
+        finally:
+            stream.synchronize()
+            ctx.rt_destroy()
