@@ -13,7 +13,8 @@ torch = pytest.importorskip("torch")
 @pytest.mark.parametrize("B,N,d,F,kw", [
     (129, 35, 128, 128, {}),                                   # one sequence more than two row tiles; one k-tile in every product
     (192, 40, 384, 640, dict(alibi=8.0)),                      # whole row tiles; 3 and 5 k-tiles of 128
-    (770, 34, 128, 4096, {}),                                  # W1 on 128 x 128 tiles, ragged last one
+    (770, 34, 128, 4096, {}),                                  # W1 on 128 x 128 tiles, ragged last one; fewer k-tiles than the ring holds
+    (642, 33, 384, 4096, dict(alibi=8.0)),                     # the same with six k-tiles: the ring wraps
     (300, 33, 1024, 4096, dict(gains="unit")),
 ])
 def test_position_batched(oracle, B, N, d, F, kw):
