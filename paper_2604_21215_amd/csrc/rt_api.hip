@@ -213,14 +213,15 @@ static void fill_dims(LayerDims &D, const rt_config &cfg, int p_min)
 }
 
 static rt_status stack_workspace(rt_ctx *c, int L, int chunk);
-// rt_layer_prefill: from this many sequences on a position of all sequences at once, with batched matrix products, is faster
-// than chunks of 16 rows on the single-launch engine (MI355X, d = 1024, 512 positions: 5 chunks take 39.3 ms, 6 take 47.1;
-// the batched steps 40.8 ms at B = 80, 41.3 at B = 96, 42.4 at B = 128)
+// rt_layer_prefill for more rows than the single-launch engine stages.  Three ways, ms per call on MI355X at d = 1024, 512 positions
+// (in brackets d = 512, 128 positions), B = 33 / 48 / 64 / 96 / 128 / 160 / 192:
+//   chunks of 16 rows on that engine                22.6 / 23.5 / 31.4 / 47.0 / 62.6 / 78.3 / 94.0   (4.69 / 4.77 / 6.34 / 9.55 / 12.7 / 15.9 / 19.1)
+//   one layer on the layer-wavefront engine         18.7 / 19.4 / 20.7 / 21.8 / 23.4 / 27.5 / 29.0   (3.56 / 3.62 / 3.63 / 3.83 / 4.00 / 4.15 / 4.33)
+//   one position of all sequences per step          26.1 / 26.5 / 27.0 / 27.9 / 28.8 / 29.6 / 30.7   (4.59 / 4.67 / 4.71 / 4.79 / 4.87 / 5.10 / 5.27)
+// The steps at once take over where the chunks fall behind them; the lines of the layer-wavefront engine were drawn with the kernels
+// before its products took 32 sequences per workgroup (49.2 ms at B = 160, chunks 23.6 at B = 48): with these it leads from 33 to
+// 192 rows.  The third row is with the products from LDS throughout (step_products in rt_parallel.hip takes them from 129 rows on).
 constexpr int kBatchedFrom = 81;
-// ... and between these batch sizes the layer-wavefront engine with a single layer (its small-M products on the matrix cores, a
-// batch tile of 16 rows per workgroup then) is faster than both (same shapes, ms per call at B = 48 / 56 / 64 / 80 / 128 / 160: chunks
-// 23.6 / 30.7 / 31.4 / 39.3 / - / -, batched steps 35.4 / 37.5 / 39.8 / 40.5 / 41.7 / 48.4, this engine 28.5 / 28.3 / 29.2 / 30.9 /
-// 33.2 / 49.2)
 constexpr int kWaveFrom = 49, kWaveTo = 128;
 
 // Scratch of the loop-free evaluations / of the backward pass for max_batch x max_seq positions: allocated once, at
@@ -707,8 +708,9 @@ static rt_status decode_impl(rt_ctx *c, const LayerDims &D, const rt_layer_weigh
 {
     const Weights W = to_weights(w);
     hipStream_t st = c->stream;
-    // up to three times the rows the single launch takes: one launch per chunk of those rows (batch rows are independent;
-    // MI355X, d = 1024, t = 511: B = 32 takes 63 us in two chunks against 85 us as eight launches, B = 64 126 against 121)
+    // up to three times the rows the single launch takes: one launch per chunk of those rows (batch rows are independent).  MI355X,
+    // d = 1024, t = 511, us in chunks / as eight launches: B = 17 61 / 68, B = 32 61 / 74, B = 33 92 / 75, B = 48 92 / 79 (85 and more before
+    // the eight took 32 sequences per workgroup, when the line was drawn), B = 64 126 / 84
     if (sizeof(T) == 2 && c->dec.available && D.B > c->dec.max_batch && D.B <= 3 * c->dec.max_batch) {
         c->engine = "decode-single-launch";
         const size_t row = (size_t)D.d * sizeof(T);

@@ -367,7 +367,10 @@ static void gemv(hipStream_t st, const T *W, int n_out, int n_in, const float *i
 // two fragments of a piece are 32 consecutive bytes of a weight row and 64 of an input row) and meet in LDS in a fixed order.
 // Workgroups of the same outputs are a multiple of eight apart, hence on one XCD, whose L2 keeps that share of the matrices (24 d^2
 // bytes / 8 = 2.9 MB at d = 1024) from one position to the next.
-// 48 rows, d = 1024, the four products of a position: 215 -> 40 us, the backward pass of 48 x 512 positions 129 -> 37.8 ms.  grid (n_out / (16 NT), ceil(B / 16)), block 512.
+// 48 rows, d = 1024, the four products of a position: 215 -> 40 us, the backward pass of 48 x 512 positions 129 -> 37.5 ms.  Also the
+// faster form for few rows, where the single launch does not run (a tile of 16 is mostly padding then, but the plain-ALU form reads
+// its matrix no less often): 128 positions, B = 1 / 8, d = 128: 4.7 / 6.3 -> 3.6 / 3.9 ms, d = 320: 5.0 / 6.6 -> 4.1 / 4.6, d = 1088: 7.7 / 10.0 -> 6.0 / 7.3.
+// grid (n_out / (16 NT), ceil(B / 16)), block 512.
 struct Parts3 {
     Frag h, m, l;
 };

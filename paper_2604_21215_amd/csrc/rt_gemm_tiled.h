@@ -36,7 +36,8 @@ template <int MT_, int NT_, int KG_, int KT_, int STAGES_> struct GemmTile {
     // piece of row r in slot c: c ^ swz(r).  A row of 64 bytes shares its 128 bytes of banks with its neighbour.
     __device__ static int swz(int r) { return kPieces == 4 ? (r >> 1) & 3 : r & 7; }
 };
-// Many rows: two workgroups per compute unit (72 KB each).
+// Many rows: two workgroups per compute unit (72 KB each).  d = 1024, 16384 rows, us: pre-pass / Wo / W2 / W1 176 / 66 / 165 / 255 (W1 is bound by its
+// 67 M GELUs and stores), with the tiles staged through registers (staged_mainloop) 181 / 65 / 169 / 258.
 using TileMany = GemmTile<4, 2, 1, 32, 3>;
 constexpr int kGtRows = TileMany::kRows, kGtCols = TileMany::kCols;
 

@@ -1107,7 +1107,7 @@ using StepTileHeads = GemmTile<1, 2, 2, 64, 4>;   // 64 x 128: two heads
 
 struct StepArgs {
     const bf16_t *A, *W, *W2nd;   // A [B][K]; W2nd: Wv (SG_KV)
-    int B, Nn, K, N, t, H, norm_free;
+    int B, Nn, K, N, t, norm_free;
     float alpha, eps;
     const bf16_t *gain;           // of the next product's input (SG_WO, SG_W2), g_k (SG_KV); may be null
     const bf16_t *x;              // SG_WO: residual rows of [B][N][d]
@@ -1226,8 +1226,10 @@ template <int EPI, class T> static void step_gemm(const StepArgs &P, hipStream_t
                        dim3(T::kThreads), 0, st, P);
 }
 
-// From 129 sequences on (fewer reach this engine only at widths the layer-wavefront engine does not take), where the split-contraction
-// kernels are slower throughout: 512 positions of 160 / 256 / 512 sequences, d = 1024: 45.7 / 49.0 / 68.2 -> 29.8 / 32.9 / 44.3 ms.
+// From 129 sequences on, where the layer-wavefront engine ends; the split-contraction kernels are slower throughout: 512 positions of
+// 160 / 256 / 512 sequences, d = 1024: 45.7 / 49.0 / 68.2 -> 29.6 / 33.0 / 44.3 ms; 128 positions of 129 / 600, d = 128: 3.9 / 4.5 -> 3.4 / 3.7,
+// d = 512: 5.8 / 10.2 -> 4.9 / 7.1.  81 to 128 sequences come here where that engine does not take them (other widths, p_min above 64, a
+// workspace of another chunk, blocks of one position) and keep the split-contraction kernels (B = 128, d = 1024: 41.7 ms against 28.8).
 // Both widths multiples of 128: whole k-tiles and column tiles.
 static bool step_products(const LayerDims &D, const Weights &W)
 {
@@ -1241,7 +1243,7 @@ static void step_position(const LayerDims &D, const Weights &W, const Scratch &S
 {
     const int d = D.d, F = D.F;
     StepArgs P = {};
-    P.B = D.B; P.N = D.N; P.t = t; P.H = D.H; P.norm_free = D.norm_free; P.alpha = D.alpha; P.eps = D.eps;
+    P.B = D.B; P.N = D.N; P.t = t; P.norm_free = D.norm_free; P.alpha = D.alpha; P.eps = D.eps;
     P.h = S.h;
     // h = x + alpha Wo a
     P.A = S.op_a; P.W = (const bf16_t *)W.Wo; P.Nn = d; P.K = d; P.gain = (const bf16_t *)W.g_mlp; P.x = (const bf16_t *)x;
