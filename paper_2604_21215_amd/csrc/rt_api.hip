@@ -3,6 +3,7 @@
 #include "../../include/rt.h"
 #include "rt_common.h"
 #include "rt_persistent.h"
+#include "rt_group.h"
 #include "rt_decode_persistent.h"
 #include "rt_backward.h"
 #include "rt_side_streams.h"
@@ -35,6 +36,7 @@ struct rt_ctx {
     std::string err;
     std::string engine;
     PersistentState persist;
+    GroupState group;                // the same loop by four groups of workgroups: taken where it covers the shape
     DecodeCoopState dec;             // single-launch decoding step
     // layer-wavefront engine: one scratch set per layer and the device copy of the layer descriptors
     void *stack_slab = nullptr;
@@ -408,6 +410,7 @@ rt_status rt_create(const rt_config *cfg, rt_ctx **out)
         if (hipMalloc(&c->kv_chunk, two) == hipSuccess) c->kv_chunk_bytes = two;
         else { (void)hipGetLastError(); c->kv_chunk = nullptr; }   // such batches then never run in chunks
     }
+    if (c->persist.available) (void)group_create(c->group, c->cfg, D);   // shapes it does not cover keep the 256-workgroup form
     (void)decode_coop_create(c->dec, c->cfg, D);   // shapes it does not cover keep the multi-launch step
     // scratch of the other entry points, when the caller wants no allocation inside a later call
     rt_status rs = RT_OK;
@@ -443,6 +446,7 @@ rt_status rt_destroy(rt_ctx *c)
     if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
     if (c->capture_stream) (void)hipStreamDestroy(c->capture_stream);
     persistent_destroy(c->persist);
+    group_destroy(c->group);
     decode_coop_destroy(c->dec);
     if (c->kv_chunk) (void)hipFree(c->kv_chunk);
     if (c->stack_slab) (void)hipFree(c->stack_slab);
@@ -463,7 +467,7 @@ static const char *static_last_error();
 const char *rt_last_error(const rt_ctx *c) { return c ? c->err.c_str() : static_last_error(); }
 uint64_t rt_workspace_bytes(const rt_ctx *c)
 {
-    return c ? (uint64_t)c->slab_bytes + c->kv_chunk_bytes + persistent_bytes(c->persist) + decode_coop_bytes(c->dec) + c->stack_bytes +
+    return c ? (uint64_t)c->slab_bytes + c->kv_chunk_bytes + persistent_bytes(c->persist) + group_bytes(c->group) + decode_coop_bytes(c->dec) + c->stack_bytes +
                    c->par_bytes + c->bw_bytes
              : 0;
 }
@@ -472,7 +476,8 @@ const char *rt_engine_name(const rt_ctx *c) { return c ? c->engine.c_str() : "";
 int32_t rt_device_wait_expired(rt_ctx *c)
 {
     if (!c) return 0;
-    const int v = persistent_wait_expired(c->persist);
+    int v = persistent_wait_expired(c->persist);
+    if (!v) v = group_wait_expired(c->group);
     if (v) {
         c->broken = true;
         c->err = "a bounded device-side wait expired in the persistent engine";
@@ -499,6 +504,7 @@ int32_t rt_device_wait_expired(rt_ctx *c)
 int32_t rt_phase_trace(rt_ctx *c, uint64_t *out, int32_t rows)
 {
     if (!c || !out || rows < 1) return 0;
+    if (c->group.launched) return group_read_trace(c->group, (unsigned long long *)out, rows);
     return persistent_read_trace(c->persist, (unsigned long long *)out, rows);
 }
 
@@ -611,6 +617,14 @@ static rt_status prefill_stepwise(rt_ctx *c, const LayerDims &D, const rt_layer_
     return RT_OK;
 }
 
+// the sequential loop as one launch: by groups of workgroups where that form covers the shape
+static rt_status single_launch_prefill(rt_ctx *c, const LayerDims &D, const Weights &W, const void *x, void *y, void *K, void *V,
+                                       std::string &err)
+{
+    if (group_supported(c->group, D)) return group_prefill(c->group, D, W, c->S, x, y, K, V, c->stream, err);
+    return persistent_prefill(c->persist, D, W, c->S, x, y, K, V, c->stream, err);
+}
+
 extern "C" rt_status rt_layer_prefill(rt_ctx *c, const rt_layer_weights *w, const void *x, int32_t B, int32_t N, void *y,
                                       void *K, void *V, int32_t kv_cap)
 {
@@ -645,7 +659,7 @@ extern "C" rt_status rt_layer_prefill(rt_ctx *c, const rt_layer_weights *w, cons
         else e = Launch<float>::prepass(D, W, c->S, x, B, N, false, c->stream);
         if (e != hipSuccess) return fail_hip(c, e, "prepass");
         std::string perr;
-        s = persistent_prefill(c->persist, D, W, c->S, x, y, K, V, c->stream, perr);
+        s = single_launch_prefill(c, D, W, x, y, K, V, perr);
         if (s != RT_OK) { c->err = perr; if (s == RT_ERR_HIP) c->broken = true; }
         return s;
     }
@@ -687,7 +701,7 @@ extern "C" rt_status rt_layer_prefill(rt_ctx *c, const rt_layer_weights *w, cons
             hipError_t e = Launch<bf16_t>::prepass(Dc, W, c->S, xc, nb, N, c->use_mfma, c->stream);
             if (e != hipSuccess) return fail_hip(c, e, "prepass");
             std::string perr;
-            s = persistent_prefill(c->persist, Dc, W, c->S, xc, yc, Kc, Vc, c->stream, perr);
+            s = single_launch_prefill(c, Dc, W, xc, yc, Kc, Vc, perr);
             if (s != RT_OK) { c->err = perr; if (s == RT_ERR_HIP) c->broken = true; return s; }
             RT_TRY(hipMemcpy2DAsync((char *)K + (size_t)b0 * row, (size_t)B * row, Kc, (size_t)nb * row, (size_t)nb * row, (size_t)N,
                                     hipMemcpyDeviceToDevice, c->stream), "hipMemcpy2DAsync");

@@ -1,0 +1,20 @@
+"""The sequential loop by groups of workgroups (p_min 32, up to 16 sequences): every number of sequences per group (1, 2, 4 rows
+of the exchanged vectors, full and ragged), every width (odd multiples of 256 leave half a contraction chunk empty), lengths at
+the edges of the direct window and of the blocks that stay in one workgroup (up to 512 keys) or are spread over a group."""
+import pytest
+
+from tests.test_gpu_parity import _run_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d", [256, 512, 768, 1024])
+@pytest.mark.parametrize("B,N,alibi", [(1, 65, 0.0), (4, 34, 8.0), (5, 97, 0.0), (8, 33, 8.0), (9, 66, 0.0), (16, 64, 8.0)])
+def test_rows_per_group(oracle, d, B, N, alibi):
+    _run_case(oracle, "bf16", B, N, d, d // 64, 4 * d, gains="random", scale=0.5, alpha=0.7, alibi=alibi, kv_cap=N + 1,
+              expect_engine="persistent")
+
+
+@pytest.mark.parametrize("B,N,alibi", [(5, 1100, 0.0), (2, 1290, 8.0)])
+def test_blocks_of_up_to_1024_keys(oracle, B, N, alibi):
+    _run_case(oracle, "bf16", B, N, 256, 4, 1024, gains="random", scale=0.125, alibi=alibi, expect_engine="persistent")
