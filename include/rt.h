@@ -25,9 +25,9 @@
  * All pointers named "device" are device (HBM) addresses valid on rt_config.device.  The calls return
  * without synchronising, and their work is ordered on rt_config.stream: it starts after everything
  * enqueued there before the call, and whatever is enqueued there after the call sees its outputs.
- * Every entry point enqueues on that stream alone except rt_stack_prefill, which puts two of its three
- * groups of layers on streams lent to the call, forked from and joined back into rt_config.stream by
- * events inside the call (see there).  The caller owns x, y, K, V and the weights; the context owns
+ * Every entry point enqueues on that stream alone except rt_stack_prefill where it runs as launches per
+ * position: that form puts two of its three groups of layers on streams lent to the call, forked from and
+ * joined back into rt_config.stream by events inside the call (see there).  The caller owns x, y, K, V and the weights; the context owns
  * only scratch memory.  No exceptions cross this boundary.
  */
 #ifndef RT_H_
@@ -166,16 +166,21 @@ rt_status rt_decode_step_static(const rt_config *cfg, const rt_layer_weights *w,
  *   y, K, V: host arrays of L device pointers: y[l] [B, N, d] output of layer l (all L are written: y[l] is layer
  *   l + 1's input), K[l], V[l] [kv_cap, B, H, head_dim] rows 0..N-1 written.  No two of these tensors may overlap.
  *   chunk: power of two >= p_min (>= 64 with the MFMA kernels); 0 = 64.
+ * Two forms.  bf16 with the MFMA kernels, p_min 32, d_model in {256, 512, 768, 1024}, d_hidden = 4 d_model, a device with 256 compute
+ * units and up to eight sequences (up to sixteen for at most six layers): four layers at a time (two, one for more than four, eight
+ * sequences) with their weights on chip, one cooperative launch per step of a chunk whose length the call chooses (64 to 256
+ * positions; `chunk` is checked and not used), on rt_config.stream alone.  Everything else, and RT_FLAG_ENGINE_STEPWISE: launches
+ * per position that carry all layers.
  * Unless rt_config.reserve_stack_layers reserved them at rt_create, the first call allocates one scratch set per layer
  * (RT_ERR_OOM if that fails); it is kept until rt_destroy and
  * reused by later calls with the same chunk and at most as many layers (another shape synchronises the stream
- * and reallocates).  The layers run as three groups: the first on rt_config.stream, the others on two streams lent to
+ * and reallocates).  The layers of the second form run as three groups: the first on rt_config.stream, the others on two streams lent to
  * the call (default priority; they start after the work already enqueued on rt_config.stream and that stream continues
  * after them; the environment variable RT_WAVE_STREAMS = 1..4 sets the number of layer groups / streams, default 3).
  * The contexts of the process share these streams: a pair is lent again to calls on the same rt_config.stream, whose
  * order it has anyway, and otherwise only when all work on it is done, so that a call never waits for what another
- * stream has queued.  They go with the last context.  A call on a stream that is being captured uses streams that its
- * context owns and needs its scratch sets beforehand (reserved, or from an earlier call); its graph can be replayed, in
+ * stream has queued.  They go with the last context.  A call on a stream that is being captured uses (in that form) streams that
+ * its context owns and needs its scratch sets beforehand (reserved, or from an earlier call); its graph can be replayed, in
  * order with the context's other calls, until they are reallocated or the context is destroyed.
  * rt_decode_step continues from the caches layer by layer. */
 rt_status rt_stack_prefill(rt_ctx *ctx, const rt_layer_weights *layers, int32_t L, const void *x, int32_t B, int32_t N,

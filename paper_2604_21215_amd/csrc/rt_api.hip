@@ -41,6 +41,7 @@ struct rt_ctx {
     // layer-wavefront engine: one scratch set per layer and the device copy of the layer descriptors
     void *stack_slab = nullptr;
     size_t stack_bytes = 0;
+    GroupStackState group_stack;     // the stack on the grouped engine
     int stack_L = 0, stack_chunk = 0;
     std::vector<Scratch> stack_S;
     WaveLayer *stack_dev = nullptr;
@@ -451,6 +452,7 @@ rt_status rt_destroy(rt_ctx *c)
     if (c->kv_chunk) (void)hipFree(c->kv_chunk);
     if (c->stack_slab) (void)hipFree(c->stack_slab);
     if (c->stack_dev) (void)hipFree(c->stack_dev);
+    group_stack_destroy(c->group_stack);
     if (c->par_slab) (void)hipFree(c->par_slab);
     if (c->bw_slab) (void)hipFree(c->bw_slab);
     for (int g = 0; g < kMaxWaveStreams; ++g) {
@@ -467,7 +469,7 @@ static const char *static_last_error();
 const char *rt_last_error(const rt_ctx *c) { return c ? c->err.c_str() : static_last_error(); }
 uint64_t rt_workspace_bytes(const rt_ctx *c)
 {
-    return c ? (uint64_t)c->slab_bytes + c->kv_chunk_bytes + persistent_bytes(c->persist) + group_bytes(c->group) + decode_coop_bytes(c->dec) + c->stack_bytes +
+    return c ? (uint64_t)c->slab_bytes + c->kv_chunk_bytes + persistent_bytes(c->persist) + group_bytes(c->group) + decode_coop_bytes(c->dec) + c->stack_bytes + c->group_stack.slab_bytes +
                    c->par_bytes + c->bw_bytes
              : 0;
 }
@@ -992,6 +994,7 @@ static rt_status stack_workspace(rt_ctx *c, int L, int chunk)
     c->stack_bytes = one * L + sizeof(WaveLayer) * L;
     c->stack_L = L;
     c->stack_chunk = chunk;
+    if (L >= 2 || cfg.max_batch <= kGroups * kGroupRows) (void)group_stack_create(c->group_stack, c->group, c->base, cfg.max_batch);   // without it: the layer-wavefront launches
     return RT_OK;
 }
 
@@ -1036,6 +1039,15 @@ extern "C" rt_status rt_stack_prefill(rt_ctx *c, const rt_layer_weights *layers,
         host[l].y = y[l]; host[l].K = K[l]; host[l].V = V[l];
         poison_partials(c, c->stack_S[l]);
     }
+    LayerDims D = c->base;
+    D.B = B; D.N = N; D.kv_cap = kv_cap;
+    c->engine = "wavefront";
+    if (!(c->cfg.flags & RT_FLAG_ENGINE_STEPWISE) && group_stack_supported(c->group_stack, c->group, D, L)) {
+        std::string gerr;
+        s = group_stack_prefill(c->group_stack, c->group, D, host.data(), L, (c->cfg.flags & RT_FLAG_DEBUG_POISON) != 0, c->stream, gerr);
+        if (s != RT_OK) { c->err = gerr; if (s == RT_ERR_HIP) c->broken = true; }
+        return s;
+    }
     hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
     if (c->stream) RT_TRY(hipStreamIsCapturing(c->stream, &capturing), "hipStreamIsCapturing");
     const bool eager = capturing == hipStreamCaptureStatusNone;
@@ -1043,9 +1055,6 @@ extern "C" rt_status rt_stack_prefill(rt_ctx *c, const rt_layer_weights *layers,
         RT_TRY(hipMemcpyAsync(c->stack_dev, host.data(), sizeof(WaveLayer) * L, hipMemcpyHostToDevice, c->stream), "descriptor copy");
     else   // a captured copy would read `host` at every replay
         RT_TRY(wavefront_descriptors(host.data(), c->stack_dev, L, c->stream), "descriptors");
-    LayerDims D = c->base;
-    D.B = B; D.N = N; D.kv_cap = kv_cap;
-    c->engine = "wavefront";
     // groups of layers on streams of their own (RT_WAVE_STREAMS = 1..4 overrides the default of 3: 12 layers, B = 4, N = 4096:
     // 302 ms with two groups, 294-295 ms with three, twice as long with four - the process has four hardware queues)
     WaveStreams WS = c->wave_streams;

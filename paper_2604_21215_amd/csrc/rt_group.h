@@ -10,10 +10,11 @@ constexpr int kGroups = 4;        // groups of workgroups, two XCDs each
 constexpr int kGroupRanks = 64;   // workgroups of a group
 constexpr int kGroupRows = 4;     // sequences a group takes at most
 
-// What one group runs: one layer's weights (re-laid by group_pack) and the positions 0 .. GroupArgs::N - 1 of the rows
+// What one group runs: one layer's weights (re-laid by group_pack) and the positions 0 .. N - 1 of the rows
 // b0, b0 + bstep, ... of its tensors.  Every pointer is that of position 0.
 struct GroupWork {
     int B;                        // sequences (0: the group has no work)
+    int N;                        // positions
     int b0, bstep;
     const bf16_t *packed;         // group_pack_elements(d) elements
     const bf16_t *g_k;            // gain of the key normalisation, or null
@@ -29,7 +30,7 @@ struct GroupWork {
 };
 
 struct GroupArgs {
-    int N, rows;                  // positions; positions between two batch rows of x and y
+    int rows;                     // positions between two batch rows of x and y
     int d, H, BH;                 // BH: batch rows times heads of the tensors
     int p_min, log2_pmin, win_rows;
     float alpha, scale, eps, alibi;
@@ -72,6 +73,22 @@ hipError_t group_pack(const LayerDims &D, const Weights &W, bf16_t *packed, hipS
 rt_status group_launch(GroupState &P, const LayerDims &D, GroupArgs &A, hipStream_t st, std::string &err);
 rt_status group_prefill(GroupState &P, const LayerDims &D, const Weights &W, const Scratch &S, const void *x, void *y, void *K, void *V,
                         hipStream_t st, std::string &err);
+// A stack of layers on the same kernel (rt_group_stack.hip): the layers run concurrently, one group or two each, a chunk of
+// positions apart.
+constexpr int kStackChunk = 256;       // positions of a chunk at most
+struct GroupStackState {
+    void *slab = nullptr;
+    size_t slab_bytes = 0;
+    bf16_t *packed[kGroups] = {};      // the weights of the layers that are running
+    float *far_m = nullptr, *far_l = nullptr, *far_o = nullptr;   // per running layer [kStackChunk][B H] ([64])
+    float *pm = nullptr, *pl = nullptr, *po = nullptr;            // and the states of the blocks inside its chunk
+};
+rt_status group_stack_create(GroupStackState &T, const GroupState &P, const LayerDims &D, int max_batch);
+void group_stack_destroy(GroupStackState &T);
+bool group_stack_supported(const GroupStackState &T, const GroupState &P, const LayerDims &D, int L);
+rt_status group_stack_prefill(GroupStackState &T, GroupState &P, const LayerDims &D, const WaveLayer *layers, int L, bool poison,
+                              hipStream_t st, std::string &err);
+
 int group_read_trace(GroupState &P, unsigned long long *out, int rows);
 int group_wait_expired(GroupState &P);
 

@@ -35,7 +35,7 @@
 // earlier; the owner adds the window's newest key from its registers.
 //
 // Measured (ms per call, this form / the 256-workgroup form of rt_persistent.hip): d = 1024, N = 2048, B = 1, 8, 16:
-// 16.9 / 28.7, 17.5 / 29.1, 19.7 / 32.5; d = 768, N = 1000, B = 5 with bias 8.4 / 15.4.  A position takes 7.9 us at B = 8, of it five
+// 17.7 / 28.7, 17.5 / 29.1, 19.7 / 32.5; d = 768, N = 1000, B = 5 with bias 8.4 / 15.4.  A position takes 7.9 us at B = 8, of it five
 // exchanges of 0.5 - 1.2 us and as many products with their epilogues of 0.6 - 0.9 us.
 //
 // Everything else - logits from unrounded operands, the block decomposition shifted by one, bounded waits - is as in
@@ -530,7 +530,7 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
                 const float vr = __uint_as_float((unsigned)w3[2]) * rz;
                 kb = f32_to_bf16(kr);
                 vb = f32_to_bf16(vr);
-                if (t < A.N) {   // the newest key is one position before the query
+                if (t < W.N) {   // the newest key is one position before the query
                     const float sn = ALIBI ? A.scale * (Sq * kscale) - alibi_slope(A.alibi, uh, A.H) : A.scale * (Sq * kscale);
                     const float m_new = fmaxf(m, sn);
                     const float e1 = __expf(m - m_new), e2 = __expf(sn - m_new);
@@ -538,7 +538,7 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
                     o = o * e1 + bf16_to_f32(vb) * e2;
                 }
             }
-            if (t < A.N) {
+            if (t < W.N) {
                 const float av = o * __builtin_amdgcn_rcpf(l);   // a crosses the chip as bf16
                 const float an = dpp_odd_neighbour(av);
                 if (!(ln & 1))
@@ -548,7 +548,7 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
             // the rest follows a: only a is on the critical path of the position
             if (t >= 1) {
                 v1 = bf16_to_f32(vb);
-                if (t + 1 < A.N && (t & (A.p_min - 1)) != 0) {   // key t - 1 is two positions before query t + 1
+                if (t + 1 < W.N && (t & (A.p_min - 1)) != 0) {   // key t - 1 is two positions before query t + 1
                     s1 = A.scale * fast_sum(pre_in[((t + 1) & 1) * kPreSlot + ln] * kr);
                     if (ALIBI) s1 -= 2.f * alibi_slope(A.alibi, uh, A.H);
                 }
@@ -575,19 +575,19 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
                         }
                         *reinterpret_cast<uint4 *>(dst + 8 * j) = make_uint4(w[0], w[1], w[2], w[3]);
                     }
-                } else if (t == A.N) {
+                } else if (t == W.N) {
                     for (int k = t & ~31; k < t; ++k)
                         W.VT[((size_t)ug * kHeadDim + ln) * A.vt_stride + k] = win_v[(k & (A.win_rows - 1)) * kHeadDim + ln];
                 }
             }
         } else if (wave == 1) {   // the residual input of phase O, ahead of it and away from the merging wavefront's polls
-            if (t < A.N && (ln >> 2) < RO && (ln & 3) < B) xs[ln] = bf16_to_f32(W.x[((size_t)(W.b0 + W.bstep * (ln & 3)) * A.rows + t) * d + rank * RO + (ln >> 2)]);
+            if (t < W.N && (ln >> 2) < RO && (ln & 3) < B) xs[ln] = bf16_to_f32(W.x[((size_t)(W.b0 + W.bstep * (ln & 3)) * A.rows + t) * d + rank * RO + (ln >> 2)]);
         } else if (is_helper) {
             // (behind an event the stored states of the next query are complete only there)
-            if ((t & (A.p_min - 1)) != 0 && t + 1 < A.N)
+            if ((t & (A.p_min - 1)) != 0 && t + 1 < W.N)
                 pre_merge<ALIBI>(A, far, t + 1, ug, pre_in + ((t + 1) & 1) * kPreSlot, win_k, win_v, pre_s + ppar * 256, ln);
         } else if (is_fetcher) {
-            if ((t & (A.p_min - 1)) != 0 && ((t + 1) & (A.p_min - 1)) != 0 && t + 2 < A.N)
+            if ((t & (A.p_min - 1)) != 0 && ((t + 1) & (A.p_min - 1)) != 0 && t + 2 < W.N)
                 pre_fetch(A, W, t + 2, ug, pre_in + (t & 1) * kPreSlot, ln);
         }
     };
@@ -612,11 +612,11 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
     };
     load_weights();
 
-    for (int t0 = 0; t0 < A.N; t0 += A.p_min) {
+    for (int t0 = 0; t0 < W.N; t0 += A.p_min) {
         // ================================================================ cross-block items of the block ending at key t0 - 1
-        if (t0 > 0 && t0 < A.N - 1) {
+        if (t0 > 0 && t0 < W.N - 1) {
             const int P = t0 & -t0;
-            const int nq = min(P, A.N - 1 - t0);
+            const int nq = min(P, W.N - 1 - t0);
             int level = A.log2_pmin;
             while ((1 << level) < P) ++level;
             unsigned char *tiles = smem + L.tiles;
@@ -662,15 +662,15 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
                 load_weights();
             }
         }
-        if (is_helper && t0 + 1 < A.N) {   // the stored states of the next queries are complete now
+        if (is_helper && t0 + 1 < W.N) {   // the stored states of the next queries are complete now
             pre_fetch(A, W, t0 + 1, ug, pre_in + ((t0 + 1) & 1) * kPreSlot, lane);
             wave_sync_lds();
             pre_merge<ALIBI>(A, far, t0 + 1, ug, pre_in + ((t0 + 1) & 1) * kPreSlot, win_k, win_v, pre_s + ((t0 + 1) & 1) * 256, lane);
-        } else if (is_fetcher && t0 + 2 < A.N) {
+        } else if (is_fetcher && t0 + 2 < W.N) {
             pre_fetch(A, W, t0 + 2, ug, pre_in + (t0 & 1) * kPreSlot, lane);
         }
 
-        const int t1 = min(A.N, t0 + A.p_min);
+        const int t1 = min(W.N, t0 + A.p_min);
         for (int t = t0; t < t1; ++t) {
             const unsigned tag = A.tag_base | (unsigned)(t + 1);
             unsigned long long *wp = words + (t & 1) * X.all;
@@ -991,12 +991,18 @@ rt_status group_launch(GroupState &P, const LayerDims &D, GroupArgs &A, hipStrea
     int rows = 1;
     for (int g = 0; g < kGroups; ++g) rows = A.w[g].B > rows ? A.w[g].B : rows;
     const int BM = rows > 2 ? 4 : rows;
-    P.nonce = (P.nonce % 4095u) + 1u;   // 1..4095; fresh buffers hold tag 0
-    A.tag_base = P.nonce << 20;
-    // when the nonce wraps, words of a call 4095 calls ago (rows of a larger batch) could carry this call's tags: cleared
-    const bool all = P.nonce == 1u && P.launched;
+    // Tags: 1 .. 4094 in turn (fresh buffers hold tag 0).  When the number wraps, words of a call 4094 calls ago (rows of a larger
+    // batch) could carry this call's tags: cleared.  A captured launch is replayed with the same number: it has one of its own and
+    // clears all words first.
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    hipError_t e = st ? hipStreamIsCapturing(st, &capturing) : hipSuccess;
+    if (e != hipSuccess) { err = std::string("hipStreamIsCapturing: ") + hipGetErrorString(e); return RT_ERR_HIP; }
+    const bool captured = capturing != hipStreamCaptureStatusNone;
+    if (!captured) P.nonce = (P.nonce % 4094u) + 1u;
+    A.tag_base = (captured ? 4095u : P.nonce) << 20;
+    const bool all = captured || (P.nonce == 1u && P.launched);
     hipLaunchKernelGGL(group_clear_kernel, dim3(all ? 256 : 1), dim3(256), 0, st, P.bar, all ? P.exchange_bytes / 8 : (size_t)kGroups * 16);
-    hipError_t e = hipGetLastError();
+    e = hipGetLastError();
     if (e != hipSuccess) { err = std::string("group_clear_kernel: ") + hipGetErrorString(e); return RT_ERR_HIP; }
     void *args[] = {&A};
     e = hipLaunchCooperativeKernel((const void *)pick_kernel(D.d, BM, D.alibi > 0.f), dim3(kGroups * kGroupRanks), dim3(kPThreads), args,
@@ -1012,12 +1018,13 @@ rt_status group_prefill(GroupState &P, const LayerDims &D, const Weights &W, con
     hipError_t e = group_pack(D, W, P.packed, st);
     if (e != hipSuccess) { err = std::string("group_pack_kernel: ") + hipGetErrorString(e); return RT_ERR_HIP; }
     GroupArgs A = {};
-    A.N = D.N; A.rows = D.N; A.BH = D.B * D.H;
+    A.rows = D.N; A.BH = D.B * D.H;
     A.vt_stride = S.vt_stride; A.levels = S.levels; A.slots = S.slots;
     for (int g = 0; g < kGroups; ++g) {
         GroupWork &w = A.w[g];
         w.B = (D.B - g + kGroups - 1) / kGroups;   // sequences g, g + 4, ...
         if (w.B < 0) w.B = 0;
+        w.N = D.N;
         w.b0 = g; w.bstep = kGroups;
         w.packed = P.packed;
         w.g_k = (const bf16_t *)W.g_k;

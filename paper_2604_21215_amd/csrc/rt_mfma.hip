@@ -127,6 +127,14 @@ __global__ __launch_bounds__(256) void scale_qkv_columns_kernel(const bf16_t *__
                    pack_bf16(w[4] * gg[4], w[5] * gg[5]), pack_bf16(w[6] * gg[6], w[7] * gg[7]));
 }
 
+hipError_t scale_qkv_launch(const Weights &W, bf16_t *out, int d, hipStream_t st)
+{
+    const size_t pieces = 3 * (size_t)d * d / 8;
+    hipLaunchKernelGGL(scale_qkv_columns_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st, (const bf16_t *)W.Wq,
+                       (const bf16_t *)W.Wk, (const bf16_t *)W.Wv, (const bf16_t *)W.g_attn, out, d);
+    return hipGetLastError();
+}
+
 constexpr int kTiledMinRows = 2048;   // below this the untiled kernel's smaller block tiles fill the chip better
 
 hipError_t prepass_mfma_launch(const LayerDims &D, const Weights &W, const Scratch &S, const void *x, int Bc, int Nc,
@@ -138,9 +146,8 @@ hipError_t prepass_mfma_launch(const LayerDims &D, const Weights &W, const Scrat
         const bool aligned = aligned16(x) && (gained || (aligned16(W.Wq) && aligned16(W.Wk) && aligned16(W.Wv)));
         const bf16_t *wq = (const bf16_t *)W.Wq, *wk = (const bf16_t *)W.Wk, *wv = (const bf16_t *)W.Wv;
         if (gained) {
-            const size_t pieces = 3 * (size_t)D.d * D.d / 8;
-            hipLaunchKernelGGL(scale_qkv_columns_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st, wq, wk, wv,
-                               (const bf16_t *)W.g_attn, S.wg_qkv, D.d);
+            const hipError_t e = scale_qkv_launch(W, S.wg_qkv, D.d, st);
+            if (e != hipSuccess) return e;
             wq = S.wg_qkv; wk = wq + (size_t)D.d * D.d; wv = wk + (size_t)D.d * D.d;
         }
         const auto kernel = aligned ? prepass_tiled_kernel<true> : prepass_tiled_kernel<false>;

@@ -5,6 +5,8 @@
 
 namespace rt {
 
+typedef __bf16 bf16_pair_t __attribute__((ext_vector_type(2)));
+
 // =============================================================================================
 // Pre-pass GEMM: C[m][c] = sum_k (x[m][k] g_attn[k]) Wqkv[c][k], rows scaled by rinv[m], then qkRMS
 // per head for the q and k_tmp parts.  Block tile 128 x 128, 4 wavefronts as 2 x 2, each 64 x 64
@@ -62,9 +64,9 @@ __device__ __forceinline__ void prepass_mfma_body(const bf16_t *__restrict__ x, 
             for (int i = 0; i < 4; ++i) {
                 const uint32_t w4[4] = {a[i].u.x, a[i].u.y, a[i].u.z, a[i].u.w};
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const float lo = __uint_as_float(w4[e] << 16), hi = __uint_as_float(w4[e] & 0xFFFF0000u);
-                    ssq[i] = fmaf(lo, lo, fmaf(hi, hi, ssq[i]));
+                for (int e = 0; e < 4; ++e) {   // lo lo + hi hi + sum in one instruction (v_dot2c_f32_bf16)
+                    const bf16_pair_t pr = __builtin_bit_cast(bf16_pair_t, w4[e]);
+                    ssq[i] = __builtin_amdgcn_fdot2_f32_bf16(pr, pr, ssq[i], false);
                 }
             }
         }

@@ -3,7 +3,9 @@ of the exchanged vectors, full and ragged), every width (odd multiples of 256 le
 the edges of the direct window and of the blocks that stay in one workgroup (up to 512 keys) or are spread over a group."""
 import pytest
 
+from paper_2604_21215_amd import inputs as gen
 from tests.test_gpu_parity import _run_case
+from tests.test_gpu_stack import EMB_UNIT, _run_elementwise
 
 pytestmark = pytest.mark.gpu
 
@@ -18,3 +20,13 @@ def test_rows_per_group(oracle, d, B, N, alibi):
 @pytest.mark.parametrize("B,N,alibi", [(5, 1100, 0.0), (2, 1290, 8.0)])
 def test_blocks_of_up_to_1024_keys(oracle, B, N, alibi):
     _run_case(oracle, "bf16", B, N, 256, 4, 1024, gains="random", scale=0.125, alibi=alibi, expect_engine="persistent")
+
+
+@pytest.mark.parametrize("B,N,layers,d,alibi", [
+    (1, 65, 1, 256, 0.0), (3, 64, 2, 512, 8.0), (4, 300, 5, 256, 0.0), (5, 129, 3, 768, 0.0), (8, 200, 4, 256, 8.0),
+    (9, 130, 2, 256, 0.0), (16, 70, 6, 256, 8.0), (12, 70, 7, 256, 0.0)])
+def test_stack(oracle, B, N, layers, d, alibi):
+    """four, two or one layer at a time, more layers than run at once, chunks with a ragged last one, the first batch that leaves the
+    engine again (nine sequences and more than six layers)"""
+    wl = gen.Workload("stack_groups", "bf16", B, N, d, d // 64, 4 * d, layers=layers, vocab=300, decode_steps=2, seed=990 + B)
+    _run_elementwise(oracle, wl, B, N, 2, emb_scale=EMB_UNIT, wavefront=True, alibi=alibi)
