@@ -109,7 +109,8 @@ rt_status rt_create(const rt_config *cfg, rt_ctx **out);
  *   y [B, N, d]  device, written
  *   K, V [kv_cap, B, H, head_dim] device, position first (Sec. 6.3); rows 0..N-1 are written in place
  *   1 <= B <= max_batch, 1 <= N <= max_seq, N <= kv_cap.
- * Batch rows are independent; where the single-launch engine applies (bf16) it stages at most 16 of them, and a larger
+ * fp32 storage with d_model 128, 256 or 384, d_hidden = 4 d_model, p_min 32 and at most 32 (d_model 384: 16) rows runs as one cooperative
+ * launch.  Batch rows are independent; where the single-launch engine applies (bf16) it stages at most 16 of them, and a larger
  * batch runs as chunks of 16 rows one after the other on the stream, each chunk's pairs copied into K, V from a
  * buffer of 2 * max_seq * 16 * d elements that rt_create allocates when max_batch > 16.  With bf16 and the matrix-core
  * kernels, 49 to 128 rows run as a stack of one layer on rt_stack_prefill's engine, and more rows step through the

@@ -36,6 +36,7 @@ struct rt_ctx {
     std::string err;
     std::string engine;
     PersistentState persist;
+    GroupF32State group_f32;
     GroupState group;                // the same loop by four groups of workgroups: taken where it covers the shape
     DecodeCoopState dec;             // single-launch decoding step
     // layer-wavefront engine: one scratch set per layer and the device copy of the layer descriptors
@@ -411,6 +412,7 @@ rt_status rt_create(const rt_config *cfg, rt_ctx **out)
         if (hipMalloc(&c->kv_chunk, two) == hipSuccess) c->kv_chunk_bytes = two;
         else { (void)hipGetLastError(); c->kv_chunk = nullptr; }   // such batches then never run in chunks
     }
+    if (!(cfg->flags & (RT_FLAG_ENGINE_STEPWISE | RT_FLAG_HIP_GRAPH))) (void)group_f32_create(c->group_f32, c->cfg, D);
     if (c->persist.available) (void)group_create(c->group, c->cfg, D);   // shapes it does not cover keep the 256-workgroup form
     (void)decode_coop_create(c->dec, c->cfg, D);   // shapes it does not cover keep the multi-launch step
     // scratch of the other entry points, when the caller wants no allocation inside a later call
@@ -448,6 +450,7 @@ rt_status rt_destroy(rt_ctx *c)
     if (c->capture_stream) (void)hipStreamDestroy(c->capture_stream);
     persistent_destroy(c->persist);
     group_destroy(c->group);
+    group_f32_destroy(c->group_f32);
     decode_coop_destroy(c->dec);
     if (c->kv_chunk) (void)hipFree(c->kv_chunk);
     if (c->stack_slab) (void)hipFree(c->stack_slab);
@@ -469,7 +472,7 @@ static const char *static_last_error();
 const char *rt_last_error(const rt_ctx *c) { return c ? c->err.c_str() : static_last_error(); }
 uint64_t rt_workspace_bytes(const rt_ctx *c)
 {
-    return c ? (uint64_t)c->slab_bytes + c->kv_chunk_bytes + persistent_bytes(c->persist) + group_bytes(c->group) + decode_coop_bytes(c->dec) + c->stack_bytes + c->group_stack.slab_bytes +
+    return c ? (uint64_t)c->slab_bytes + c->kv_chunk_bytes + persistent_bytes(c->persist) + group_bytes(c->group) + c->group_f32.slab_bytes + decode_coop_bytes(c->dec) + c->stack_bytes + c->group_stack.slab_bytes +
                    c->par_bytes + c->bw_bytes
              : 0;
 }
@@ -480,6 +483,7 @@ int32_t rt_device_wait_expired(rt_ctx *c)
     if (!c) return 0;
     int v = persistent_wait_expired(c->persist);
     if (!v) v = group_wait_expired(c->group);
+    if (!v) v = group_f32_wait_expired(c->group_f32);
     if (v) {
         c->broken = true;
         c->err = "a bounded device-side wait expired in the persistent engine";
@@ -652,6 +656,16 @@ extern "C" rt_status rt_layer_prefill(rt_ctx *c, const rt_layer_weights *w, cons
     c->last_hp = false;
     poison_partials(c, c->S);
     const bool want_stepwise = (c->cfg.flags & RT_FLAG_ENGINE_STEPWISE) != 0;
+    if (group_f32_supported(c->group_f32, D)) {
+        c->engine = "persistent";
+        const Weights W = to_weights(w);
+        const hipError_t e = Launch<float>::prepass(D, W, c->S, x, B, N, false, c->stream);
+        if (e != hipSuccess) return fail_hip(c, e, "prepass");
+        std::string perr;
+        s = group_f32_prefill(c->group_f32, D, W, c->S, x, y, K, V, c->stream, perr);
+        if (s != RT_OK) { c->err = perr; if (s == RT_ERR_HIP) c->broken = true; }
+        return s;
+    }
     if (!want_stepwise && persistent_supported(c->persist, D)) {
         c->engine = "persistent";
         c->last_hp = true;

@@ -89,6 +89,24 @@ bool group_stack_supported(const GroupStackState &T, const GroupState &P, const 
 rt_status group_stack_prefill(GroupStackState &T, GroupState &P, const LayerDims &D, const WaveLayer *layers, int L, bool poison,
                               hipStream_t st, std::string &err);
 
+// fp32 storage, d = 128, 256, 384 (rt_group_f32.hip)
+struct GroupF32State {
+    bool available = false, launched = false;
+    void *slab = nullptr;
+    size_t slab_bytes = 0, exchange_bytes = 0, group_stride = 0, lds = 0;
+    unsigned long long *bar = nullptr, *words = nullptr;
+    void *packed = nullptr;
+    long long spin_limit = 0;
+    unsigned nonce = 0;
+    int groups = 0, max_batch = 0;
+};
+rt_status group_f32_create(GroupF32State &P, const rt_config &cfg, const LayerDims &D);
+void group_f32_destroy(GroupF32State &P);
+bool group_f32_supported(const GroupF32State &P, const LayerDims &D);
+rt_status group_f32_prefill(GroupF32State &P, const LayerDims &D, const Weights &W, const Scratch &S, const void *x, void *y, void *K, void *V,
+                            hipStream_t st, std::string &err);
+int group_f32_wait_expired(GroupF32State &P);
+
 int group_read_trace(GroupState &P, unsigned long long *out, int rows);
 int group_wait_expired(GroupState &P);
 

@@ -41,7 +41,7 @@
 // Everything else - logits from unrounded operands, the block decomposition shifted by one, bounded waits - is as in
 // rt_persistent.hip.
 #include "rt_group.h"
-#include "rt_ll.h"
+#include "rt_group_device.h"
 #include "rt_cross_tile.h"
 
 #include <cstdlib>
@@ -86,29 +86,11 @@ __host__ __device__ inline GroupWords group_words(int d)
     return w;
 }
 
-// A pointer read out of the kernel's arguments by a computed index is a generic address to the compiler; all of these are
-// global memory.
-template <typename T> __device__ __forceinline__ T *as_global(T *p)
-{
-    return (T *)(__attribute__((address_space(1))) T *)(uintptr_t)p;
-}
-
-struct GroupWait {   // what the bounded waits of rt_ll.h need
-    long long spin_limit;
-    unsigned long long *bar;
-};
-
 // word of element pair (k, k + 1), k even, of batch row b: 16-byte pieces of four elements, runs of RUN pieces per batch row
 template <int RUN, int BM> __device__ __forceinline__ unsigned piece_word(unsigned k, unsigned b)
 {
     const unsigned p = k >> 2;
     return (((p / RUN) * BM + b) * RUN + p % RUN) * 2 + ((k >> 1) & 1);
-}
-
-// a word at a 32-bit offset from a uniform base: no 64-bit address per lane
-__device__ __forceinline__ void word_store(unsigned long long *base, unsigned idx, unsigned tag, unsigned payload)
-{
-    ll_store(reinterpret_cast<ll_t *>(reinterpret_cast<char *>(base) + (size_t)(idx * 8u)), tag, payload);
 }
 
 // Operands of v_mfma_f32_4x4x4_16b_bf16 (16 blocks, block i = lanes 4i .. 4i+3): A: lane holds A[row = lane%4][k = 0..3] of
@@ -129,10 +111,6 @@ union WFrag {
 // holds elements 64 m + 4 (l/4) .. + 3 of batch row l%4 % BM - the A operand of the product, nothing is staged in LDS.  With
 // fewer than four batch rows the lanes of the unused rows fetch the pieces of the chunks that follow, and a move inside the
 // four lanes of a block brings them where they belong.
-template <int CTRL> __device__ __forceinline__ unsigned quad_move(unsigned v)
-{
-    return (unsigned)__builtin_amdgcn_mov_dpp((int)v, CTRL, 0xF, 0xF, true);
-}
 template <int NC, int LEN, int RUN, int BM>
 __device__ __forceinline__ void slice_pull(const ll_t *vec, int wave, int lane, int B, unsigned tag, const GroupWait &A, Piece (&act)[NC],
                                            int &fail, int units)
@@ -193,18 +171,6 @@ __device__ __forceinline__ f32x4_t chunk_product(const Piece &a, const WFrag &w0
     acc = mfma4<2>(a, w1.h[0], acc);
     return mfma4<3>(a, w1.h[1], acc);
 }
-// The four rows of 16 lanes hold partial sums: fold2 adds the halves of two accumulators (low lanes get a's sum, high lanes
-// b's), fold1 the rows 0 + 1 and 2 + 3 (row 0: a low, row 1: b low, row 2: a high, row 3: b high).
-__device__ __forceinline__ float fold2(float a, float b)
-{
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-__device__ __forceinline__ float fold1(float a, float b)
-{
-    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
 // partial products of NT tiles -> red[wave][16 tile + lane%16][batch row]
 template <int NT> __device__ __forceinline__ void tiles_store(float *red, int wave, int lane, const f32x4_t (&acc)[NT])
 {
@@ -227,27 +193,6 @@ template <int NT> __device__ __forceinline__ void tiles_store(float *red, int wa
     }
     if (tile < NT) *reinterpret_cast<f32x4_t *>(red + ((size_t)wave * 64 + tile * 16 + (lane & 15)) * 4) = s;
 }
-__device__ __forceinline__ float tile_sum(const float *red, int row4b)   // row4b = 4 row + batch row
-{
-    float v[kPW];
-#pragma unroll
-    for (int w = 0; w < kPW; ++w) v[w] = red[w * 256 + row4b];
-    return ((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7]));
-}
-// value of lane + 4 inside a row of 16 lanes (row_shl:4): the partner of a bf16 pair where the lanes are [row][4]
-__device__ __forceinline__ float row_partner(float v)
-{
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x104, 0xF, 0xF, true));
-}
-// sum over the lanes that are equal modulo 4
-__device__ __forceinline__ float sum_mod4(float v)
-{
-    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xF, 0xF, true));   // row_ror:8
-    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x124, 0xF, 0xF, true));
-    v = fold1(v, v);
-    return fold2(v, v);
-}
-
 // ---- Pre-merge of query t (everything but its two newest keys).  slot (floats of LDS): q, k_tmp, v_tmp rows; m[20], l[20] of
 // the stored states; their o rows.
 __device__ __forceinline__ int pre_levels(const GroupArgs &A, int t) { return t >= 2 ? (t - 1) >> A.log2_pmin : 0; }
@@ -417,16 +362,6 @@ __host__ __device__ constexpr GroupLds group_lds(int KSD, int win_rows)
         if (A.trace && wave == 0 && lane == 0 && grp == 0 && (rank == 0 || rank == A.trace_rank))                                     \
             A.trace[((size_t)(rank == 0 ? 0 : A.trace_rows) + t) * 16 + (k)] = wall_clock64();                          \
     } while (0)
-#define RT_GROUP_SYNC(cond)                                                                                               \
-    do {                                                                                                                  \
-        if (cond) flag_s[1] = 1;                                                                                          \
-        __syncthreads();                                                                                                  \
-        if (flag_s[1] != 0) {                                                                                             \
-            if (threadIdx.x == 0) __hip_atomic_store(G.bar + 8, 1ULL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);        \
-            return;                                                                                                       \
-        }                                                                                                                 \
-    } while (0)
-
 // KSD = d / 256; BM: sequences per group the exchanged vectors are laid out for (1, 2 or 4)
 template <int KSD, int BM, bool ALIBI>
 __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)

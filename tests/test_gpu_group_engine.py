@@ -30,3 +30,11 @@ def test_stack(oracle, B, N, layers, d, alibi):
     engine again (nine sequences and more than six layers)"""
     wl = gen.Workload("stack_groups", "bf16", B, N, d, d // 64, 4 * d, layers=layers, vocab=300, decode_steps=2, seed=990 + B)
     _run_elementwise(oracle, wl, B, N, 2, emb_scale=EMB_UNIT, wavefront=True, alibi=alibi)
+
+
+@pytest.mark.parametrize("B,N,d,alibi", [(1, 1, 128, 0.0), (2, 34, 256, 8.0), (3, 65, 384, 0.0), (8, 130, 128, 8.0), (9, 66, 256, 0.0),
+                                         (16, 97, 384, 8.0), (4, 290, 256, 0.0), (1, 515, 128, 0.0), (32, 40, 128, 0.0)])
+def test_fp32(oracle, B, N, d, alibi):
+    """fp32 storage: one sequence per group and several, widths whose share of a contraction ends inside a chunk, blocks of 32 to 512 keys"""
+    _run_case(oracle, "f32", B, N, d, d // 64, 4 * d, gains="random", scale=0.5, alpha=0.7, alibi=alibi, kv_cap=N + 1,
+              expect_engine="persistent")
