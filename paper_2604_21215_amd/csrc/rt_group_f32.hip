@@ -7,9 +7,9 @@
 //
 // What bounds it: five exchanges per position.  The launch-per-position engine it replaces (rt_stepwise.hip, which keeps every
 // other shape, parameter and RT_FLAG_HIP_GRAPH) spends six dependent launches on one.
-// Measured (ms per call, launches per position / here): d = 128, B = 1, N = 256: 7.9 / 2.0; d = 256, B = 4, N = 512: F32A / 5.4;
-// d = 384, B = 3, N = 300: F32B / 3.2.  Blocks of 64 keys and more are plain fp32 dot products of the owning workgroup, 5 - 8 % of
-// these calls.  Distance from fp64 as before or smaller (y 1.0e-7 at d = 256, N = 290; launches 1.3e-7 at N = 150).
+// Measured (ms per call, launches per position / here): d = 128, B = 1, N = 256: 7.9 / 1.8, N = 2000: 64 / 15.4; d = 256, B = 4, N = 512:
+// 19.1 / 4.5; d = 256, B = 32, N = 300: 43 / 3.0; d = 384, B = 3, N = 300: 10.8 / 3.0.  Distance from fp64 as before or smaller (y 1.0e-7
+// at d = 256, N = 290; launches 1.3e-7 at N = 150).
 #include "rt_group.h"
 #include "rt_group_device.h"
 
@@ -20,7 +20,9 @@ namespace rt {
 
 constexpr int kF32Levels = 16;     // stored-partial levels of a query
 constexpr int kF32Slot = 3 * 64 + 2 * 20 + kF32Levels * 64;
-constexpr int kF32SpreadP = 128;   // blocks of at least this many keys are spread over the group, between two fenced barriers
+// Blocks of at least this many keys are spread over the group, between two fenced barriers.  ms per call with 64 / 128 / never:
+// d = 128, N = 256 1.78 / 1.87 / 1.97; d = 256, B = 4, N = 512 4.51 / 4.61 / 5.41; d = 128, N = 2000 15.4 / 15.8 / 36.9
+constexpr int kF32SpreadP = 64;
 constexpr int kF32Tile = 8;        // outputs of a tile
 
 constexpr int f32_ranks(int D) { return D <= 2 ? 32 : 64; }    // workgroups of a group, D = d / 128
