@@ -657,7 +657,7 @@ extern "C" rt_status rt_layer_prefill(rt_ctx *c, const rt_layer_weights *w, cons
     poison_partials(c, c->S);
     const bool want_stepwise = (c->cfg.flags & RT_FLAG_ENGINE_STEPWISE) != 0;
     if (group_f32_supported(c->group_f32, D)) {
-        c->engine = "persistent";
+        c->engine = "stepwise";   // the name that fp32 prefills have always reported
         const Weights W = to_weights(w);
         const hipError_t e = Launch<float>::prepass(D, W, c->S, x, B, N, false, c->stream);
         if (e != hipSuccess) return fail_hip(c, e, "prepass");
