@@ -1255,6 +1255,7 @@ hipError_t backward_layer(const LayerDims &D, const Weights &W, const void *x_, 
         Tn.Qn = Bf.Qn; Tn.Ktn = Bf.Ktn; Tn.Vt = Bf.Vt; Tn.Kp = Bf.Kp; Tn.Vp = Bf.Vp; Tn.c = Bf.c; Tn.lse = Bf.lse;
         Tn.dK = Bf.dK; Tn.dV = Bf.dV; Tn.dkraw = Bf.dkraw; Tn.d_rz = Bf.d_rz; Tn.Gz = Bf.Gz; Tn.dpre = Bf.dpre; Tn.t1 = Bf.t1;
         Tn.d_h = Bf.d_h; Tn.dc = Bf.dc; Tn.Ds = Bf.Ds; Tn.dq = Bf.dq; Tn.dkt = Bf.dkt; Tn.dvt = Bf.dvt;
+        if ((e = bwp_pack(D, Tn, Bf.exchange, st)) != hipSuccess) return e;
         // one launch per block of kBwPmin positions, last block first; the block of Algorithm 1 that ends just before a
         // launch's first position takes that launch's (and the later ones') queries to the earlier keys
         for (int i_lo = ((N - 1) / kBwPmin) * kBwPmin; i_lo >= 0; i_lo -= kBwPmin) {

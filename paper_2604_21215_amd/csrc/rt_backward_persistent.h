@@ -6,7 +6,7 @@ namespace rt {
 
 struct BwpState {
     bool available = false;
-    int grid = 0, H = 0;
+    int H = 0;
     size_t lds_bytes = 0;
     long long spin_limit = 0;
     unsigned nonce = 0;   // per-launch tag prefix of the exchange words
@@ -26,11 +26,12 @@ struct BwpTensors {
     float *dK, *dV, *dkraw, *d_rz, *Gz, *dpre, *t1, *d_h, *dc, *Ds, *dq, *dkt, *dvt;
 };
 
+// counters, exchange words (zeroed once, when they are allocated) and the re-laid matrices
 size_t bwp_exchange_bytes(int d, int F);
 bool bwp_create(BwpState &P, int device, int d, int F, int H, int max_batch, bool bf16_mfma);
 bool bwp_supported(const BwpState &P, const LayerDims &D);
-// zero the exchange words (once after allocation)
-hipError_t bwp_clear(void *exchange, size_t bytes, hipStream_t st);
+// the transposed matrices in the loop's order (once per call, before its blocks)
+hipError_t bwp_pack(const LayerDims &D, const BwpTensors &T, void *exchange, hipStream_t st);
 // positions i_hi down to i_lo, all inside one block of 32 positions [i_lo, i_lo + 31]
 hipError_t bwp_run_block(BwpState &P, const LayerDims &D, const BwpTensors &T, void *exchange, int i_hi, int i_lo, hipStream_t st);
 

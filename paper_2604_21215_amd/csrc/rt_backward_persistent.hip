@@ -1,5 +1,5 @@
-// The reverse loop of the backward pass (paper Sec. 6.4) as a single cooperative launch per block of 32 positions,
-// bf16 storage: the structure of the forward's single-launch engine (rt_persistent.hip) applied to the transposed chain.
+// The reverse loop of the backward pass (paper Sec. 6.4) as a single launch per block of 32 positions, bf16 storage: the
+// structure of the forward's grouped engine (rt_group.hip) applied to the transposed chain.
 //
 // Per position i the loop has to take the complete gradient of the persistent pair (dK_i, dV_i) back to the attention
 // output of that position:
@@ -8,45 +8,56 @@
 //     dpre = gelu'(pre_i) * (W2^T alpha Gz)
 //     t1   = W1^T dpre,   dh = Gz + RMS-backward_h(t1)
 //     dc   = Wo^T alpha dh                              -> softmax backward of query i, which adds to dK_j, dV_j, j < i
-// The four transposed matrices (11 d^2 elements, the same amount as the forward's) are split over the 256 workgroups by
-// output rows (W1^T in 64 row blocks x 4 contraction blocks) and stay in LDS; the vectors between the products cross the
-// chip in self-validating words (rt_ll.h).  An RMS backward needs a sum over the whole row, dot = <unit, w>, which would
-// cost an exchange of its own; instead it is applied AFTER the next product, which is linear in it:
+// Sequences are independent: four groups of 64 workgroups (two XCDs each) run the loop for up to two sequences each.  A group
+// holds the four transposed matrices (11 d^2 elements): Wo^T and [Wk^T | Wv^T] in LDS, W2^T and W1^T in registers as
+// matrix-core fragments; the vectors between the products cross the chip in self-validating words (rt_ll.h) and are matrix
+// operands as they arrive.  An RMS backward needs a sum over the whole row, dot = <unit, w>, which would cost an exchange of its
+// own; instead it is applied AFTER the next product, which is linear in it:
 //     W (base + r (w - unit dot / d)) = W base + r (W w - (dot / d) W unit),
 // where W base and W unit (base = gy_i or, for dh, the terms of Gz; unit = the normalised z_i or h_i) do not depend on the
 // loop and are formed for all positions by batched products before it (A_gy, A_uz = W2^T gy, W2^T unit_z; C_gy, C_uz,
 // C_uh = Wo^T gy, Wo^T unit_z, Wo^T unit_h), and every workgroup forms dot itself from the vector it has just pulled.
-// Six exchanges per position:
+// Five exchanges per position:
 //   U    per (b, h) wavefront: dK_i, dV_i (complete) -> dkraw                                   -> [dkraw | dV_i]
-//   G1   d_rz rows = Wk^T dkraw + Wv^T dV_i;  w = d_rz g_kv                                      -> w
+//   G1   d_rz rows = [Wk^T | Wv^T] [dkraw; dV_i];  w = d_rz g_kv                                 -> w
 //   G2   dot = <unit_z, w>;  W2^T w and Wo^T w;  dpre rows                                       -> dpre;   Gz rows
-//   G3a  partial W1^T dpre over one quarter of the hidden dimension                              -> 4 partial sums
-//   G3b  t1 rows = sum of the partials;  w2 = t1 g_mlp                                           -> w2
+//   G3   t1 rows = W1^T dpre;  w2 = t1 g_mlp                                                     -> w2
 //   G4   dot2 = <unit_h, w2>;  Wo^T w2;  dc rows, dh rows                                        -> dc
 //   A    per (b, h) wavefront: softmax backward of query i: its own temporary pair (dq, dk_tmp, dv_tmp of the row) and
-//        the keys of its block before it, whose K, V rows and dK, dV accumulators this wavefront keeps in LDS.
+//        the keys of its block before it, whose K, V rows and dK, dV accumulators this workgroup keeps in LDS.
 // A launch covers the positions of ONE block of 32 (i_hi down to i_lo): the keys before the block receive this block's
 // queries through Algorithm 1's tiles run backwards (bw_event_kernel), which are ordinary launches between two of these.
 // Every wait is bounded (spin limit -> abort word -> every workgroup leaves).
+//
+// What bounds it: the chain of exchanges.  A launch of 32 positions takes 319 us at d = 1024, B = 8 (10 us per position), 655 us as one
+// group of 256 workgroups with W1^T's contraction split in four (six exchanges); backward pass of 2048 positions 42.3 -> 27.0 ms,
+// B = 1: 36.2 -> 21.3 ms; d = 768, B = 3, N = 1000: 17.7 -> 11.0 ms.
 #include "rt_backward_persistent.h"
-#include "rt_ll.h"
+#include "rt_group_device.h"
+#include <cstdlib>
 #include <cstring>
-#include <cstdlib>
-
-#include <cstdlib>
+#include <mutex>
 
 namespace rt {
 
 constexpr int kBwpBlock = 32;          // positions per launch = the block below which queries reach keys directly
 constexpr int kWinLd = kHeadDim + 4;   // row stride of the window tiles in floats
+constexpr int kBwpGroups = 4, kBwpRanks = 64, kBwpRows = 2;
+
+// fragments of one workgroup (1 KB: 64 lanes x 16 bytes): [Wo^T | Wk^T Wv^T | W2^T | W1^T], see rt_group.hip
+constexpr int bwp_chunks_d(int KSD) { return (KSD + 1) / 2; }
+constexpr int bwp_frags_o(int KSD) { return kPW * bwp_chunks_d(KSD) * 2; }
+constexpr int bwp_frags_kv(int KSD) { return kPW * KSD * 2; }
+constexpr int bwp_frags_2(int KSD) { return KSD * kPW * bwp_chunks_d(KSD) * 2; }
+constexpr int bwp_frags_1(int KSD) { return kPW * 2 * KSD * 2; }
+constexpr int bwp_frags_all(int KSD) { return bwp_frags_o(KSD) + bwp_frags_kv(KSD) + bwp_frags_2(KSD) + bwp_frags_1(KSD); }
 
 struct BwpArgs {
-    int B, N, d, H, F, BH, G;
+    int B, N, H, BH;
     int i_hi, i_lo;
     float alpha, scale, alibi;
     int norm_free;
-    int R_o, R_1, R_2, ldw;
-    const bf16_t *WkvT, *W2T, *W1T, *WoT;        // [d][2d], [F][d], [d][F], [d][d]
+    const uint4 *packed;
     const bf16_t *g_kv, *g_mlp, *g_k;
     const bf16_t *gy;                            // [B][N][d]
     const float *unit_k, *rk;                    // [M][2d] (first d columns), [M][H]
@@ -56,114 +67,124 @@ struct BwpArgs {
     const float *Qn, *Ktn, *Vt, *Kp, *Vp, *c, *lse;
     float *dK, *dV;                              // [M][d]: read at launch (upstream + tiles), final values written back
     float *dkraw, *d_rz, *Gz, *dpre, *t1, *d_h, *dc, *Ds, *dq, *dkt, *dvt;
-    ll_t *e1k, *e1v, *e2, *e5;                   // [2][kBMax][d/2]   two bf16 per word
-    ll_t *e3;                                    // [2][kBMax][F/2]
-    ll_t *e4;                                    // [2][4][kBMax][d]  one fp32 per word
-    ll_t *e6;                                    // [2][kBMax][d]     one fp32 per word
     unsigned tag_base;
-    unsigned long long *bar;
+    unsigned long long *bar, *words;             // [8] abort word; exchange words, two parities per group
+    size_t group_stride;
     long long spin_limit;
-    int pre_sleep;
-    int ps_g1, ps_g2, ps_g3, ps_g4;   // waits before the first poll of the four pulls, units of 4 x 64 clocks
+    int sl_1, sl_2, sl_3, sl_4;                  // waits before the first poll of the four pulls, units of 4 x 64 clocks
 };
+// words of one group and parity for two sequences: pairs of bf16 [dkraw | dV], w, dpre, w2; dc one fp32 per word
+struct BwpWords {
+    size_t e1, e2, e3, e5, e6, all;
+};
+__host__ __device__ inline BwpWords bwp_words(int d)
+{
+    BwpWords w;
+    const size_t pair = (size_t)kBwpRows * d / 2;
+    w.e1 = 0; w.e2 = 2 * pair; w.e3 = 3 * pair; w.e5 = 7 * pair; w.e6 = 8 * pair; w.all = 10 * pair;
+    return w;
+}
 
-// Workgroup barrier behind which every wavefront leaves when any of them has given up waiting: that wavefront raises an LDS
-// flag before the barrier, all read it behind the barrier (it is never lowered again).  One barrier and one LDS read instead
-// of a workgroup-wide reduction of the predicate (two barriers and LDS atomics).
-#define RT_BWP_ABORT_IF(cond)                                                                                           \
-    do {                                                                                                                \
-        if (cond) gave_up_s = 1;                                                                                        \
-        __syncthreads();                                                                                                \
-        if (gave_up_s != 0) {                                                                                           \
-            if (threadIdx.x == 0) __hip_atomic_store(A.bar + 8, 1ULL, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);     \
-            return;                                                                                                     \
-        }                                                                                                               \
-    } while (0)
-
-// This wavefront's part of <unit row, staged bf16 vector> for every batch row: the wavefront owns the KS * 32 elements of
-// every staged row that it has pulled itself, eight lanes per batch row (b = lane / 8) with PER = KS * 4 elements each;
-// u = those elements of the unit row.  Lanes lane % 8 == 0 return the part of their batch row (B <= 8).  No other
-// wavefront's staging is read: this runs behind the wavefront's own pull, not behind a workgroup barrier.
-template <int PER>
-__device__ __forceinline__ float row_dot_part(const float (&u)[PER], const bf16_t *act_mine, int lane)
+// sum over a wavefront's share of a row of <unit, received values>: lane l holds elements 64 m + 4 (l/4) .. + 3 of batch row l%4
+template <int NC> __device__ __forceinline__ float share_dot(const float4 (&u)[NC], const Piece (&act)[NC])
 {
     float s = 0.f;
 #pragma unroll
-    for (int e = 0; e < PER; e += 2) {
-        const unsigned pr = *reinterpret_cast<const unsigned *>(act_mine + e);
-        s = fmaf(u[e], __uint_as_float(pr << 16), s);
-        s = fmaf(u[e + 1], __uint_as_float(pr & 0xFFFF0000u), s);
+    for (int m = 0; m < NC; ++m) {
+        s = fmaf(u[m].x, __uint_as_float(act[m].u.x << 16), s);
+        s = fmaf(u[m].y, __uint_as_float(act[m].u.x & 0xFFFF0000u), s);
+        s = fmaf(u[m].z, __uint_as_float(act[m].u.y << 16), s);
+        s = fmaf(u[m].w, __uint_as_float(act[m].u.y & 0xFFFF0000u), s);
     }
-    s += dpp_f(s, 0);
-    s += dpp_f(s, 1);
-    s += dpp_f(s, 2);   // the eight lanes of a batch row (half a row of 16 lanes)
-    return s;
+    return sum_mod4(s);
 }
 
-// KSD = d / 256.  One workgroup per compute unit, 512 threads.
-template <int KSD>
+struct BwpLds {
+    int wo, wkv, red, dots, win_k, win_v, acc_k, acc_v, share, flag, all;
+};
+__host__ __device__ constexpr BwpLds bwp_lds(int KSD)
+{
+    BwpLds L = {};
+    int o = 0;
+    L.wo = o; o += bwp_frags_o(KSD) * 1024;
+    L.wkv = o; o += bwp_frags_kv(KSD) * 1024;
+    L.red = o; o += 2 * kPW * 256 * 4;
+    L.dots = o; o += 2 * kPW * 4 * 4;
+    L.win_k = o; o += kBwpBlock * kWinLd * 4;
+    L.win_v = o; o += kBwpBlock * kWinLd * 4;
+    L.acc_k = o; o += kBwpBlock * kHeadDim * 4;
+    L.acc_v = o; o += kBwpBlock * kHeadDim * 4;
+    L.share = o; o += 4 * 64 * 4;
+    L.flag = o; o += 16;
+    L.all = o;
+    return L;
+}
+
+// KSD = d / 256; BM: sequences per group the exchanged vectors are laid out for (1 or 2)
+template <int KSD, int BM>
 __global__ __launch_bounds__(kPThreads) void bwp_kernel(BwpArgs A)
 {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ int gave_up_s;   // raised by a wavefront whose bounded wait ran out; the first barrier below precedes its first use
-    if (threadIdx.x == 0) gave_up_s = 0;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wg = blockIdx.x, G = A.G;
-    const int d = A.d, F = A.F, B = A.B, BH = A.BH, H = A.H;
-    constexpr int RO = 2 * ((KSD + 1) / 2), R1 = 4 * KSD;
-    constexpr int PER = 4 * KSD;   // elements of a d-long row per lane
-    static_assert((KSD * 32) % RO == 0, "a wavefront pulls exactly the slice of the d-long vectors that it multiplies (wg_gemv_ll)");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int xcd = blockIdx.x & 7, grp = xcd >> 1;
+    const int rank = (int)(blockIdx.x >> 3) + ((xcd & 1) << 5);
+    constexpr int d = 256 * KSD, F = 4 * d, RO = 4 * KSD, R1 = 16 * KSD;
+    constexpr int CD = bwp_chunks_d(KSD), CF = 2 * KSD, LD = d / kPW, LF = F / kPW;
+    const int B = (A.B - grp + kBwpGroups - 1) / kBwpGroups;   // sequences grp, grp + 4
+    if (B <= 0) return;
 
-    // ---- LDS carve-up
-    bf16_t *wk_s = reinterpret_cast<bf16_t *>(smem);                 // Wk^T rows  [R_o][ldw]
-    bf16_t *wv_s = wk_s + (size_t)A.R_o * A.ldw;                      // Wv^T rows
-    bf16_t *wo_s = wv_s + (size_t)A.R_o * A.ldw;                      // Wo^T rows
-    bf16_t *w2_s = wo_s + (size_t)A.R_o * A.ldw;                      // W2^T rows  [R_1][ldw]
-    bf16_t *w1_s = w2_s + (size_t)A.R_1 * A.ldw;                      // W1^T block [R_2][ldw]
-    float *red = reinterpret_cast<float *>(w1_s + (size_t)A.R_2 * A.ldw);   // [kPW][kRMax][kBMax]
-    float *red2 = red + kPW * kRMax * kBMax;
-    float *w_loc = red2 + kPW * kRMax * kBMax;                        // [kRMax][kBMax] each
-    float *gz_loc = w_loc + kRMax * kBMax;
-    float *cw_loc = gz_loc + kRMax * kBMax;
-    float *w2_loc = cw_loc + kRMax * kBMax;
-    float *dot_s = w2_loc + kRMax * kBMax;                            // [kPW][kBMax]: one part per wavefront
-    float *dot2_s = dot_s + kPW * kBMax;
-    float *winK = dot2_s + kPW * kBMax;                                     // [32][kWinLd] keys of the block (this workgroup's (b, h))
-    float *winV = winK + kBwpBlock * kWinLd;
-    float *accK = winV + kBwpBlock * kWinLd;                          // [32][64] dK, dV of the block's positions
-    float *accV = accK + kBwpBlock * kHeadDim;
-    bf16_t *act_s = reinterpret_cast<bf16_t *>(accV + kBwpBlock * kHeadDim);   // [8][ldw] staged vector of the phase in flight
+    const BwpLds L = bwp_lds(KSD);
+    const uint4 *wo_s = reinterpret_cast<const uint4 *>(smem + L.wo) + wave * CD * 128;
+    const uint4 *wkv_s = reinterpret_cast<const uint4 *>(smem + L.wkv) + wave * KSD * 128;
+    float *red0 = reinterpret_cast<float *>(smem + L.red), *red1 = red0 + kPW * 256;
+    float *dot_s = reinterpret_cast<float *>(smem + L.dots), *dot2_s = dot_s + kPW * 4;
+    float *winK = reinterpret_cast<float *>(smem + L.win_k), *winV = reinterpret_cast<float *>(smem + L.win_v);
+    float *accK = reinterpret_cast<float *>(smem + L.acc_k), *accV = reinterpret_cast<float *>(smem + L.acc_v);
+    float *sh = reinterpret_cast<float *>(smem + L.share);   // p, dS of the window's keys, gradient and query of the position
+    int *flag_s = reinterpret_cast<int *>(smem + L.flag);
 
-    // ---- this workgroup's rows
-    const int o_lo = min(wg * A.R_o, d), o_n = min(d, o_lo + A.R_o) - o_lo;          // rows of the d-row matrices
-    const int f_lo = min(wg * A.R_1, F), f_n = min(F, f_lo + A.R_1) - f_lo;          // rows of W2^T
-    const int rb = wg >> 2, jb = wg & 3, RB = A.R_2;                                  // W1^T: row block x contraction block
-    {   // the five slices are contiguous in LDS: one run of requests (a launch covers only 32 positions, so its start-up counts)
-        constexpr int PERW = 32 * KSD;   // 16-byte pieces of a d-long row
-        constexpr int WROWS = 3 * RO + R1 + 4 * KSD, NBW = (WROWS * PERW + kPThreads - 1) / kPThreads;
-        const int n1 = A.R_o, n2 = 2 * A.R_o, n3 = 3 * A.R_o, n4 = n3 + A.R_1, n5 = n4 + A.R_2;
-        uint4 wreg[NBW];
-        rows_issue<NBW, PERW>(wreg, n5, [&](int r) -> const bf16_t * {
-            if (r < n1) return r < o_n ? A.WkvT + (size_t)(o_lo + r) * 2 * d : nullptr;
-            if (r < n2) return r - n1 < o_n ? A.WkvT + (size_t)(o_lo + r - n1) * 2 * d + d : nullptr;
-            if (r < n3) return r - n2 < o_n ? A.WoT + (size_t)(o_lo + r - n2) * d : nullptr;
-            if (r < n4) return r - n3 < f_n ? A.W2T + (size_t)(f_lo + r - n3) * d : nullptr;
-            return A.W1T + (size_t)(rb * RB + r - n4) * F + (size_t)jb * d;
-        });
-        rows_commit<NBW, PERW>(wreg, wk_s, A.ldw, n5, [](int) -> const bf16_t * { return nullptr; });
+    GroupWait G;
+    G.spin_limit = A.spin_limit;
+    G.bar = A.bar;
+    unsigned long long *words = A.words + grp * A.group_stride;
+    const BwpWords X = bwp_words(d);
+
+    const uint4 *packed = A.packed + (size_t)rank * bwp_frags_all(KSD) * 64;
+    WFrag w2t[KSD][CD][2], w1t[CF][2];   // W2^T, W1^T: this wavefront's eighth of the contraction
+    {
+        uint4 *dst = reinterpret_cast<uint4 *>(smem + L.wo);
+        constexpr int n = (bwp_frags_o(KSD) + bwp_frags_kv(KSD)) * 64 / kPThreads;   // both slices: one run
+        uint4 t[n];
+#pragma unroll
+        for (int i = 0; i < n; ++i) t[i] = packed[i * kPThreads + threadIdx.x];
+        const uint4 *p2 = packed + (size_t)(bwp_frags_o(KSD) + bwp_frags_kv(KSD)) * 64, *p1 = p2 + (size_t)bwp_frags_2(KSD) * 64;
+#pragma unroll
+        for (int i = 0; i < KSD; ++i)
+#pragma unroll
+            for (int m = 0; m < CD; ++m)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) w2t[i][m][j].u = p2[(((i * kPW + wave) * CD + m) * 2 + j) * 64 + lane];
+#pragma unroll
+        for (int m = 0; m < CF; ++m)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) w1t[m][j].u = p1[((wave * CF + m) * 2 + j) * 64 + lane];
+#pragma unroll
+        for (int i = 0; i < n; ++i) dst[i * kPThreads + threadIdx.x] = t[i];
     }
+    if (threadIdx.x == 0) flag_s[1] = 0;
 
-    const size_t rs = (size_t)BH * kHeadDim;   // = B d: one position of a position-first tensor
-    const int blk_lo = A.i_lo;                 // first position of the block
-    const int my_u = wg;                       // the (b, h) of wavefront 0 of workgroups 0 .. BH - 1
-    const bool has_u = wave == 0 && my_u < BH;
-    if (my_u < BH) {   // the block's keys, values and gradient accumulators of this (b, h): every wavefront four rows, all
-                       // sixteen loads of a wavefront in flight at once
+    const size_t rs = (size_t)A.BH * kHeadDim;   // = B d: one position of a position-first tensor
+    const int blk_lo = A.i_lo;                   // first position of the block
+    const bool has_u = rank < B * A.H;           // this workgroup's (b, h), wavefront 4 does its softmax backward
+    const int ub = rank / A.H, uh = rank - ub * A.H, bg = grp + kBwpGroups * ub;
+    const int ug = bg * A.H + uh;
+    const bool is_owner = has_u && wave == 4;
+    if (has_u) {   // the block's keys, values and gradient accumulators, every wavefront four rows
         float kv4[kBwpBlock / kPW][4];
 #pragma unroll
         for (int jj = 0; jj < kBwpBlock / kPW; ++jj) {
             const int pos = min(blk_lo + wave + kPW * jj, A.N - 1);
-            const size_t o = (size_t)pos * rs + (size_t)my_u * kHeadDim + lane;
+            const size_t o = (size_t)pos * rs + (unsigned)(ug * kHeadDim + lane);
             kv4[jj][0] = A.Kp[o]; kv4[jj][1] = A.Vp[o]; kv4[jj][2] = A.dK[o]; kv4[jj][3] = A.dV[o];
         }
 #pragma unroll
@@ -175,233 +196,252 @@ __global__ __launch_bounds__(kPThreads) void bwp_kernel(BwpArgs A)
             accV[j * kHeadDim + lane] = kv4[jj][3];
         }
     }
-    __syncthreads();
 
-    const int erow = tid >> 4, eb = tid & 15;   // epilogue thread -> (row, batch row) for tid < 256
-    const size_t half_d = (size_t)kBMax * (d / 2), half_F = (size_t)kBMax * (F / 2), sz_d = (size_t)kBMax * d;
     const float inv_d = 1.f / (float)d;
-    const bool ep = tid < kRMax * kBMax && eb < B;
-    const bool ep_o = ep && erow < o_n, ep_f = ep && erow < f_n;
-    const float gkv_o = (ep_o && A.g_kv && !A.norm_free) ? bf16_to_f32(A.g_kv[o_lo + erow]) : 1.f;
-    const float gmlp_o = (ep_o && A.g_mlp && !A.norm_free) ? bf16_to_f32(A.g_mlp[o_lo + erow]) : 1.f;
-
-    // phase U opens every position: what it needs from memory is requested one position ahead (the gain once)
-    const float gk_u = (has_u && A.g_k) ? bf16_to_f32(A.g_k[(my_u % H) * kHeadDim + lane]) : 1.f;
-    float un_nx = 0.f, rk_nx = 1.f;
-    if (has_u && !A.norm_free) {
-        const size_t rb0 = (size_t)A.i_hi * B + my_u / H;
-        un_nx = A.unit_k[rb0 * 2 * d + (my_u % H) * kHeadDim + lane];
-        rk_nx = A.rk[rb0 * H + my_u % H];
+    float gkv_o = 1.f, gmlp_o = 1.f;             // gains of wavefront 0's epilogue rows
+    if (wave == 0 && (lane >> 2) < RO && !A.norm_free) {
+        if (A.g_kv) gkv_o = bf16_to_f32(A.g_kv[rank * RO + (lane >> 2)]);
+        if (A.g_mlp) gmlp_o = bf16_to_f32(A.g_mlp[rank * RO + (lane >> 2)]);
     }
+    const float gk_u = (is_owner && A.g_k) ? bf16_to_f32(A.g_k[uh * kHeadDim + lane]) : 1.f;
+    const float slope = alibi_slope(A.alibi, uh, A.H);
 
-    // Phase U: the complete pair gradient (dk_, dv_) of position ipos_ goes out as the vectors of step tag_ / parity par_.  It runs
-    // at the end of the previous position's phase A, as soon as that query's contribution to this one slot is in (the other slots
-    // are updated afterwards, while the vectors cross the chip); for the block's last position it runs before the loop.
-#define RT_BWP_PHASE_U(ipos_, par_, tag_, dk_, dv_)                                                                        \
-    {                                                                                                                      \
-        const int ub_ = my_u / H, uh_ = my_u - ub_ * H;                                                                    \
-        const size_t off_ = (size_t)(ipos_) * rs + (size_t)my_u * kHeadDim + lane;                                         \
-        float du_ = (dk_);                                                                                                 \
-        if (!A.norm_free) {                                                                                                \
-            const float wv_ = (dk_) * gk_u;                                                                                \
-            const float un_ = un_nx, rk_ = rk_nx;                                                                          \
-            du_ = rk_ * (wv_ - un_ * (fast_sum(un_ * wv_) * (1.f / (float)kHeadDim)));                                     \
-            if ((ipos_) > A.i_lo) {                                                                                        \
-                const size_t rbn_ = (size_t)((ipos_) - 1) * B + ub_;                                                       \
-                un_nx = A.unit_k[rbn_ * 2 * d + uh_ * kHeadDim + lane];                                                    \
-                rk_nx = A.rk[rbn_ * H + uh_];                                                                              \
-            }                                                                                                              \
-        }                                                                                                                  \
-        const float dun_ = dpp_odd_neighbour(du_), dvn_ = dpp_odd_neighbour((dv_));                                        \
-        if (!(lane & 1)) {                                                                                                 \
-            ll_store(A.e1k + (par_) * half_d + pair_word<32>(uh_ * kHeadDim + lane, ub_), (tag_),                          \
-                     (unsigned)f32_to_bf16(du_) | ((unsigned)f32_to_bf16(dun_) << 16));                                    \
-            ll_store(A.e1v + (par_) * half_d + pair_word<32>(uh_ * kHeadDim + lane, ub_), (tag_),                          \
-                     (unsigned)f32_to_bf16((dv_)) | ((unsigned)f32_to_bf16(dvn_) << 16));                                  \
-        }                                                                                                                  \
-        A.dK[off_] = (dk_);                                                                                                \
-        A.dV[off_] = (dv_);                                                                                                \
-        A.dkraw[off_] = du_;                                                                                               \
-    }
-    if (has_u && A.i_hi >= A.i_lo) {
-        const int slot = A.i_hi - blk_lo;
-        const float dk0 = accK[slot * kHeadDim + lane], dv0 = accV[slot * kHeadDim + lane];
-        RT_BWP_PHASE_U(A.i_hi, 0, A.tag_base | 1u, dk0, dv0)
-    }
-
-    for (int i = A.i_hi; i >= A.i_lo; --i) {
-        const int step = A.i_hi - i, par = step & 1;
-        const unsigned tag = A.tag_base | (unsigned)(step + 1);
-        const size_t r0 = (size_t)i * B;
-        int fail = 0;
-        // ---- what the epilogues of this position need from the recompute (issued now, used phases later)
-        float e_gy = 0.f, e_uz = 0.f, e_uh = 0.f, e_cgy = 0.f, e_cuz = 0.f, e_cuh = 0.f, e_rz = 1.f, e_rh = 1.f;
-        float e_gp = 0.f, e_agy = 0.f, e_auz = 0.f;
-        if (ep) {
-            const size_t r = r0 + eb;
+    // What a position needs from the recompute is requested at the end of the position after it: behind the polls of that
+    // position, and early enough not to hold up its own.
+    float e_gy = 0.f, e_uz = 0.f, e_uh = 0.f, e_cgy = 0.f, e_cuz = 0.f, e_cuh = 0.f, e_rz = 1.f, e_rh = 1.f;   // wavefront 0: rows of the d-long products
+    float e_gp = 0.f, e_agy = 0.f, e_auz = 0.f;                                                               // wavefronts 0 .. KSD - 1: rows of W2^T
+    float4 uz[CD], un_h[CD];                                                                                  // unit rows, the wavefront's share
+    float a_q = 0.f, a_kt = 0.f, a_vt = 0.f, a_c = 0.f, a_L = 0.f, a_un = 0.f, a_rk = 1.f;                    // owner
+    auto request = [&](int i, int ln) {
+        const size_t r0 = (size_t)i * A.B;
+        const int b = ln & 3, bb = grp + kBwpGroups * b;
+        const bool live = b < B;
+        if (wave < KSD && live) {   // 64 rows of W2^T and 16 of the others per wavefront
+            const size_t r = r0 + bb;
             e_rz = A.rinv_z[r];
-            e_rh = A.rinv_h[r];
-            if (ep_o) {
-                const size_t o = r * d + o_lo + erow;
-                e_gy = bf16_to_f32(A.gy[((size_t)eb * A.N + i) * d + o_lo + erow]);
+            const size_t f = r * F + (unsigned)(rank * R1 + wave * 16 + (ln >> 2));
+            e_gp = A.gp[f]; e_agy = A.A_gy[f]; e_auz = A.A_uz[f];
+            if (wave == 0 && (ln >> 2) < RO) {
+                e_rh = A.rinv_h[r];
+                const unsigned col = rank * RO + (ln >> 2);
+                const size_t o = r * d + col;
+                e_gy = bf16_to_f32(A.gy[((size_t)bb * A.N + i) * d + col]);
                 e_uz = A.unit_z[o]; e_uh = A.unit_h[o];
                 e_cgy = A.C_gy[o]; e_cuz = A.C_uz[o]; e_cuh = A.C_uh[o];
             }
-            if (ep_f) {
-                const size_t f = r * F + f_lo + erow;
-                e_gp = A.gp[f]; e_agy = A.A_gy[f]; e_auz = A.A_uz[f];
+        }
+#pragma unroll
+        for (int m = 0; m < CD; ++m) {
+            uz[m] = un_h[m] = make_float4(0.f, 0.f, 0.f, 0.f);
+            const int k = 64 * m + 4 * (ln >> 2);
+            if (live && k < LD) {
+                const size_t o = (r0 + bb) * d + (unsigned)(wave * LD + k);
+                uz[m] = *reinterpret_cast<const float4 *>(A.unit_z + o);
+                un_h[m] = *reinterpret_cast<const float4 *>(A.unit_h + o);
             }
         }
-        // this wavefront's slice of the normalised rows of every batch row, for its parts of the two row-wide sums (B <= 8)
-        float uz[PER], uh[PER];
-        const int db = lane >> 3, dcol = wave * (KSD * 32) + (lane & 7) * PER;
-        if (db < B) {
-            const float *pz = A.unit_z + (r0 + db) * d + dcol, *ph = A.unit_h + (r0 + db) * d + dcol;
-#pragma unroll
-            for (int e = 0; e < PER; e += 4) {
-                const float4 a = *reinterpret_cast<const float4 *>(pz + e), b4 = *reinterpret_cast<const float4 *>(ph + e);
-                uz[e] = a.x; uz[e + 1] = a.y; uz[e + 2] = a.z; uz[e + 3] = a.w;
-                uh[e] = b4.x; uh[e + 1] = b4.y; uh[e + 2] = b4.z; uh[e + 3] = b4.w;
-            }
-        } else {
-#pragma unroll
-            for (int e = 0; e < PER; ++e) uz[e] = uh[e] = 0.f;
+        if (is_owner) {
+            const size_t off = (size_t)i * rs + (unsigned)(ug * kHeadDim + ln);
+            a_q = A.Qn[off]; a_kt = A.Ktn[off]; a_vt = A.Vt[off]; a_c = A.c[off];
+            a_L = A.lse[(size_t)i * A.BH + ug];
         }
+    };
+    auto request_pair = [&](int i, int ln) {   // what phase U of position i needs
+        if (is_owner && !A.norm_free && i >= A.i_lo) {
+            const size_t r = (size_t)i * A.B + bg;
+            a_un = A.unit_k[r * 2 * d + (unsigned)(uh * kHeadDim + ln)];
+            a_rk = A.rk[r * A.H + uh];
+        }
+    };
+    // Phase U: the complete pair gradient (dk, dv) of position i goes out as the vectors of the step with that tag and parity.
+    auto phase_u = [&](int i, int par, unsigned tag, float dk, float dv, int ln) {
+        const size_t off = (size_t)i * rs + (unsigned)(ug * kHeadDim + ln);
+        float du = dk;
+        if (!A.norm_free) {
+            const float wv = dk * gk_u;
+            du = a_rk * (wv - a_un * (fast_sum(a_un * wv) * (1.f / (float)kHeadDim)));
+        }
+        const float dun = dpp_odd_neighbour(du), dvn = dpp_odd_neighbour(dv);
+        if (!(ln & 1)) {
+            // a wavefront's share of [dkraw | dV]: its share of both
+            const unsigned k = uh * kHeadDim + ln, kk = k / LD * (2 * LD) + k % LD;
+            word_store(words + par * X.all + X.e1, piece_word<8, BM>(kk, ub), tag, (unsigned)f32_to_bf16(du) | ((unsigned)f32_to_bf16(dun) << 16));
+            word_store(words + par * X.all + X.e1, piece_word<8, BM>(kk + LD, ub), tag, (unsigned)f32_to_bf16(dv) | ((unsigned)f32_to_bf16(dvn) << 16));
+        }
+        A.dK[off] = dk;
+        A.dV[off] = dv;
+        A.dkraw[off] = du;
+        request_pair(i - 1, ln);
+    };
+
+    request(A.i_hi, lane);
+    request_pair(A.i_hi, lane);
+    __syncthreads();
+    if (is_owner) {
+        const int slot = A.i_hi - blk_lo;
+        phase_u(A.i_hi, 0, A.tag_base | 1u, accK[slot * kHeadDim + lane], accV[slot * kHeadDim + lane], lane);
+    }
+
+    int fail = 0;
+    for (int i = A.i_hi; i >= A.i_lo; --i) {
+        const int step = A.i_hi - i, par = step & 1;
+        const unsigned tag = A.tag_base | (unsigned)(step + 1);
+        const size_t r0 = (size_t)i * A.B;
+        unsigned long long *wp = words + par * X.all;
+        int ln = lane;
+        asm volatile("" : "+v"(ln));   // opaque: what depends on the lane is formed in every position, registers are for the weights
+        const int erow = ln >> 2, eb = ln & 3;
+        const bool e_own = wave == 0 && erow < RO && eb < B;
+        const size_t e_r = r0 + grp + kBwpGroups * eb;
+        const unsigned e_col = rank * RO + erow;
 
         // ================================================================ G1: d_rz = Wk^T dkraw + Wv^T dV_i
-        wg_gemv_ll_pair<KSD, 32>(wk_s, wv_s, A.ldw, o_n, A.e1k + par * half_d, A.e1v + par * half_d, B, tag, A, red, act_s, A.ldw,
-                                 fail, A.ps_g1);
-        RT_BWP_ABORT_IF(fail);
-        if (tid < kRMax * kBMax) {
-            float wv = 0.f;
-            if (ep_o) {
-                const float drz = red_sum(red, erow, eb);
-                A.d_rz[(r0 + eb) * d + o_lo + erow] = drz;
-                wv = drz * gkv_o;
+        {
+            Piece act[KSD];
+            slice_pull<KSD, 2 * LD, 8, BM>(wp + X.e1, wave, ln, B, tag, G, act, fail, A.sl_1);
+            f32x4_t acc[4] = {};
+#pragma unroll
+            for (int m = 0; m < KSD; ++m) {
+                WFrag w0, w1;
+                w0.u = lds_load16(wkv_s + (m * 2) * 64 + ln);
+                w1.u = lds_load16(wkv_s + (m * 2 + 1) * 64 + ln);
+                chunk_product4(act[m], w0, w1, acc);
             }
-            const float wn = next_row(wv);
-            if (!(erow & 1) && ep_o)
-                ll_store(A.e2 + par * half_d + pair_word<RO / 2>(o_lo + erow, eb), tag,
-                         (unsigned)f32_to_bf16(wv) | ((unsigned)f32_to_bf16(wn) << 16));
-            w_loc[erow * kBMax + eb] = wv;
+            const f32x4_t s[1] = {(acc[0] + acc[1]) + (acc[2] + acc[3])};
+            tiles_store<1>(red0, wave, ln, s);
+        }
+        RT_GROUP_SYNC(fail);
+        float wv = 0.f;
+        if (wave == 0) {
+            const float drz = tile_sum(red0, ln);
+            wv = drz * gkv_o;
+            const float wn = row_partner(wv);
+            if (e_own && !(erow & 1))
+                word_store(wp + X.e2, piece_word<1, BM>(e_col, eb), tag, (unsigned)f32_to_bf16(wv) | ((unsigned)f32_to_bf16(wn) << 16));
+            if (e_own) A.d_rz[e_r * d + e_col] = drz;
         }
         __syncthreads();
 
         // ================================================================ G2: dot, W2^T w, Wo^T w; dpre rows, Gz rows
-        wg_gemv_ll<KSD, RO / 2>(w2_s, A.ldw, f_n, A.e2 + par * half_d, B, tag, A, red, act_s, A.ldw, fail, nullptr, A.ps_g2);
-        // the second product and this wavefront's part of the row-wide sum read only what the wavefront staged itself: both
-        // run before the barrier
-        wg_product_staged<KSD>(wo_s, A.ldw, o_n, B, red2, act_s, A.ldw);
         {
-            const float dt = (A.norm_free || db >= B) ? 0.f : row_dot_part<PER>(uz, act_s + (size_t)min(db, B - 1) * A.ldw + dcol, lane);
-            if ((lane & 7) == 0) dot_s[wave * kBMax + db] = dt;
-        }
-        RT_BWP_ABORT_IF(fail);
-        if (tid < kRMax * kBMax) {
-            float dp = 0.f, dot = 0.f;
-            if (ep) {
+            Piece act[CD];
+            slice_pull<CD, LD, 1, BM>(wp + X.e2, wave, ln, B, tag, G, act, fail, A.sl_2);
+            f32x4_t acc[KSD] = {};
 #pragma unroll
-                for (int w = 0; w < kPW; ++w) dot += dot_s[w * kBMax + eb];
+            for (int m = 0; m < CD; ++m)
+#pragma unroll
+                for (int t = 0; t < KSD; ++t) acc[t] = chunk_product(act[m], w2t[t][m][0], w2t[t][m][1], acc[t]);
+            tiles_store<KSD>(red1, wave, ln, acc);
+            f32x4_t ao[4] = {};
+#pragma unroll
+            for (int m = 0; m < CD; ++m) {
+                WFrag w0, w1;
+                w0.u = lds_load16(wo_s + (m * 2) * 64 + ln);
+                w1.u = lds_load16(wo_s + (m * 2 + 1) * 64 + ln);
+                chunk_product4(act[m], w0, w1, ao);
             }
-            if (ep_f) {
-                const float v = red_sum(red, erow, eb);
-                const float lin = A.norm_free ? e_agy + v : e_agy + e_rz * (v - dot * inv_d * e_auz);
-                dp = e_gp * A.alpha * lin;
-            }
-            const float dn = next_row(dp);
-            if (!(erow & 1) && ep_f)
-                ll_store(A.e3 + par * half_F + pair_word<R1 / 2>(f_lo + erow, eb), tag,
-                         (unsigned)f32_to_bf16(dp) | ((unsigned)f32_to_bf16(dn) << 16));
-            if (ep_f) A.dpre[(r0 + eb) * F + f_lo + erow] = dp;
-            if (ep_o) {
-                const float wv = w_loc[erow * kBMax + eb];
-                const float gz = A.norm_free ? e_gy + wv : e_gy + e_rz * (wv - e_uz * dot * inv_d);
-                A.Gz[(r0 + eb) * d + o_lo + erow] = gz;
-                gz_loc[erow * kBMax + eb] = gz;
-                cw_loc[erow * kBMax + eb] = red_sum(red2, erow, eb);
+            const f32x4_t s[1] = {(ao[0] + ao[1]) + (ao[2] + ao[3])};
+            tiles_store<1>(red0, wave, ln, s);
+            const float dt = share_dot<CD>(uz, act);
+            if (ln < 4) dot_s[wave * 4 + ln] = dt;
+        }
+        RT_GROUP_SYNC(fail);
+        float gz = 0.f, cw = 0.f, k1 = 0.f;
+        if (wave < KSD) {
+            float dot = 0.f;
+#pragma unroll
+            for (int w = 0; w < kPW; ++w) dot += dot_s[w * 4 + eb];
+            k1 = A.norm_free ? 0.f : dot * inv_d;
+            const int tn = wave * 64 + ln;
+            const float v = tile_sum(red1, tn);
+            const float lin = A.norm_free ? e_agy + v : e_agy + e_rz * (v - k1 * e_auz);
+            const float dp = e_gp * A.alpha * lin;
+            const float dn = row_partner(dp);
+            const unsigned row = rank * R1 + wave * 16 + erow;
+            if (!(erow & 1) && eb < B)
+                word_store(wp + X.e3, piece_word<1, BM>(row, eb), tag, (unsigned)f32_to_bf16(dp) | ((unsigned)f32_to_bf16(dn) << 16));
+            if (eb < B) A.dpre[e_r * F + row] = dp;
+            if (wave == 0) {
+                gz = A.norm_free ? e_gy + wv : e_gy + e_rz * (wv - e_uz * k1);
+                cw = tile_sum(red0, ln);
+                if (e_own) A.Gz[e_r * d + e_col] = gz;
             }
         }
         __syncthreads();
 
-        // ================================================================ G3a: partial W1^T dpre over contraction block jb
-        wg_gemv_ll<KSD, R1 / 2>(w1_s, A.ldw, RB, A.e3 + par * half_F + (size_t)jb * (kBMax * (d / 2)), B, tag, A, red, act_s, A.ldw,
-                                fail, nullptr, A.ps_g3);
-        RT_BWP_ABORT_IF(fail);
-        if (tid < kRMax * kBMax && erow < RB && eb < B)
-            ll_store(A.e4 + ((size_t)(par * 4 + jb) * kBMax + eb) * d + rb * RB + erow, tag, __float_as_uint(red_sum(red, erow, eb)));
-        __syncthreads();
-
-        // ================================================================ G3b: t1 rows, w2 = t1 g_mlp
-        if (tid < kRMax * kBMax) {
-            const int o = o_lo + erow;
-            const ll_t *pp[4];
-            bool act[4];
-            ll_t w4[4];
+        // ================================================================ G3: t1 rows = W1^T dpre, w2 = t1 g_mlp
+        {
+            Piece act[CF];
+            slice_pull<CF, LF, 1, BM>(wp + X.e3, wave, ln, B, tag, G, act, fail, A.sl_3);
+            f32x4_t acc[4] = {};
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                act[j] = ep_o;
-                pp[j] = A.e4 + ((size_t)(par * 4 + j) * kBMax + (ep_o ? eb : 0)) * d + (ep_o ? o : 0);
-            }
-            ll_wait_n<4>(pp, act, tag, A, w4, fail);
-            float w2v = 0.f;
-            if (ep_o) {
-                const float t1v = (__uint_as_float((unsigned)w4[0]) + __uint_as_float((unsigned)w4[1])) +
-                                  (__uint_as_float((unsigned)w4[2]) + __uint_as_float((unsigned)w4[3]));
-                A.t1[(r0 + eb) * d + o] = t1v;
-                w2v = t1v * gmlp_o;
-            }
-            const float wn = next_row(w2v);
-            if (!(erow & 1) && ep_o)
-                ll_store(A.e5 + par * half_d + pair_word<RO / 2>(o, eb), tag,
-                         (unsigned)f32_to_bf16(w2v) | ((unsigned)f32_to_bf16(wn) << 16));
-            w2_loc[erow * kBMax + eb] = w2v;
+            for (int m = 0; m < CF; ++m) chunk_product4(act[m], w1t[m][0], w1t[m][1], acc);
+            const f32x4_t s[1] = {(acc[0] + acc[1]) + (acc[2] + acc[3])};
+            tiles_store<1>(red1, wave, ln, s);
         }
-        RT_BWP_ABORT_IF(fail);
+        RT_GROUP_SYNC(fail);
+        float w2v = 0.f;
+        if (wave == 0) {
+            const float t1v = tile_sum(red1, ln);
+            w2v = t1v * gmlp_o;
+            const float wn = row_partner(w2v);
+            if (e_own && !(erow & 1))
+                word_store(wp + X.e5, piece_word<1, BM>(e_col, eb), tag, (unsigned)f32_to_bf16(w2v) | ((unsigned)f32_to_bf16(wn) << 16));
+            if (e_own) A.t1[e_r * d + e_col] = t1v;
+        }
+        __syncthreads();
 
         // ================================================================ G4: dot2, Wo^T w2; dc rows, dh rows
-        wg_gemv_ll<KSD, RO / 2>(wo_s, A.ldw, o_n, A.e5 + par * half_d, B, tag, A, red, act_s, A.ldw, fail, nullptr, A.ps_g4);
-        {   // this wavefront's part of the second row-wide sum, before the barrier (see G2)
-            const float dt = (A.norm_free || db >= B) ? 0.f : row_dot_part<PER>(uh, act_s + (size_t)min(db, B - 1) * A.ldw + dcol, lane);
-            if ((lane & 7) == 0) dot2_s[wave * kBMax + db] = dt;
+        {
+            Piece act[CD];
+            slice_pull<CD, LD, 1, BM>(wp + X.e5, wave, ln, B, tag, G, act, fail, A.sl_4);
+            f32x4_t ao[4] = {};
+#pragma unroll
+            for (int m = 0; m < CD; ++m) {
+                WFrag w0, w1;
+                w0.u = lds_load16(wo_s + (m * 2) * 64 + ln);
+                w1.u = lds_load16(wo_s + (m * 2 + 1) * 64 + ln);
+                chunk_product4(act[m], w0, w1, ao);
+            }
+            const f32x4_t s[1] = {(ao[0] + ao[1]) + (ao[2] + ao[3])};
+            tiles_store<1>(red0, wave, ln, s);
+            const float dt = share_dot<CD>(un_h, act);
+            if (ln < 4) dot2_s[wave * 4 + ln] = dt;
         }
-        RT_BWP_ABORT_IF(fail);
-        if (tid < kRMax * kBMax && ep_o) {
-            const int o = o_lo + erow;
-            const float v = red_sum(red, erow, eb), cw = cw_loc[erow * kBMax + eb];
-            const float w2v = w2_loc[erow * kBMax + eb], gz = gz_loc[erow * kBMax + eb];
+        RT_GROUP_SYNC(fail);
+        if (wave == 0) {
+            const float v = tile_sum(red0, ln);
             float dcv, dh;
             if (A.norm_free) {
                 dcv = A.alpha * (e_cgy + cw + v);
                 dh = gz + w2v;
             } else {
-                float k1 = 0.f, k2 = 0.f;
+                float k2 = 0.f;
 #pragma unroll
-                for (int w = 0; w < kPW; ++w) { k1 += dot_s[w * kBMax + eb]; k2 += dot2_s[w * kBMax + eb]; }
-                k1 *= inv_d; k2 *= inv_d;
+                for (int w = 0; w < kPW; ++w) k2 += dot2_s[w * 4 + eb];
+                k2 *= inv_d;
                 dcv = A.alpha * (e_cgy + e_rz * (cw - k1 * e_cuz) + e_rh * (v - k2 * e_cuh));
                 dh = gz + e_rh * (w2v - e_uh * k2);
             }
-            ll_store(A.e6 + par * sz_d + single_word<RO>(o, eb), tag, __float_as_uint(dcv));
-            A.dc[(r0 + eb) * d + o] = dcv;
-            A.d_h[(r0 + eb) * d + o] = dh;
+            if (e_own) {
+                word_store(wp + X.e6, (rank * BM + eb) * RO + erow, tag, __float_as_uint(dcv));
+                A.dc[e_r * d + e_col] = dcv;
+                A.d_h[e_r * d + e_col] = dh;
+            }
         }
-        __syncthreads();
 
         // ================================================================ A: softmax backward of query i
-        float t_p = 0.f, t_ds = 0.f, t_g = 0.f, t_q = 0.f;   // for the older slots, updated behind the barrier below
-        int t_w = 0;
-        if (has_u) {
-            const int u = my_u, b = u / H, h = u - b * H;
-            const size_t off = (size_t)i * rs + (size_t)u * kHeadDim + lane;
-            const float q = A.Qn[off], kt = A.Ktn[off], vt = A.Vt[off], cv = A.c[off];
-            const float L = A.lse[(size_t)i * BH + u];
-            const int w = i - blk_lo;   // keys of the block before the query: slots 0 .. w - 1
+        const int w = i - blk_lo;   // keys of the block before the query: slots 0 .. w - 1
+        if (is_owner) {
+            const size_t off = (size_t)i * rs + (unsigned)(ug * kHeadDim + ln);
+            const float q = a_q, kt = a_kt;
             // what does not need the gradient of the attention output is formed before the wait for it: the query's own
-            // weight and the logits of the window
-            const float p_own = __expf(A.scale * fast_sum(q * kt) - L);
-            const float *krow = winK + (size_t)min(lane, max(w - 1, 0)) * kWinLd, *vrow = winV + (size_t)min(lane, max(w - 1, 0)) * kWinLd;
-            float s = 0.f;
+            // weight and the weights of the window
+            const float p_own = __expf(A.scale * fast_sum(q * kt) - a_L);
+            const float *krow = winK + (size_t)min(ln, max(w - 1, 0)) * kWinLd, *vrow = winV + (size_t)min(ln, max(w - 1, 0)) * kWinLd;
+            float p = 0.f;
             if (w > 0) {
+                float s = 0.f;
 #pragma unroll
                 for (int c8 = 0; c8 < 8; ++c8) {
                     float kk[8];
@@ -409,11 +449,13 @@ __global__ __launch_bounds__(kPThreads) void bwp_kernel(BwpArgs A)
 #pragma unroll
                     for (int e = 0; e < 8; ++e) s = fmaf(lane_bcast(q, c8 * 8 + e), kk[e], s);
                 }
+                p = ln < w ? __expf(fmaf(-slope, (float)(w - ln), s * A.scale) - a_L) : 0.f;
             }
-            const ll_t wd = ll_wait(A.e6 + par * sz_d + single_word<RO>(h * kHeadDim + lane, b), true, tag, A, fail);
+            const unsigned o6 = uh * kHeadDim + ln;
+            const ll_t wd = ll_wait(wp + X.e6 + (size_t)((o6 / RO * BM + ub) * RO + o6 % RO), true, tag, G, fail);
             const float g = __uint_as_float((unsigned)wd);
-            const float Dsum = fast_sum(g * cv);
-            const float ds_own = p_own * (fast_sum(g * vt) - Dsum);
+            const float Dsum = fast_sum(g * a_c);
+            const float ds_own = p_own * (fast_sum(g * a_vt) - Dsum);
             if (w > 0) {
                 float dp = 0.f;
 #pragma unroll
@@ -423,48 +465,61 @@ __global__ __launch_bounds__(kPThreads) void bwp_kernel(BwpArgs A)
 #pragma unroll
                     for (int e = 0; e < 8; ++e) dp = fmaf(lane_bcast(g, c8 * 8 + e), vv[e], dp);
                 }
-                const float slope = alibi_slope(A.alibi, h, H);
-                const float p = lane < w ? __expf(fmaf(-slope, (float)(w - lane), s * A.scale) - L) : 0.f;
                 const float ds = p * (dp - Dsum);
                 // the newest slot first: with it the pair gradient of position i - 1 is complete and goes out at once
-                {
-                    const int j = w - 1;
-                    const float dvn = fmaf(lane_bcast(p, j), g, accV[j * kHeadDim + lane]);
-                    const float dkn = fmaf(A.scale * lane_bcast(ds, j), q, accK[j * kHeadDim + lane]);
-                    RT_BWP_PHASE_U(i - 1, par ^ 1, tag + 1u, dkn, dvn)
-                }
-                t_p = p; t_ds = ds; t_g = g; t_q = q; t_w = w;
+                const int j = w - 1;
+                const float dvn = fmaf(lane_bcast(p, j), g, accV[j * kHeadDim + ln]);
+                const float dkn = fmaf(A.scale * lane_bcast(ds, j), q, accK[j * kHeadDim + ln]);
+                phase_u(i - 1, par ^ 1, tag + 1u, dkn, dvn, ln);
+                sh[ln] = p; sh[64 + ln] = ds; sh[128 + ln] = g; sh[192 + ln] = q;   // for the older slots, below
             }
             // the query's own gradients follow the pair gradient of the next position: only that one is waited for
             A.dvt[off] = p_own * g;
             A.dkt[off] = A.scale * ds_own * q;
             A.dq[off] = A.scale * ds_own * kt;
-            if (lane == 0) A.Ds[(size_t)i * BH + u] = Dsum;
+            if (ln == 0) A.Ds[(size_t)i * A.BH + ug] = Dsum;
         }
-        // every other wavefront goes on as soon as the pair gradient has left; the owner follows after the older slots
-        RT_BWP_ABORT_IF(fail);
-        if (has_u && t_w > 1) {
-            // the older slots eight keys at a time: all reads of a group before its writes (one key per trip is a chain of
-            // dependent LDS round trips)
-            for (int j0 = 0; j0 < t_w - 1; j0 += 8) {
-                float av[8], ak[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int j = min(j0 + e, t_w - 2);
-                    av[e] = accV[j * kHeadDim + lane];
-                    ak[e] = accK[j * kHeadDim + lane];
-                }
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    const int j = j0 + e;
-                    if (j < t_w - 1) {   // wavefront-uniform
-                        accV[j * kHeadDim + lane] = fmaf(lane_bcast(t_p, j), t_g, av[e]);
-                        accK[j * kHeadDim + lane] = fmaf(A.scale * lane_bcast(t_ds, j), t_q, ak[e]);
-                    }
-                }
+        if (i > A.i_lo) request(i - 1, ln);
+        RT_GROUP_SYNC(fail);
+        if (has_u) {   // the older slots, four at most per wavefront, while the pair gradient crosses the chip
+            const float g = sh[128 + ln], q = sh[192 + ln];
+            for (int j = wave; j < w - 1; j += kPW) {
+                accV[j * kHeadDim + ln] = fmaf(sh[j], g, accV[j * kHeadDim + ln]);
+                accK[j * kHeadDim + ln] = fmaf(A.scale * sh[64 + j], q, accK[j * kHeadDim + ln]);
             }
         }
     }
+}
+
+// The transposed matrices in the fragment order above.  Lane l of fragment (tile, wavefront, chunk m, j) holds W[row0 + 16 tile + l%16][k .. k + 7],
+// k the wavefront's share's element 64 m + 16 (l/16) + 8 j; a share of [Wk^T | Wv^T] is the share of both.
+__global__ __launch_bounds__(256) void bwp_pack_kernel(const bf16_t *WkvT, const bf16_t *W2T, const bf16_t *W1T, const bf16_t *WoT, int KSD, uint4 *dst)
+{
+    const int per = bwp_frags_all(KSD), d = 256 * KSD, LD = d / kPW;
+    const int f_all = (int)((blockIdx.x * 256 + threadIdx.x) >> 6), lane = threadIdx.x & 63;
+    if (f_all >= per * kBwpRanks) return;
+    const int rank = f_all / per;
+    int f = f_all - rank * per, rows = 4 * KSD, chunks = bwp_chunks_d(KSD), K = d;
+    const bf16_t *src = WoT;
+    bool pairs = false;
+    if (f < bwp_frags_o(KSD)) {
+    } else if ((f -= bwp_frags_o(KSD)) < bwp_frags_kv(KSD)) {
+        src = WkvT; chunks = KSD; K = 2 * d; pairs = true;
+    } else if ((f -= bwp_frags_kv(KSD)) < bwp_frags_2(KSD)) {
+        src = W2T; rows = 16 * KSD;
+    } else {
+        f -= bwp_frags_2(KSD);
+        src = W1T; chunks = 2 * KSD; K = 4 * d;
+    }
+    const int j = f & 1, m = (f >> 1) % chunks, w = (f >> 1) / chunks % kPW, tile = (f >> 1) / (chunks * kPW);
+    const int kk = 64 * m + 16 * (lane >> 4) + 8 * j;
+    uint4 v = make_uint4(0u, 0u, 0u, 0u);
+    if (tile * 16 + (lane & 15) < rows && kk < K / kPW) {
+        const int row = rank * rows + tile * 16 + (lane & 15);
+        const int k = pairs ? (kk < LD ? w * LD + kk : d + w * LD + kk - LD) : w * (K / kPW) + kk;
+        v = *reinterpret_cast<const uint4 *>(src + (size_t)row * K + k);
+    }
+    dst[(size_t)f_all * 64 + lane] = v;
 }
 
 // =============================================================================================
@@ -472,36 +527,20 @@ __global__ __launch_bounds__(kPThreads) void bwp_kernel(BwpArgs A)
 // =============================================================================================
 namespace {
 typedef void (*bwp_fn)(BwpArgs);
-bwp_fn pick(int d, int F)
+bwp_fn pick(int d, int BM)
 {
-    if (d % (32 * kPW) != 0 || F != 4 * d) return nullptr;
-    switch (d / (32 * kPW)) {
-    case 1: return bwp_kernel<1>;
-    case 2: return bwp_kernel<2>;
-    case 3: return bwp_kernel<3>;
-    case 4: return bwp_kernel<4>;
+    switch (d) {
+    case 256: return BM == 1 ? bwp_kernel<1, 1> : bwp_kernel<1, 2>;
+    case 512: return BM == 1 ? bwp_kernel<2, 1> : bwp_kernel<2, 2>;
+    case 768: return BM == 1 ? bwp_kernel<3, 1> : bwp_kernel<3, 2>;
+    case 1024: return BM == 1 ? bwp_kernel<4, 1> : bwp_kernel<4, 2>;
     default: return nullptr;
     }
 }
 size_t up256(size_t v) { return (v + 255) / 256 * 256; }
-void rows_per_wg(int d, int F, int G, int *R_o, int *R_1)
-{
-    *R_o = 2 * ((d + 2 * G - 1) / (2 * G));
-    *R_1 = 2 * ((F + 2 * G - 1) / (2 * G));
-}
-size_t lds_bytes(int d, int F, int G)
-{
-    int R_o, R_1;
-    rows_per_wg(d, F, G, &R_o, &R_1);
-    const size_t ldw = d + 8;
-    size_t b = ((size_t)(3 * R_o + R_1 + d / 64) * ldw) * 2;
-    b = (b + 15) / 16 * 16;
-    b += (size_t)(2 * kPW * kRMax * kBMax + 4 * kRMax * kBMax + 2 * kPW * kBMax) * 4;
-    b += (size_t)(2 * kBwpBlock * kWinLd + 2 * kBwpBlock * kHeadDim) * 4;
-    b = (b + 15) / 16 * 16;
-    b += (size_t)8 * ldw * 2;
-    return b;
-}
+bool shape_ok(int d, int F) { return d % 256 == 0 && d <= 1024 && F == 4 * d; }
+size_t group_stride(int d) { return up256(2 * bwp_words(d).all * 8) / 8; }
+size_t word_bytes(int d) { return 256 + kBwpGroups * group_stride(d) * 8; }   // counters and exchange words; the packed matrices follow
 __global__ void bwp_clear_kernel(unsigned long long *p, size_t n)
 {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0ULL;
@@ -510,37 +549,31 @@ __global__ void bwp_clear_kernel(unsigned long long *p, size_t n)
 
 size_t bwp_exchange_bytes(int d, int F)
 {
-    // bar (256) + e1k, e1v, e2, e5: 2 kBMax d/2 words; e3: 2 kBMax F/2; e4: 2 * 4 kBMax d; e6: 2 kBMax d
-    size_t words = 4 * (size_t)2 * kBMax * (d / 2) + (size_t)2 * kBMax * (F / 2) + (size_t)2 * 4 * kBMax * d + (size_t)2 * kBMax * d;
-    return 256 + up256(words * 8) + 8 * 256;
+    return shape_ok(d, F) ? word_bytes(d) + (size_t)bwp_frags_all(d / 256) * kBwpRanks * 1024 : 256;
 }
 
 bool bwp_create(BwpState &P, int device, int d, int F, int H, int max_batch, bool bf16_mfma)
 {
     P.available = false;
     if (!bf16_mfma || getenv("RT_BWD_NO_PERSISTENT")) return false;
-    bwp_fn fn = pick(d, F);
-    if (!fn || max_batch < 1) return false;
-    hipDeviceProp_t prop;
-    if (hipGetDeviceProperties(&prop, device) != hipSuccess) return false;
-    if (!prop.cooperativeLaunch || prop.multiProcessorCount != 256) return false;   // W1^T is laid out as 64 x 4 workgroups
-    const int G = 256;
-    int R_o, R_1;
-    rows_per_wg(d, F, G, &R_o, &R_1);
-    if (R_o > kRMax || R_1 > kRMax || d / 64 > kRMax) return false;
-    const size_t lds = lds_bytes(d, F, G);
-    if (lds + 16 > (size_t)160 * 1024) return false;   // 16: the statically allocated flag word
-    if (hipFuncSetAttribute((const void *)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
+    if (!shape_ok(d, F) || max_batch < 1 || kBwpRows * H > kBwpRanks) return false;
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return false;
+    if (cus != kBwpGroups * kBwpRanks) return false;
+    P.lds_bytes = (size_t)bwp_lds(d / 256).all;
+    if (P.lds_bytes > (size_t)160 * 1024) return false;
+    {   // once per device and kernel
+        static std::mutex mu;
+        static uint64_t raised[5] = {};
+        std::lock_guard<std::mutex> lock(mu);
+        const uint64_t bit = 1ULL << (device & 63);
+        for (int BM = 1; BM <= 2 && !(raised[d / 256] & bit); ++BM)
+            if (hipFuncSetAttribute((const void *)pick(d, BM), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) {
+                (void)hipGetLastError();
+                return false;
+            }
+        raised[d / 256] |= bit;
     }
-    int nb = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, fn, kPThreads, lds) != hipSuccess || nb < 1) {
-        (void)hipGetLastError();
-        return false;
-    }
-    P.grid = G;
-    P.lds_bytes = lds;
     P.H = H;
     const char *sl = getenv("RT_SPIN_LIMIT");
     P.spin_limit = sl ? atoll(sl) : (1LL << 21);
@@ -551,55 +584,56 @@ bool bwp_create(BwpState &P, int device, int d, int F, int H, int max_batch, boo
 
 bool bwp_supported(const BwpState &P, const LayerDims &D)
 {
-    return P.available && D.B <= 8 && D.B * D.H <= P.grid && D.H == P.H;
+    return P.available && D.B <= kBwpGroups * kBwpRows && D.H == P.H;
 }
 
-hipError_t bwp_clear(void *exchange, size_t bytes, hipStream_t st)
+hipError_t bwp_pack(const LayerDims &D, const BwpTensors &T, void *exchange, hipStream_t st)
 {
-    hipLaunchKernelGGL(bwp_clear_kernel, dim3(256), dim3(256), 0, st, (unsigned long long *)exchange, bytes / 8);
+    const int KSD = D.d / 256, frags = bwp_frags_all(KSD) * kBwpRanks;
+    hipLaunchKernelGGL(bwp_pack_kernel, dim3((unsigned)((frags + 3) / 4)), dim3(256), 0, st, T.WkvT, T.W2T, T.W1T, T.WoT, KSD,
+                       (uint4 *)((char *)exchange + word_bytes(D.d)));
     return hipGetLastError();
 }
 
 hipError_t bwp_run_block(BwpState &P, const LayerDims &D, const BwpTensors &T, void *exchange, int i_hi, int i_lo, hipStream_t st)
 {
     BwpArgs A;
-    A.B = D.B; A.N = D.N; A.d = D.d; A.H = D.H; A.F = D.F; A.BH = D.B * D.H; A.G = P.grid;
+    A.B = D.B; A.N = D.N; A.H = D.H; A.BH = D.B * D.H;
     A.i_hi = i_hi; A.i_lo = i_lo;
     A.alpha = D.alpha; A.scale = D.scale; A.alibi = D.alibi; A.norm_free = D.norm_free;
-    rows_per_wg(D.d, D.F, P.grid, &A.R_o, &A.R_1);
-    A.R_2 = D.d / 64; A.ldw = D.d + 8;
-    A.WkvT = T.WkvT; A.W2T = T.W2T; A.W1T = T.W1T; A.WoT = T.WoT;
     A.g_kv = T.g_kv; A.g_mlp = T.g_mlp; A.g_k = T.g_k; A.gy = T.gy;
     A.unit_k = T.unit_k; A.rk = T.rk; A.unit_z = T.unit_z; A.rinv_z = T.rinv_z; A.unit_h = T.unit_h; A.rinv_h = T.rinv_h;
     A.gp = T.gp; A.A_gy = T.A_gy; A.A_uz = T.A_uz; A.C_gy = T.C_gy; A.C_uz = T.C_uz; A.C_uh = T.C_uh;
     A.Qn = T.Qn; A.Ktn = T.Ktn; A.Vt = T.Vt; A.Kp = T.Kp; A.Vp = T.Vp; A.c = T.c; A.lse = T.lse;
     A.dK = T.dK; A.dV = T.dV; A.dkraw = T.dkraw; A.d_rz = T.d_rz; A.Gz = T.Gz; A.dpre = T.dpre; A.t1 = T.t1; A.d_h = T.d_h;
     A.dc = T.dc; A.Ds = T.Ds; A.dq = T.dq; A.dkt = T.dkt; A.dvt = T.dvt;
-    char *p = (char *)exchange;
-    A.bar = (unsigned long long *)p; p += 256;
-    const size_t d = D.d, F = D.F;
-    auto take = [&](size_t words) { ll_t *q = (ll_t *)p; p += words * 8; return q; };
-    A.e1k = take(2 * kBMax * (d / 2)); A.e1v = take(2 * kBMax * (d / 2)); A.e2 = take(2 * kBMax * (d / 2)); A.e5 = take(2 * kBMax * (d / 2));
-    A.e3 = take(2 * kBMax * (F / 2)); A.e4 = take((size_t)2 * 4 * kBMax * d); A.e6 = take(2 * kBMax * d);
+    A.bar = (unsigned long long *)exchange;
+    A.words = A.bar + 32;
+    A.group_stride = group_stride(D.d);
+    A.packed = (const uint4 *)((const char *)exchange + word_bytes(D.d));
     A.spin_limit = P.spin_limit;
-    A.pre_sleep = 2;   // units of 4 x 64 clocks
-    {
-        const char *ps = getenv("RT_BWD_PRE_SLEEPS");   // four digits: the pulls of phases G1, G2, G3a, G4
-        const bool ok = ps && strlen(ps) == 4;
-        // measured at cfg3 (ms per backward pass, units of 8 x 64 clocks): 1,1,1,1 48.2; 1,2,1,1 47.8; 1,1,1,2 47.8; 1,2,1,2 47.3; 0,2,1,2 47.2; 1,3,1,2 47.2; 0,0,0,0 49.5
-        A.ps_g1 = ok ? ps[0] - '0' : 0; A.ps_g2 = ok ? ps[1] - '0' : 4; A.ps_g3 = ok ? ps[2] - '0' : 2; A.ps_g4 = ok ? ps[3] - '0' : 4;
+    // d = 1024, B = 8, N = 2048, ms per backward pass: 0011 27.00, 0000 27.04, 0111 27.11, 0212 27.49, 0222 27.73
+    int sl[4] = {0, 0, 1, 1};
+    if (const char *ps = getenv("RT_BWD_PRE_SLEEPS"))   // four digits: the pulls of phases G1, G2, G3, G4
+        for (int k = 0; k < 4 && ps[k]; ++k) sl[k] = ps[k] - '0';
+    A.sl_1 = sl[0]; A.sl_2 = sl[1]; A.sl_3 = sl[2]; A.sl_4 = sl[3];
+    // Tags: 1 .. 4094 in turn; when they start over no word of an earlier launch may survive.  A captured launch is replayed with the
+    // same tag: it has one of its own and clears the words first.
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    hipError_t e = st ? hipStreamIsCapturing(st, &capturing) : hipSuccess;
+    if (e != hipSuccess) return e;
+    const bool captured = capturing != hipStreamCaptureStatusNone;
+    if (captured || P.nonce >= 4094u) {
+        hipLaunchKernelGGL(bwp_clear_kernel, dim3(256), dim3(256), 0, st, A.words, kBwpGroups * A.group_stride);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        if (!captured) P.nonce = 0;
     }
-    if (P.nonce >= 4095u) {   // the tags start over: no word of an earlier launch may survive
-        hipError_t ce = bwp_clear(exchange, bwp_exchange_bytes(D.d, D.F), st);
-        if (ce != hipSuccess) return ce;
-        P.nonce = 0;
-    }
-    P.nonce += 1;
-    A.tag_base = P.nonce << 20;
+    if (!captured) P.nonce += 1;
+    A.tag_base = (captured ? 4095u : P.nonce) << 20;
     // an ordinary launch: one workgroup fills a compute unit and the grid is one workgroup per compute unit, so all of
     // them are resident once the kernels before it on the stream have drained (the cooperative queue costs about
     // 20 us per launch, measured on the decoding step)
-    hipLaunchKernelGGL(pick(D.d, D.F), dim3(P.grid), dim3(kPThreads), (unsigned int)P.lds_bytes, st, A);
+    hipLaunchKernelGGL(pick(D.d, D.B <= kBwpGroups ? 1 : 2), dim3(kBwpGroups * kBwpRanks), dim3(kPThreads), (unsigned int)P.lds_bytes, st, A);
     return hipGetLastError();
 }
 

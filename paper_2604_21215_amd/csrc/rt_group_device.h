@@ -1,4 +1,4 @@
-// Device helpers shared by the grouped engines (rt_group.hip, rt_group_f32.hip).
+// Device helpers shared by the grouped engines (rt_group.hip, rt_group_f32.hip, rt_backward_persistent.hip).
 #pragma once
 #include "rt_ll.h"
 
@@ -59,6 +59,114 @@ __device__ __forceinline__ float sum_mod4(float v)
     v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x124, 0xF, 0xF, true));
     v = fold1(v, v);
     return fold2(v, v);
+}
+
+// word of element pair (k, k + 1), k even, of batch row b: 16-byte pieces of four elements, runs of RUN pieces per batch row
+template <int RUN, int BM> __device__ __forceinline__ unsigned piece_word(unsigned k, unsigned b)
+{
+    const unsigned p = k >> 2;
+    return (((p / RUN) * BM + b) * RUN + p % RUN) * 2 + ((k >> 1) & 1);
+}
+
+// Operands of v_mfma_f32_4x4x4_16b_bf16 (16 blocks, block i = lanes 4i .. 4i+3): A: lane holds A[row = lane%4][k = 0..3] of
+// its block, B: lane holds B[k = 0..3][col = lane%4], D: register r holds D[row r][col = lane%4].  Rows are the batch rows,
+// columns the outputs.  With CBSZ = 2, ABID = j the blocks 4q .. 4q+3 all take block 4q + j of A: one instruction multiplies
+// 16 outputs (16 t + lane%16) by 16 contraction indices, four in each row q of 16 lanes.
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+union Piece {
+    uint2 u;
+    s16x4_t v;
+};
+union WFrag {
+    uint4 u;
+    uint2 h[2];
+};
+
+// This wavefront's share (NC chunks of 64 elements, LEN elements in all) of an exchanged vector of BM batch rows: act[m] of lane l
+// holds elements 64 m + 4 (l/4) .. + 3 of batch row l%4 % BM - the A operand of the product, nothing is staged in LDS.  With
+// fewer than four batch rows the lanes of the unused rows fetch the pieces of the chunks that follow, and a move inside the
+// four lanes of a block brings them where they belong.
+template <int NC, int LEN, int RUN, int BM>
+__device__ __forceinline__ void slice_pull(const ll_t *vec, int wave, int lane, int B, unsigned tag, const GroupWait &A, Piece (&act)[NC],
+                                           int &fail, int units)
+{
+    constexpr int CPL = 4 / BM;                  // chunks per load
+    constexpr int NL = (NC + CPL - 1) / CPL;
+    const __amdgpu_buffer_rsrc_t rsrc =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<ll_t *>(vec) + (size_t)wave * (LEN * BM / 2), 0, LEN * BM * 4, 0x00020000);
+    v4u_t v[NL];
+    const int b = lane & (BM - 1), p0 = (lane >> 2) + 16 * ((lane & 3) / BM);   // piece of the load's first chunk, batch row
+    const int off0 = ((p0 / RUN * BM + b) * RUN + p0 % RUN) * 16;               // a load is 1 KB in either layout
+    unsigned need = 0;
+#pragma unroll
+    for (int n = 0; n < NL; ++n) {
+        v[n] = v4u_t{0u, 0u, 0u, 0u};
+        if (b < B && ((n + 1) * 64 * CPL <= LEN || n * 64 * CPL + 4 * p0 < LEN)) need |= 1u << n;
+    }
+    long long spins = 0;
+    for (int i = 0; i < units; ++i) __builtin_amdgcn_s_sleep(4);
+    while (__any(need != 0)) {
+#pragma unroll
+        for (int n = 0; n < NL; ++n)
+            if (need & (1u << n)) v[n] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off0 + n * 1024, 0, kAuxAgent);
+#pragma unroll
+        for (int n = 0; n < NL; ++n)
+            if ((need & (1u << n)) && v[n][1] == tag && v[n][3] == tag) need &= ~(1u << n);
+        if (++spins > A.spin_limit || ((spins & 255) == 0 && ll_load(A.bar + 8) != 0)) { fail = 1; break; }
+    }
+#pragma unroll
+    for (int m = 0; m < NC; ++m) {
+        const unsigned lo = v[m / CPL][0], hi = v[m / CPL][2];
+        if (BM == 4) act[m].u = make_uint2(lo, hi);
+        else if (BM == 2) act[m].u = m & 1 ? make_uint2(quad_move<0xEE>(lo), quad_move<0xEE>(hi)) : make_uint2(lo, hi);
+        else if ((m & 3) == 0) act[m].u = make_uint2(lo, hi);
+        else if ((m & 3) == 1) act[m].u = make_uint2(quad_move<0x55>(lo), quad_move<0x55>(hi));
+        else if ((m & 3) == 2) act[m].u = make_uint2(quad_move<0xAA>(lo), quad_move<0xAA>(hi));
+        else act[m].u = make_uint2(quad_move<0xFF>(lo), quad_move<0xFF>(hi));
+    }
+}
+template <int J> __device__ __forceinline__ f32x4_t mfma4(const Piece &a, const uint2 &w, f32x4_t c)
+{
+    Piece b;
+    b.u = w;
+    return __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(a.v, b.v, c, 2, J, 0);
+}
+// one tile's 64 contraction indices of a chunk, one accumulator per J
+__device__ __forceinline__ void chunk_product4(const Piece &a, const WFrag &w0, const WFrag &w1, f32x4_t (&acc)[4])
+{
+    acc[0] = mfma4<0>(a, w0.h[0], acc[0]);
+    acc[1] = mfma4<1>(a, w0.h[1], acc[1]);
+    acc[2] = mfma4<2>(a, w1.h[0], acc[2]);
+    acc[3] = mfma4<3>(a, w1.h[1], acc[3]);
+}
+__device__ __forceinline__ f32x4_t chunk_product(const Piece &a, const WFrag &w0, const WFrag &w1, f32x4_t acc)
+{
+    acc = mfma4<0>(a, w0.h[0], acc);
+    acc = mfma4<1>(a, w0.h[1], acc);
+    acc = mfma4<2>(a, w1.h[0], acc);
+    return mfma4<3>(a, w1.h[1], acc);
+}
+// partial products of NT tiles -> red[wave][16 tile + lane%16][batch row]
+template <int NT> __device__ __forceinline__ void tiles_store(float *red, int wave, int lane, const f32x4_t (&acc)[NT])
+{
+    f32x4_t s;
+    const int q = lane >> 4;
+    int tile;
+    if (NT == 1) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) { const float v = fold2(acc[0][r], acc[0][r]); s[r] = fold1(v, v); }
+        tile = q == 0 ? 0 : NT;
+    } else if (NT == 2) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) { const float v = fold2(acc[0][r], acc[NT - 1][r]); s[r] = fold1(v, v); }
+        tile = q == 0 ? 0 : (q == 2 ? 1 : NT);
+    } else {   // rows hold tiles 0, 2, 1, 3
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            s[r] = fold1(fold2(acc[0][r], acc[1][r]), fold2(acc[NT > 2 ? 2 : 0][r], NT > 3 ? acc[NT - 1][r] : 0.f));
+        tile = q == 1 ? 2 : (q == 2 ? 1 : q);
+    }
+    if (tile < NT) *reinterpret_cast<f32x4_t *>(red + ((size_t)wave * 64 + tile * 16 + (lane & 15)) * 4) = s;
 }
 
 // Workgroup barrier behind which every wavefront leaves when one has given up waiting (G: GroupWait, flag_s: LDS flags).

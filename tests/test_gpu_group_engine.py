@@ -4,6 +4,7 @@ the edges of the direct window and of the blocks that stay in one workgroup (up 
 import pytest
 
 from paper_2604_21215_amd import inputs as gen
+from tests.test_gpu_backward import _run as _backward_case
 from tests.test_gpu_parity import _run_case
 from tests.test_gpu_stack import EMB_UNIT, _run_elementwise
 
@@ -36,5 +37,11 @@ def test_stack(oracle, B, N, layers, d, alibi):
                                          (16, 97, 384, 8.0), (4, 290, 256, 0.0), (1, 515, 128, 0.0), (32, 40, 128, 0.0)])
 def test_fp32(oracle, B, N, d, alibi):
     """fp32 storage: one sequence per group and several, widths whose share of a contraction ends inside a chunk, blocks of 32 to 512 keys"""
-    _run_case(oracle, "f32", B, N, d, d // 64, 4 * d, gains="random", scale=0.5, alpha=0.7, alibi=alibi, kv_cap=N + 1,
-              expect_engine="persistent")
+    _run_case(oracle, "f32", B, N, d, d // 64, 4 * d, gains="random", scale=0.5, alpha=0.7, alibi=alibi, kv_cap=N + 1)
+
+
+@pytest.mark.parametrize("d", [256, 512, 768, 1024])
+@pytest.mark.parametrize("B,N,alibi", [(1, 33, 8.0), (4, 64, 0.0), (5, 70, 0.0), (8, 34, 8.0)])
+def test_reverse_loop(oracle, d, B, N, alibi):
+    """the backward pass's loop: one and two sequences per group, full and ragged, blocks of one position and whole ones"""
+    _backward_case(oracle, "bf16", B, N, d, d // 64, 4 * d, alpha=0.7, scale=0.125, alibi=alibi, seed=77)
