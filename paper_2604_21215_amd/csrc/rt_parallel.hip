@@ -591,6 +591,135 @@ __global__ __launch_bounds__(64) void par_merge_kernel(const bf16_t *__restrict_
     a_out[((size_t)b * N + t - row0) * ((size_t)H * kHeadDim) + h * kHeadDim + threadIdx.x] = f32_to_bf16(a);
 }
 
+// The same merge for p_min = 32 and at most eight levels, eight lanes per row: lane 8 g + c holds dimensions 8 c .. + 7, a group g of
+// lanes the window's keys g, g + 8, .. and the stored state of level g.  Every row of the window is one 128-byte line of eight
+// consecutive lanes, all of them are requested before anything is computed, and a logit is three moves inside eight lanes (with a
+// key per lane, merge_body, a wavefront's loads touch as many lines as it has lanes, half of the lanes have no key, and every product
+// reads its query element through the scalar registers).  Bound: the window's rows, 6 KB per (b, h) on average.  1024 sequences, d = 1024 (16384
+// heads): 42.6 us a position (merge_body) -> 24.5 = 4.7 TB/s.
+// grid (ceil(B*H / 4), positions), block 256.
+__device__ __forceinline__ float sum8(float v)   // over the eight lanes of a group
+{
+    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, true));    // quad_perm [1,0,3,2]
+    v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x4E, 0xF, 0xF, true));    // quad_perm [2,3,0,1]
+    return v + __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x141, 0xF, 0xF, true));   // row_half_mirror
+}
+__device__ __forceinline__ float ror8(float v)   // the other group of a row of 16 lanes
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xF, 0xF, true));
+}
+__device__ __forceinline__ void unpack8(const uint4 &u, float *o)
+{
+    o[0] = __uint_as_float(u.x << 16); o[1] = __uint_as_float(u.x & 0xFFFF0000u);
+    o[2] = __uint_as_float(u.y << 16); o[3] = __uint_as_float(u.y & 0xFFFF0000u);
+    o[4] = __uint_as_float(u.z << 16); o[5] = __uint_as_float(u.z & 0xFFFF0000u);
+    o[6] = __uint_as_float(u.w << 16); o[7] = __uint_as_float(u.w & 0xFFFF0000u);
+}
+constexpr int kMerge32Levels = 8;
+__global__ __launch_bounds__(256) void par_merge32_kernel(const float *__restrict__ Qf, const float *__restrict__ Ktf,
+                                                          const bf16_t *__restrict__ Vt, const bf16_t *__restrict__ K,
+                                                          const bf16_t *__restrict__ Klo, const bf16_t *__restrict__ V,
+                                                          const float *__restrict__ pm, const float *__restrict__ pl,
+                                                          const float *__restrict__ po, bf16_t *__restrict__ a_out, int BH, int H, int N,
+                                                          int levels, int slots, float scale, float alibi, int t0, int row0)
+{
+    const int lane = threadIdx.x & 63, g = lane >> 3, c = lane & 7;
+    const int bh = blockIdx.x * 4 + (int)(threadIdx.x >> 6), t = t0 + blockIdx.y;
+    if (bh >= BH) return;
+    const size_t rs = (size_t)BH * kHeadDim, at = (size_t)bh * kHeadDim + 8 * c;
+    const int w = t & 31;
+    const size_t first = (size_t)(t - w) * rs + at;
+    uint4 kh[4], kl[4], vv[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        kh[r] = kl[r] = vv[r] = make_uint4(0u, 0u, 0u, 0u);
+        const int j = g + 8 * r;
+        if (j < w) {
+            kh[r] = *reinterpret_cast<const uint4 *>(K + first + (size_t)j * rs);
+            kl[r] = *reinterpret_cast<const uint4 *>(Klo + first + (size_t)j * rs);
+            vv[r] = *reinterpret_cast<const uint4 *>(V + first + (size_t)j * rs);
+        }
+    }
+    float q[8], kt[8], vt[8], so[8];
+    load8(Qf + (size_t)t * rs + at, q);
+    load8(Ktf + (size_t)t * rs + at, kt);
+    const uint4 vtu = *reinterpret_cast<const uint4 *>(Vt + (size_t)t * rs + at);
+    const bool on = g < levels && ((t >> (g + 5)) & 1);
+    float sm = -INFINITY, sl = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) so[e] = 0.f;
+    if (on) {
+        const size_t idx = partial_index(g, partial_slot(g + 5, t), slots, BH, bh);
+        sm = pm[idx];
+        sl = pl[idx];
+        load8(po + idx * kHeadDim + 8 * c, so);
+    }
+    float m0 = 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) m0 = fmaf(q[e], kt[e], m0);
+    m0 = scale * sum8(m0);
+    const float slope = alibi_slope(alibi, bh % H, H);
+    float p[4], mx = fmaxf(m0, sm);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        float hi[8], lo[8], s = 0.f;
+        unpack8(kh[r], hi);
+        unpack8(kl[r], lo);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s = fmaf(q[e], hi[e] + lo[e], s);
+        const int j = g + 8 * r;
+        p[r] = j < w ? fmaf(-slope, (float)(w - j), sum8(s) * scale) : -INFINITY;   // key j is w - j positions before the query
+        mx = fmaxf(mx, p[r]);
+    }
+    mx = fmaxf(mx, ror8(mx));
+    {
+        const unsigned u = __float_as_uint(mx);
+        const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+        mx = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+        const unsigned x = __float_as_uint(mx);
+        const auto b = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+        mx = fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+    }
+    const float e0 = g == 0 ? expf(m0 - mx) : 0.f, f = on ? expf(sm - mx) : 0.f;
+    float l = fmaf(f, sl, e0), o[8];
+    unpack8(vtu, vt);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) o[e] = fmaf(f, so[e], e0 * vt[e]);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const float x = expf(p[r] - mx);   // exp(-inf) = 0 beyond the window
+        float v8[8];
+        unpack8(vv[r], v8);
+        l += x;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = fmaf(x, v8[e], o[e]);
+    }
+    // sums over the groups: halves of the wavefront, rows of 16 lanes, groups of a row; row i ends with dimensions 2 i, 2 i + 1
+    auto fold = [](float a, float b, bool rows) {
+        const unsigned x = __float_as_uint(a), y = __float_as_uint(b);
+        if (rows) {
+            const auto r = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+            return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+        }
+        const auto r = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+        return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    };
+    l = fold(l, l, true);
+    l = fold(l, l, false);
+    l += ror8(l);
+    float x4[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x4[e] = fold(o[e], o[e + 4], false);
+    float y0 = fold(x4[0], x4[2], true), y1 = fold(x4[1], x4[3], true);
+    y0 += ror8(y0);
+    y1 += ror8(y1);
+    if ((lane & 8) == 0) {
+        const int b = bh / H, h = bh - b * H, row = lane >> 4;
+        *reinterpret_cast<uint32_t *>(a_out + ((size_t)b * N + t - row0) * ((size_t)H * kHeadDim) + h * kHeadDim + 8 * c + 2 * row) =
+            pack_bf16(y0 / l, y1 / l);
+    }
+}
+
 // ---------------------------------------------------------------------------------------------
 // Attention of ALL positions in one launch when every key-value pair is known in advance (Sec. 6.1 recompute,
 // Sec. 2.1 Transformer layer): query i against the cache rows j < i plus its own temporary pair, as one masked
@@ -1309,16 +1438,23 @@ hipError_t blocked_layer(const LayerDims &D, const Weights &W, const Scratch &S,
     hipError_t e = Launch<bf16_t>::prepass(D, W, S, x, B, N, true, st);   // q and temporary pairs of every position
     if (e != hipSuccess) return e;
     // the temporary pairs of ALL positions go into the cache rows at once: a block reads rows below its own end only, and its
-    // rows receive the persistent pairs when it is done
-    hipLaunchKernelGGL(par_export_tile_kernel, dim3(BH, (N + 63) / 64), dim3(256), 0, st, (const bf16_t *)S.Kt, S.Ktf,
-                       (const bf16_t *)S.Vt, (bf16_t *)K, (bf16_t *)V, S.Klo, S.Kh, S.VT, S.vt_stride, BH, N);
+    // rows receive the persistent pairs when it is done.  (Blocks of one position: the position's own temporary pair is merged from
+    // the pre-pass rows, so the cache rows are first read behind their persistent pairs.)
+    if (Sblk > 1)
+        hipLaunchKernelGGL(par_export_tile_kernel, dim3(BH, (N + 63) / 64), dim3(256), 0, st, (const bf16_t *)S.Kt, S.Ktf,
+                           (const bf16_t *)S.Vt, (bf16_t *)K, (bf16_t *)V, S.Klo, S.Kh, S.VT, S.vt_stride, BH, N);
     const bool by_steps = D.p_min % 32 == 0 && step_products(D, W);
     for (int t0 = 0; t0 < N; t0 += Sblk) {
         const int nr = Sblk < N - t0 ? Sblk : N - t0;
         const bool step = Sblk == 1 && by_steps;
-        hipLaunchKernelGGL(par_merge_kernel, dim3(BH, nr), dim3(64), 0, st, (const bf16_t *)S.Q, S.Qf, (const bf16_t *)S.Kt, S.Ktf,
-                           (const bf16_t *)S.Vt, (const bf16_t *)K, S.Klo, (const bf16_t *)V, S.pm, S.pl, S.po, step ? S.op_a : a_b, BH,
-                           D.H, step ? 1 : N, D.p_min, D.log2_pmin, S.levels, S.slots, D.scale, D.alibi, t0, step ? t0 : 0);
+        if (D.p_min == 32 && S.levels <= kMerge32Levels)
+            hipLaunchKernelGGL(par_merge32_kernel, dim3((BH + 3) / 4, nr), dim3(256), 0, st, S.Qf, S.Ktf, (const bf16_t *)S.Vt, (const bf16_t *)K,
+                               S.Klo, (const bf16_t *)V, S.pm, S.pl, S.po, step ? S.op_a : a_b, BH, D.H, step ? 1 : N, S.levels, S.slots, D.scale,
+                               D.alibi, t0, step ? t0 : 0);
+        else
+            hipLaunchKernelGGL(par_merge_kernel, dim3(BH, nr), dim3(64), 0, st, (const bf16_t *)S.Q, S.Qf, (const bf16_t *)S.Kt, S.Ktf,
+                               (const bf16_t *)S.Vt, (const bf16_t *)K, S.Klo, (const bf16_t *)V, S.pm, S.pl, S.po, step ? S.op_a : a_b, BH,
+                               D.H, step ? 1 : N, D.p_min, D.log2_pmin, S.levels, S.slots, D.scale, D.alibi, t0, step ? t0 : 0);
         if (step) step_position(D, Wp, S, x, y, K, V, t0, st);
         else block_gemms(D, W, x, y, a_b, h_f, h_b, u_b, S.rinv, t0, nr, st);
         // persistent pairs of the block from its outputs (rows t0.. of the pre-pass buffers are free again)

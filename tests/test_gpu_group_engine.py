@@ -45,3 +45,9 @@ def test_fp32(oracle, B, N, d, alibi):
 def test_reverse_loop(oracle, d, B, N, alibi):
     """the backward pass's loop: one and two sequences per group, full and ragged, blocks of one position and whole ones"""
     _backward_case(oracle, "bf16", B, N, d, d // 64, 4 * d, alpha=0.7, scale=0.125, alibi=alibi, seed=77)
+
+
+@pytest.mark.parametrize("B,N,d,alibi", [(130, 70, 256, 0.0), (129, 100, 320, 8.0)])
+def test_merge_of_eight_lanes_per_row(oracle, B, N, d, alibi):
+    """the position-batched merge: windows of 0 to 31 keys, none to two stored levels, heads that do not fill the last workgroup"""
+    _run_case(oracle, "bf16", B, N, d, d // 64, 4 * d, gains="random", scale=0.5, alibi=alibi, expect_engine="position-batched")
