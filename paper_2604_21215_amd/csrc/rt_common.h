@@ -219,12 +219,20 @@ __host__ __device__ __forceinline__ size_t partial_index(int level_rel, int slot
 // compact slot of 0-based query i0 at absolute level l (bit l of i0 must be set)
 __host__ __device__ __forceinline__ int partial_slot(int l, int i0) { return ((i0 >> (l + 1)) << l) | (i0 & ((1 << l) - 1)); }
 
+// What a pre-pass whose temporary pairs are the layer's persistent ones (Kt, Vt of its Scratch are then the caller's cache rows)
+// writes beside them: the key copies of the tiles; null pointers of the Scratch (Q, Qf, Ktf) are not written.  Matrix-core kernels.
+struct PrepassPairs {
+    bf16_t *Klo;
+    uint16_t *Kh;
+    bool pairs_only;   // no queries are wanted
+};
+
 // ---------------------------------------------------------------- launchers (one per kernel family)
 template <typename T> struct Launch {
     // rows n0 .. n0+Nc-1 of every batch row of x (batch rows x_bstride elements apart; 0 = Nc * d, a dense
     // [Bc][Nc][d] tensor) -> Q, Kt, Vt rows ((n0 + n)*Bc + b)
     static hipError_t prepass(const LayerDims &D, const Weights &W, const Scratch &S, const void *x, int Bc, int Nc,
-                              bool mfma, hipStream_t st, size_t x_bstride = 0, int n0 = 0);
+                              bool mfma, hipStream_t st, size_t x_bstride = 0, int n0 = 0, const PrepassPairs *pairs = nullptr);
     // one position's q, k_tmp, v_tmp (decoding step): rows b of Q, Kt, Vt
     static hipError_t prepass_one(const LayerDims &D, const Weights &W, const Scratch &S, const void *x_t, size_t x_stride,
                                   hipStream_t st, bool matrix_cores = false);

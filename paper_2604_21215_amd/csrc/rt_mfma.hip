@@ -24,10 +24,11 @@ __global__ __launch_bounds__(256) void prepass_mfma_kernel(const bf16_t *__restr
                                                            bf16_t *__restrict__ Q, bf16_t *__restrict__ Kt,
                                                            bf16_t *__restrict__ Vt, float *__restrict__ Qf,
                                                            float *__restrict__ Ktf, int Bc, int Nc, size_t x_bstride,
-                                                           int n0, int d, int H, float eps, int norm_free)
+                                                           int n0, int d, int H, float eps, int norm_free, bf16_t *__restrict__ Klo,
+                                                           uint16_t *__restrict__ Kh)
 {
     prepass_mfma_body<false>(x, rinv, Wq, Wk, Wv, g_attn, g_q, g_k, Q, Kt, Vt, Qf, Ktf, Bc, Nc, x_bstride, n0, d, H, eps, norm_free,
-                             blockIdx.x, blockIdx.y);
+                             blockIdx.x, blockIdx.y, Klo, Kh);
 }
 
 // The same projection with both operands staged in LDS (tiled_mainloop), for many rows and d a multiple of 128: a
@@ -42,7 +43,8 @@ __global__ __launch_bounds__(256) void prepass_tiled_kernel(const bf16_t *__rest
                                                             bf16_t *__restrict__ Q, bf16_t *__restrict__ Kt,
                                                             bf16_t *__restrict__ Vt, float *__restrict__ Qf,
                                                             float *__restrict__ Ktf, int Bc, int Nc, size_t x_bstride,
-                                                            int n0, int d, int H, float eps, int norm_free)
+                                                            int n0, int d, int H, float eps, int norm_free, int first_col,
+                                                            bf16_t *__restrict__ Klo, uint16_t *__restrict__ Kh)
 {
     __shared__ __align__(16) unsigned char lds[kManyLds<ALIGNED>];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -50,7 +52,7 @@ __global__ __launch_bounds__(256) void prepass_tiled_kernel(const bf16_t *__rest
     const int l32 = lane & 31, hi = lane >> 5;
     const int M = Bc * Nc;
     const int m0 = blockIdx.x * kGtRows;
-    const int c0 = blockIdx.y * kGtCols;          // first of the block's columns of [q | k_tmp | v_tmp]
+    const int c0 = first_col + blockIdx.y * kGtCols;   // first of the block's columns of [q | k_tmp | v_tmp]
     const int bw = c0 / d;                         // d is a multiple of 128: a block lies within one of the three
     const bf16_t *Wb = (bw == 0 ? Wq : (bw == 1 ? Wk : Wv)) + (size_t)(c0 - bw * d) * d;
     f32x16_t acc[4][2];
@@ -98,9 +100,13 @@ __global__ __launch_bounds__(256) void prepass_tiled_kernel(const bf16_t *__rest
                 }
                 const size_t oo = ((size_t)(n0 + n) * Bc + b) * d + hcol + l32;
                 const float o0 = v0 * sc * gc[0], o1 = v1 * sc * gc[1];
-                dst[oo] = f32_to_bf16(o0);
-                dst[oo + 32] = f32_to_bf16(o1);
+                const bf16_t b0 = f32_to_bf16(o0), b1 = f32_to_bf16(o1);
+                if (dst) { dst[oo] = b0; dst[oo + 32] = b1; }
                 if (dstf) { dstf[oo] = o0; dstf[oo + 32] = o1; }
+                if (bw == 1 && Kh) {   // the copies that the tiles multiply
+                    Klo[oo] = f32_to_bf16(o0 - bf16_to_f32(b0)); Klo[oo + 32] = f32_to_bf16(o1 - bf16_to_f32(b1));
+                    Kh[oo] = f32_to_f16_bits(o0); Kh[oo + 32] = f32_to_f16_bits(o1);
+                }
             }
         }
     }
@@ -138,9 +144,11 @@ hipError_t scale_qkv_launch(const Weights &W, bf16_t *out, int d, hipStream_t st
 constexpr int kTiledMinRows = 2048;   // below this the untiled kernel's smaller block tiles fill the chip better
 
 hipError_t prepass_mfma_launch(const LayerDims &D, const Weights &W, const Scratch &S, const void *x, int Bc, int Nc,
-                               size_t x_bstride, int n0, hipStream_t st)
+                               size_t x_bstride, int n0, hipStream_t st, const PrepassPairs *pairs)
 {
     const int M = Bc * Nc;
+    bf16_t *const Klo = pairs ? pairs->Klo : nullptr;
+    uint16_t *const Kh = pairs ? pairs->Kh : nullptr;
     const bool gained = W.g_attn && !D.norm_free;   // the tiled kernel wants the gain in the matrices' columns
     if (M >= kTiledMinRows && D.d % 128 == 0 && (!gained || S.wg_qkv)) {
         const bool aligned = aligned16(x) && (gained || (aligned16(W.Wq) && aligned16(W.Wk) && aligned16(W.Wv)));
@@ -151,15 +159,16 @@ hipError_t prepass_mfma_launch(const LayerDims &D, const Weights &W, const Scrat
             wq = S.wg_qkv; wk = wq + (size_t)D.d * D.d; wv = wk + (size_t)D.d * D.d;
         }
         const auto kernel = aligned ? prepass_tiled_kernel<true> : prepass_tiled_kernel<false>;
-        hipLaunchKernelGGL(kernel, dim3((M + kGtRows - 1) / kGtRows, 3 * D.d / kGtCols), dim3(256), 0, st,
+        const int first_col = pairs && pairs->pairs_only ? D.d : 0;   // no queries wanted
+        hipLaunchKernelGGL(kernel, dim3((M + kGtRows - 1) / kGtRows, (3 * D.d - first_col) / kGtCols), dim3(256), 0, st,
                            (const bf16_t *)x, S.rinv, wq, wk, wv, (const bf16_t *)W.g_q, (const bf16_t *)W.g_k, (bf16_t *)S.Q,
-                           (bf16_t *)S.Kt, (bf16_t *)S.Vt, S.Qf, S.Ktf, Bc, Nc, x_bstride, n0, D.d, D.H, D.eps, D.norm_free);
+                           (bf16_t *)S.Kt, (bf16_t *)S.Vt, S.Qf, S.Ktf, Bc, Nc, x_bstride, n0, D.d, D.H, D.eps, D.norm_free, first_col, Klo, Kh);
         return hipGetLastError();
     }
     hipLaunchKernelGGL(prepass_mfma_kernel, dim3((M + 127) / 128, (3 * D.H + 1) / 2), dim3(256), 0, st, (const bf16_t *)x,
                        S.rinv, (const bf16_t *)W.Wq, (const bf16_t *)W.Wk, (const bf16_t *)W.Wv, (const bf16_t *)W.g_attn,
                        (const bf16_t *)W.g_q, (const bf16_t *)W.g_k, (bf16_t *)S.Q, (bf16_t *)S.Kt, (bf16_t *)S.Vt, S.Qf, S.Ktf,
-                       Bc, Nc, x_bstride, n0, D.d, D.H, D.eps, D.norm_free);
+                       Bc, Nc, x_bstride, n0, D.d, D.H, D.eps, D.norm_free, Klo, Kh);
     return hipGetLastError();
 }
 

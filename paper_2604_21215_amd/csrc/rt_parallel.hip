@@ -520,6 +520,31 @@ __global__ __launch_bounds__(64) void par_export_kernel(const bf16_t *__restrict
     VT[((size_t)bh * kHeadDim + lane) * vt_stride + t] = v;
 }
 
+// The transposed values of all N positions from the cache rows, 64 positions of one (b, h) per workgroup, through LDS; columns N ..
+// 64 ceil(N / 64) - 1 are written as zeros.  grid (B*H, ceil(N / 64)), block 256.
+__global__ __launch_bounds__(256) void par_vt_tile_kernel(const bf16_t *__restrict__ V, bf16_t *__restrict__ VT, int vt_stride, int BH, int N)
+{
+    constexpr int kLd = 72;
+    __shared__ __align__(16) bf16_t tile[64 * kLd];
+    const int tid = threadIdx.x, r = tid >> 2, c = tid & 3, bh = blockIdx.x, t0 = blockIdx.y * 64;
+    uint4 v0 = make_uint4(0u, 0u, 0u, 0u), v1 = v0;
+    if (t0 + r < N) {
+        const bf16_t *src = V + ((size_t)(t0 + r) * BH + bh) * kHeadDim + 16 * c;
+        v0 = *reinterpret_cast<const uint4 *>(src);
+        v1 = *reinterpret_cast<const uint4 *>(src + 8);
+    }
+    *reinterpret_cast<uint4 *>(tile + r * kLd + 16 * c) = v0;
+    *reinterpret_cast<uint4 *>(tile + r * kLd + 16 * c + 8) = v1;
+    __syncthreads();
+    uint32_t w[8];   // row r of V^T (head dimension r), positions t0 + 16 c .. + 15
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        w[j] = (uint32_t)tile[(16 * c + 2 * j) * kLd + r] | ((uint32_t)tile[(16 * c + 2 * j + 1) * kLd + r] << 16);
+    bf16_t *dst = VT + ((size_t)bh * kHeadDim + r) * vt_stride + t0 + 16 * c;
+    *reinterpret_cast<uint4 *>(dst) = make_uint4(w[0], w[1], w[2], w[3]);
+    *reinterpret_cast<uint4 *>(dst + 8) = make_uint4(w[4], w[5], w[6], w[7]);
+}
+
 // The same export for all N positions, 64 positions of one (b, h) per workgroup: every global access is a run of
 // 32 bytes or more (the kernel above writes V^T two bytes at a time); the values are transposed through LDS.
 // V^T columns N .. 64 ceil(N / 64) - 1 are written as zeros.  grid (B*H, ceil(N / 64)), block 256.
@@ -1193,10 +1218,17 @@ hipError_t parallel_layer(const LayerDims &D, const Weights &W, const Scratch &S
 
     Weights Wp = W;
     if (!pairs_are_temporary) Wp.g_attn = W.g_kv;
-    hipError_t e = Launch<bf16_t>::prepass(D, Wp, S, pairs_src, B, N, true, st);
+    // The pre-pass writes the pairs straight into the cache rows (the same layout) and the keys' copies beside them; only the transposed
+    // values take a pass of their own.  (An export pass over everything read 133 and wrote 167 MB at 16384 rows, d = 1024: 62 us; now
+    // 17, and 10 more in the pre-pass.)  Pairs that come from z want neither queries nor unrounded temporary keys: a third of that product is not formed.
+    Scratch Sp = S;
+    Sp.Q = nullptr; Sp.Kt = K; Sp.Vt = V;
+    if (!pairs_are_temporary) { Sp.Qf = nullptr; Sp.Ktf = nullptr; }
+    const PrepassPairs pairs = {S.Klo, S.Kh, !pairs_are_temporary};
+    hipError_t e = Launch<bf16_t>::prepass(D, Wp, Sp, pairs_src, B, N, true, st, 0, 0, &pairs);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(par_export_tile_kernel, dim3(BH, (N + 63) / 64), dim3(256), 0, st, (const bf16_t *)S.Kt, S.Ktf,
-                       (const bf16_t *)S.Vt, (bf16_t *)K, (bf16_t *)V, S.Klo, S.Kh, S.VT, S.vt_stride, BH, N);
+    hipLaunchKernelGGL(par_vt_tile_kernel, dim3(BH, (N + 63) / 64), dim3(256), 0, st, (const bf16_t *)V, S.VT, S.vt_stride, BH, N);
+    const bf16_t *vt_own = pairs_are_temporary ? (const bf16_t *)V : (const bf16_t *)S.Vt;   // the queries' own temporary values
     if (!pairs_are_temporary) {
         e = Launch<bf16_t>::prepass(D, W, S, x, B, N, true, st);
         if (e != hipSuccess) return e;
@@ -1207,10 +1239,10 @@ hipError_t parallel_layer(const LayerDims &D, const Weights &W, const Scratch &S
         const dim3 grid((unsigned)(ntiles * BH));
         const bf16_t *Kh = (const bf16_t *)S.Kh;   // 2-byte elements either way; the kernel reads them as fp16
         if (D.alibi > 0.f)
-            hipLaunchKernelGGL(par_flash_kernel<true>, grid, dim3(256), lds, st, S.Qf, S.Ktf, (const bf16_t *)S.Vt, (const bf16_t *)K,
+            hipLaunchKernelGGL(par_flash_kernel<true>, grid, dim3(256), lds, st, S.Qf, S.Ktf, vt_own, (const bf16_t *)K,
                                Kh, S.VT, S.vt_stride, a_b, BH, D.H, N, ntiles, D.scale, D.alibi);
         else
-            hipLaunchKernelGGL(par_flash_kernel<false>, grid, dim3(256), lds, st, S.Qf, S.Ktf, (const bf16_t *)S.Vt, (const bf16_t *)K,
+            hipLaunchKernelGGL(par_flash_kernel<false>, grid, dim3(256), lds, st, S.Qf, S.Ktf, vt_own, (const bf16_t *)K,
                                Kh, S.VT, S.vt_stride, a_b, BH, D.H, N, ntiles, D.scale, D.alibi);
     }
     block_gemms(D, W, x, y, a_b, h_f, h_b, u_b, S.rinv, 0, N, st);

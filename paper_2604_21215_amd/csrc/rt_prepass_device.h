@@ -23,7 +23,8 @@ __device__ __forceinline__ void prepass_mfma_body(const bf16_t *__restrict__ x, 
                                                   bf16_t *__restrict__ Vt, float *__restrict__ Qf,
                                                   float *__restrict__ Ktf, int Bc, int Nc, size_t x_bstride,
                                                   int n0, int d, int H, float eps, int norm_free, int block_x,
-                                                  int block_y)
+                                                  int block_y, bf16_t *__restrict__ Klo = nullptr,
+                                                  uint16_t *__restrict__ Kh = nullptr)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int wm = wave >> 1, wn = wave & 1;
@@ -127,8 +128,13 @@ __device__ __forceinline__ void prepass_mfma_body(const bf16_t *__restrict__ x, 
                 for (int j = 0; j < 4; ++j) {
                     float val = v[j] * sc;
                     if (which < 2 && !norm_free && gn) val *= bf16_to_f32(gn[h * kHeadDim + j * 16 + l16]);
-                    dst[oo + j * 16] = f32_to_bf16(val);
+                    const bf16_t vb = f32_to_bf16(val);
+                    if (dst) dst[oo + j * 16] = vb;
                     if (dstf) dstf[oo + j * 16] = val;
+                    if (which == 1 && Kh) {   // the copies that the tiles multiply
+                        Klo[oo + j * 16] = f32_to_bf16(val - bf16_to_f32(vb));
+                        Kh[oo + j * 16] = f32_to_f16_bits(val);
+                    }
                 }
             }
         }

@@ -329,19 +329,19 @@ __global__ __launch_bounds__(256) void prepass_generic_kernel(const T *__restric
 // Launchers
 // =============================================================================================
 hipError_t prepass_mfma_launch(const LayerDims &D, const Weights &W, const Scratch &S, const void *x, int Bc, int Nc,
-                               size_t x_bstride, int n0, hipStream_t st);
+                               size_t x_bstride, int n0, hipStream_t st, const PrepassPairs *pairs);
 hipError_t cross_mfma_launch(const LayerDims &D, const Scratch &S, const void *K, int t1, int P, int nq, bool hp,
                              hipStream_t st);
 
 template <typename T>
 hipError_t Launch<T>::prepass(const LayerDims &D, const Weights &W, const Scratch &S, const void *x, int Bc, int Nc,
-                              bool mfma, hipStream_t st, size_t x_bstride, int n0)
+                              bool mfma, hipStream_t st, size_t x_bstride, int n0, const PrepassPairs *pairs)
 {
     const int M = Bc * Nc;
     if (x_bstride == 0) x_bstride = (size_t)Nc * D.d;
     hipLaunchKernelGGL(row_rinv_kernel<T>, dim3((M + 3) / 4), dim3(256), 0, st, (const T *)x, S.rinv, M, Nc, x_bstride, n0,
                        D.d, D.eps, D.norm_free);
-    if (mfma && sizeof(T) == 2) return prepass_mfma_launch(D, W, S, x, Bc, Nc, x_bstride, n0, st);
+    if (mfma && sizeof(T) == 2) return prepass_mfma_launch(D, W, S, x, Bc, Nc, x_bstride, n0, st, pairs);
     hipLaunchKernelGGL(prepass_generic_kernel<T>, dim3((M + 63) / 64, 3 * D.H), dim3(256), 0, st, (const T *)x, S.rinv,
                        (const T *)W.Wq, (const T *)W.Wk, (const T *)W.Wv, (const T *)W.g_attn, (const T *)W.g_q,
                        (const T *)W.g_k, (T *)S.Q, (T *)S.Kt, (T *)S.Vt, Bc, Nc, x_bstride, n0, D.d, D.H, D.eps,
