@@ -61,17 +61,20 @@ __global__ __launch_bounds__(64) void decode_split_kernel(const T *__restrict__ 
 // 8 i + lane / 8, columns 8 (lane % 8) .. + 7 (eight lanes cover one 128-byte row); the logits are summed over the
 // eight lanes of a row and stay there (the value rows have the same layout), and the eight lanes that share columns
 // are summed at the end.  Rows past the split's end are read from its last row with weight zero.
-// One split per wavefront: grid (ceil(nsplit / 4), B*H), block 256.
+// One split of one (b, h) per wavefront, four neighbouring heads per workgroup, the heads of a split before the next split: the
+// wavefronts in flight read whole cache rows (B*H runs of 128 bytes), not 128 bytes of each of many rows.
+// d = 1024, B = 200, t = 511: 98 us with the splits of one head in a workgroup, 84 (5 TB/s) like this.
+// grid (ceil(B*H / 4), nsplit), block 256.
 __global__ __launch_bounds__(256) void decode_split64_bf16_kernel(const bf16_t *__restrict__ Q, const bf16_t *__restrict__ K,
                                                                  const bf16_t *__restrict__ V, float *__restrict__ pm,
                                                                  float *__restrict__ pl, float *__restrict__ po, int BH, int t,
                                                                  int slots, float scale, float alibi, int H)
 {
     const int lane = threadIdx.x & 63;
-    const int split = blockIdx.x * 4 + (threadIdx.x >> 6), bh = blockIdx.y;   // one split per wavefront
+    const int split = blockIdx.y, bh = blockIdx.x * 4 + (threadIdx.x >> 6);
     const size_t rs = (size_t)BH * kHeadDim;
     const int k_lo = split * 64, cnt = min(t - k_lo, 64);
-    if (cnt <= 0) return;   // no barriers in this kernel
+    if (cnt <= 0 || bh >= BH) return;   // no barriers in this kernel
     uint4 kr[8], vr[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
@@ -461,7 +464,7 @@ hipError_t Launch<T>::decode_split(const LayerDims &D, const Scratch &S, const v
                                    int nsplit, hipStream_t st)
 {
     if (sizeof(T) == 2 && chunk == 64)
-        hipLaunchKernelGGL(decode_split64_bf16_kernel, dim3((nsplit + 3) / 4, D.B * D.H), dim3(256), 0, st, (const bf16_t *)S.Q,
+        hipLaunchKernelGGL(decode_split64_bf16_kernel, dim3((D.B * D.H + 3) / 4, nsplit), dim3(256), 0, st, (const bf16_t *)S.Q,
                            (const bf16_t *)K, (const bf16_t *)V, S.pm, S.pl, S.po, D.B * D.H, t, S.slots, D.scale, D.alibi, D.H);
     else
         hipLaunchKernelGGL(decode_split_kernel<T>, dim3(nsplit, D.B * D.H), dim3(64), 0, st, (const T *)S.Q, (const T *)K,
