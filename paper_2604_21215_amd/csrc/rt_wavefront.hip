@@ -150,6 +150,15 @@ __device__ __forceinline__ float rms_scale_from_parts(const float *__restrict__ 
 
 constexpr int EPI_QKV = 4;
 // 1 / rms of a head whose 64 values lie in the four row groups of the workgroup (hss [4][ncol]); a barrier for every wavefront
+// v where it stands, not where it was read from: a choice between members of a kernel argument is otherwise compiled as a
+// choice between their addresses, which copies the whole argument to every thread's scratch.  The products of [Wq; Wk; Wv] for
+// more than kWideFrom batch rows spent half their time on that (d = 1024, B = 200: 30.6 us, now 17.7).
+template <class T> __device__ __forceinline__ T *in_register(T *v)
+{
+    asm("" : "+s"(v));
+    return v;
+}
+
 __device__ __forceinline__ float head_scale(const float *v, bool owner, bool live, int g, int rg, int col, int ncol, float *hss, float eps)
 {
     float ss = live ? (v[0] * v[0] + v[1] * v[1]) + (v[2] * v[2] + v[3] * v[3]) : 0.f;
@@ -226,12 +235,14 @@ __device__ __forceinline__ void mm_epilogue(const WaveLayer &Y, int t, const f32
         const int which = block_x / H, h = block_x - which * H, hd = 16 * rg + 4 * g;
         if (which < 2 && !norm_free) {
             const float sc = head_scale(v, owner, live, g, rg, col, ncol, hss, eps);
-            const bf16_t *gn = (const bf16_t *)(which == 0 ? Y.W.g_q : Y.W.g_k);
+            const void *gq = in_register(Y.W.g_q), *gk = in_register(Y.W.g_k);
+            const bf16_t *gn = (const bf16_t *)(which == 0 ? gq : gk);
 #pragma unroll
             for (int r = 0; r < 4; ++r) v[r] *= sc * (gn ? bf16_to_f32(gn[h * kHeadDim + hd + r]) : 1.f);
         }
+        void *q = in_register(Y.S.Q), *k = in_register(Y.S.Kt), *vv = in_register(Y.S.Vt);
         if (live)
-            *reinterpret_cast<uint2 *>((bf16_t *)(which == 0 ? Y.S.Q : (which == 1 ? Y.S.Kt : Y.S.Vt)) + ((size_t)b * H + h) * kHeadDim + hd) =
+            *reinterpret_cast<uint2 *>((bf16_t *)(which == 0 ? q : (which == 1 ? k : vv)) + ((size_t)b * H + h) * kHeadDim + hd) =
                 make_uint2(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]));
     } else {
         // the workgroup is head hh of [k heads | v heads]; this wavefront holds head dimensions 16 rg + 4g .. + 3
@@ -440,14 +451,15 @@ __global__ __launch_bounds__(64 * NW) void step_mm_kernel(const WaveLayer Y, int
 // eight partial tiles meet in LDS once, and wavefront w finishes tile w (row group w % NO, batch columns 16 (w / NO) ..).
 // 32 columns, because an operand row costs a head and a remainder row: 64 x 32 outputs read as many bytes of W as of x.
 // NO = 2 where n_out is only d: twice the workgroups (B = 100: 128 instead of 64).  Measured
-// at d = 1024: B = 100 in the stack engine 5.3, 8.1, 11.3, 9.1 us; a decoding step at B = 200 QKV 31 (89 before), W1 19, W2 18
+// at d = 1024: B = 100 in the stack engine 5.3, 8.1, 11.3, 9.1 us; a decoding step at B = 200 QKV 16 (89 before), W1 17, W2 18
 // (44), [Wk; Wv] 11 (21) us.  The operand rows come in fragment order (operand_offsets): as plain rows, whose fragments are
 // 64-byte pieces of sixteen lines, W2 at B = 100 took 19.2 us.
 // grid (n_out / (16 NO), layers, batch tiles of 32), block 512, LDS 14 NO KB + 512 B.  EPI_KV and EPI_QKV need NO = 4: a
 // workgroup is one head, and EPI_QKV writes the normalised rows Q, Kt, Vt of a decoding step (no finalize launch).
 // ---------------------------------------------------------------------------------------------
 constexpr int kWideBatch = 32, kWideWaves = 8;
-template <int EPI, int NO, bool PACKED>
+// DEPTH: groups of two steps requested ahead.
+template <int EPI, int NO, bool PACKED, int DEPTH = 2>
 __device__ __forceinline__ void wide_body(const WaveLayer &Y, int t, int block_x, int batch_tile, int B, int N, int d, int F, int H,
                                           float eps, int norm_free, float alpha, unsigned char *wide_smem)
 {
@@ -467,7 +479,8 @@ __device__ __forceinline__ void wide_body(const WaveLayer &Y, int t, int block_x
         Wr = row0 < d ? (const bf16_t *)Y.W.Wk + (size_t)row0 * K : (const bf16_t *)Y.W.Wv + (size_t)(row0 - d) * K;
     } else {
         Wp = nullptr; X = Y.S.op_x;
-        Wr = (const bf16_t *)(row0 < d ? Y.W.Wq : (row0 < 2 * d ? Y.W.Wk : Y.W.Wv)) + (size_t)(row0 % d) * K;
+        const void *wq = in_register(Y.W.Wq), *wk = in_register(Y.W.Wk), *wv = in_register(Y.W.Wv);
+        Wr = (const bf16_t *)(row0 < d ? wq : (row0 < 2 * d ? wk : wv)) + (size_t)(row0 % d) * K;
     }
     const bf16_t *wr = PACKED ? Wp + ((size_t)(row0 / 16) * (K / 32) + (size_t)wave * nk) * 512 + lane * 8
                               : Wr + (size_t)c16 * K + (size_t)wave * nk * 32 + 8 * g;
@@ -487,7 +500,7 @@ __device__ __forceinline__ void wide_body(const WaveLayer &Y, int t, int block_x
     for (int j = 0; j < NO; ++j)
 #pragma unroll
         for (int c = 0; c < 2; ++c) acc[j][c] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    Frag w[2][2][NO], xh[2][2][2], xl[2][2][2];
+    Frag w[DEPTH][2][NO], xh[DEPTH][2][2], xl[DEPTH][2][2];
 #define RT_WIDE_LOAD(buf, s0)                                                             \
     _Pragma("unroll") for (int e = 0; e < 2; ++e)                                         \
     {                                                                                     \
@@ -512,7 +525,7 @@ __device__ __forceinline__ void wide_body(const WaveLayer &Y, int t, int block_x
         }                                                                                 \
     }
     RT_WIDE_LOAD(0, 0)
-    if (nk > 2) { RT_WIDE_LOAD(1, 2) }
+    if (DEPTH == 2 && nk > 2) { RT_WIDE_LOAD(DEPTH - 1, 2) }
     // the tile that this wavefront finishes, and the RMS scale of its batch column's input
     const bool owner = wave < 2 * NO;
     const int rg = wave % NO, col = 16 * ((wave / NO) & 1) + c16;
@@ -520,11 +533,13 @@ __device__ __forceinline__ void wide_body(const WaveLayer &Y, int t, int block_x
     float rscale = 1.f;
     if (!norm_free && (EPI == EPI_W1 || EPI == EPI_KV || EPI == EPI_QKV))
         rscale = rms_scale_from_parts(EPI == EPI_W1 ? Y.S.ssq_h : (EPI == EPI_KV ? Y.S.ssq_z : Y.S.ssq_x), cb, g, d / 16, d, eps);
-    for (int s = 0; s < nk; s += 4) {
+    for (int s = 0; s < nk; s += 2 * DEPTH) {
         RT_WIDE_COMPUTE(0, s)
-        if (s + 4 < nk) { RT_WIDE_LOAD(0, s + 4) }
-        RT_WIDE_COMPUTE(1, s + 2)
-        if (s + 6 < nk) { RT_WIDE_LOAD(1, s + 6) }
+        if (s + 2 * DEPTH < nk) { RT_WIDE_LOAD(0, s + 2 * DEPTH) }
+        if constexpr (DEPTH == 2) {
+            RT_WIDE_COMPUTE(1, s + 2)
+            if (s + 6 < nk) { RT_WIDE_LOAD(1, s + 6) }
+        }
     }
 #undef RT_WIDE_LOAD
 #undef RT_WIDE_COMPUTE
@@ -553,12 +568,12 @@ __global__ __launch_bounds__(64 * kWideWaves) void wf_wide_kernel(const WaveLaye
     wide_body<EPI, NO, true>(layers[l], layer_pos(s, l, chunk), (int)blockIdx.x, (int)blockIdx.z, B, N, d, F, H, eps, norm_free, alpha,
                              wide_smem);
 }
-template <int EPI, int NO>
-__global__ __launch_bounds__(64 * kWideWaves) void step_wide_kernel(const WaveLayer Y, int B, int d, int F, int H, float eps,
-                                                                    int norm_free, float alpha)
+template <int EPI, int NO, int DEPTH>
+__global__ __launch_bounds__(64 * kWideWaves, DEPTH == 1 ? 4 : 2) void step_wide_kernel(const WaveLayer Y, int B, int d, int F, int H,
+                                                                                        float eps, int norm_free, float alpha)
 {
     extern __shared__ __align__(16) unsigned char wide_smem[];
-    wide_body<EPI, NO, false>(Y, 0, (int)blockIdx.x, (int)blockIdx.z, B, 1, d, F, H, eps, norm_free, alpha, wide_smem);
+    wide_body<EPI, NO, false, DEPTH>(Y, 0, (int)blockIdx.x, (int)blockIdx.z, B, 1, d, F, H, eps, norm_free, alpha, wide_smem);
 }
 
 // A decoding step's input rows x_t [B][d] as operand rows: head + remainder of x * g_attn, and the sums of squares of
@@ -787,7 +802,8 @@ static hipError_t mm_launch(int n_out, unsigned nl, hipStream_t st, const WaveLa
 
 // Batches and widths from which the products take 32 sequences per workgroup.  Measured (us, tiles of 16 / these): decoding step at
 // t = 511, d = 1024: B = 49 110 / 82, B = 64 120 / 87, B = 128 206 / 140, B = 256 407 / 225; B = 80: d = 768 99 / 80, d = 512 65 / 63,
-// d = 256 44 / 53; a position of the stack engine with one layer: B = 49 55 / 39, B = 128 64 / 46; B = 60: d = 512 35 / 29.
+// d = 256 44 / 53; (all before [Wq; Wk; Wv] and W1 got faster: now B = 200 161);
+// a position of the stack engine with one layer: B = 49 55 / 39, B = 128 64 / 46; B = 60: d = 512 35 / 29.
 // Up to 32 rows there are two tiles of 16 at most, and smaller batches mostly run on the single-launch engines.
 constexpr int kWideFrom = 33, kWideWidth = 512;
 constexpr size_t wide_lds_bytes(int NO) { return (size_t)2 * NO * (kWideWaves - 1) * 1024 + 4 * kWideBatch * 4; }
@@ -801,8 +817,14 @@ static void wide_launch(int n_out, unsigned nl, hipStream_t st, const WaveLayer 
 template <int EPI, int NO> static void step_wide_launch(const WaveLayer &Y, int n_out, const LayerDims &D, hipStream_t st)
 {
     const dim3 grid((unsigned)(n_out / (16 * NO)), 1, (unsigned)((D.B + kWideBatch - 1) / kWideBatch));
-    hipLaunchKernelGGL((step_wide_kernel<EPI, NO>), grid, dim3(64 * kWideWaves), wide_lds_bytes(NO), st, Y, D.B, D.d, D.F, D.H, D.eps,
-                       D.norm_free, D.alpha);
+    // Two groups ahead take 192 registers at NO = 4: one workgroup on a compute unit.  More workgroups than compute units share
+    // them two by two with one group ahead each (d = 1024, us, two groups / one: B = 200 W1 19.6 / 16.7, QKV 17.7 / 16.0).
+    if (NO == 4 && grid.x * grid.z > 256)
+        hipLaunchKernelGGL((step_wide_kernel<EPI, NO, 1>), grid, dim3(64 * kWideWaves), wide_lds_bytes(NO), st, Y, D.B, D.d, D.F,
+                           D.H, D.eps, D.norm_free, D.alpha);
+    else
+        hipLaunchKernelGGL((step_wide_kernel<EPI, NO, 2>), grid, dim3(64 * kWideWaves), wide_lds_bytes(NO), st, Y, D.B, D.d, D.F,
+                           D.H, D.eps, D.norm_free, D.alpha);
 }
 
 // The steps of one prefill.  The layers are dealt to W.n groups of consecutive layers, each group enqueued on its own
