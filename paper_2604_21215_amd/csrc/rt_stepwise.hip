@@ -244,11 +244,18 @@ __global__ __launch_bounds__(256) void row_rinv_kernel(const T *__restrict__ x, 
     if (m >= M) return;
     const T *xr = x + (size_t)(m / Nc) * x_bstride + (size_t)(n0 + m % Nc) * d;
     float ss = 0.f;
-    for (int k = 8 * lane; k < d; k += 512) {   // d is a multiple of eight: 16-byte loads (bf16, 131072 rows of 1024: 146 -> 56 us)
-        float v[8];
-        load8(xr + k, v);
+    if constexpr (sizeof(T) == 4) {   // rows of fp32 layers are narrow and few: the shorter sums per lane stay
+        for (int k = lane; k < d; k += 64) {
+            const float v = to_f32(xr[k]);
+            ss = fmaf(v, v, ss);
+        }
+    } else {
+        for (int k = 8 * lane; k < d; k += 512) {   // d is a multiple of eight: 16-byte loads (131072 rows of 1024: 146 -> 56 us)
+            float v[8];
+            load8(xr + k, v);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) ss = fmaf(v[e], v[e], ss);
+            for (int e = 0; e < 8; ++e) ss = fmaf(v[e], v[e], ss);
+        }
     }
     ss = wave_sum(ss);
     if (lane == 0) rinv[m] = norm_free ? 1.f : rsqrtf(ss / (float)d + eps);
