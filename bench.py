@@ -262,7 +262,8 @@ def main():
     traffic = measured_traffic(args.workload, engine)
     roofline = {
         "bound": "hbm",
-        "kernel": ("persistent_kernel (one launch per call; the call's two small pre-pass kernels are inside the timed events)"
+        "kernel": ("%s (one launch per call; the call's two small pre-pass kernels are inside the timed events)"
+                   % ("group_kernel" if p_min == 32 else "persistent_kernel")
                    if resident else "rt_layer_prefill (%s engine, all launches of one call)" % engine),
         "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
         "traffic": traffic["bytes"] if traffic else None, "traffic_source": traffic,

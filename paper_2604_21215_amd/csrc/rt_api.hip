@@ -219,12 +219,12 @@ static void fill_dims(LayerDims &D, const rt_config &cfg, int p_min)
 static rt_status stack_workspace(rt_ctx *c, int L, int chunk);
 // rt_layer_prefill for more rows than the single-launch engine stages.  Three ways, ms per call on MI355X at d = 1024, 512 positions
 // (in brackets d = 512, 128 positions), B = 33 / 48 / 64 / 96 / 128 / 160 / 192:
-//   chunks of 16 rows on that engine                22.6 / 23.5 / 31.4 / 47.0 / 62.6 / 78.3 / 94.0   (4.69 / 4.77 / 6.34 / 9.55 / 12.7 / 15.9 / 19.1)
+//   chunks of 16 rows on that engine                14.2 / 14.6                                     (2.94 / 2.97)
 //   one layer on the layer-wavefront engine         18.7 / 19.4 / 20.7 / 21.8 / 23.4 / 27.5 / 29.0   (3.56 / 3.62 / 3.63 / 3.83 / 4.00 / 4.15 / 4.33)
 //   one position of all sequences per step          26.1 / 26.5 / 27.0 / 27.9 / 28.8 / 29.6 / 30.7   (4.59 / 4.67 / 4.71 / 4.79 / 4.87 / 5.10 / 5.27)
 // The steps at once take over where the chunks fall behind them; the lines of the layer-wavefront engine were drawn with the kernels
-// before its products took 32 sequences per workgroup (49.2 ms at B = 160, chunks 23.6 at B = 48): with these it leads from 33 to
-// 192 rows.  The third row is with the products from LDS throughout (step_products in rt_parallel.hip takes them from 129 rows on).
+// before its products took 32 sequences per workgroup (49.2 ms at B = 160) and with chunks on all 256 workgroups (22.6 / 23.5 / 31.4 ms
+// at B = 33 / 48 / 64): now it leads from 49 to 192 rows.  The third row is with the products from LDS throughout (step_products in rt_parallel.hip takes them from 129 rows on).
 constexpr int kBatchedFrom = 81;
 constexpr int kWaveFrom = 49, kWaveTo = 128;
 

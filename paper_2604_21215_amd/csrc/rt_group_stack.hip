@@ -10,8 +10,8 @@
 // Why: the layer-wavefront engine streams every layer's 23 MB (d = 1024) from memory for every position, with five dependent launches
 // per position; here a layer's weights are read once per chunk and a position costs five exchanges.
 // Measured (ms per call, launches of rt_wavefront.hip / here): 12 layers, d = 1024, N = 4096, B = 4: 284 / 130; N = 1024, B = 8:
-// 112 / 63; N = 128, B = 3: 46 / 9.0; 2 layers, N = 1024, B = 2: 33.8 / 11.0.  Of a step of 128 positions (12 layers, B = 4) the loop
-// takes 1.17 ms, the GEMM ahead of it 74 us (87 with the gain applied to its input rows), the far tile 17.
+// 112 / 63; N = 128, B = 3: 46 / 9.0; 2 layers, N = 1024, B = 2: 33.8 / 11.0.  Of a step of 256 positions (12 layers, B = 4) the loop
+// takes 2.36 ms, the GEMM ahead of it 107 us (at 128 positions 74, and 87 with the gain applied to its input rows), the far tile 53.
 #include "rt_group.h"
 #include "rt_cross_tile.h"
 #include "rt_prepass_device.h"
