@@ -168,10 +168,12 @@ rt_status rt_decode_step_static(const rt_config *cfg, const rt_layer_weights *w,
  *   l + 1's input), K[l], V[l] [kv_cap, B, H, head_dim] rows 0..N-1 written.  No two of these tensors may overlap.
  *   chunk: power of two >= p_min (>= 64 with the MFMA kernels); 0 = 64.
  * Two forms.  bf16 with the MFMA kernels, p_min 32, d_model in {256, 512, 768, 1024}, d_hidden = 4 d_model, a device with 256 compute
- * units and up to eight sequences (up to sixteen for at most six layers): four layers at a time (two, one for more than four, eight
+ * units and up to sixteen sequences: four layers at a time (two, one for more than four, eight
  * sequences) with their weights on chip, one cooperative launch per step of a chunk whose length the call chooses (64 to 256
- * positions; `chunk` is checked and not used), on rt_config.stream alone.  Everything else, and RT_FLAG_ENGINE_STEPWISE: launches
- * per position that carry all layers.
+ * positions; `chunk` is checked and not used), on rt_config.stream alone.  Everything else, RT_FLAG_ENGINE_STEPWISE, and stacks so deep
+ * that the layers one after the other take longer (where their passes times N exceed 3.1 (N + 64 (L - 1)), at d_model 1024 4.4 times):
+ * launches per position that carry all layers.  Both forms feed their products bf16 head and remainder of each vector, and the
+ * weights as they are.
  * Unless rt_config.reserve_stack_layers reserved them at rt_create, the first call allocates one scratch set per layer
  * (RT_ERR_OOM if that fails); it is kept until rt_destroy and
  * reused by later calls with the same chunk and at most as many layers (another shape synchronises the stream

@@ -1008,7 +1008,7 @@ static rt_status stack_workspace(rt_ctx *c, int L, int chunk)
     c->stack_bytes = one * L + sizeof(WaveLayer) * L;
     c->stack_L = L;
     c->stack_chunk = chunk;
-    if (L >= 2 || cfg.max_batch <= kGroups * kGroupRows) (void)group_stack_create(c->group_stack, c->group, c->base, cfg.max_batch);   // without it: the layer-wavefront launches
+    if (L >= 2 || cfg.max_batch <= kGroups * kGroupRows) (void)group_stack_create(c->group_stack, c->group, c->base, cfg.device, cfg.max_batch);   // without it: the layer-wavefront launches
     return RT_OK;
 }
 

@@ -302,9 +302,6 @@ hipError_t step_qkv_mm(const LayerDims &D, const Weights &W, const Scratch &S, c
 hipError_t step_base_case_mm(const LayerDims &D, const Weights &W, const Scratch &S, const void *x_t, void *y_t, void *K_row,
                              void *V_row, hipStream_t st);
 
-// [Wq; Wk; Wv] with the columns multiplied by the attention gain, rounded once: out [3d][d]
-hipError_t scale_qkv_launch(const Weights &W, bf16_t *out, int d, hipStream_t st);
-
 // Whole-sequence evaluation when every key-value pair is known in advance (rt_parallel.hip): the recompute of a
 // layer from its input and output (Sec. 6.1) and the standard Transformer layer (Sec. 2.1).  bf16 + matrix cores.
 bool parallel_supported(const LayerDims &D, bool mfma_bf16);

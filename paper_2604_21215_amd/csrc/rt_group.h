@@ -42,6 +42,9 @@ struct GroupArgs {
     unsigned long long *bar;      // per group 16 words: [0] barrier counter, [8] abort word
     unsigned long long *words;    // exchange words, group_words() per group and parity
     size_t group_stride;          // words between two groups
+    // gains of RMS(h) and RMS(z) of each group's layer where they are not in the packed weights, or null (not in GroupWork: two more
+    // members there cost the kernels without them 1 %, by other register moves)
+    const bf16_t *gains[kGroups][2];
     unsigned long long *trace;    // optional: [2][trace_rows][16] wall-clock stamps
     int trace_rank, trace_rows;
     GroupWork w[kGroups];
@@ -68,9 +71,11 @@ rt_status group_create(GroupState &P, const rt_config &cfg, const LayerDims &D);
 void group_destroy(GroupState &P);
 size_t group_bytes(const GroupState &P);
 bool group_supported(const GroupState &P, const LayerDims &D);
-hipError_t group_pack(const LayerDims &D, const Weights &W, bf16_t *packed, hipStream_t st);
-// launches the loop for the work items in A.w (the other fields of A are filled here)
-rt_status group_launch(GroupState &P, const LayerDims &D, GroupArgs &A, hipStream_t st, std::string &err);
+// gains: W1 and [Wk; Wv] multiplied by g_mlp and g_kv
+hipError_t group_pack(const LayerDims &D, const Weights &W, bf16_t *packed, bool gains, hipStream_t st);
+// launches the loop for the work items in A.w (the other fields of A are filled here); hp: the kernels with head and remainder
+rt_status group_launch(GroupState &P, const LayerDims &D, GroupArgs &A, bool hp, hipStream_t st, std::string &err);
+bool group_stack_kernels(int device, const LayerDims &D);   // readies those
 rt_status group_prefill(GroupState &P, const LayerDims &D, const Weights &W, const Scratch &S, const void *x, void *y, void *K, void *V,
                         hipStream_t st, std::string &err);
 // A stack of layers on the same kernel (rt_group_stack.hip): the layers run concurrently, one group or two each, a chunk of
@@ -83,7 +88,7 @@ struct GroupStackState {
     float *far_m = nullptr, *far_l = nullptr, *far_o = nullptr;   // per running layer [kStackChunk][B H] ([64])
     float *pm = nullptr, *pl = nullptr, *po = nullptr;            // and the states of the blocks inside its chunk
 };
-rt_status group_stack_create(GroupStackState &T, const GroupState &P, const LayerDims &D, int max_batch);
+rt_status group_stack_create(GroupStackState &T, const GroupState &P, const LayerDims &D, int device, int max_batch);
 void group_stack_destroy(GroupStackState &T);
 bool group_stack_supported(const GroupStackState &T, const GroupState &P, const LayerDims &D, int L);
 rt_status group_stack_prefill(GroupStackState &T, GroupState &P, const LayerDims &D, const WaveLayer *layers, int L, bool poison,

@@ -69,11 +69,11 @@ constexpr int frags_all(int KSD) { return frags_o(KSD) + frags_1(KSD) + frags_2(
 
 // exchange words of one group and one parity
 struct GroupWords {
-    size_t a, h, u, z, kv, zss, all;
+    size_t a, h, u, z, kv, zss, hss, lo, all;   // lo: remainders of a, h, z, u, each so many words behind its heads
 };
-__host__ __device__ inline GroupWords group_words(int d)
+__host__ __device__ constexpr GroupWords group_words(int d, bool hp)
 {
-    GroupWords w;
+    GroupWords w = {};
     size_t o = 0;
     const size_t pair = (size_t)kGroupRows * d / 2;
     w.a = o; o += pair;
@@ -82,6 +82,10 @@ __host__ __device__ inline GroupWords group_words(int d)
     w.u = o; o += 4 * pair;
     w.kv = o; o += 4 * pair;
     w.zss = o; o += (size_t)kGroupRows * kGroupRanks;
+    if (hp) {
+        w.hss = o; o += (size_t)kGroupRows * kGroupRanks;
+        w.lo = o; o += 7 * pair;
+    }
     w.all = o;
     return w;
 }
@@ -115,8 +119,10 @@ __device__ __forceinline__ void pre_fetch(const GroupArgs &A, const GroupWork &W
     }
     slot[lane] = q; slot[64 + lane] = kt; slot[128 + lane] = vt;
 }
+// HP: with the full-precision exponential (the operands that follow keep 16 bits)
+template <bool HP> __device__ __forceinline__ float merge_exp(float x) { return HP ? expf(x) : __expf(x); }
 // the state of the query -> out: rows q, m, l, o
-template <bool ALIBI>
+template <bool ALIBI, bool HP>
 __device__ __forceinline__ void pre_merge(const GroupArgs &A, bool far, int t, int u, const float *slot, const float *wk, const bf16_t *wv, float *out,
                                           int lane)
 {
@@ -144,15 +150,15 @@ __device__ __forceinline__ void pre_merge(const GroupArgs &A, bool far, int t, i
         logit = valid ? (ALIBI ? fmaf(-alibi_slope(A.alibi, u % A.H, A.H), (float)(w + 2 - lane), s) : s) : -INFINITY;
         m = fmaxf(m, fast_max(logit));
     }
-    const float e0 = __expf(s0 - m);
+    const float e0 = merge_exp<HP>(s0 - m);
     float l = e0, o = slot[128 + lane] * e0;
     for (int i = 0; i < n; ++i) {
-        const float f = __expf(sm[i] - m);
+        const float f = merge_exp<HP>(sm[i] - m);
         l = fmaf(sl[i], f, l);
         o = fmaf(so[i * 64 + lane], f, o);
     }
     if (w > 0) {
-        const float p = __expf(logit - m);   // exp(-inf) = 0 for the lanes without a key
+        const float p = merge_exp<HP>(logit - m);   // exp(-inf) = 0 for the lanes without a key
         l += fast_sum(p);
         for (int j0 = 0; j0 < w; j0 += 8) {   // rows past the end are read from the last row with weight zero
             float vv[8];
@@ -228,7 +234,7 @@ __device__ __forceinline__ void window_block(const GroupArgs &A, const GroupWork
 
 // Dynamic LDS of the kernel, in bytes from its start.
 struct GroupLds {
-    int wo, wkv, red, sqh, xs, flag, win_k, win_v, pre, tiles, all;
+    int wo, wkv, red, sqh, xs, gain, flag, win_k, win_v, pre, tiles, all;
 };
 __host__ __device__ constexpr GroupLds group_lds(int KSD, int win_rows)
 {
@@ -239,6 +245,7 @@ __host__ __device__ constexpr GroupLds group_lds(int KSD, int win_rows)
     L.red = o; o += 2 * kPW * 256 * 4;
     L.sqh = o; o += kPW * kGroupRows * 4;
     L.xs = o; o += 16 * kGroupRows * 4;
+    L.gain = o; o += 2 * 16 * 4;
     L.flag = o; o += 16;
     L.win_k = o; o += win_rows * (kHeadDim + 4) * 4;
     L.win_v = o; o += win_rows * kHeadDim * 2;
@@ -255,8 +262,19 @@ __host__ __device__ constexpr GroupLds group_lds(int KSD, int win_rows)
         if (A.trace && wave == 0 && lane == 0 && grp == 0 && (rank == 0 || rank == A.trace_rank))                                     \
             A.trace[((size_t)(rank == 0 ? 0 : A.trace_rows) + t) * 16 + (k)] = wall_clock64();                          \
     } while (0)
-// KSD = d / 256; BM: sequences per group the exchanged vectors are laid out for (1, 2 or 4)
-template <int KSD, int BM, bool ALIBI>
+// Pair (v, vn) of the elements k, k + 1 as a word of heads and, lo words behind it, one of remainders.
+__device__ __forceinline__ void word_store_split(unsigned long long *base, unsigned idx, unsigned lo, unsigned tag, float v, float vn)
+{
+    const unsigned h = pack_bf16(v, vn);
+    word_store(base, idx, tag, h);
+    word_store(base, idx + lo, tag, pack_bf16(v - __uint_as_float(h << 16), vn - __uint_as_float(h & 0xFFFF0000u)));
+}
+
+// KSD = d / 256; BM: sequences per group the exchanged vectors are laid out for (1, 2 or 4).
+// HP: the inputs of the four products cross the chip as bf16 head and remainder (16 bits and more of each value), the gains are applied to
+// them and not to the weights, the mean square of h is that of the unrounded rows, gelu and the softmax use the exact functions - the
+// arithmetic of rt_wavefront.hip, for stacks.  Otherwise one bf16 per value and gains in the weights, as in rt_persistent.hip.
+template <int KSD, int BM, bool ALIBI, bool HP>
 __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
 {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -279,6 +297,7 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
     float *red0 = reinterpret_cast<float *>(smem + L.red), *red1 = red0 + kPW * 256;   // [kPW][64][4], phases in turn
     float *sqh = reinterpret_cast<float *>(smem + L.sqh);        // [kPW][4]
     float *xs = reinterpret_cast<float *>(smem + L.xs);          // [16][4]
+    float *gain_s = reinterpret_cast<float *>(smem + L.gain);    // [2][16] gains of the workgroup's rows of h and of z
     int *flag_s = reinterpret_cast<int *>(smem + L.flag);
     float *win_k = reinterpret_cast<float *>(smem + L.win_k);    // [win_rows][64 + 4] unrounded keys
     bf16_t *win_v = reinterpret_cast<bf16_t *>(smem + L.win_v);  // [win_rows][64]
@@ -288,7 +307,7 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
     G.spin_limit = A.spin_limit;
     G.bar = as_global(A.bar) + grp * 16;
     unsigned long long *words = as_global(A.words) + grp * A.group_stride;
-    const GroupWords X = group_words(d);
+    constexpr GroupWords X = group_words(d, HP);
 
     const uint4 *packed = reinterpret_cast<const uint4 *>(W.packed) + (size_t)rank * frags_all(KSD) * 64;
     const uint4 *p_1 = packed + (size_t)frags_o(KSD) * 64, *p_2 = p_1 + (size_t)frags_1(KSD) * 64;
@@ -300,6 +319,11 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
         for (int i = tid; i < frags_kv(KSD) * 64; i += kPThreads) dst[i] = p_kv[i];
     }
     if (tid == 0) flag_s[1] = 0;   // "a wavefront of this workgroup gave up waiting"
+    if (HP && tid < 2 * 16) {
+        const bf16_t *g = as_global(A.gains[grp][tid >> 4]);
+        const int r = tid & 15;
+        gain_s[tid] = g && r < RO ? bf16_to_f32(g[rank * RO + r]) : 1.f;
+    }
 
     const size_t rs = (size_t)A.BH * kHeadDim;
     const int units = B * A.H;                  // (sequence, head) pairs of the group; this workgroup owns number `rank`
@@ -317,7 +341,7 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
     if (is_helper) {
         pre_fetch(A, W, 0, ug, pre_in, lane);
         wave_sync_lds();
-        pre_merge<ALIBI>(A, far, 0, ug, pre_in, win_k, win_v, pre_s, lane);
+        pre_merge<ALIBI, HP>(A, far, 0, ug, pre_in, win_k, win_v, pre_s, lane);
     }
     __syncthreads();
 
@@ -343,7 +367,7 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
                 ll_t w3[3];
                 if (((t - 1) & (A.p_min - 1)) != 0) {   // key t - 2, the newest of the window
                     const float mn = fmaxf(m, s1);
-                    const float e1 = __expf(m - mn), e2 = __expf(s1 - mn);
+                    const float e1 = merge_exp<HP>(m - mn), e2 = merge_exp<HP>(s1 - mn);
                     l = l * e1 + e2;
                     o = o * e1 + v1 * e2;
                     m = mn;
@@ -361,17 +385,19 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
                 if (t < W.N) {   // the newest key is one position before the query
                     const float sn = ALIBI ? A.scale * (Sq * kscale) - alibi_slope(A.alibi, uh, A.H) : A.scale * (Sq * kscale);
                     const float m_new = fmaxf(m, sn);
-                    const float e1 = __expf(m - m_new), e2 = __expf(sn - m_new);
+                    const float e1 = merge_exp<HP>(m - m_new), e2 = merge_exp<HP>(sn - m_new);
                     l = l * e1 + e2;
                     o = o * e1 + bf16_to_f32(vb) * e2;
                 }
             }
             if (t < W.N) {
-                const float av = o * __builtin_amdgcn_rcpf(l);   // a crosses the chip as bf16
+                const float av = HP ? o / l : o * __builtin_amdgcn_rcpf(l);   // (one bf16: the rounding hides the reciprocal's)
                 const float an = dpp_odd_neighbour(av);
-                if (!(ln & 1))
-                    word_store(words + par * X.all + X.a, piece_word<8, BM>(uh * kHeadDim + ln, ub), tag,
-                             (unsigned)f32_to_bf16(av) | ((unsigned)f32_to_bf16(an) << 16));
+                if (!(ln & 1)) {
+                    const unsigned at = piece_word<8, BM>(uh * kHeadDim + ln, ub);
+                    if (HP) word_store_split(words + par * X.all + X.a, at, (unsigned)X.lo, tag, av, an);
+                    else word_store(words + par * X.all + X.a, at, tag, (unsigned)f32_to_bf16(av) | ((unsigned)f32_to_bf16(an) << 16));
+                }
             }
             // the rest follows a: only a is on the critical path of the position
             if (t >= 1) {
@@ -413,7 +439,7 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
         } else if (is_helper) {
             // (behind an event the stored states of the next query are complete only there)
             if ((t & (A.p_min - 1)) != 0 && t + 1 < W.N)
-                pre_merge<ALIBI>(A, far, t + 1, ug, pre_in + ((t + 1) & 1) * kPreSlot, win_k, win_v, pre_s + ppar * 256, ln);
+                pre_merge<ALIBI, HP>(A, far, t + 1, ug, pre_in + ((t + 1) & 1) * kPreSlot, win_k, win_v, pre_s + ppar * 256, ln);
         } else if (is_fetcher) {
             if ((t & (A.p_min - 1)) != 0 && ((t + 1) & (A.p_min - 1)) != 0 && t + 2 < W.N)
                 pre_fetch(A, W, t + 2, ug, pre_in + (t & 1) * kPreSlot, ln);
@@ -493,7 +519,7 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
         if (is_helper && t0 + 1 < W.N) {   // the stored states of the next queries are complete now
             pre_fetch(A, W, t0 + 1, ug, pre_in + ((t0 + 1) & 1) * kPreSlot, lane);
             wave_sync_lds();
-            pre_merge<ALIBI>(A, far, t0 + 1, ug, pre_in + ((t0 + 1) & 1) * kPreSlot, win_k, win_v, pre_s + ((t0 + 1) & 1) * 256, lane);
+            pre_merge<ALIBI, HP>(A, far, t0 + 1, ug, pre_in + ((t0 + 1) & 1) * kPreSlot, win_k, win_v, pre_s + ((t0 + 1) & 1) * 256, lane);
         } else if (is_fetcher && t0 + 2 < W.N) {
             pre_fetch(A, W, t0 + 2, ug, pre_in + (t0 & 1) * kPreSlot, lane);
         }
@@ -515,12 +541,17 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
                 for (int m = 0; m < CD; ++m)
 #pragma unroll
                     for (int j = 0; j < 2; ++j) w[m][j].u = lds_load16(wo_s + (m * 2 + j) * 64 + ln);
-                Piece act[CD];
-                slice_pull<CD, LD, 8, BM>(wp + X.a, wave, ln, B, tag, G, act, fail, A.sl_o);
+                Piece act[CD], rem[CD];
+                float none;
+                if constexpr (HP) slice_pull_split<CD, LD, 8, BM, false>(wp + X.a, (unsigned)X.lo, wp, wave, ln, B, tag, G, act, rem, none, fail, A.sl_o);
+                else slice_pull<CD, LD, 8, BM>(wp + X.a, wave, ln, B, tag, G, act, fail, A.sl_o);
                 RT_GROUP_STAMP(1);
                 f32x4_t acc[4] = {};
 #pragma unroll
-                for (int m = 0; m < CD; ++m) chunk_product4(act[m], w[m][0], w[m][1], acc);
+                for (int m = 0; m < CD; ++m) {
+                    chunk_product4(act[m], w[m][0], w[m][1], acc);
+                    if constexpr (HP) chunk_product4(rem[m], w[m][0], w[m][1], acc);
+                }
                 const f32x4_t s[1] = {(acc[0] + acc[1]) + (acc[2] + acc[3])};
                 tiles_store<1>(red0, wave, ln, s);
             }
@@ -529,17 +560,29 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
             float hv = 0.f;
             if (wave == 0) {
                 hv = xs[ln] + A.alpha * tile_sum(red0, ln);
-                const float hn = row_partner(hv);
-                if (e_own && !(erow & 1))
-                    word_store(wp + X.h, piece_word<1, BM>(rank * RO + erow, eb), tag, (unsigned)f32_to_bf16(hv) | ((unsigned)f32_to_bf16(hn) << 16));
+                const float hg = HP ? hv * gain_s[erow] : hv;
+                const float hn = row_partner(hg);
+                if (e_own && !(erow & 1)) {
+                    const unsigned at = piece_word<1, BM>(rank * RO + erow, eb);
+                    if (HP) word_store_split(wp + X.h, at, (unsigned)X.lo, tag, hg, hn);
+                    else word_store(wp + X.h, at, tag, (unsigned)f32_to_bf16(hg) | ((unsigned)f32_to_bf16(hn) << 16));
+                }
+                if (HP) {
+                    const float s = sum_mod4(e_own ? hv * hv : 0.f);
+                    if (ln < B) word_store(wp + X.hss, rank * BM + ln, tag, __float_as_uint(s));
+                }
             }
             RT_GROUP_STAMP(3);
             __syncthreads();
 
             // ============================================================ phase 1:  u = gelu(W1 h / rms(h))
             {
-                Piece act[CD];
-                slice_pull<CD, LD, 1, BM>(wp + X.h, wave, ln, B, tag, G, act, fail, A.sl_1);
+                Piece act[CD], rem[CD];
+                float ss = 0.f;   // |h|^2: the partial sums of its producers, or of the received values
+                if constexpr (HP)
+                    slice_pull_split<CD, LD, 1, BM, true>(wp + X.h, (unsigned)X.lo, wp + X.hss, wave, ln, B, tag, G, act, rem, ss, fail, A.sl_1);
+                else
+                    slice_pull<CD, LD, 1, BM>(wp + X.h, wave, ln, B, tag, G, act, fail, A.sl_1);
                 RT_GROUP_STAMP(4);
                 f32x4_t acc[KSD] = {};
 #pragma unroll
@@ -552,16 +595,21 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
                     for (int i = 0; i < KSD; ++i) acc[i] = mfma4<2>(act[m], w1[i][m][1].h[0], acc[i]);
 #pragma unroll
                     for (int i = 0; i < KSD; ++i) acc[i] = mfma4<3>(act[m], w1[i][m][1].h[1], acc[i]);
-                }
-                float ss = 0.f;   // |h|^2 of the received values
+                    if constexpr (HP) {
 #pragma unroll
-                for (int m = 0; m < CD; ++m) {
-                    const bf16x2_t p0 = __builtin_bit_cast(bf16x2_t, act[m].u.x), p1 = __builtin_bit_cast(bf16x2_t, act[m].u.y);
-                    ss = __builtin_amdgcn_fdot2_f32_bf16(p0, p0, ss, false);
-                    ss = __builtin_amdgcn_fdot2_f32_bf16(p1, p1, ss, false);
+                        for (int i = 0; i < KSD; ++i) acc[i] = chunk_product(rem[m], w1[i][m][0], w1[i][m][1], acc[i]);
+                    }
                 }
-                ss = sum_mod4(ss);
-                if (ln < 4) sqh[wave * 4 + ln] = ss;
+                if constexpr (!HP) {
+#pragma unroll
+                    for (int m = 0; m < CD; ++m) {
+                        const bf16x2_t p0 = __builtin_bit_cast(bf16x2_t, act[m].u.x), p1 = __builtin_bit_cast(bf16x2_t, act[m].u.y);
+                        ss = __builtin_amdgcn_fdot2_f32_bf16(p0, p0, ss, false);
+                        ss = __builtin_amdgcn_fdot2_f32_bf16(p1, p1, ss, false);
+                    }
+                    ss = sum_mod4(ss);
+                }
+                if (ln < (HP ? BM : 4)) sqh[wave * 4 + ln] = ss;
                 tiles_store<KSD>(red1, wave, ln, acc);
             }
             RT_GROUP_SYNC(fail);
@@ -572,10 +620,14 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
 #pragma unroll
                 for (int w = 0; w < kPW; ++w) s += sqh[w * 4 + b];
                 const float rinv = A.norm_free ? 1.f : rsqrtf(s / (float)d + A.eps);
-                const float uv = gelu_bf16_out(tile_sum(red1, tn) * rinv);   // u crosses the chip as bf16
+                const float pre = tile_sum(red1, tn) * rinv;
+                const float uv = HP ? gelu_erf(pre) : gelu_bf16_out(pre);
                 const float un = row_partner(uv);
-                if (!(row & 1) && b < B)
-                    word_store(wp + X.u, piece_word<1, BM>(rank * R1 + row, b), tag, (unsigned)f32_to_bf16(uv) | ((unsigned)f32_to_bf16(un) << 16));
+                if (!(row & 1) && b < B) {
+                    const unsigned at = piece_word<1, BM>(rank * R1 + row, b);
+                    if (HP) word_store_split(wp + X.u, at, (unsigned)X.lo, tag, uv, un);
+                    else word_store(wp + X.u, at, tag, (unsigned)f32_to_bf16(uv) | ((unsigned)f32_to_bf16(un) << 16));
+                }
             }
             RT_GROUP_STAMP(6);
             __syncthreads();
@@ -583,12 +635,17 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
 
             // ============================================================ phase 2:  z = h + alpha W2 u
             {
-                Piece act[CF];
-                slice_pull<CF, LF, 1, BM>(wp + X.u, wave, ln, B, tag, G, act, fail, A.sl_2);
+                Piece act[CF], rem[CF];
+                float none;
+                if constexpr (HP) slice_pull_split<CF, LF, 1, BM, false>(wp + X.u, (unsigned)X.lo, wp, wave, ln, B, tag, G, act, rem, none, fail, A.sl_2);
+                else slice_pull<CF, LF, 1, BM>(wp + X.u, wave, ln, B, tag, G, act, fail, A.sl_2);
                 RT_GROUP_STAMP(8);
                 f32x4_t acc[4] = {};
 #pragma unroll
-                for (int m = 0; m < CF; ++m) chunk_product4(act[m], w2[m][0], w2[m][1], acc);
+                for (int m = 0; m < CF; ++m) {
+                    chunk_product4(act[m], w2[m][0], w2[m][1], acc);
+                    if constexpr (HP) chunk_product4(rem[m], w2[m][0], w2[m][1], acc);
+                }
                 const f32x4_t s[1] = {(acc[0] + acc[1]) + (acc[2] + acc[3])};
                 tiles_store<1>(red0, wave, ln, s);
             }
@@ -596,9 +653,13 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
             RT_GROUP_STAMP(9);
             if (wave == 0) {
                 const float zv = hv + A.alpha * tile_sum(red0, ln);
-                const float zn = row_partner(zv);
-                if (e_own && !(erow & 1))   // the gain of RMS(z) is folded into the stationary Wk, Wv
-                    word_store(wp + X.z, piece_word<1, BM>(rank * RO + erow, eb), tag, (unsigned)f32_to_bf16(zv) | ((unsigned)f32_to_bf16(zn) << 16));
+                const float zg = HP ? zv * gain_s[16 + erow] : zv;   // (without HP the gain of RMS(z) is in the stationary Wk, Wv)
+                const float zn = row_partner(zg);
+                if (e_own && !(erow & 1)) {
+                    const unsigned at = piece_word<1, BM>(rank * RO + erow, eb);
+                    if (HP) word_store_split(wp + X.z, at, (unsigned)X.lo, tag, zg, zn);
+                    else word_store(wp + X.z, at, tag, (unsigned)f32_to_bf16(zg) | ((unsigned)f32_to_bf16(zn) << 16));
+                }
                 const float s = sum_mod4(e_own ? zv * zv : 0.f);
                 if (ln < B) word_store(wp + X.zss, rank * BM + ln, tag, __float_as_uint(s));
                 if (e_own) (W.y + (size_t)t * d)[(size_t)(W.b0 + W.bstep * eb) * A.rows * d + (unsigned)(rank * RO + erow)] = f32_to_bf16(zv);
@@ -615,14 +676,19 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
                     for (int m = 0; m < CD; ++m)
 #pragma unroll
                         for (int j = 0; j < 2; ++j) w[i][m][j].u = lds_load16(wkv_s + ((i * kPW * CD + m) * 2 + j) * 64 + ln);
-                Piece act[CD];
-                slice_pull<CD, LD, 1, BM>(wp + X.z, wave, ln, B, tag, G, act, fail, A.sl_kv);
+                Piece act[CD], rem[CD];
+                float none;
+                if constexpr (HP) slice_pull_split<CD, LD, 1, BM, false>(wp + X.z, (unsigned)X.lo, wp, wave, ln, B, tag, G, act, rem, none, fail, A.sl_kv);
+                else slice_pull<CD, LD, 1, BM>(wp + X.z, wave, ln, B, tag, G, act, fail, A.sl_kv);
                 RT_GROUP_STAMP(11);
                 f32x4_t acc[TKV] = {};
 #pragma unroll
                 for (int m = 0; m < CD; ++m)
 #pragma unroll
-                    for (int i = 0; i < TKV; ++i) acc[i] = chunk_product(act[m], w[i][m][0], w[i][m][1], acc[i]);
+                    for (int i = 0; i < TKV; ++i) {
+                        acc[i] = chunk_product(act[m], w[i][m][0], w[i][m][1], acc[i]);
+                        if constexpr (HP) acc[i] = chunk_product(rem[m], w[i][m][0], w[i][m][1], acc[i]);
+                    }
                 tiles_store<TKV>(red1, wave, ln, acc);
             }
             RT_GROUP_SYNC(fail);
@@ -642,7 +708,7 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
     RT_GROUP_SYNC(fail);
 }
 
-// The loop matrices in the fragment order above, gains folded in (W diag(g), rounded once).  Lane l of fragment (tile, wave,
+// The loop matrices in the fragment order above, with the gains given folded in (W diag(g), rounded once).  Lane l of fragment (tile, wave,
 // chunk m, j) holds W[row0 + 16 tile + l%16][k .. k + 3] and [k + 4 .. k + 7], k = wave * (K / 8) + 64 m + 16 (l/16) + 8 j;
 // rows beyond the workgroup's and indices beyond the wavefront's share are zero.
 __global__ __launch_bounds__(256) void group_pack_kernel(const bf16_t *Wo, const bf16_t *W1, const bf16_t *W2, const bf16_t *Wk,
@@ -698,22 +764,42 @@ __global__ void group_clear_kernel(unsigned long long *p, size_t n)
 }
 
 typedef void (*group_fn)(GroupArgs);
-template <int BM, bool ALIBI> static group_fn pick_width(int d)
+template <int BM, bool ALIBI, bool HP> static group_fn pick_width(int d)
 {
     switch (d) {
-    case 256: return group_kernel<1, BM, ALIBI>;
-    case 512: return group_kernel<2, BM, ALIBI>;
-    case 768: return group_kernel<3, BM, ALIBI>;
-    case 1024: return group_kernel<4, BM, ALIBI>;
+    case 256: return group_kernel<1, BM, ALIBI, HP>;
+    case 512: return group_kernel<2, BM, ALIBI, HP>;
+    case 768: return group_kernel<3, BM, ALIBI, HP>;
+    case 1024: return group_kernel<4, BM, ALIBI, HP>;
     default: return nullptr;
     }
 }
-static group_fn pick_kernel(int d, int BM, bool alibi)
+template <bool ALIBI, bool HP> static group_fn pick_rows(int d, int BM)
 {
-    if (BM == 1) return alibi ? pick_width<1, true>(d) : pick_width<1, false>(d);
-    if (BM == 2) return alibi ? pick_width<2, true>(d) : pick_width<2, false>(d);
-    return alibi ? pick_width<4, true>(d) : pick_width<4, false>(d);
+    return BM == 1 ? pick_width<1, ALIBI, HP>(d) : (BM == 2 ? pick_width<2, ALIBI, HP>(d) : pick_width<4, ALIBI, HP>(d));
 }
+static group_fn pick_kernel(int d, int BM, bool alibi, bool hp)
+{
+    if (hp) return alibi ? pick_rows<true, true>(d, BM) : pick_rows<false, true>(d, BM);
+    return alibi ? pick_rows<true, false>(d, BM) : pick_rows<false, false>(d, BM);
+}
+// LDS beyond the default, once per device and kernel: contexts are created often, and the call is not cheap
+static bool raise_lds(int device, int d, bool alibi, bool hp)
+{
+    static std::mutex mu;
+    static uint64_t raised[2][2][5] = {};   // a bit per device
+    std::lock_guard<std::mutex> lock(mu);
+    uint64_t &done = raised[hp][alibi][d / 256];
+    const uint64_t bit = 1ULL << (device & 63);
+    for (int BM = 1; BM <= kGroupRows && !(done & bit); BM *= 2)
+        if (hipFuncSetAttribute((const void *)pick_kernel(d, BM, alibi, hp), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+    done |= bit;
+    return true;
+}
+bool group_stack_kernels(int device, const LayerDims &D) { return raise_lds(device, D.d, D.alibi > 0.f, true); }
 
 size_t group_pack_elements(int d) { return (size_t)kGroupRanks * frags_all(d / 256) * 512; }
 
@@ -723,31 +809,18 @@ static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 rt_status group_create(GroupState &P, const rt_config &cfg, const LayerDims &D)
 {
     P.available = false;
-    if (cfg.dtype != RT_BF16 || (cfg.flags & RT_FLAG_NO_MFMA) || D.F != 4 * D.d || !pick_kernel(D.d, 1, false)) return RT_ERR_UNSUPPORTED;
+    if (cfg.dtype != RT_BF16 || (cfg.flags & RT_FLAG_NO_MFMA) || D.F != 4 * D.d || !pick_kernel(D.d, 1, false, false)) return RT_ERR_UNSUPPORTED;
     if (D.p_min != 32) return RT_ERR_UNSUPPORTED;   // a wider window does not fit beside the weights at every width
     P.win_rows = D.p_min;
     P.lds = (size_t)group_lds(D.d / 256, P.win_rows).all;
     if (P.lds > (size_t)160 * 1024) return RT_ERR_UNSUPPORTED;
-    {   // once per device and kernel: contexts are created often, and the call is not cheap
-        static std::mutex mu;
-        static uint64_t raised[2][5] = {};   // a bit per device
-        std::lock_guard<std::mutex> lock(mu);
-        uint64_t &done = raised[D.alibi > 0.f][D.d / 256];
-        const uint64_t bit = 1ULL << (cfg.device & 63);
-        for (int BM = 1; BM <= kGroupRows && !(done & bit); BM *= 2)
-            if (hipFuncSetAttribute((const void *)pick_kernel(D.d, BM, D.alibi > 0.f), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    160 * 1024) != hipSuccess) {
-                (void)hipGetLastError();
-                return RT_ERR_UNSUPPORTED;
-            }
-        done |= bit;
-    }
+    if (!raise_lds(cfg.device, D.d, D.alibi > 0.f, false)) return RT_ERR_UNSUPPORTED;
     const int most = kGroups * kGroupRows;
     P.max_batch = cfg.max_batch < most ? cfg.max_batch : most;
     size_t off = 0;
     auto carve = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
     const size_t o_bar = carve((size_t)kGroups * 16 * 8);
-    P.group_stride = align_up(2 * group_words(D.d).all, 32);
+    P.group_stride = align_up(2 * group_words(D.d, true).all, 32);
     const size_t o_w = carve(P.group_stride * kGroups * 8);
     P.exchange_bytes = off;
     const size_t o_p = carve(group_pack_elements(D.d) * 2);
@@ -791,17 +864,17 @@ bool group_supported(const GroupState &P, const LayerDims &D)
     return P.available && D.B <= P.max_batch && D.N >= 1 && D.N < (1 << 20) - 2;
 }
 
-hipError_t group_pack(const LayerDims &D, const Weights &W, bf16_t *packed, hipStream_t st)
+hipError_t group_pack(const LayerDims &D, const Weights &W, bf16_t *packed, bool gains, hipStream_t st)
 {
     const int KSD = D.d / 256;
     const long long frags = (long long)frags_all(KSD) * kGroupRanks;
     hipLaunchKernelGGL(group_pack_kernel, dim3((unsigned)((frags + 3) / 4)), dim3(256), 0, st, (const bf16_t *)W.Wo, (const bf16_t *)W.W1,
-                       (const bf16_t *)W.W2, (const bf16_t *)W.Wk, (const bf16_t *)W.Wv, D.norm_free ? nullptr : (const bf16_t *)W.g_mlp,
-                       D.norm_free ? nullptr : (const bf16_t *)W.g_kv, KSD, (uint4 *)packed);
+                       (const bf16_t *)W.W2, (const bf16_t *)W.Wk, (const bf16_t *)W.Wv, gains ? (const bf16_t *)W.g_mlp : nullptr,
+                       gains ? (const bf16_t *)W.g_kv : nullptr, KSD, (uint4 *)packed);
     return hipGetLastError();
 }
 
-rt_status group_launch(GroupState &P, const LayerDims &D, GroupArgs &A, hipStream_t st, std::string &err)
+rt_status group_launch(GroupState &P, const LayerDims &D, GroupArgs &A, bool hp, hipStream_t st, std::string &err)
 {
     A.d = D.d; A.H = D.H;
     A.p_min = D.p_min; A.log2_pmin = D.log2_pmin; A.win_rows = P.win_rows;
@@ -833,7 +906,7 @@ rt_status group_launch(GroupState &P, const LayerDims &D, GroupArgs &A, hipStrea
     e = hipGetLastError();
     if (e != hipSuccess) { err = std::string("group_clear_kernel: ") + hipGetErrorString(e); return RT_ERR_HIP; }
     void *args[] = {&A};
-    e = hipLaunchCooperativeKernel((const void *)pick_kernel(D.d, BM, D.alibi > 0.f), dim3(kGroups * kGroupRanks), dim3(kPThreads), args,
+    e = hipLaunchCooperativeKernel((const void *)pick_kernel(D.d, BM, D.alibi > 0.f, hp), dim3(kGroups * kGroupRanks), dim3(kPThreads), args,
                                    (unsigned int)P.lds, st);
     if (e != hipSuccess) { err = std::string("hipLaunchCooperativeKernel: ") + hipGetErrorString(e); return RT_ERR_HIP; }
     P.launched = true;
@@ -843,7 +916,7 @@ rt_status group_launch(GroupState &P, const LayerDims &D, GroupArgs &A, hipStrea
 rt_status group_prefill(GroupState &P, const LayerDims &D, const Weights &W, const Scratch &S, const void *x, void *y, void *K, void *V,
                         hipStream_t st, std::string &err)
 {
-    hipError_t e = group_pack(D, W, P.packed, st);
+    hipError_t e = group_pack(D, W, P.packed, !D.norm_free, st);
     if (e != hipSuccess) { err = std::string("group_pack_kernel: ") + hipGetErrorString(e); return RT_ERR_HIP; }
     GroupArgs A = {};
     A.rows = D.N; A.BH = D.B * D.H;
@@ -861,7 +934,7 @@ rt_status group_prefill(GroupState &P, const LayerDims &D, const Weights &W, con
         w.pm = S.pm; w.pl = S.pl; w.po = S.po;
         w.far_m = w.far_l = w.far_o = nullptr;
     }
-    return group_launch(P, D, A, st, err);
+    return group_launch(P, D, A, false, st, err);
 }
 
 int group_read_trace(GroupState &P, unsigned long long *out, int rows)

@@ -82,6 +82,22 @@ union WFrag {
     uint2 h[2];
 };
 
+// What the loads of a pull brought -> the A operands: with fewer than four batch rows by moves inside the four lanes of a block.
+template <int BM, int NC, int NL> __device__ __forceinline__ void rows_in_place(const v4u_t (&v)[NL], Piece (&act)[NC])
+{
+    constexpr int CPL = 4 / BM;
+#pragma unroll
+    for (int m = 0; m < NC; ++m) {
+        const unsigned lo = v[m / CPL][0], hi = v[m / CPL][2];
+        if (BM == 4) act[m].u = make_uint2(lo, hi);
+        else if (BM == 2) act[m].u = m & 1 ? make_uint2(quad_move<0xEE>(lo), quad_move<0xEE>(hi)) : make_uint2(lo, hi);
+        else if ((m & 3) == 0) act[m].u = make_uint2(lo, hi);
+        else if ((m & 3) == 1) act[m].u = make_uint2(quad_move<0x55>(lo), quad_move<0x55>(hi));
+        else if ((m & 3) == 2) act[m].u = make_uint2(quad_move<0xAA>(lo), quad_move<0xAA>(hi));
+        else act[m].u = make_uint2(quad_move<0xFF>(lo), quad_move<0xFF>(hi));
+    }
+}
+
 // This wavefront's share (NC chunks of 64 elements, LEN elements in all) of an exchanged vector of BM batch rows: act[m] of lane l
 // holds elements 64 m + 4 (l/4) .. + 3 of batch row l%4 % BM - the A operand of the product, nothing is staged in LDS.  With
 // fewer than four batch rows the lanes of the unused rows fetch the pieces of the chunks that follow, and a move inside the
@@ -114,15 +130,58 @@ __device__ __forceinline__ void slice_pull(const ll_t *vec, int wave, int lane, 
             if ((need & (1u << n)) && v[n][1] == tag && v[n][3] == tag) need &= ~(1u << n);
         if (++spins > A.spin_limit || ((spins & 255) == 0 && ll_load(A.bar + 8) != 0)) { fail = 1; break; }
     }
+    rows_in_place<BM, NC, NL>(v, act);
+}
+
+// The same for a vector of which bf16 heads and bf16 remainders are exchanged (the remainders lie lo_words behind the heads), and,
+// with SUMS, the producers' partial sums of squares: 64 words of each batch row, of which this wavefront takes eight; lanes below
+// BM hold their sum.
+template <int NC, int LEN, int RUN, int BM, bool SUMS>
+__device__ __forceinline__ void slice_pull_split(const ll_t *vec, unsigned lo_words, const ll_t *sums, int wave, int lane, int B, unsigned tag,
+                                                 const GroupWait &A, Piece (&hi)[NC], Piece (&lo)[NC], float &ss, int &fail, int units)
+{
+    constexpr int CPL = 4 / BM;
+    constexpr int NL = (NC + CPL - 1) / CPL;
+    const int lo_off = (int)(lo_words * 8u);
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<ll_t *>(vec) + (size_t)wave * (LEN * BM / 2), 0,
+                                                                          lo_off + LEN * BM * 4, 0x00020000);
+    v4u_t vh[NL], vl[NL];
+    ll_t sw = 0;
+    const int b = lane & (BM - 1), p0 = (lane >> 2) + 16 * ((lane & 3) / BM);
+    const int off0 = ((p0 / RUN * BM + b) * RUN + p0 % RUN) * 16;
+    const ll_t *sp = sums + (wave * 8 * BM + (lane & (8 * BM - 1)));
+    unsigned need = 0;
 #pragma unroll
-    for (int m = 0; m < NC; ++m) {
-        const unsigned lo = v[m / CPL][0], hi = v[m / CPL][2];
-        if (BM == 4) act[m].u = make_uint2(lo, hi);
-        else if (BM == 2) act[m].u = m & 1 ? make_uint2(quad_move<0xEE>(lo), quad_move<0xEE>(hi)) : make_uint2(lo, hi);
-        else if ((m & 3) == 0) act[m].u = make_uint2(lo, hi);
-        else if ((m & 3) == 1) act[m].u = make_uint2(quad_move<0x55>(lo), quad_move<0x55>(hi));
-        else if ((m & 3) == 2) act[m].u = make_uint2(quad_move<0xAA>(lo), quad_move<0xAA>(hi));
-        else act[m].u = make_uint2(quad_move<0xFF>(lo), quad_move<0xFF>(hi));
+    for (int n = 0; n < NL; ++n) {
+        vh[n] = vl[n] = v4u_t{0u, 0u, 0u, 0u};
+        if (b < B && ((n + 1) * 64 * CPL <= LEN || n * 64 * CPL + 4 * p0 < LEN)) need |= 0x10001u << n;
+    }
+    if (SUMS && lane < 8 * BM && b < B) need |= 0x8000u;
+    static_assert(NL <= 15, "bit 15 is the sums'");
+    long long spins = 0;
+    for (int i = 0; i < units; ++i) __builtin_amdgcn_s_sleep(4);
+    while (__any(need != 0)) {
+#pragma unroll
+        for (int n = 0; n < NL; ++n) {
+            if (need & (1u << n)) vh[n] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off0 + n * 1024, 0, kAuxAgent);
+            if (need & (0x10000u << n)) vl[n] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, off0 + n * 1024, lo_off, kAuxAgent);
+        }
+        if (SUMS && (need & 0x8000u)) sw = ll_load(sp);
+#pragma unroll
+        for (int n = 0; n < NL; ++n) {
+            if ((need & (1u << n)) && vh[n][1] == tag && vh[n][3] == tag) need &= ~(1u << n);
+            if ((need & (0x10000u << n)) && vl[n][1] == tag && vl[n][3] == tag) need &= ~(0x10000u << n);
+        }
+        if (SUMS && (need & 0x8000u) && (unsigned)(sw >> 32) == tag) need &= ~0x8000u;
+        if (++spins > A.spin_limit || ((spins & 255) == 0 && ll_load(A.bar + 8) != 0)) { fail = 1; break; }
+    }
+    rows_in_place<BM, NC, NL>(vh, hi);
+    rows_in_place<BM, NC, NL>(vl, lo);
+    if (SUMS) {
+        ss = lane < 8 * BM && b < B ? __uint_as_float((unsigned)sw) : 0.f;
+        ss += __shfl_xor(ss, BM, 64);
+        ss += __shfl_xor(ss, 2 * BM, 64);
+        ss += __shfl_xor(ss, 4 * BM, 64);
     }
 }
 template <int J> __device__ __forceinline__ f32x4_t mfma4(const Piece &a, const uint2 &w, f32x4_t c)

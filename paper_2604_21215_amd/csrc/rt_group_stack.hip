@@ -9,9 +9,12 @@
 //
 // Why: the layer-wavefront engine streams every layer's 23 MB (d = 1024) from memory for every position, with five dependent launches
 // per position; here a layer's weights are read once per chunk and a position costs five exchanges.
-// Measured (ms per call, launches of rt_wavefront.hip / here): 12 layers, d = 1024, N = 4096, B = 4: 284 / 130; N = 1024, B = 8:
-// 112 / 63; N = 128, B = 3: 46 / 9.0; 2 layers, N = 1024, B = 2: 33.8 / 11.0.  Of a step of 256 positions (12 layers, B = 4) the loop
-// takes 2.36 ms, the GEMM ahead of it 107 us (at 128 positions 74, and 87 with the gain applied to its input rows), the far tile 53.
+// The vectors are exchanged as bf16 head and remainder (group_kernel's HP form): the arithmetic of the launches, whose products take
+// theirs that way.  With one bf16 per value, as rt_layer_prefill has it, the listed call below took 130 ms, and its first layer's keys
+// and values were 3.0e-3 of their norm from fp64; the launches 1.73e-3, this form 1.73e-3 (storage alone: 1.67e-3).
+// Measured (ms per call, launches of rt_wavefront.hip / here): 12 layers, d = 1024, N = 4096, B = 4: 284 / 161; N = 1024, B = 8:
+// 112 / 78; N = 128, B = 3: 29.5 / 11.2; 2 layers, N = 1024, B = 2: 33.7 / 13.8.  A position takes 10.9 us in the loop (d = 1024, four
+// sequences per group), 1.6 of it for u (128 KB) to arrive.
 #include "rt_group.h"
 #include "rt_cross_tile.h"
 #include "rt_prepass_device.h"
@@ -85,9 +88,10 @@ static int splits_for(int B, int L)
 
 static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
-rt_status group_stack_create(GroupStackState &T, const GroupState &P, const LayerDims &D, int max_batch)
+rt_status group_stack_create(GroupStackState &T, const GroupState &P, const LayerDims &D, int device, int max_batch)
 {
     if (T.slab || !P.available) return RT_OK;
+    if (!group_stack_kernels(device, D)) return RT_ERR_UNSUPPORTED;
     // states of the layers that run at once: at most four sequences of each group
     const int most = kGroups * kGroupRows;
     const size_t BH = (size_t)(4 * max_batch < most ? 4 * max_batch : most) * D.H;
@@ -119,11 +123,16 @@ void group_stack_destroy(GroupStackState &T)
 
 bool group_stack_supported(const GroupStackState &T, const GroupState &P, const LayerDims &D, int L)
 {
-    // One to eight sequences run four or two layers at once and win at every depth that was measured (2 to 12 layers, d = 256 to
-    // 1024, N = 128 to 4096: 1.05 to 4 times; 0.98 at d = 768, B = 5, N = 4096).  Nine to sixteen run one layer at a time, its N positions
-    // against (N + 64 (L - 1)) steps of the launches, whose cost grows slowly with the layers: N = 1024, 4 layers, d = 1024 41 / 80 ms,
-    // 6 layers at N = 4096, d = 512 193 / 224, but 12 layers at N = 1024, d = 512 92 / 82.
-    return T.slab && P.available && D.B <= kGroups * kGroupRows && (D.B <= 2 * kGroupRows || L <= 6) && D.N < (1 << 20) - 2;
+    // ceil(L / slots) N positions here against N + 64 (L - 1) steps of the launches, which carry all layers: a position costs 9 to
+    // 12.5 us (d = 256 to 1024), a step 28 us and more, with d = 1024 from 50 us where the ratio of the two counts is large (twelve
+    // layers, or nine sequences and more).  Measured, launches / here, by that ratio (B = 1 .. 16, L = 1 .. 24, N = 128 .. 4096):
+    //   d < 1024: up to 2.9 1.22 - 3.2 times, 3.28 1.08 - 1.32, 3.4 - 3.7 0.93 - 1.24, 3.9 - 5.6 0.76 - 1.03
+    //   d = 1024: up to 3.5 1.21 - 4.0, 4.4 - 5.2 0.99 - 1.16
+    // (0.76: d = 768, B = 5, N = 4096, 12 layers, 208.6 / 275.3 ms; 4.0: one layer, B = 16, N = 2048, 101.9 / 25.4 ms.)
+    if (!T.slab || !P.available || D.B > kGroups * kGroupRows || D.N >= (1 << 20) - 2) return false;
+    const int slots = kGroups / splits_for(D.B, L);
+    const long long here = (long long)((L + slots - 1) / slots) * D.N, steps = D.N + 64LL * (L - 1);
+    return 10 * here <= (D.d == 1024 ? 44 : 31) * steps;
 }
 
 rt_status group_stack_prefill(GroupStackState &T, GroupState &P, const LayerDims &D, const WaveLayer *layers, int L, bool poison,
@@ -161,17 +170,9 @@ rt_status group_stack_prefill(GroupStackState &T, GroupState &P, const LayerDims
             const int l = act[i], slot = l % slots, t0 = done[l] * C;
             const int n = D.N - t0 < C ? D.N - t0 : C;
             const WaveLayer &Y = layers[l];
-            if (done[l] == 0 && (e = group_pack(D, Y.W, T.packed[slot], st)) != hipSuccess) return hip_fail(e, "group_pack_kernel");
+            if (done[l] == 0 && (e = group_pack(D, Y.W, T.packed[slot], false, st)) != hipSuccess) return hip_fail(e, "group_pack_kernel");
             StackEntry E;
             E.W = Y.W;
-            if (l > 0 && Y.W.g_attn && !D.norm_free) {
-                // the gain goes into copies of the matrices, once per layer: applied to the input rows it was most of the vector work
-                // of the chunk's GEMM
-                if (t0 == 0 && (e = scale_qkv_launch(Y.W, Y.S.wg_qkv, D.d, st)) != hipSuccess) return hip_fail(e, "scale_qkv_columns_kernel");
-                const size_t dd = (size_t)D.d * D.d;
-                E.W.Wq = Y.S.wg_qkv; E.W.Wk = Y.S.wg_qkv + dd; E.W.Wv = Y.S.wg_qkv + 2 * dd;
-                E.W.g_attn = nullptr;
-            }
             E.x = (const bf16_t *)Y.x; E.K = (const bf16_t *)Y.K;
             E.Q = (bf16_t *)Y.S.Q; E.Kt = (bf16_t *)Y.S.Kt; E.Vt = (bf16_t *)Y.S.Vt; E.Qf = Y.S.Qf; E.Ktf = Y.S.Ktf;
             E.Kh = (const bf16_t *)Y.S.Kh; E.VT = Y.S.VT;
@@ -187,6 +188,8 @@ rt_status group_stack_prefill(GroupStackState &T, GroupState &P, const LayerDims
                 w.N = n; w.b0 = s; w.bstep = splits;
                 w.packed = T.packed[slot];
                 w.g_k = (const bf16_t *)Y.W.g_k;
+                A.gains[slot * splits + s][0] = D.norm_free ? nullptr : (const bf16_t *)Y.W.g_mlp;
+                A.gains[slot * splits + s][1] = D.norm_free ? nullptr : (const bf16_t *)Y.W.g_kv;
                 w.x = (const bf16_t *)Y.x + (size_t)t0 * D.d;
                 w.y = (bf16_t *)Y.y + (size_t)t0 * D.d;
                 w.K = (bf16_t *)Y.K + row; w.V = (bf16_t *)Y.V + row;
@@ -212,7 +215,7 @@ rt_status group_stack_prefill(GroupStackState &T, GroupState &P, const LayerDims
                 hipLaunchKernelGGL(group_stack_far_kernel<false>, grid, dim3(256), 0, st, far, BH, nqb, A.vt_stride, D.scale, D.alibi, D.H);
             if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "group_stack_far_kernel");
         }
-        const rt_status s = group_launch(P, D, A, st, err);
+        const rt_status s = group_launch(P, D, A, true, st, err);
         if (s != RT_OK) return s;
         for (int i = 0; i < n_act; ++i) ++done[act[i]];
     }

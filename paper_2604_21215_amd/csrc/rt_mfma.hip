@@ -133,7 +133,7 @@ __global__ __launch_bounds__(256) void scale_qkv_columns_kernel(const bf16_t *__
                    pack_bf16(w[4] * gg[4], w[5] * gg[5]), pack_bf16(w[6] * gg[6], w[7] * gg[7]));
 }
 
-hipError_t scale_qkv_launch(const Weights &W, bf16_t *out, int d, hipStream_t st)
+static hipError_t scale_qkv_launch(const Weights &W, bf16_t *out, int d, hipStream_t st)
 {
     const size_t pieces = 3 * (size_t)d * d / 8;
     hipLaunchKernelGGL(scale_qkv_columns_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st, (const bf16_t *)W.Wq,

@@ -7,7 +7,7 @@
 // the small-M products of the base case then move L times the weight bytes per launch, which is what
 // they need to come near the memory rate.
 //
-// Up to sixteen bf16 sequences the layers run on groups of workgroups that hold a layer's weights instead (rt_group_stack.hip).
+// Up to sixteen bf16 sequences most stacks run on groups of workgroups that hold a layer's weights instead (rt_group_stack.hip).
 //
 // Schedule.  Layer l runs C positions (one "chunk", a power of two) behind layer l - 1: at step s it
 // works on position t = s - l * C.  When it enters a chunk, the layer below has finished that chunk, so
