@@ -285,7 +285,7 @@ const char *rt_status_string(rt_status s);
 uint64_t rt_workspace_bytes(const rt_ctx *ctx);
 
 /* After the stream has been synchronised: 0 if every bounded device-side wait of the last call on
- * this context completed, non-zero if one expired (the call's outputs are then invalid). */
+ * this context completed, in all of the call's launches, non-zero if one expired (the call's outputs are then invalid). */
 int32_t rt_device_wait_expired(rt_ctx *ctx);
 
 /* Name of the engine the last prefill call on this context used: "stepwise", "stepwise+graph",

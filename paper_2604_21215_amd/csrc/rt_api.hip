@@ -624,11 +624,12 @@ static rt_status prefill_stepwise(rt_ctx *c, const LayerDims &D, const rt_layer_
 }
 
 // the sequential loop as one launch: by groups of workgroups where that form covers the shape
-static rt_status single_launch_prefill(rt_ctx *c, const LayerDims &D, const Weights &W, const void *x, void *y, void *K, void *V,
+// (first: the call's first chunk of rows)
+static rt_status single_launch_prefill(rt_ctx *c, const LayerDims &D, const Weights &W, const void *x, void *y, void *K, void *V, bool first,
                                        std::string &err)
 {
-    if (group_supported(c->group, D)) return group_prefill(c->group, D, W, c->S, x, y, K, V, c->stream, err);
-    return persistent_prefill(c->persist, D, W, c->S, x, y, K, V, c->stream, err);
+    if (group_supported(c->group, D)) return group_prefill(c->group, D, W, c->S, x, y, K, V, first, c->stream, err);
+    return persistent_prefill(c->persist, D, W, c->S, x, y, K, V, first, c->stream, err);
 }
 
 extern "C" rt_status rt_layer_prefill(rt_ctx *c, const rt_layer_weights *w, const void *x, int32_t B, int32_t N, void *y,
@@ -675,7 +676,7 @@ extern "C" rt_status rt_layer_prefill(rt_ctx *c, const rt_layer_weights *w, cons
         else e = Launch<float>::prepass(D, W, c->S, x, B, N, false, c->stream);
         if (e != hipSuccess) return fail_hip(c, e, "prepass");
         std::string perr;
-        s = single_launch_prefill(c, D, W, x, y, K, V, perr);
+        s = single_launch_prefill(c, D, W, x, y, K, V, true, perr);
         if (s != RT_OK) { c->err = perr; if (s == RT_ERR_HIP) c->broken = true; }
         return s;
     }
@@ -717,7 +718,7 @@ extern "C" rt_status rt_layer_prefill(rt_ctx *c, const rt_layer_weights *w, cons
             hipError_t e = Launch<bf16_t>::prepass(Dc, W, c->S, xc, nb, N, c->use_mfma, c->stream);
             if (e != hipSuccess) return fail_hip(c, e, "prepass");
             std::string perr;
-            s = single_launch_prefill(c, Dc, W, xc, yc, Kc, Vc, perr);
+            s = single_launch_prefill(c, Dc, W, xc, yc, Kc, Vc, b0 == 0, perr);
             if (s != RT_OK) { c->err = perr; if (s == RT_ERR_HIP) c->broken = true; return s; }
             RT_TRY(hipMemcpy2DAsync((char *)K + (size_t)b0 * row, (size_t)B * row, Kc, (size_t)nb * row, (size_t)nb * row, (size_t)N,
                                     hipMemcpyDeviceToDevice, c->stream), "hipMemcpy2DAsync");

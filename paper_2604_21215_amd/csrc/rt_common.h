@@ -1,5 +1,7 @@
 // Shared device helpers and the internal launch interface of the RT layer library (gfx950 only).
 #pragma once
+#include <cstdlib>
+#include <cstring>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -225,6 +227,27 @@ struct PrepassPairs {
     bf16_t *Klo;
     uint16_t *Kh;
     bool pairs_only;   // no queries are wanted
+};
+
+// Polls after which a device-side wait gives up.  RT_SPIN_LIMIT at rt_create: n, or n:k for the first k launches of the context only
+// (tests of a wait that expires in one launch of many).
+struct SpinLimit {
+    static constexpr long long kDefault = 1LL << 21;
+    long long limit = kDefault;
+    int left = -1;   // launches that `limit` still applies to, all if negative
+    void read()
+    {
+        const char *s = getenv("RT_SPIN_LIMIT"), *k = s ? strchr(s, ':') : nullptr;
+        limit = s ? atoll(s) : kDefault;
+        if (limit < 1) limit = 1;
+        left = k ? atoi(k + 1) : -1;
+    }
+    long long of_launch()
+    {
+        if (left == 0) return kDefault;
+        if (left > 0) --left;
+        return limit;
+    }
 };
 
 // ---------------------------------------------------------------- launchers (one per kernel family)

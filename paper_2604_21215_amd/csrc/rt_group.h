@@ -57,7 +57,7 @@ struct GroupState {
     unsigned long long *bar = nullptr, *words = nullptr;
     bf16_t *packed = nullptr;     // one layer's weights in fragment order
     size_t group_stride = 0;
-    long long spin_limit = 0;
+    SpinLimit spin;
     unsigned nonce = 0;
     int max_batch = 0;            // sequences one launch takes (all groups)
     int win_rows = 0;
@@ -73,11 +73,12 @@ size_t group_bytes(const GroupState &P);
 bool group_supported(const GroupState &P, const LayerDims &D);
 // gains: W1 and [Wk; Wv] multiplied by g_mlp and g_kv
 hipError_t group_pack(const LayerDims &D, const Weights &W, bf16_t *packed, bool gains, hipStream_t st);
-// launches the loop for the work items in A.w (the other fields of A are filled here); hp: the kernels with head and remainder
-rt_status group_launch(GroupState &P, const LayerDims &D, GroupArgs &A, bool hp, hipStream_t st, std::string &err);
+// launches the loop for the work items in A.w (the other fields of A are filled here); hp: the kernels with head and remainder;
+// first: the first launch of a call, which alone clears the abort words
+rt_status group_launch(GroupState &P, const LayerDims &D, GroupArgs &A, bool hp, bool first, hipStream_t st, std::string &err);
 bool group_stack_kernels(int device, const LayerDims &D);   // readies those
 rt_status group_prefill(GroupState &P, const LayerDims &D, const Weights &W, const Scratch &S, const void *x, void *y, void *K, void *V,
-                        hipStream_t st, std::string &err);
+                        bool first, hipStream_t st, std::string &err);
 // A stack of layers on the same kernel (rt_group_stack.hip): the layers run concurrently, one group or two each, a chunk of
 // positions apart.
 constexpr int kStackChunk = 256;       // positions of a chunk at most

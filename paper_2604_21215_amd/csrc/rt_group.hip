@@ -318,7 +318,8 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
         dst = reinterpret_cast<uint4 *>(smem + L.wkv);
         for (int i = tid; i < frags_kv(KSD) * 64; i += kPThreads) dst[i] = p_kv[i];
     }
-    if (tid == 0) flag_s[1] = 0;   // "a wavefront of this workgroup gave up waiting"
+    // "a wavefront of this workgroup gave up waiting", or (stacks, many launches) a wait of this group expired earlier in the call
+    if (tid == 0) flag_s[1] = HP ? ll_load(G.bar + 8) != 0 : 0;
     if (HP && tid < 2 * 16) {
         const bf16_t *g = as_global(A.gains[grp][tid >> 4]);
         const int r = tid & 15;
@@ -338,6 +339,7 @@ __global__ __launch_bounds__(kPThreads) void group_kernel(GroupArgs A)
     float s1 = 0.f, v1 = 0.f;
 
     __syncthreads();
+    if (HP && flag_s[1] != 0) return;   // the whole workgroup
     if (is_helper) {
         pre_fetch(A, W, 0, ug, pre_in, lane);
         wave_sync_lds();
@@ -757,10 +759,12 @@ __global__ __launch_bounds__(256) void group_pack_kernel(const bf16_t *Wo, const
 // =============================================================================================
 // Host side
 // =============================================================================================
-// a captured stream must not record memset nodes: words are cleared with a kernel
-__global__ void group_clear_kernel(unsigned long long *p, size_t n)
+// a captured stream must not record memset nodes: words are cleared with a kernel.  The groups' abort words among the first
+// counters are kept between the launches of a call: they say that one of its waits expired.
+__global__ void group_clear_kernel(unsigned long long *p, size_t n, size_t counters, int keep_abort)
 {
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0ULL;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
+        if (!(keep_abort && i < counters && (i & 15) == 8)) p[i] = 0ULL;
 }
 
 typedef void (*group_fn)(GroupArgs);
@@ -843,9 +847,7 @@ rt_status group_create(GroupState &P, const rt_config &cfg, const LayerDims &D)
     P.packed = (bf16_t *)(p + o_p);
     P.trace = want_trace ? (unsigned long long *)(p + o_tr) : nullptr;
     P.trace_rows = want_trace ? cfg.max_seq : 0;
-    const char *sl = getenv("RT_SPIN_LIMIT");
-    P.spin_limit = sl ? atoll(sl) : (1LL << 21);
-    if (P.spin_limit < 1) P.spin_limit = 1;
+    P.spin.read();
     P.available = true;
     return RT_OK;
 }
@@ -874,12 +876,12 @@ hipError_t group_pack(const LayerDims &D, const Weights &W, bf16_t *packed, bool
     return hipGetLastError();
 }
 
-rt_status group_launch(GroupState &P, const LayerDims &D, GroupArgs &A, bool hp, hipStream_t st, std::string &err)
+rt_status group_launch(GroupState &P, const LayerDims &D, GroupArgs &A, bool hp, bool first, hipStream_t st, std::string &err)
 {
     A.d = D.d; A.H = D.H;
     A.p_min = D.p_min; A.log2_pmin = D.log2_pmin; A.win_rows = P.win_rows;
     A.alpha = D.alpha; A.scale = D.scale; A.eps = D.eps; A.alibi = D.alibi; A.norm_free = D.norm_free;
-    A.spin_limit = P.spin_limit; A.bar = P.bar; A.words = P.words; A.group_stride = P.group_stride;
+    A.spin_limit = P.spin.of_launch(); A.bar = P.bar; A.words = P.words; A.group_stride = P.group_stride;
     A.trace = P.trace; A.trace_rows = P.trace_rows;
     const char *tw = getenv("RT_PERSIST_TRACE_WG");
     A.trace_rank = tw ? atoi(tw) : kGroupRanks - 1;
@@ -902,7 +904,8 @@ rt_status group_launch(GroupState &P, const LayerDims &D, GroupArgs &A, bool hp,
     if (!captured) P.nonce = (P.nonce % 4094u) + 1u;
     A.tag_base = (captured ? 4095u : P.nonce) << 20;
     const bool all = captured || (P.nonce == 1u && P.launched);
-    hipLaunchKernelGGL(group_clear_kernel, dim3(all ? 256 : 1), dim3(256), 0, st, P.bar, all ? P.exchange_bytes / 8 : (size_t)kGroups * 16);
+    hipLaunchKernelGGL(group_clear_kernel, dim3(all ? 256 : 1), dim3(256), 0, st, P.bar, all ? P.exchange_bytes / 8 : (size_t)kGroups * 16,
+                       (size_t)kGroups * 16, first ? 0 : 1);
     e = hipGetLastError();
     if (e != hipSuccess) { err = std::string("group_clear_kernel: ") + hipGetErrorString(e); return RT_ERR_HIP; }
     void *args[] = {&A};
@@ -914,7 +917,7 @@ rt_status group_launch(GroupState &P, const LayerDims &D, GroupArgs &A, bool hp,
 }
 
 rt_status group_prefill(GroupState &P, const LayerDims &D, const Weights &W, const Scratch &S, const void *x, void *y, void *K, void *V,
-                        hipStream_t st, std::string &err)
+                        bool first, hipStream_t st, std::string &err)
 {
     hipError_t e = group_pack(D, W, P.packed, !D.norm_free, st);
     if (e != hipSuccess) { err = std::string("group_pack_kernel: ") + hipGetErrorString(e); return RT_ERR_HIP; }
@@ -934,7 +937,7 @@ rt_status group_prefill(GroupState &P, const LayerDims &D, const Weights &W, con
         w.pm = S.pm; w.pl = S.pl; w.po = S.po;
         w.far_m = w.far_l = w.far_o = nullptr;
     }
-    return group_launch(P, D, A, false, st, err);
+    return group_launch(P, D, A, false, first, st, err);
 }
 
 int group_read_trace(GroupState &P, unsigned long long *out, int rows)

@@ -10,7 +10,7 @@
 // Why: the layer-wavefront engine streams every layer's 23 MB (d = 1024) from memory for every position, with five dependent launches
 // per position; here a layer's weights are read once per chunk and a position costs five exchanges.
 // The vectors are exchanged as bf16 head and remainder (group_kernel's HP form): the arithmetic of the launches, whose products take
-// theirs that way.  With one bf16 per value, as rt_layer_prefill has it, the listed call below took 130 ms, and its first layer's keys
+// theirs that way.  With one bf16 per value, as rt_layer_prefill has it, the first call below took 130 ms, and its first layer's keys
 // and values were 3.0e-3 of their norm from fp64; the launches 1.73e-3, this form 1.73e-3 (storage alone: 1.67e-3).
 // Measured (ms per call, launches of rt_wavefront.hip / here): 12 layers, d = 1024, N = 4096, B = 4: 284 / 161; N = 1024, B = 8:
 // 112 / 78; N = 128, B = 3: 29.5 / 11.2; 2 layers, N = 1024, B = 2: 33.7 / 13.8.  A position takes 10.9 us in the loop (d = 1024, four
@@ -156,6 +156,7 @@ rt_status group_stack_prefill(GroupStackState &T, GroupState &P, const LayerDims
     hipError_t e = Launch<bf16_t>::prepass(D, layers[0].W, layers[0].S, layers[0].x, D.B, D.N, true, st);
     if (e != hipSuccess) return hip_fail(e, "prepass");
 
+    bool first = true;             // launch of the call
     std::vector<int> done(L, 0);   // chunks of a layer that are finished
     while (done[L - 1] < nch) {
         GroupArgs A = {};
@@ -215,8 +216,9 @@ rt_status group_stack_prefill(GroupStackState &T, GroupState &P, const LayerDims
                 hipLaunchKernelGGL(group_stack_far_kernel<false>, grid, dim3(256), 0, st, far, BH, nqb, A.vt_stride, D.scale, D.alibi, D.H);
             if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "group_stack_far_kernel");
         }
-        const rt_status s = group_launch(P, D, A, true, st, err);
+        const rt_status s = group_launch(P, D, A, true, first, st, err);
         if (s != RT_OK) return s;
+        first = false;
         for (int i = 0; i < n_act; ++i) ++done[act[i]];
     }
     return RT_OK;

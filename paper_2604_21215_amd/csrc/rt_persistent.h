@@ -15,7 +15,7 @@ struct PersistentState {
     int num_cu = 0;
     int grid = 0;
     size_t lds_bytes = 0;
-    long long spin_limit = 0;
+    SpinLimit spin;
     // exchange buffers between the phases of a position (device)
     unsigned long long *bar = nullptr;   // [0] fenced-barrier counter, [8] abort word (non-zero once a wait expired)
     void *a_ll = nullptr, *h_ll = nullptr, *u_ll = nullptr, *z_ll = nullptr;
@@ -32,7 +32,7 @@ void persistent_destroy(PersistentState &P);
 size_t persistent_bytes(const PersistentState &P);
 bool persistent_supported(const PersistentState &P, const LayerDims &D);
 rt_status persistent_prefill(PersistentState &P, const LayerDims &D, const Weights &W, const Scratch &S, const void *x,
-                             void *y, void *K, void *V, hipStream_t st, std::string &err);
+                             void *y, void *K, void *V, bool first, hipStream_t st, std::string &err);   // first: of a call's launches, clears the abort word
 int persistent_wait_expired(PersistentState &P);
 int persistent_read_trace(PersistentState &P, unsigned long long *out, int rows);
 

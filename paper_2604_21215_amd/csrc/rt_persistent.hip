@@ -671,14 +671,11 @@ __global__ __launch_bounds__(kPThreads) void persistent_kernel(PersistArgs A)
 // Host side
 // =============================================================================================
 // a captured stream must not record memset nodes: clear the counters with a kernel
-__global__ void clear_words_kernel(unsigned long long *p, int n)
+// keep_abort: word 8 of the counters stands, so that a wait which expired in an earlier launch of the call is still reported
+__global__ void clear_words_kernel(unsigned long long *p, size_t n, int keep_abort)
 {
-    if ((int)threadIdx.x < n) p[threadIdx.x] = 0ULL;
-}
-
-__global__ void clear_slab_kernel(unsigned long long *p, size_t n)
-{
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0ULL;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
+        if (!(keep_abort && i == 8)) p[i] = 0ULL;
 }
 
 typedef void (*persist_fn)(PersistArgs);
@@ -780,9 +777,7 @@ rt_status persistent_create(PersistentState &P, const rt_config &cfg, const Laye
     P.kv_ll = p + o_kv; P.zss_ll = p + o_zss; P.zp_ll = p + o_zp;
     P.trace = want_trace ? (unsigned long long *)(p + o_tr) : nullptr;
     P.trace_rows = want_trace ? cfg.max_seq : 0;
-    const char *sl = getenv("RT_SPIN_LIMIT");
-    P.spin_limit = sl ? atoll(sl) : (1LL << 21);
-    if (P.spin_limit < 1) P.spin_limit = 1;
+    P.spin.read();
     P.available = true;
     return RT_OK;
 }
@@ -802,7 +797,7 @@ bool persistent_supported(const PersistentState &P, const LayerDims &D)
 }
 
 rt_status persistent_prefill(PersistentState &P, const LayerDims &D, const Weights &W, const Scratch &S, const void *x,
-                             void *y, void *K, void *V, hipStream_t st, std::string &err)
+                             void *y, void *K, void *V, bool first, hipStream_t st, std::string &err)
 {
     PersistArgs A;
     A.B = D.B; A.N = D.N; A.d = D.d; A.H = D.H; A.F = D.F; A.BH = D.B * D.H;
@@ -823,7 +818,7 @@ rt_status persistent_prefill(PersistentState &P, const LayerDims &D, const Weigh
     A.a_ll = (ll_t *)P.a_ll; A.h_ll = (ll_t *)P.h_ll; A.u_ll = (ll_t *)P.u_ll; A.z_ll = (ll_t *)P.z_ll;
     A.kv_ll = (ll_t *)P.kv_ll; A.zss_ll = (ll_t *)P.zss_ll; A.zp_ll = (ll_t *)P.zp_ll;
     A.R_2 = D.d / 64;
-    A.bar = P.bar; A.trace = P.trace; A.spin_limit = P.spin_limit;
+    A.bar = P.bar; A.trace = P.trace; A.spin_limit = P.spin.of_launch();
     A.trace_rows = P.trace_rows;
     // Waits before the first poll of the pulls of phases O, 1, 2a, KV in units of 4 x 64 clocks (0.1 us): a poll that leaves
     // before the producers' stores have landed costs a whole extra trip.  Measured at cfg3 (ms per call, units of 0.2 us):
@@ -847,15 +842,11 @@ rt_status persistent_prefill(PersistentState &P, const LayerDims &D, const Weigh
     }
     P.nonce = (P.nonce % 4095u) + 1u;          // 1..4095; fresh buffers hold tag 0
     A.tag_base = P.nonce << 20;
-    if (P.nonce == 1u && P.launched) {
-        // the nonce has wrapped: words left by a call 4095 calls ago (rows of a larger batch, positions of a longer
-        // sequence) could carry this call's tags.  Start over from cleared buffers.
-        hipLaunchKernelGGL(clear_slab_kernel, dim3(256), dim3(256), 0, st, (unsigned long long *)P.slab, P.exchange_bytes / 8);
-        hipError_t ce = hipGetLastError();
-        if (ce != hipSuccess) { err = std::string("clear_slab_kernel: ") + hipGetErrorString(ce); return RT_ERR_HIP; }
-    }
-
-    hipLaunchKernelGGL(clear_words_kernel, dim3(1), dim3(64), 0, st, P.bar, 32);
+    // When the nonce has wrapped, words left by a call 4095 calls ago (rows of a larger batch, positions of a longer sequence)
+    // could carry this call's tags: all of them are cleared (the counters come first), else the counters alone.
+    const bool all = P.nonce == 1u && P.launched;
+    hipLaunchKernelGGL(clear_words_kernel, dim3(all ? 256 : 1), dim3(all ? 256 : 64), 0, st, P.bar, all ? P.exchange_bytes / 8 : 32,
+                       first ? 0 : 1);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) { err = std::string("clear_words_kernel: ") + hipGetErrorString(e); return RT_ERR_HIP; }
     void *args[] = {&A};
