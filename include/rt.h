@@ -29,6 +29,17 @@
  * position: that form puts two of its three groups of layers on streams lent to the call, forked from and
  * joined back into rt_config.stream by events inside the call (see there).  The caller owns x, y, K, V and the weights; the context owns
  * only scratch memory.  No exceptions cross this boundary.
+ *
+ * Workgroups that wait for one another.  These calls run kernels of one workgroup per compute unit whose workgroups exchange
+ * vectors, and so want the whole device at once: rt_layer_prefill as one cooperative launch (bf16, up to 48 rows; small fp32 layers),
+ * rt_stack_prefill on groups of workgroups, rt_decode_step as a single launch, rt_layer_backward for up to eight bf16 sequences
+ * (for the shapes see each of them).  Two that run at the same time could each hold a part of the chip and wait for the rest.  On one
+ * stream they follow each other; where the contexts of a process have several streams, such a call is put behind what the stream of
+ * the last such call on that device holds (an event between the two streams), from any thread.  Not ordered that way are
+ * calls that are being captured and the replays of their graphs, hipStreamPerThread, and the calls of other processes: those the caller
+ * keeps apart.  If two do meet, their waits are bounded: they expire instead of hanging, and rt_device_wait_expired says so.
+ * Everything else, and every call of a context created with RT_FLAG_ENGINE_STEPWISE, is ordinary launches that share the device
+ * with anything.  Until rt_destroy a context's stream has to exist.
  */
 #ifndef RT_H_
 #define RT_H_
@@ -129,10 +140,8 @@ rt_status rt_layer_prefill(rt_ctx *ctx, const rt_layer_weights *w, const void *x
  * bf16 storage with the MFMA kernels, d_model in {256, 512, 768, 1024}, d_hidden = 4 d_model, B n_heads <= 256, on a
  * device with 256 compute units: the whole step is ONE kernel launch of one workgroup per compute unit (engine name
  * "decode-single-launch"): the cache rows and the rows of all six matrices are requested at its start, the base case
- * runs on weight slices held in LDS, and the workgroups exchange the vectors between the products through memory.  The
- * workgroups wait for one another, so two such steps must not run at the same time on one device (two contexts on two
- * streams): each could hold part of the chip and wait for the rest; their bounded waits would then expire
- * (rt_device_wait_expired) instead of hanging.  Steps on one stream are ordered and safe.  A batch of up to three times
+ * runs on weight slices held in LDS, and the workgroups exchange the vectors between the products through memory: they
+ * wait for one another (see the beginning of this file).  A batch of up to three times
  * the rows one launch takes (min(16, 256 / n_heads)) runs as one such launch per chunk of rows, one after the other.  Any
  * other shape, dtype or batch size, and contexts created with RT_FLAG_ENGINE_STEPWISE, take eight launches per step instead. */
 rt_status rt_decode_step(rt_ctx *ctx, const rt_layer_weights *w, const void *x_t, int32_t B, int32_t t, void *y_t,

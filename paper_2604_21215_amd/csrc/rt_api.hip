@@ -7,12 +7,14 @@
 #include "rt_decode_persistent.h"
 #include "rt_backward.h"
 #include "rt_side_streams.h"
+#include "rt_launch_order.h"
 
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <optional>
 #include <string>
 #include <vector>
 
@@ -87,6 +89,29 @@ struct HipStreams {
 };
 using SideStreams = SidePool<HipStreams, kMaxWaveStreams - 1>;
 SideStreams g_side;
+
+// Calls whose workgroups wait for one another, in order over the process's streams (rt_launch_order.h).
+struct HipLaunches {
+    using Stream = hipStream_t;
+    using Event = hipEvent_t;
+    static bool ok(hipError_t e)
+    {
+        if (e != hipSuccess) (void)hipGetLastError();
+        return e == hipSuccess;
+    }
+    static Stream per_thread() { return hipStreamPerThread; }
+    static bool capturing(Stream st)   // also true where it cannot be told
+    {
+        hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+        return !ok(hipStreamIsCapturing(st, &s)) || s != hipStreamCaptureStatusNone;
+    }
+    static bool create(Event *e) { return ok(hipEventCreateWithFlags(e, hipEventDisableTiming)); }
+    static bool record(Event e, Stream st) { return ok(hipEventRecord(e, st)); }   // an error: the stream is gone, and its work done
+    static bool wait(Stream st, Event e) { return ok(hipStreamWaitEvent(st, e, 0)); }
+    static void destroy(Event e) { (void)hipEventDestroy(e); }
+};
+using WaitingLaunches = LaunchOrder<HipLaunches>;
+WaitingLaunches g_order;
 }  // namespace
 
 static rt_status fail(rt_ctx *c, rt_status s, const char *fmt, const char *detail = "")
@@ -446,6 +471,7 @@ rt_status rt_destroy(rt_ctx *c)
 {
     if (!c) return RT_OK;
     (void)hipSetDevice(c->cfg.device);
+    g_order.forget(c);
     if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
     if (c->capture_stream) (void)hipStreamDestroy(c->capture_stream);
     persistent_destroy(c->persist);
@@ -658,6 +684,7 @@ extern "C" rt_status rt_layer_prefill(rt_ctx *c, const rt_layer_weights *w, cons
     poison_partials(c, c->S);
     const bool want_stepwise = (c->cfg.flags & RT_FLAG_ENGINE_STEPWISE) != 0;
     if (group_f32_supported(c->group_f32, D)) {
+        WaitingLaunches::Turn turn(g_order, c->cfg.device, c, c->stream);
         c->engine = "stepwise";   // the name that fp32 prefills have always reported
         const Weights W = to_weights(w);
         const hipError_t e = Launch<float>::prepass(D, W, c->S, x, B, N, false, c->stream);
@@ -668,6 +695,7 @@ extern "C" rt_status rt_layer_prefill(rt_ctx *c, const rt_layer_weights *w, cons
         return s;
     }
     if (!want_stepwise && persistent_supported(c->persist, D)) {
+        WaitingLaunches::Turn turn(g_order, c->cfg.device, c, c->stream);
         c->engine = "persistent";
         c->last_hp = true;
         const Weights W = to_weights(w);
@@ -703,6 +731,7 @@ extern "C" rt_status rt_layer_prefill(rt_ctx *c, const rt_layer_weights *w, cons
     if (!want_stepwise && c->kv_chunk && B > c->persist.max_batch && persistent_supported(c->persist, Dc)) {
         // batch rows are independent: chunks of the engine's rows, one after the other on the stream; x and y of a chunk are
         // contiguous slices, its pairs go through the chunk buffers (the cache is position-major over the whole batch)
+        WaitingLaunches::Turn turn(g_order, c->cfg.device, c, c->stream);
         c->engine = "persistent";
         c->last_hp = true;
         c->last_B = 0;   // the scratch holds the last chunk only: no stand-alone tile on it
@@ -743,6 +772,7 @@ static rt_status decode_impl(rt_ctx *c, const LayerDims &D, const rt_layer_weigh
     // d = 1024, t = 511, us in chunks / as eight launches: B = 17 61 / 68, B = 32 61 / 74, B = 33 92 / 75, B = 48 92 / 79 (85 and more before
     // the eight took 32 sequences per workgroup, when the line was drawn), B = 64 126 / 84
     if (sizeof(T) == 2 && c->dec.available && D.B > c->dec.max_batch && D.B <= 3 * c->dec.max_batch) {
+        WaitingLaunches::Turn turn(g_order, c->cfg.device, c, c->stream);
         c->engine = "decode-single-launch";
         const size_t row = (size_t)D.d * sizeof(T);
         for (int b0 = 0; b0 < D.B; b0 += c->dec.max_batch) {
@@ -756,6 +786,7 @@ static rt_status decode_impl(rt_ctx *c, const LayerDims &D, const rt_layer_weigh
         return RT_OK;
     }
     if (sizeof(T) == 2 && decode_coop_supported(c->dec, D)) {   // the whole step as one cooperative launch
+        WaitingLaunches::Turn turn(g_order, c->cfg.device, c, c->stream);
         c->engine = "decode-single-launch";
         std::string derr;
         const rt_status ds = decode_coop_step(c->dec, D, W, x_t, t, y_t, K, V, st, derr);
@@ -1058,6 +1089,7 @@ extern "C" rt_status rt_stack_prefill(rt_ctx *c, const rt_layer_weights *layers,
     D.B = B; D.N = N; D.kv_cap = kv_cap;
     c->engine = "wavefront";
     if (!(c->cfg.flags & RT_FLAG_ENGINE_STEPWISE) && group_stack_supported(c->group_stack, c->group, D, L)) {
+        WaitingLaunches::Turn turn(g_order, c->cfg.device, c, c->stream);
         std::string gerr;
         s = group_stack_prefill(c->group_stack, c->group, D, host.data(), L, (c->cfg.flags & RT_FLAG_DEBUG_POISON) != 0, c->stream, gerr);
         if (s != RT_OK) { c->err = gerr; if (s == RT_ERR_HIP) c->broken = true; }
@@ -1217,6 +1249,8 @@ extern "C" rt_status rt_layer_backward(rt_ctx *c, const rt_layer_weights *w, con
     BwGrads G = {grads->Wq, grads->Wk, grads->Wv, grads->Wo, grads->W1, grads->W2,
                  grads->g_attn, grads->g_mlp, grads->g_kv, grads->g_q, grads->g_k};
     c->engine = "backward";
+    std::optional<WaitingLaunches::Turn> turn;
+    if (c->use_mfma && bwp_supported(c->bw_loop, D)) turn.emplace(g_order, c->cfg.device, c, c->stream);
     hipError_t e = c->cfg.dtype == RT_BF16 ? backward_layer<bf16_t>(D, W, x, z, gy, gK, gV, dx, G, c->bw_slab, c->use_mfma, c->stream, &c->bw_loop)
                                            : backward_layer<float>(D, W, x, z, gy, gK, gV, dx, G, c->bw_slab, false, c->stream);
     if (e != hipSuccess) return fail_hip(c, e, "backward_layer");

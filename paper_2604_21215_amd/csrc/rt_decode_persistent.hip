@@ -700,7 +700,7 @@ rt_status decode_coop_step(DecodeCoopState &P, const LayerDims &D, const Weights
     // workgroup becomes resident as soon as the kernels before it on the stream have drained.  (A cooperative launch
     // guarantees the same, but goes through the device's cooperative queue, which measured 19 us per step between
     // two launches against 39 us of kernel.)  Two such launches on different streams at the same time could each
-    // hold a part of the chip and wait for the rest: their bounded waits then expire (rt_device_wait_expired).
+    // hold a part of the chip and wait for the rest until their bounded waits expire (rt_device_wait_expired): the caller orders them.
     hipError_t e;
     if (P.cooperative) {
         void *args[] = {&A};
