@@ -67,7 +67,7 @@ typedef enum { RT_F32 = 0, RT_BF16 = 1 } rt_dtype; /* storage type of x, y, K, V
 #define RT_FLAG_NORM_FREE 0x1u       /* every RMS / qkRMS is the identity (Appendix A's norm-free layer) */
 #define RT_FLAG_ENGINE_STEPWISE 0x2u /* drive the sequential loop as one set of kernel launches per position */
 #define RT_FLAG_ENGINE_PERSISTENT 0x4u /* require the single persistent weight-stationary kernel (error if it cannot run) */
-#define RT_FLAG_NO_MFMA 0x8u         /* use the plain-ALU kernels also for bf16 storage (cross-checks) */
+#define RT_FLAG_NO_MFMA 0x8u         /* use the plain-ALU kernels, for bf16 storage and for fp32 (cross-checks) */
 #define RT_FLAG_HIP_GRAPH 0x10u      /* stepwise engine: capture the launches of a prefill in a HIP graph and replay it */
 #define RT_FLAG_DEBUG_POISON 0x20u   /* debugging: before every prefill (any engine, stacks, blocked recurrence) all stored
                                         partial softmax states are set to NaN, so that a state read before this call has
@@ -121,7 +121,7 @@ rt_status rt_create(const rt_config *cfg, rt_ctx **out);
  *   K, V [kv_cap, B, H, head_dim] device, position first (Sec. 6.3); rows 0..N-1 are written in place
  *   1 <= B <= max_batch, 1 <= N <= max_seq, N <= kv_cap.
  * fp32 storage with d_model 128, 256 or 384, d_hidden = 4 d_model, p_min 32 and at most 32 (d_model 384: 16) rows runs as one cooperative
- * launch.  Batch rows are independent; where the single-launch engine applies (bf16) it stages at most 16 of them, and a larger
+ * launch (fp32 products on the matrix cores; not with RT_FLAG_NO_MFMA, RT_FLAG_HIP_GRAPH or RT_FLAG_ENGINE_STEPWISE).  Batch rows are independent; where the single-launch engine applies (bf16) it stages at most 16 of them, and a larger
  * batch runs as chunks of 16 rows one after the other on the stream, each chunk's pairs copied into K, V from a
  * buffer of 2 * max_seq * 16 * d elements that rt_create allocates when max_batch > 16.  With bf16 and the matrix-core
  * kernels, 49 to 128 rows run as a stack of one layer on rt_stack_prefill's engine, and more rows step through the

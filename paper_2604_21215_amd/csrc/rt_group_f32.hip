@@ -491,7 +491,8 @@ static size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 rt_status group_f32_create(GroupF32State &P, const rt_config &cfg, const LayerDims &D)
 {
     P.available = false;
-    if (cfg.dtype != RT_F32 || D.F != 4 * D.d || !pick_kernel(D.d, 1) || D.p_min != 32) return RT_ERR_UNSUPPORTED;
+    if (cfg.dtype != RT_F32 || (cfg.flags & RT_FLAG_NO_MFMA) || D.F != 4 * D.d || !pick_kernel(D.d, 1) || D.p_min != 32)
+        return RT_ERR_UNSUPPORTED;
     int cus = 0, coop = 0;
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, cfg.device) != hipSuccess ||
         hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, cfg.device) != hipSuccess)
