@@ -297,9 +297,15 @@ uint64_t rt_workspace_bytes(const rt_ctx *ctx);
  * this context completed, in all of the call's launches, non-zero if one expired (the call's outputs are then invalid). */
 int32_t rt_device_wait_expired(rt_ctx *ctx);
 
-/* Name of the engine the last prefill call on this context used: "stepwise", "stepwise+graph",
- * "persistent", "wavefront" (rt_stack_prefill), "recompute", "transformer", "blocked", "backward", or "" before the first call. */
+/* Name of the engine the last call on this context used: "stepwise" (also where an fp32 rt_layer_prefill runs as one cooperative
+ * launch), "stepwise+graph", "persistent", "position-batched", "wavefront" (rt_stack_prefill), "decode-single-launch", "recompute",
+ * "transformer", "blocked", "backward", or "" before the first call. */
 const char *rt_engine_name(const rt_ctx *ctx);
+
+/* How that engine ran the loop: "groups" (one or more launches of one workgroup per compute unit, in groups that hold a layer each
+ * and whose workgroups wait for one another), "one-launch" (all workgroups as one such group), "launches" (ordinary launches), or ""
+ * before the first call. */
+const char *rt_engine_form(const rt_ctx *ctx);
 
 /* Diagnostics of the persistent engine, after the stream has been synchronised: when the environment
  * variable RT_PERSIST_TRACE was set at rt_create, copies for each of the first `rows` positions sixteen

@@ -24,7 +24,7 @@ RT_FLAG_DEBUG_POISON = 0x20
 RT_RESERVE_LOOP_FREE, RT_RESERVE_BACKWARD = 0x1, 0x2
 
 EXPORTS = ("rt_create", "rt_layer_prefill", "rt_decode_step", "rt_destroy", "rt_last_error", "rt_status_string",
-           "rt_workspace_bytes", "rt_device_wait_expired", "rt_engine_name", "rt_schedule_events", "rt_partial_slot",
+           "rt_workspace_bytes", "rt_device_wait_expired", "rt_engine_name", "rt_engine_form", "rt_schedule_events", "rt_partial_slot",
            "rt_version", "rt_phase_trace", "rt_schedule_events_shifted", "rt_embed_rows", "rt_lm_head", "rt_cross_block_event",
            "rt_stack_prefill", "rt_schedule_events_chunked", "rt_layer_recompute", "rt_transformer_layer",
            "rt_layer_prefill_blocked", "rt_decode_step_static", "rt_layer_backward", "rt_decode_phase_trace")
@@ -92,6 +92,8 @@ def load():
     L.rt_device_wait_expired.restype = C.c_int32
     L.rt_engine_name.argtypes = [ctxp]
     L.rt_engine_name.restype = C.c_char_p
+    L.rt_engine_form.argtypes = [ctxp]
+    L.rt_engine_form.restype = C.c_char_p
     L.rt_schedule_events.argtypes = [C.c_int32, C.c_int32, C.POINTER(C.c_int32), C.c_int32]
     L.rt_schedule_events.restype = C.c_int32
     L.rt_schedule_events_shifted.argtypes = [C.c_int32, C.c_int32, C.POINTER(C.c_int32), C.c_int32]
@@ -313,6 +315,9 @@ class RTContext:
 
     def engine_name(self) -> str:
         return self._L.rt_engine_name(self._ctx).decode()
+
+    def engine_form(self) -> str:
+        return self._L.rt_engine_form(self._ctx).decode()
 
     def workspace_bytes(self) -> int:
         return int(self._L.rt_workspace_bytes(self._ctx))

@@ -37,6 +37,7 @@ struct rt_ctx {
     bool last_hp = false;         // that prefill formed high-precision logits (scratch holds unrounded queries and key remainders)
     std::string err;
     std::string engine;
+    const char *form = "";           // how the last call ran (rt_engine_form)
     PersistentState persist;
     GroupF32State group_f32;
     GroupState group;                // the same loop by four groups of workgroups: taken where it covers the shape
@@ -65,6 +66,7 @@ struct rt_ctx {
 };
 
 static const char *kNoCtx = "no context";
+static const char *kFormLaunches = "launches", *kFormOne = "one-launch", *kFormGroups = "groups";
 
 // Side streams of the layer-wavefront engine (rt_side_streams.h).  A call that is being captured uses streams of its own context:
 // a pooled stream would stay part of the capture.
@@ -503,6 +505,7 @@ uint64_t rt_workspace_bytes(const rt_ctx *c)
              : 0;
 }
 const char *rt_engine_name(const rt_ctx *c) { return c ? c->engine.c_str() : ""; }
+const char *rt_engine_form(const rt_ctx *c) { return c ? c->form : ""; }
 
 int32_t rt_device_wait_expired(rt_ctx *c)
 {
@@ -654,7 +657,8 @@ static rt_status prefill_stepwise(rt_ctx *c, const LayerDims &D, const rt_layer_
 static rt_status single_launch_prefill(rt_ctx *c, const LayerDims &D, const Weights &W, const void *x, void *y, void *K, void *V, bool first,
                                        std::string &err)
 {
-    if (group_supported(c->group, D)) return group_prefill(c->group, D, W, c->S, x, y, K, V, first, c->stream, err);
+    c->form = group_supported(c->group, D) ? kFormGroups : kFormOne;
+    if (c->form == kFormGroups) return group_prefill(c->group, D, W, c->S, x, y, K, V, first, c->stream, err);
     return persistent_prefill(c->persist, D, W, c->S, x, y, K, V, first, c->stream, err);
 }
 
@@ -681,11 +685,13 @@ extern "C" rt_status rt_layer_prefill(rt_ctx *c, const rt_layer_weights *w, cons
     D.B = B; D.N = N; D.kv_cap = kv_cap;
     c->last_B = B; c->last_N = N;
     c->last_hp = false;
+    c->form = kFormLaunches;
     poison_partials(c, c->S);
     const bool want_stepwise = (c->cfg.flags & RT_FLAG_ENGINE_STEPWISE) != 0;
     if (group_f32_supported(c->group_f32, D)) {
         WaitingLaunches::Turn turn(g_order, c->cfg.device, c, c->stream);
-        c->engine = "stepwise";   // the name that fp32 prefills have always reported
+        c->engine = "stepwise";   // the name that fp32 prefills have always reported; rt_engine_form tells them apart
+        c->form = kFormGroups;
         const Weights W = to_weights(w);
         const hipError_t e = Launch<float>::prepass(D, W, c->S, x, B, N, false, c->stream);
         if (e != hipSuccess) return fail_hip(c, e, "prepass");
@@ -773,6 +779,7 @@ static rt_status decode_impl(rt_ctx *c, const LayerDims &D, const rt_layer_weigh
     // the eight took 32 sequences per workgroup, when the line was drawn), B = 64 126 / 84
     if (sizeof(T) == 2 && c->dec.available && D.B > c->dec.max_batch && D.B <= 3 * c->dec.max_batch) {
         WaitingLaunches::Turn turn(g_order, c->cfg.device, c, c->stream);
+        c->form = kFormOne;
         c->engine = "decode-single-launch";
         const size_t row = (size_t)D.d * sizeof(T);
         for (int b0 = 0; b0 < D.B; b0 += c->dec.max_batch) {
@@ -788,6 +795,7 @@ static rt_status decode_impl(rt_ctx *c, const LayerDims &D, const rt_layer_weigh
     if (sizeof(T) == 2 && decode_coop_supported(c->dec, D)) {   // the whole step as one cooperative launch
         WaitingLaunches::Turn turn(g_order, c->cfg.device, c, c->stream);
         c->engine = "decode-single-launch";
+        c->form = kFormOne;
         std::string derr;
         const rt_status ds = decode_coop_step(c->dec, D, W, x_t, t, y_t, K, V, st, derr);
         if (ds != RT_OK) { c->err = derr; if (ds == RT_ERR_HIP) c->broken = true; }
@@ -840,6 +848,7 @@ extern "C" rt_status rt_decode_step(rt_ctx *c, const rt_layer_weights *w, const 
     LayerDims D = c->base;
     D.B = B; D.N = 1; D.kv_cap = kv_cap;
     c->engine = "stepwise";
+    c->form = kFormLaunches;
     if (c->cfg.dtype == RT_BF16) return decode_impl<bf16_t>(c, D, w, x_t, t, y_t, K, V);
     return decode_impl<float>(c, D, w, x_t, t, y_t, K, V);
 }
@@ -1088,8 +1097,10 @@ extern "C" rt_status rt_stack_prefill(rt_ctx *c, const rt_layer_weights *layers,
     LayerDims D = c->base;
     D.B = B; D.N = N; D.kv_cap = kv_cap;
     c->engine = "wavefront";
+    c->form = kFormLaunches;
     if (!(c->cfg.flags & RT_FLAG_ENGINE_STEPWISE) && group_stack_supported(c->group_stack, c->group, D, L)) {
         WaitingLaunches::Turn turn(g_order, c->cfg.device, c, c->stream);
+        c->form = kFormGroups;
         std::string gerr;
         s = group_stack_prefill(c->group_stack, c->group, D, host.data(), L, (c->cfg.flags & RT_FLAG_DEBUG_POISON) != 0, c->stream, gerr);
         if (s != RT_OK) { c->err = gerr; if (s == RT_ERR_HIP) c->broken = true; }
@@ -1168,6 +1179,7 @@ static rt_status parallel_entry(rt_ctx *c, const rt_layer_weights *w, const void
         c->last_B = B; c->last_N = N;
         c->last_hp = false;
         c->engine = block ? "blocked" : (transformer ? "transformer" : "recompute");
+        c->form = kFormLaunches;
         const Weights Wg = to_weights(w);
         hipError_t e;
         if (block)
@@ -1183,6 +1195,7 @@ static rt_status parallel_entry(rt_ctx *c, const rt_layer_weights *w, const void
     c->last_B = B; c->last_N = N;
     c->last_hp = true;
     c->engine = block ? "blocked" : (transformer ? "transformer" : "recompute");
+    c->form = kFormLaunches;
     const Weights W = to_weights(w);
     hipError_t e = block ? blocked_layer(D, W, c->S, x, block, y, K, V, c->par_slab, c->stream)
                          : parallel_layer(D, W, c->S, x, pairs_src, transformer, y, K, V, c->par_slab, c->stream);
@@ -1250,7 +1263,11 @@ extern "C" rt_status rt_layer_backward(rt_ctx *c, const rt_layer_weights *w, con
                  grads->g_attn, grads->g_mlp, grads->g_kv, grads->g_q, grads->g_k};
     c->engine = "backward";
     std::optional<WaitingLaunches::Turn> turn;
-    if (c->use_mfma && bwp_supported(c->bw_loop, D)) turn.emplace(g_order, c->cfg.device, c, c->stream);
+    c->form = kFormLaunches;
+    if (c->use_mfma && bwp_supported(c->bw_loop, D)) {
+        turn.emplace(g_order, c->cfg.device, c, c->stream);
+        c->form = kFormGroups;
+    }
     hipError_t e = c->cfg.dtype == RT_BF16 ? backward_layer<bf16_t>(D, W, x, z, gy, gK, gV, dx, G, c->bw_slab, c->use_mfma, c->stream, &c->bw_loop)
                                            : backward_layer<float>(D, W, x, z, gy, gK, gV, dx, G, c->bw_slab, false, c->stream);
     if (e != hipSuccess) return fail_hip(c, e, "backward_layer");

@@ -15,7 +15,7 @@ GAINS = ("g_attn", "g_mlp", "g_kv", "g_q", "g_k")
 
 
 def _run(oracle, dtype, B, N, d, H, F, *, gains="random", alpha=1.0, scale=1.0, alibi=0.0, seed=31, shared_kv_gain=False,
-         norm_free=False, with_pair_grads=True, z_from_gpu=False, tol=None, no_mfma=False):
+         norm_free=False, with_pair_grads=True, z_from_gpu=False, tol=None, no_mfma=False, expect_form=None):
     if not torch.cuda.is_available():
         pytest.fail("no GPU visible")
     from oracle import rt_backward as bwd
@@ -55,6 +55,8 @@ def _run(oracle, dtype, B, N, d, H, F, *, gains="random", alpha=1.0, scale=1.0, 
         torch.cuda.synchronize()
         assert ctx.device_wait_expired() == 0
         assert ctx.engine_name() == "backward"
+        if expect_form:
+            assert ctx.engine_form() == expect_form
         got_dx = dx.cpu().numpy().astype(np.float64)
         got = {k: v.cpu().numpy().astype(np.float64) for k, v in grads.items()}
     finally:

@@ -15,36 +15,67 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("B,N,alibi", [(1, 65, 0.0), (4, 34, 8.0), (5, 97, 0.0), (8, 33, 8.0), (9, 66, 0.0), (16, 64, 8.0)])
 def test_rows_per_group(oracle, d, B, N, alibi):
     _run_case(oracle, "bf16", B, N, d, d // 64, 4 * d, gains="random", scale=0.5, alpha=0.7, alibi=alibi, kv_cap=N + 1,
-              expect_engine="persistent")
+              expect_engine="persistent", expect_form="groups")
 
 
 @pytest.mark.parametrize("B,N,alibi", [(5, 1100, 0.0), (2, 1290, 8.0)])
 def test_blocks_of_up_to_1024_keys(oracle, B, N, alibi):
-    _run_case(oracle, "bf16", B, N, 256, 4, 1024, gains="random", scale=0.125, alibi=alibi, expect_engine="persistent")
+    _run_case(oracle, "bf16", B, N, 256, 4, 1024, gains="random", scale=0.125, alibi=alibi, expect_engine="persistent",
+              expect_form="groups")
+
+
+@pytest.mark.parametrize("B,N,d,p_min", [(16, 140, 1024, 128), (8, 100, 1024, 64), (16, 70, 256, 64), (35, 70, 256, 64)])
+def test_windows_that_keep_the_other_form(oracle, B, N, d, p_min):
+    """a direct window of 64 keys and more: one launch of all 256 workgroups, with a (b, h) in each of them in the first case, and in
+    chunks of sixteen sequences in the last"""
+    _run_case(oracle, "bf16", B, N, d, d // 64, 4 * d, p_min=p_min, gains="random", scale=0.5, alpha=0.7, expect_engine="persistent",
+              expect_form="one-launch")
 
 
 @pytest.mark.parametrize("B,N,layers,d,alibi", [
     (1, 65, 1, 256, 0.0), (3, 64, 2, 512, 8.0), (4, 300, 5, 256, 0.0), (5, 129, 3, 768, 0.0), (8, 200, 4, 256, 8.0),
     (9, 130, 2, 256, 0.0), (16, 70, 6, 256, 8.0), (12, 70, 7, 256, 0.0)])
 def test_stack(oracle, B, N, layers, d, alibi):
-    """four, two or one layer at a time, more layers than run at once, chunks with a ragged last one, the first batch that leaves the
-    engine again (nine sequences and more than six layers)"""
+    """four, two or one layer at a time, more layers than run at once, chunks with a ragged last one"""
     wl = gen.Workload("stack_groups", "bf16", B, N, d, d // 64, 4 * d, layers=layers, vocab=300, decode_steps=2, seed=990 + B)
-    _run_elementwise(oracle, wl, B, N, 2, emb_scale=EMB_UNIT, wavefront=True, alibi=alibi)
+    _run_elementwise(oracle, wl, B, N, 2, emb_scale=EMB_UNIT, wavefront=True, alibi=alibi, expect_form="groups")
+
+
+@pytest.mark.parametrize("B,N,layers,d,F,p_min", [(17, 70, 2, 256, 1024, 0), (2, 70, 3, 256, 512, 0), (2, 150, 3, 256, 1024, 64),
+                                                  (9, 290, 8, 256, 1024, 0), (9, 100, 8, 256, 1024, 0)])
+def test_stacks_that_keep_the_launches(oracle, B, N, layers, d, F, p_min):
+    """more than sixteen sequences, another hidden width, a wider window, and on either side of where passes over the layers take
+    longer than launches that carry all of them: 8 * 290 > 3.1 (290 + 64 * 7), 8 * 100 < 3.1 (100 + 64 * 7)"""
+    wl = gen.Workload("stack_launches", "bf16", B, N, d, d // 64, F, layers=layers, vocab=300, decode_steps=2, seed=970 + B)
+    passes, steps = -(-layers // (4 if B <= 4 else 1)) * N, N + 64 * (layers - 1)
+    deep = 10 * passes > 31 * steps
+    refused = B > 16 or F != 4 * d or p_min == 64
+    _run_elementwise(oracle, wl, B, N, 2, emb_scale=EMB_UNIT, wavefront=True, p_min=p_min,
+                     expect_form="launches" if refused or deep else "groups")
 
 
 @pytest.mark.parametrize("B,N,d,alibi", [(1, 1, 128, 0.0), (2, 34, 256, 8.0), (3, 65, 384, 0.0), (8, 130, 128, 8.0), (9, 66, 256, 0.0),
                                          (16, 97, 384, 8.0), (4, 290, 256, 0.0), (1, 515, 128, 0.0), (32, 40, 128, 0.0)])
 def test_fp32(oracle, B, N, d, alibi):
     """fp32 storage: one sequence per group and several, widths whose share of a contraction ends inside a chunk, blocks of 32 to 512 keys"""
-    _run_case(oracle, "f32", B, N, d, d // 64, 4 * d, gains="random", scale=0.5, alpha=0.7, alibi=alibi, kv_cap=N + 1)
+    _run_case(oracle, "f32", B, N, d, d // 64, 4 * d, gains="random", scale=0.5, alpha=0.7, alibi=alibi, kv_cap=N + 1, expect_form="groups")
+
+
+@pytest.mark.parametrize("B,N,d,F,p_min", [(33, 40, 128, 512, 32), (17, 40, 384, 1536, 32), (2, 40, 512, 2048, 32), (2, 40, 256, 512, 32), (2, 70, 256, 1024, 16)])
+def test_fp32_shapes_that_keep_the_launches(oracle, B, N, d, F, p_min):
+    _run_case(oracle, "f32", B, N, d, d // 64, F, p_min=p_min, gains="random", scale=0.5, alpha=0.7, expect_engine="stepwise",
+              expect_form="launches")
 
 
 @pytest.mark.parametrize("d", [256, 512, 768, 1024])
 @pytest.mark.parametrize("B,N,alibi", [(1, 33, 8.0), (4, 64, 0.0), (5, 70, 0.0), (8, 34, 8.0)])
 def test_reverse_loop(oracle, d, B, N, alibi):
     """the backward pass's loop: one and two sequences per group, full and ragged, blocks of one position and whole ones"""
-    _backward_case(oracle, "bf16", B, N, d, d // 64, 4 * d, alpha=0.7, scale=0.125, alibi=alibi, seed=77)
+    _backward_case(oracle, "bf16", B, N, d, d // 64, 4 * d, alpha=0.7, scale=0.125, alibi=alibi, seed=77, expect_form="groups")
+
+
+def test_reverse_loop_of_nine_sequences(oracle):
+    _backward_case(oracle, "bf16", 9, 40, 256, 4, 1024, alpha=0.7, scale=0.125, seed=78, expect_form="launches")
 
 
 @pytest.mark.parametrize("B,N,d,alibi", [(130, 70, 256, 0.0), (129, 100, 320, 8.0)])

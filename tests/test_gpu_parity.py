@@ -23,7 +23,7 @@ def _gpu():
 
 
 def _run_case(oracle, dtype, B, N, d, H, F, *, flags=0, p_min=0, gains="unit", seed=5, alpha=1.0, scale=1.0,
-              eps=1e-6, kv_cap=None, li=None, tol_scale=1.0, expect_engine=None, alibi=0.0, n_decode=0):
+              eps=1e-6, kv_cap=None, li=None, tol_scale=1.0, expect_engine=None, expect_form=None, alibi=0.0, n_decode=0):
     binding, tio = _gpu()
     if li is None:
         li = gen.make_custom(seed, dtype, B, N, d, H, F, gains=gains)
@@ -39,6 +39,8 @@ def _run_case(oracle, dtype, B, N, d, H, F, *, flags=0, p_min=0, gains="unit", s
         assert ctx.device_wait_expired() == 0
         if expect_engine:
             assert ctx.engine_name() == expect_engine
+        if expect_form:
+            assert ctx.engine_form() == expect_form
         got = (tio.to_host(y), tio.to_host(K), tio.to_host(V))
         # the last n_decode positions once more, one rt_decode_step each over the cache the prefill left
         for t in range(N - n_decode, N):

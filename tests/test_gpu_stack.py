@@ -77,7 +77,7 @@ def _fmt(rows):
 
 
 def _run_elementwise(oracle, wl, B, N, n_dec, flags=0, emb_scale=1.0, wavefront=False, chunk=0, p_min=0, alibi=0.0,
-                     attn_scale=1.0):
+                     attn_scale=1.0, expect_form=None):
     from paper_2604_21215_amd import torch_io as tio
     _need_gpu()
     T = N + n_dec
@@ -90,6 +90,8 @@ def _run_elementwise(oracle, wl, B, N, n_dec, flags=0, emb_scale=1.0, wavefront=
         torch.cuda.synchronize()
         assert ctx.device_wait_expired() == 0
         assert (ctx.engine_name() == "wavefront") == wavefront
+        if expect_form:
+            assert ctx.engine_form() == expect_form
         tol = TOL[wl.dtype]
         rows = _layer_errors(ds, ref_layers, N)
         e_log = rel_err_rows(logits.cpu().numpy().astype(np.float64), ref_logits).max()
