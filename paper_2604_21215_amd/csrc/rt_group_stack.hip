@@ -149,6 +149,10 @@ rt_status group_stack_prefill(GroupStackState &T, GroupState &P, const LayerDims
     const long long passes = (L + slots - 1) / slots;
     int C = 64;
     while (C < kStackChunk && 2LL * C * C * 10 <= 28 * passes * D.N) C *= 2;
+    if (const char *s = getenv("RT_GROUP_CHUNK")) {   // 64, 128 or 256 instead
+        const int v = atoi(s);
+        if (v == 64 || v == 128 || v == 256) C = v;
+    }
     const int nch = (D.N + C - 1) / C;
     if (poison)
         hipLaunchKernelGGL(group_stack_poison_kernel, dim3(1024), dim3(256), 0, st, (float *)T.slab, T.slab_bytes / 4);

@@ -41,6 +41,16 @@ def test_stack(oracle, B, N, layers, d, alibi):
     _run_elementwise(oracle, wl, B, N, 2, emb_scale=EMB_UNIT, wavefront=True, alibi=alibi, expect_form="groups")
 
 
+@pytest.mark.parametrize("chunk", [128, 256])
+@pytest.mark.parametrize("B,N,layers,alibi,poison", [(1, 515, 1, 8.0, False), (2, 300, 5, 0.0, True), (5, 391, 2, 8.0, False), (9, 290, 3, 8.0, True)])
+def test_stack_with_longer_chunks(oracle, monkeypatch, chunk, B, N, layers, alibi, poison):
+    """the chunks that long stacks take: blocks of 64 and 128 keys inside a chunk, the far tile for more than 128 queries, a ragged last
+    chunk; four layers at a time, two and one"""
+    monkeypatch.setenv("RT_GROUP_CHUNK", str(chunk))
+    wl = gen.Workload("stack_chunks", "bf16", B, N, 256, 4, 1024, layers=layers, vocab=300, decode_steps=2, seed=960 + B)
+    _run_elementwise(oracle, wl, B, N, 2, flags=0x20 if poison else 0, emb_scale=EMB_UNIT, wavefront=True, alibi=alibi, expect_form="groups")
+
+
 @pytest.mark.parametrize("B,N,layers,d,F,p_min", [(17, 70, 2, 256, 1024, 0), (2, 70, 3, 256, 512, 0), (2, 150, 3, 256, 1024, 64),
                                                   (9, 290, 8, 256, 1024, 0), (9, 100, 8, 256, 1024, 0)])
 def test_stacks_that_keep_the_launches(oracle, B, N, layers, d, F, p_min):

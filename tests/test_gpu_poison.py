@@ -32,18 +32,24 @@ def test_poisoned_states_stepwise_bf16_matrix_core_tiles(oracle):
               expect_engine="stepwise")
 
 
-def test_poisoned_states_persistent_engine(oracle):
+@pytest.mark.parametrize("p_min,form", [(64, "one-launch"), (0, "groups")])
+def test_poisoned_states_persistent_engine(oracle, p_min, form):
     b = _b()
-    _run_case(oracle, "bf16", 3, 700, 256, 4, 1024, flags=b.RT_FLAG_DEBUG_POISON | b.RT_FLAG_ENGINE_PERSISTENT,
-              expect_engine="persistent")
+    _run_case(oracle, "bf16", 3, 700, 256, 4, 1024, p_min=p_min, flags=b.RT_FLAG_DEBUG_POISON | b.RT_FLAG_ENGINE_PERSISTENT,
+              expect_engine="persistent", expect_form=form)
 
 
-@pytest.mark.parametrize("dtype,N,chunk,p_min", [("f32", 130, 16, 4), ("bf16", 300, 64, 0)])
-def test_poisoned_states_layer_wavefront(oracle, dtype, N, chunk, p_min):
+def test_poisoned_states_fp32_groups(oracle):
+    _run_case(oracle, "f32", 3, 300, 256, 4, 1024, flags=_b().RT_FLAG_DEBUG_POISON, expect_form="groups")
+
+
+@pytest.mark.parametrize("dtype,N,chunk,p_min,stepwise", [("f32", 130, 16, 4, False), ("bf16", 300, 64, 0, True), ("bf16", 300, 64, 0, False)])
+def test_poisoned_states_layer_wavefront(oracle, dtype, N, chunk, p_min, stepwise):
     wl = gen.Workload("stack_poison", dtype, 2, N, 256 if dtype == "bf16" else 128, 4 if dtype == "bf16" else 2,
                       1024 if dtype == "bf16" else 512, layers=3, vocab=300, decode_steps=2, seed=996)
-    _run_elementwise(oracle, wl, 2, N, 2, flags=_b().RT_FLAG_DEBUG_POISON, emb_scale=EMB_UNIT, wavefront=True, chunk=chunk,
-                     p_min=p_min)
+    _run_elementwise(oracle, wl, 2, N, 2, flags=_b().RT_FLAG_DEBUG_POISON | (_b().RT_FLAG_ENGINE_STEPWISE if stepwise else 0),
+                     emb_scale=EMB_UNIT, wavefront=True, chunk=chunk, p_min=p_min,
+                     expect_form="groups" if dtype == "bf16" and not stepwise else "launches")
 
 
 def test_poisoned_states_blocked_recurrence(oracle):

@@ -130,16 +130,22 @@ def test_small_fp32_stack_wavefront(oracle, N, chunk, p_min):
     _run_elementwise(oracle, wl, 2, N, 4, emb_scale=EMB_UNIT, wavefront=True, chunk=chunk, p_min=p_min)
 
 
+STEPWISE = 0x2   # RT_FLAG_ENGINE_STEPWISE: a stack runs as launches per position
+
+
+@pytest.mark.parametrize("flags", [STEPWISE, 0])
 @pytest.mark.parametrize("N,chunk", [(200, 0), (300, 128)])
-def test_small_bf16_stack_wavefront(oracle, N, chunk):
+def test_small_bf16_stack_wavefront(oracle, N, chunk, flags):
     """The same on the bf16 path (MFMA tiles with unrounded logit inputs for the blocks inside a chunk and for the
-    keys before it)."""
+    keys before it); and on groups of workgroups, which choose their chunk themselves."""
     wl = gen.Workload("stack_small_bf16_wf", "bf16", 3, N, 256, 4, 1024, layers=4, vocab=1000, decode_steps=4, seed=994)
-    _run_elementwise(oracle, wl, 3, N, 4, emb_scale=EMB_UNIT, wavefront=True, chunk=chunk)
+    _run_elementwise(oracle, wl, 3, N, 4, flags=flags, emb_scale=EMB_UNIT, wavefront=True, chunk=chunk,
+                     expect_form="launches" if flags else "groups")
 
 
-@pytest.mark.parametrize("dtype,N,chunk,p_min", [("f32", 130, 16, 4), ("bf16", 300, 64, 0), ("bf16", 300, 128, 0)])
-def test_stack_wavefront_with_alibi(oracle, dtype, N, chunk, p_min):
+@pytest.mark.parametrize("dtype,N,chunk,p_min,flags", [("f32", 130, 16, 4, 0), ("bf16", 300, 64, 0, STEPWISE), ("bf16", 300, 128, 0, STEPWISE),
+                                                       ("bf16", 300, 64, 0, 0)])
+def test_stack_wavefront_with_alibi(oracle, dtype, N, chunk, p_min, flags):
     """rt_stack_prefill with the linear positional bias (maximum bias 8): blocks inside a chunk, the far tile over
     all earlier keys (bias relative to its last key, moved into each query's frame when stored), decoding after it."""
     if dtype == "f32":
@@ -147,21 +153,23 @@ def test_stack_wavefront_with_alibi(oracle, dtype, N, chunk, p_min):
         _run_elementwise(oracle, wl, 2, N, 4, emb_scale=EMB_UNIT, wavefront=True, chunk=chunk, p_min=p_min, alibi=8.0)
     else:
         wl = gen.Workload("stack_alibi_bf16", "bf16", 3, N, 256, 4, 1024, layers=4, vocab=1000, decode_steps=4, seed=996)
-        _run_elementwise(oracle, wl, 3, N, 4, emb_scale=EMB_UNIT, wavefront=True, chunk=chunk, alibi=8.0)
+        _run_elementwise(oracle, wl, 3, N, 4, flags=flags, emb_scale=EMB_UNIT, wavefront=True, chunk=chunk, alibi=8.0,
+                         expect_form="launches" if flags else "groups")
 
 
 def test_stack_wavefront_batch_tiles(oracle):
     """18 sequences: the matrix-core products then run two batch tiles (16 + a ragged 2), in the stack engine and in the
     decoding steps that follow."""
     wl = gen.Workload("stack_b18_wf", "bf16", 18, 130, 256, 4, 1024, layers=2, vocab=500, decode_steps=2, seed=998)
-    _run_elementwise(oracle, wl, 18, 130, 2, emb_scale=EMB_UNIT, wavefront=True)
+    _run_elementwise(oracle, wl, 18, 130, 2, emb_scale=EMB_UNIT, wavefront=True, expect_form="launches")
 
 
-def test_stack_wavefront_width_768(oracle):
+@pytest.mark.parametrize("flags", [STEPWISE, 0])
+def test_stack_wavefront_width_768(oracle, flags):
     """Two layers of the 150M-like shape (d = 768, 12 heads, hidden 3072): the contraction shares of the matrix-core
     products are then 192 and 768 columns (step pairs outside the blocks of four), batch of 8."""
     wl = gen.Workload("stack_768_wf", "bf16", 8, 200, 768, 12, 3072, layers=2, vocab=500, decode_steps=3, seed=997)
-    _run_elementwise(oracle, wl, 8, 200, 3, emb_scale=EMB_UNIT, wavefront=True)
+    _run_elementwise(oracle, wl, 8, 200, 3, flags=flags, emb_scale=EMB_UNIT, wavefront=True, expect_form="launches" if flags else "groups")
 
 
 def test_stack_prefill_argument_checks():
@@ -229,10 +237,11 @@ def test_config5_reduced_length_elementwise(oracle):
     _run_elementwise(oracle, wl, wl.B, 384, 16, emb_scale=EMB_UNIT)
 
 
-def test_config5_reduced_length_wavefront(oracle):
-    """The same through rt_stack_prefill with the default chunk."""
+@pytest.mark.parametrize("flags", [STEPWISE, 0])
+def test_config5_reduced_length_wavefront(oracle, flags):
+    """The same through rt_stack_prefill, as launches per position with the default chunk and on groups of workgroups."""
     wl = gen.WORKLOADS["cfg5"]
-    _run_elementwise(oracle, wl, wl.B, 384, 16, emb_scale=EMB_UNIT, wavefront=True)
+    _run_elementwise(oracle, wl, wl.B, 384, 16, flags=flags, emb_scale=EMB_UNIT, wavefront=True, expect_form="launches" if flags else "groups")
 
 
 @pytest.mark.parametrize("wavefront", [False, True])
@@ -324,7 +333,7 @@ def test_config5_full_size(variant, emb_scale, attn_scale):
     paper's unscaled logits, and the table as drawn with logits scaled by 1/8 (the table as drawn with unscaled
     logits is ill-conditioned: test_oracle_pins.py).  Beside that, what holds at any size: the two engines agree at
     every position, and prefill + decoding steps agree with one long prefill."""
-    from paper_2604_21215_amd import torch_io as tio
+    from paper_2604_21215_amd import binding, torch_io as tio
     _need_gpu()
     wl = gen.WORKLOADS["cfg5"]
     N, n_dec = wl.N, wl.decode_steps
@@ -358,25 +367,32 @@ def test_config5_full_size(variant, emb_scale, attn_scale):
         print("  [cfg5 %s, prefill of %d, layer by layer, vs oracle rows] %s | logits %.1e" % (variant, N, _fmt(rows), e_log),
               flush=True)
         assert rows.max() <= tol and e_log <= tol
-        # the layer-wavefront engine on the same inputs
+        # all layers in one call on the same inputs: launches per position on a context of their own, then groups of workgroups
         y_seq, K_seq, V_seq = ds.y, ds.K, ds.V
-        logits_wf = ds.prefill(idd, N, kv_cap=T, wavefront=True)
-        torch.cuda.synchronize()
-        assert ctx.engine_name() == "wavefront"
-        rows_wf = _rows_errors(ds, g, 0, N)
-        e_log = _logit_error(logits_wf, g, N - 1)
-        print("  [cfg5 %s, wavefront engine, vs oracle rows] %s | logits %.1e" % (variant, _fmt(rows_wf), e_log), flush=True)
-        assert rows_wf.max() <= tol and e_log <= tol
-        d_seq = np.zeros(3)
-        for l in range(wl.layers):
-            d_seq = np.maximum(d_seq, [rel_err_rows(tio.to_host(ds.y[l]), tio.to_host(y_seq[l])).max(),
-                                       rel_err_rows(tio.to_host(ds.K[l][:N]), tio.to_host(K_seq[l][:N])).max(),
-                                       rel_err_rows(tio.to_host(ds.V[l][:N]), tio.to_host(V_seq[l][:N])).max()])
-        e_lw = rel_err_rows(logits_wf.cpu().numpy().astype(np.float64), logits.cpu().numpy().astype(np.float64)).max()
-        print("  [cfg5 %s, wavefront vs layer-by-layer, all positions] y %.1e K %.1e V %.1e logits %.1e" % (variant, *d_seq, e_lw),
-              flush=True)
-        assert d_seq.max() <= 2 * tol and e_lw <= 2 * tol
-        # decoding continues from the wavefront engine's caches
+        launches = binding.RTContext(wl.d, wl.H, wl.F, wl.B, N, wl.dtype, resid_scale=wl.resid_scale, rms_eps=1e-6, flags=STEPWISE,
+                                     stream=torch.cuda.current_stream().cuda_stream, attn_scale=attn_scale)
+        try:
+            for form, ds.ctx in (("launches", launches), ("groups", ctx)):
+                logits_wf = ds.prefill(idd, N, kv_cap=T, wavefront=True)
+                torch.cuda.synchronize()
+                assert ds.ctx.device_wait_expired() == 0
+                assert ds.ctx.engine_name() == "wavefront" and ds.ctx.engine_form() == form
+                rows_wf = _rows_errors(ds, g, 0, N)
+                e_log = _logit_error(logits_wf, g, N - 1)
+                print("  [cfg5 %s, wavefront engine, %s, vs oracle rows] %s | logits %.1e" % (variant, form, _fmt(rows_wf), e_log), flush=True)
+                assert rows_wf.max() <= tol and e_log <= tol
+                d_seq = np.zeros(3)
+                for l in range(wl.layers):
+                    d_seq = np.maximum(d_seq, [rel_err_rows(tio.to_host(ds.y[l]), tio.to_host(y_seq[l])).max(),
+                                               rel_err_rows(tio.to_host(ds.K[l][:N]), tio.to_host(K_seq[l][:N])).max(),
+                                               rel_err_rows(tio.to_host(ds.V[l][:N]), tio.to_host(V_seq[l][:N])).max()])
+                e_lw = rel_err_rows(logits_wf.cpu().numpy().astype(np.float64), logits.cpu().numpy().astype(np.float64)).max()
+                print("  [cfg5 %s, wavefront engine, %s, vs layer-by-layer, all positions] y %.1e K %.1e V %.1e logits %.1e"
+                      % (variant, form, *d_seq, e_lw), flush=True)
+                assert d_seq.max() <= 2 * tol and e_lw <= 2 * tol
+        finally:
+            launches.rt_destroy()
+        # decoding continues from the caches of the groups
         worst = np.zeros(3)
         worst_o = np.zeros(2)
         for t in range(N, T):
@@ -405,9 +421,10 @@ def test_config5_full_size(variant, emb_scale, attn_scale):
         ctx.rt_destroy()
 
 
-def test_stack_prefill_is_ordered_on_the_callers_stream_and_reserved_scratch_is_not_reallocated(oracle):
+@pytest.mark.parametrize("flags", [STEPWISE, 0])
+def test_stack_prefill_is_ordered_on_the_callers_stream_and_reserved_scratch_is_not_reallocated(oracle, flags):
     """(1) Work enqueued on rt_config.stream right after rt_stack_prefill sees its outputs without any device-wide
-    synchronisation in between, although half of the layers run on a second stream inside the call: copies of the last
+    synchronisation in between, although (as launches per position) half of the layers run on a second stream inside the call: copies of the last
     layer's y, K, V enqueued on the same (non-default) stream directly after the call equal the tensors read back after a
     full synchronisation, and those meet the oracle.  (2) With rt_config.reserve_stack_layers / reserve the scratch of
     rt_stack_prefill, the loop-free layers and the backward pass is allocated by rt_create: the context's workspace size
@@ -420,7 +437,7 @@ def test_stack_prefill_is_ordered_on_the_callers_stream_and_reserved_scratch_is_
     emb = gen.round_to_bf16(tabs["embedding"] * np.float32(EMB_UNIT))
     side = torch.cuda.Stream()   # default priority
     ctx = binding.RTContext(wl.d, wl.H, wl.F, wl.B, wl.N, wl.dtype, resid_scale=wl.resid_scale, rms_eps=1e-6,
-                            stream=side.cuda_stream, reserve_stack_layers=wl.layers, reserve_stack_chunk=64,
+                            stream=side.cuda_stream, reserve_stack_layers=wl.layers, reserve_stack_chunk=64, flags=flags,
                             reserve=binding.RT_RESERVE_LOOP_FREE | binding.RT_RESERVE_BACKWARD)
     try:
         ws0 = ctx.workspace_bytes()
@@ -439,7 +456,7 @@ def test_stack_prefill_is_ordered_on_the_callers_stream_and_reserved_scratch_is_
         side.synchronize()
         snap = [tio.to_host(t) for t in (y_c, K_c, V_c)]
         torch.cuda.synchronize()
-        assert ctx.engine_name() == "wavefront"
+        assert ctx.engine_name() == "wavefront" and ctx.engine_form() == ("launches" if flags else "groups")
         full = [tio.to_host(t) for t in (ds.y[-1], ds.K[-1], ds.V[-1])]
         for a, b in zip(snap, full):
             assert np.array_equal(a, b)

@@ -1,5 +1,6 @@
-"""rt_stack_prefill on several contexts of one process, whose calls take their side streams from one pool: calls of different
-contexts queued behind each other, on different streams and from different threads give what one context alone gives."""
+"""rt_stack_prefill on several contexts of one process: calls of different contexts queued behind each other, on different streams and
+from different threads give what one context alone gives - as launches per position (RT_FLAG_ENGINE_STEPWISE), whose calls take their side
+streams from one pool, and on groups of workgroups."""
 import threading
 
 import pytest
@@ -10,8 +11,9 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 
+@pytest.mark.parametrize("form", ["launches", "groups"])
 @pytest.mark.parametrize("threads", [False, True])
-def test_contexts_share_side_streams(threads):
+def test_contexts_share_side_streams(threads, form):
     from paper_2604_21215_amd import binding, torch_io as tio
     if not torch.cuda.is_available():
         pytest.fail("no GPU visible")
@@ -26,7 +28,8 @@ def test_contexts_share_side_streams(threads):
                 [torch.empty((N, B, 4, 64), dtype=x.dtype, device=x.device) for _ in range(L)])
 
     streams = [torch.cuda.Stream() for _ in range(n)]
-    ctxs = [binding.RTContext(d, 4, 4 * d, B, N, "bf16", resid_scale=0.5, rms_eps=1e-6, reserve_stack_layers=L, stream=s.cuda_stream)
+    ctxs = [binding.RTContext(d, 4, 4 * d, B, N, "bf16", resid_scale=0.5, rms_eps=1e-6, reserve_stack_layers=L, stream=s.cuda_stream,
+                              flags=binding.RT_FLAG_ENGINE_STEPWISE if form == "launches" else 0)
             for s in streams]
     outs = [tensors() for _ in range(n)]
     torch.cuda.synchronize()
@@ -45,6 +48,7 @@ def test_contexts_share_side_streams(threads):
             for k in range(n):
                 go(k)
         torch.cuda.synchronize()
+        assert all(c.engine_form() == form and c.device_wait_expired() == 0 for c in ctxs)
         for k in range(1, n):
             for a, b in zip(outs[0], outs[k]):
                 assert all(torch.equal(p, q) for p, q in zip(a, b))
@@ -54,7 +58,8 @@ def test_contexts_share_side_streams(threads):
             c.rt_destroy()
 
 
-def test_captured_call_replays():
+@pytest.mark.parametrize("form", ["launches", "groups"])
+def test_captured_call_replays(form):
     """a call recorded in a HIP graph: its replays read the tensors of the recorded call whatever ran on the context since, and give the
     eager call's bits on the inputs of the moment"""
     from paper_2604_21215_amd import binding, torch_io as tio
@@ -71,7 +76,8 @@ def test_captured_call_replays():
 
     stream = torch.cuda.Stream()
     with torch.cuda.stream(stream):
-        ctx = binding.RTContext(d, 4, 4 * d, B, N, "bf16", resid_scale=0.5, rms_eps=1e-6, reserve_stack_layers=L, stream=stream.cuda_stream)
+        ctx = binding.RTContext(d, 4, 4 * d, B, N, "bf16", resid_scale=0.5, rms_eps=1e-6, reserve_stack_layers=L, stream=stream.cuda_stream,
+                                flags=binding.RT_FLAG_ENGINE_STEPWISE if form == "launches" else 0)
         try:
             refs = []
             for x in xs:
@@ -88,6 +94,7 @@ def test_captured_call_replays():
                 graph.replay()
                 stream.synchronize()
                 assert all(torch.equal(p, q) for a, b in zip(out, ref) for p, q in zip(a, b))
+            assert ctx.engine_form() == form and ctx.device_wait_expired() == 0
         finally:
             stream.synchronize()
             ctx.rt_destroy()
