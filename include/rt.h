@@ -307,10 +307,18 @@ const char *rt_engine_name(const rt_ctx *ctx);
  * before the first call. */
 const char *rt_engine_form(const rt_ctx *ctx);
 
-/* Diagnostics of the persistent engine, after the stream has been synchronised: when the environment
+/* Diagnostics of the single-launch prefill, after the stream has been synchronised: when the environment
  * variable RT_PERSIST_TRACE was set at rt_create, copies for each of the first `rows` positions sixteen
- * 100 MHz clock stamps of workgroup 0 (slot 0 start, 1..6 end of phases M, cross-block items, O, 1, 2, KV,
- * 7..13 points inside the phases, 14 and 15 the end of the first grid barrier and of the tile work of a cross-block event) into out[rows][16] (host memory).  Returns the number of rows written, 0 if tracing is off. */
+ * 100 MHz clock stamps of workgroup 0 into out[rows][16] (host memory; rows from max_seq on: the same of workgroup
+ * RT_PERSIST_TRACE_WG, default the last).
+ * On groups of workgroups (the first group's workgroups): 0 start of the position, 1 attention output received, 2 its product summed,
+ * 3 h sent, 4 h received, 5 W1's product summed, 6 u sent, 7 a barrier later, 8 u received, 9 W2's product summed, 10 z sent,
+ * 11 z received, 12 the product of [Wk; Wv] summed, 13 raw keys and values sent, 14 the next position's attention output sent (phase M),
+ * 15 a barrier later.  Cross-block events lie between stamp 15 and the next position's 0.  After rt_stack_prefill the rows are those of the
+ * last layer that the first group ran.
+ * As one launch of all workgroups (p_min 64 and more): 0 start, 1..6 end of phases M, cross-block items, O, 1, 2, KV,
+ * 7..13 points inside the phases, 14 and 15 the end of the first grid barrier and of the tile work of a cross-block event.
+ * Returns the number of rows written, 0 if tracing is off; fp32 contexts have none. */
 int32_t rt_phase_trace(rt_ctx *ctx, uint64_t *out, int32_t rows);
 
 /* Diagnostics of the single-launch decoding step, after the stream has been synchronised: when the environment variable

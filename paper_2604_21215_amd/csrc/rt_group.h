@@ -73,7 +73,7 @@ size_t group_bytes(const GroupState &P);
 bool group_supported(const GroupState &P, const LayerDims &D);
 // gains: W1 and [Wk; Wv] multiplied by g_mlp and g_kv
 hipError_t group_pack(const LayerDims &D, const Weights &W, bf16_t *packed, bool gains, hipStream_t st);
-// launches the loop for the work items in A.w (the other fields of A are filled here); hp: the kernels with head and remainder;
+// launches the loop for the work items in A.w (the caller sets them, the tensors' strides and the stamps' place, the rest of A is filled here); hp: the kernels with head and remainder;
 // first: the first launch of a call, which alone clears the abort words
 rt_status group_launch(GroupState &P, const LayerDims &D, GroupArgs &A, bool hp, bool first, hipStream_t st, std::string &err);
 bool group_stack_kernels(int device, const LayerDims &D);   // readies those

@@ -882,7 +882,7 @@ rt_status group_launch(GroupState &P, const LayerDims &D, GroupArgs &A, bool hp,
     A.p_min = D.p_min; A.log2_pmin = D.log2_pmin; A.win_rows = P.win_rows;
     A.alpha = D.alpha; A.scale = D.scale; A.eps = D.eps; A.alibi = D.alibi; A.norm_free = D.norm_free;
     A.spin_limit = P.spin.of_launch(); A.bar = P.bar; A.words = P.words; A.group_stride = P.group_stride;
-    A.trace = P.trace; A.trace_rows = P.trace_rows;
+    A.trace_rows = P.trace_rows;
     const char *tw = getenv("RT_PERSIST_TRACE_WG");
     A.trace_rank = tw ? atoi(tw) : kGroupRanks - 1;
     // Waits before the first polls of phases O, 1, 2, KV in units of 4 x 64 clocks (RT_GROUP_SLEEPS, four digits, overrides them).
@@ -923,6 +923,7 @@ rt_status group_prefill(GroupState &P, const LayerDims &D, const Weights &W, con
     if (e != hipSuccess) { err = std::string("group_pack_kernel: ") + hipGetErrorString(e); return RT_ERR_HIP; }
     GroupArgs A = {};
     A.rows = D.N; A.BH = D.B * D.H;
+    A.trace = P.trace;
     A.vt_stride = S.vt_stride; A.levels = S.levels; A.slots = S.slots;
     for (int g = 0; g < kGroups; ++g) {
         GroupWork &w = A.w[g];

@@ -183,6 +183,7 @@ rt_status group_stack_prefill(GroupStackState &T, GroupState &P, const LayerDims
             E.Kh = (const bf16_t *)Y.S.Kh; E.VT = Y.S.VT;
             E.far_m = T.far_m + slot * far_set; E.far_l = T.far_l + slot * far_set; E.far_o = T.far_o + slot * far_set * kHeadDim;
             E.t0 = t0; E.n = n;
+            if (slot == 0 && P.trace) A.trace = P.trace + (size_t)t0 * 16;   // rows are positions, of the last layer that group 0 ran
             if (l > 0) pre.e[n_pre++] = E;
             if (t0 > 0) far.e[n_far++] = E;
             longest = n > longest ? n : longest;

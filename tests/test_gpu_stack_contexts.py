@@ -98,3 +98,26 @@ def test_captured_call_replays(form):
         finally:
             stream.synchronize()
             ctx.rt_destroy()
+
+
+@pytest.mark.parametrize("L", [3, 6])
+def test_phase_stamps_of_a_stack(monkeypatch, L):
+    """rt_phase_trace after a stack on groups: a row per position of the last layer that the first group ran, not one per position of a chunk"""
+    from paper_2604_21215_amd import binding, torch_io as tio
+    if not torch.cuda.is_available():
+        pytest.fail("no GPU visible")
+    B, N, d = 2, 150, 256
+    monkeypatch.setenv("RT_PERSIST_TRACE", "1")
+    ctx = binding.RTContext(d, 4, 4 * d, B, N, "bf16", resid_scale=0.5, rms_eps=1e-6, reserve_stack_layers=L)
+    try:
+        dl = tio.DeviceLayer(gen.make_layer_weights(98, 0, d, 4 * d, "bf16"), None, "bf16")
+        x = tio.to_device(gen.make_custom(99, "bf16", B, N, d, 4, 4 * d).x, "bf16")
+        y, K, V = ([torch.zeros(s, dtype=x.dtype, device=x.device) for _ in range(L)] for s in ((B, N, d), (N, B, 4, 64), (N, B, 4, 64)))
+        torch.cuda.synchronize()
+        ctx.rt_stack_prefill([dl.struct] * L, x, y, K, V)
+        torch.cuda.synchronize()
+        assert ctx.engine_form() == "groups"
+        rows = ctx.phase_trace(N).astype("int64").reshape(-1)
+        assert rows.size == 16 * N and rows[0] > 0 and (rows[1:] >= rows[:-1]).all()
+    finally:
+        ctx.rt_destroy()
