@@ -74,9 +74,10 @@ def algorithmic_bytes(B, N, d, H, F, E, p_min, weights_resident):
 
 
 def stack_section(stream, layer_by_layer=True, reps=2, alibi=0.0, layers=0, positions=0):
-    """The 12-layer stack workload (cfg5: B = 4, N = 4096) through the layer-wavefront engine (rt_stack_prefill: the
-    layers run concurrently, a chunk of positions apart) and, for comparison, layer by layer (12 x rt_layer_prefill).
-    Its bound is the weight stream: every (layer, position) reads the layer's five loop matrices once."""
+    """The 12-layer stack workload (cfg5: B = 4, N = 4096) through rt_stack_prefill (the layers run concurrently, a chunk of
+    positions apart) and, for comparison, layer by layer (12 x rt_layer_prefill).  As launches per position its bound is the
+    weight stream: every (layer, position) reads the layer's five loop matrices once.  On groups of workgroups the matrices
+    stay on chip for a chunk and the chain of exchanges bounds it: the bytes given are then those no form can do without."""
     import numpy as np
     import torch
     from paper_2604_21215_amd import binding, inputs as gen, torch_io as tio
@@ -104,17 +105,20 @@ def stack_section(stream, layer_by_layer=True, reps=2, alibi=0.0, layers=0, posi
         return (time.perf_counter() - t0) / reps
 
     t_wf = timed(reps, wavefront=True)
-    w_bytes = float(ws.N) * ws.layers * (3 * ws.d * ws.d + 2 * ws.d * ws.F) * 2
+    groups = sctx.engine_form() == "groups"
+    matrices = 3 * ws.d * ws.d + 2 * ws.d * ws.F
+    w_bytes = 2.0 * ws.layers * (matrices + 3 * ws.B * ws.N * ws.d if groups else ws.N * matrices)
     sec = {
         "workload": "cfg5: %d RT layers, bf16, B=%d, N=%d, d_model=%d, embedding + read-out included"
                     % (ws.layers, ws.B, ws.N, ws.d),
         "us_per_step": t_wf * 1e6 / (ws.N + (ws.layers - 1) * 64),
         "ms_per_prefill": t_wf * 1e3, "tokens_per_s": ws.B * ws.N / t_wf,
         "layer_tokens_per_s": ws.B * ws.N * ws.layers / t_wf,
-        "bound": "hbm", "algorithmic_bytes": w_bytes, "achieved": w_bytes / t_wf / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+        "form": sctx.engine_form(),
+        "bound": "latency" if groups else "hbm", "algorithmic_bytes": w_bytes, "achieved": w_bytes / t_wf / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
         "frac": w_bytes / t_wf / 1e9 / HBM_PEAK_GBS,
-        "note": "algorithmic bytes = the loop matrices (3 d^2 + 2 d F elements) once per layer and position; "
-                "host-timed over whole calls",
+        "note": "algorithmic bytes = the loop matrices (3 d^2 + 2 d F elements) once per layer%s; host-timed over whole calls"
+                % (", the layers' outputs and pairs" if groups else " and position"),
     }
     if layer_by_layer:
         t_seq = timed(1)
@@ -251,7 +255,8 @@ def main():
 
     E = 2 if wl.dtype == "bf16" else 4
     p_min = ctx.cfg.p_min if ctx.cfg.p_min else 32
-    resident = engine == "persistent"
+    form = ctx.engine_form()
+    resident = form != "launches"   # one launch per call, weights on chip
     terms = algorithmic_bytes(wl.B, wl.N, wl.d, wl.H, wl.F, E, p_min, resident)
     streamed = algorithmic_bytes(wl.B, wl.N, wl.d, wl.H, wl.F, E, p_min, False)
     design_bytes = sum(terms.values())
@@ -263,7 +268,7 @@ def main():
     roofline = {
         "bound": "hbm",
         "kernel": ("%s (one launch per call; the call's two small pre-pass kernels are inside the timed events)"
-                   % ("group_kernel" if p_min == 32 else "persistent_kernel")
+                   % ("persistent_kernel" if form == "one-launch" else ("group_kernel" if wl.dtype == "bf16" else "group_f32_kernel"))
                    if resident else "rt_layer_prefill (%s engine, all launches of one call)" % engine),
         "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": achieved / HBM_PEAK_GBS,
         "traffic": traffic["bytes"] if traffic else None, "traffic_source": traffic,

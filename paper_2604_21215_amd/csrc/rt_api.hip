@@ -246,12 +246,14 @@ static void fill_dims(LayerDims &D, const rt_config &cfg, int p_min)
 static rt_status stack_workspace(rt_ctx *c, int L, int chunk);
 // rt_layer_prefill for more rows than the single-launch engine stages.  Three ways, ms per call on MI355X at d = 1024, 512 positions
 // (in brackets d = 512, 128 positions), B = 33 / 48 / 64 / 96 / 128 / 160 / 192:
-//   chunks of 16 rows on that engine                14.2 / 14.6                                     (2.94 / 2.97)
+//   chunks of 16 rows on that engine                13.7 / 14.6 / 19.5 / 29.2                       (2.92 / 2.91 / 3.88 / 5.82)
 //   one layer on the layer-wavefront engine         18.7 / 19.4 / 20.7 / 21.8 / 23.4 / 27.5 / 29.0   (3.56 / 3.62 / 3.63 / 3.83 / 4.00 / 4.15 / 4.33)
 //   one position of all sequences per step          26.1 / 26.5 / 27.0 / 27.9 / 28.8 / 29.6 / 30.7   (4.59 / 4.67 / 4.71 / 4.79 / 4.87 / 5.10 / 5.27)
 // The steps at once take over where the chunks fall behind them; the lines of the layer-wavefront engine were drawn with the kernels
 // before its products took 32 sequences per workgroup (49.2 ms at B = 160) and with chunks on all 256 workgroups (22.6 / 23.5 / 31.4 ms
-// at B = 33 / 48 / 64): now it leads from 49 to 192 rows.  The third row is with the products from LDS throughout (step_products in rt_parallel.hip takes them from 129 rows on).
+// at B = 33 / 48 / 64): now it leads from 49 to 192 rows, but for 49 to 64 at d = 1024 (B = 49 / 64: chunks 19.1 / 19.5, this
+// engine 19.7 / 20.6; d = 768 17.6 / 18.1 and 17.4 / 18.2; d = 256 14.2 / 14.3 and 12.4 / 12.4).  There the line stays for the operands: this engine
+// feeds its products head and remainder, the chunks one bf16.  The third row is with the products from LDS throughout (step_products in rt_parallel.hip takes them from 129 rows on).
 constexpr int kBatchedFrom = 81;
 constexpr int kWaveFrom = 49, kWaveTo = 128;
 
@@ -775,8 +777,9 @@ static rt_status decode_impl(rt_ctx *c, const LayerDims &D, const rt_layer_weigh
     const Weights W = to_weights(w);
     hipStream_t st = c->stream;
     // up to three times the rows the single launch takes: one launch per chunk of those rows (batch rows are independent).  MI355X,
-    // d = 1024, t = 511, us in chunks / as eight launches: B = 17 61 / 68, B = 32 61 / 74, B = 33 92 / 75, B = 48 92 / 79 (85 and more before
-    // the eight took 32 sequences per workgroup, when the line was drawn), B = 64 126 / 84
+    // t = 511, us in chunks / as eight launches: d = 1024, B = 17 61 / 67, B = 32 61 / 79, B = 33 91 / 68, B = 48 92 / 71; d = 768 56 / 57,
+    // 57 / 66, 84 / 61, 85 / 64; d = 512 45 / 46, 44 / 50, 68 / 49, 66 / 51; d = 256 43 / 37, 40 / 37, 63 / 38, 61 / 38.  The line is from
+    // when the eight took 85 us and more at d = 1024; with products of 32 sequences per workgroup they lead from 33 rows on, and at d = 256 from 17.
     if (sizeof(T) == 2 && c->dec.available && D.B > c->dec.max_batch && D.B <= 3 * c->dec.max_batch) {
         WaitingLaunches::Turn turn(g_order, c->cfg.device, c, c->stream);
         c->form = kFormOne;
