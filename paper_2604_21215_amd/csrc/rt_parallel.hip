@@ -1203,6 +1203,12 @@ bool parallel_supported(const LayerDims &D, bool mfma_bf16) { return mfma_bf16 &
 
 size_t parallel_scratch_bytes(size_t M, size_t d, size_t F) { return M * d * 2 + M * d * 4 + M * d * 2 + M * F * 2 + 1024; }
 
+// Whether the loop-free layers' pre-pass writes the pairs and the keys' copies itself.  For few rows of a narrow layer its extra stores
+// take longer than an export launch behind it (us per rt_transformer_layer, export / itself: 64 rows, d = 256 51.8 / 53.3, d = 512
+// 64.9 / 66.4; 1000 rows, d = 256 80.4 / 81.9, d = 512 111.8 / 113.5; 2000 rows, d = 384 104.2 / 105.6; but 2048 rows, which take the
+// LDS-tiled pre-pass, d = 256 90.1 / 90.2, d = 512 117.5 / 116.3, 16384 rows, d = 512 373 / 352; 400 rows, d = 768 114.8 / 114.2, d = 1024 150.2 / 148.5).
+static bool pairs_from_prepass(int d, int M) { return d > 512 || M >= 2048; }
+
 // pairs_src: the rows the persistent pairs are projected from (z for the recompute, x for the Transformer layer);
 // pairs_gain: the RMS gain that goes with them (g_kv or g_attn).  par: parallel_scratch_bytes(B * N, d, F) bytes.
 hipError_t parallel_layer(const LayerDims &D, const Weights &W, const Scratch &S, const void *x, const void *pairs_src,
@@ -1218,17 +1224,24 @@ hipError_t parallel_layer(const LayerDims &D, const Weights &W, const Scratch &S
 
     Weights Wp = W;
     if (!pairs_are_temporary) Wp.g_attn = W.g_kv;
-    // The pre-pass writes the pairs straight into the cache rows (the same layout) and the keys' copies beside them; only the transposed
-    // values take a pass of their own.  (An export pass over everything read 133 and wrote 167 MB at 16384 rows, d = 1024: 62 us; now
-    // 17, and 10 more in the pre-pass.)  Pairs that come from z want neither queries nor unrounded temporary keys: a third of that product is not formed.
-    Scratch Sp = S;
-    Sp.Q = nullptr; Sp.Kt = K; Sp.Vt = V;
-    if (!pairs_are_temporary) { Sp.Qf = nullptr; Sp.Ktf = nullptr; }
-    const PrepassPairs pairs = {S.Klo, S.Kh, !pairs_are_temporary};
-    hipError_t e = Launch<bf16_t>::prepass(D, Wp, Sp, pairs_src, B, N, true, st, 0, 0, &pairs);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(par_vt_tile_kernel, dim3(BH, (N + 63) / 64), dim3(256), 0, st, (const bf16_t *)V, S.VT, S.vt_stride, BH, N);
-    const bf16_t *vt_own = pairs_are_temporary ? (const bf16_t *)V : (const bf16_t *)S.Vt;   // the queries' own temporary values
+    hipError_t e;
+    const bf16_t *vt_own = (const bf16_t *)S.Vt;   // the queries' own temporary values
+    if (pairs_from_prepass(d, M)) {
+        // The pre-pass writes the pairs straight into the cache rows (the same layout) and the keys' copies beside them; only the transposed
+        // values take a pass of their own.  (An export pass over everything read 133 and wrote 167 MB at 16384 rows, d = 1024: 62 us; now
+        // 17, and 10 more in the pre-pass.)  Pairs that come from z want neither queries nor unrounded temporary keys: a third of that product is not formed.
+        Scratch Sp = S;
+        Sp.Q = nullptr; Sp.Kt = K; Sp.Vt = V;
+        if (!pairs_are_temporary) { Sp.Qf = nullptr; Sp.Ktf = nullptr; }
+        const PrepassPairs pairs = {S.Klo, S.Kh, !pairs_are_temporary};
+        if ((e = Launch<bf16_t>::prepass(D, Wp, Sp, pairs_src, B, N, true, st, 0, 0, &pairs)) != hipSuccess) return e;
+        hipLaunchKernelGGL(par_vt_tile_kernel, dim3(BH, (N + 63) / 64), dim3(256), 0, st, (const bf16_t *)V, S.VT, S.vt_stride, BH, N);
+        if (pairs_are_temporary) vt_own = (const bf16_t *)V;
+    } else {
+        if ((e = Launch<bf16_t>::prepass(D, Wp, S, pairs_src, B, N, true, st)) != hipSuccess) return e;
+        hipLaunchKernelGGL(par_export_tile_kernel, dim3(BH, (N + 63) / 64), dim3(256), 0, st, (const bf16_t *)S.Kt, S.Ktf,
+                           (const bf16_t *)S.Vt, (bf16_t *)K, (bf16_t *)V, S.Klo, S.Kh, S.VT, S.vt_stride, BH, N);
+    }
     if (!pairs_are_temporary) {
         e = Launch<bf16_t>::prepass(D, W, S, x, B, N, true, st);
         if (e != hipSuccess) return e;

@@ -33,6 +33,8 @@ def _check(name, x64, ref, got, tol):
 
 @pytest.mark.parametrize("B,N,d,H,F,alibi,gains,alpha,scale", [
     (2, 200, 256, 4, 1024, 0.0, "unit", 1.0, 1.0),
+    (3, 77, 576, 9, 2304, 8.0, "random", 0.7, 0.5),        # pairs written by the pre-pass without LDS tiles, odd head count
+    (1, 2047, 256, 4, 1024, 0.0, "random", 0.7, 0.5),      # the longest that exports them
     (3, 333, 320, 5, 1280, 8.0, "random", 0.7, 0.5),       # odd head count, ragged N, bias, gains
     (2, 700, 1024, 16, 4096, 0.0, "unit", 1.0, 1.0),       # blocks up to 512 keys, several query workgroups
     (1, 33, 256, 4, 1024, 0.0, "unit", 1.0, 1.0),
@@ -84,6 +86,7 @@ def test_recompute_of_an_arbitrary_z_and_of_the_prefill_output(oracle):
 
 @pytest.mark.parametrize("B,N,d,H,F,alibi", [(2, 200, 256, 4, 1024, 0.0), (3, 333, 320, 5, 1280, 8.0), (2, 600, 1024, 16, 4096, 0.0),
                                                (6, 450, 384, 6, 1536, 0.0),    # 2700 rows: the LDS-tiled products
+                                               (3, 77, 576, 9, 2304, 8.0),     # pairs written by the pre-pass without LDS tiles
                                                (2, 1, 256, 4, 1024, 0.0),      # a single position: only the temporary pair
                                                (2, 128, 256, 4, 1024, 8.0),    # exactly one query tile of the masked pass
                                                (2, 129, 256, 4, 1024, 8.0)])   # ... and one position more
