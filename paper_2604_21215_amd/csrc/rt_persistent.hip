@@ -840,14 +840,20 @@ rt_status persistent_prefill(PersistentState &P, const LayerDims &D, const Weigh
         const char *tw = getenv("RT_PERSIST_TRACE_WG");
         A.trace_wg = tw ? atoi(tw) : P.grid - 1;
     }
-    P.nonce = (P.nonce % 4095u) + 1u;          // 1..4095; fresh buffers hold tag 0
-    A.tag_base = P.nonce << 20;
-    // When the nonce has wrapped, words left by a call 4095 calls ago (rows of a larger batch, positions of a longer sequence)
+    // 1..4094 in turn; fresh buffers hold tag 0.  A captured launch is replayed with the number it was captured with: it has 4095 for its
+    // own and clears all words first, so that a replay waits for its own words and not for those of the one before.
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    hipError_t e = st ? hipStreamIsCapturing(st, &capturing) : hipSuccess;
+    if (e != hipSuccess) { err = std::string("hipStreamIsCapturing: ") + hipGetErrorString(e); return RT_ERR_HIP; }
+    const bool captured = capturing != hipStreamCaptureStatusNone;
+    if (!captured) P.nonce = (P.nonce % 4094u) + 1u;
+    A.tag_base = (captured ? 4095u : P.nonce) << 20;
+    // When the nonce has wrapped, words left by a call 4094 calls ago (rows of a larger batch, positions of a longer sequence)
     // could carry this call's tags: all of them are cleared (the counters come first), else the counters alone.
-    const bool all = P.nonce == 1u && P.launched;
+    const bool all = captured || (P.nonce == 1u && P.launched);
     hipLaunchKernelGGL(clear_words_kernel, dim3(all ? 256 : 1), dim3(all ? 256 : 64), 0, st, P.bar, all ? P.exchange_bytes / 8 : 32,
                        first ? 0 : 1);
-    hipError_t e = hipGetLastError();
+    e = hipGetLastError();
     if (e != hipSuccess) { err = std::string("clear_words_kernel: ") + hipGetErrorString(e); return RT_ERR_HIP; }
     void *args[] = {&A};
     A.alibi = D.alibi;
