@@ -120,7 +120,7 @@ rt_status rt_create(const rt_config *cfg, rt_ctx **out);
  *   y [B, N, d]  device, written
  *   K, V [kv_cap, B, H, head_dim] device, position first (Sec. 6.3); rows 0..N-1 are written in place
  *   1 <= B <= max_batch, 1 <= N <= max_seq, N <= kv_cap.
- * fp32 storage with d_model 128, 256 or 384, d_hidden = 4 d_model, p_min 32 and at most 32 (d_model 384: 16) rows runs as one cooperative
+ * fp32 storage with d_model 128, 256 or 384, d_hidden = 4 d_model, p_min 32, at most 32 (d_model 384: 16) rows and N >= 2 (3) runs as one cooperative
  * launch (fp32 products on the matrix cores; not with RT_FLAG_NO_MFMA, RT_FLAG_HIP_GRAPH or RT_FLAG_ENGINE_STEPWISE).  Batch rows are independent; where the single-launch engine applies (bf16) it stages at most 16 of them, and a larger
  * batch runs as chunks of 16 rows one after the other on the stream, each chunk's pairs copied into K, V from a
  * buffer of 2 * max_seq * 16 * d elements that rt_create allocates when max_batch > 16.  With bf16 and the matrix-core
@@ -180,7 +180,7 @@ rt_status rt_decode_step_static(const rt_config *cfg, const rt_layer_weights *w,
  * units and up to sixteen sequences: four layers at a time (two, one for more than four, eight
  * sequences) with their weights on chip, one cooperative launch per step of a chunk whose length the call chooses (64 to 256
  * positions; `chunk` is checked and not used), on rt_config.stream alone.  Everything else, RT_FLAG_ENGINE_STEPWISE, and stacks so deep
- * that the layers one after the other take longer (where their passes times N exceed 3.1 (N + 64 (L - 1)), at d_model 1024 4.4 times):
+ * that the layers one after the other take longer (where their passes times N exceed 3.1 (N + 64 (L - 1)), at d_model 1024 4.4 times), or one layer's first two positions:
  * launches per position that carry all layers.  Both forms feed their products bf16 head and remainder of each vector, and the
  * weights as they are.
  * Unless rt_config.reserve_stack_layers reserved them at rt_create, the first call allocates one scratch set per layer

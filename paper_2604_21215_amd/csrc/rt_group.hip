@@ -863,7 +863,10 @@ size_t group_bytes(const GroupState &P) { return P.slab ? P.slab_bytes : 0; }
 
 bool group_supported(const GroupState &P, const LayerDims &D)
 {
-    return P.available && D.B <= P.max_batch && D.N >= 1 && D.N < (1 << 20) - 2;
+    // Laying out the weights (d = 1024: 12 us) takes longer than the groups save on the first positions (us per call, all workgroups /
+    // groups, B = 1 .. 16): N = 1 56 - 92 / 58 - 103 at every width; N = 2 d = 256 68 / 65, d = 512 78 / 76, d = 768 91 - 100 / 91 - 100, d = 1024
+    // 103 - 111 / 104 - 115; N = 3, d = 1024, B = 16 130 / 129, N = 4 130 / 121
+    return P.available && D.B <= P.max_batch && D.N >= (D.d == 1024 ? 3 : 2) && D.N < (1 << 20) - 2;
 }
 
 hipError_t group_pack(const LayerDims &D, const Weights &W, bf16_t *packed, bool gains, hipStream_t st)

@@ -553,7 +553,9 @@ void group_f32_destroy(GroupF32State &P)
 
 bool group_f32_supported(const GroupF32State &P, const LayerDims &D)
 {
-    return P.available && D.B <= P.max_batch && D.N >= 1 && D.N < (1 << 20) - 2;
+    // the first positions do not pay for laying out the weights (us per call, launches per position / here, B = 2): N = 1 54 / 63, 73 / 87 and
+    // 93 / 127 at d = 128, 256, 384; N = 2 88 / 70, 106 / 95 and 124 / 136; N = 3, d = 384 155 / 144
+    return P.available && D.B <= P.max_batch && D.N >= (D.d == 384 ? 3 : 2) && D.N < (1 << 20) - 2;
 }
 
 rt_status group_f32_prefill(GroupF32State &P, const LayerDims &D, const Weights &W, const Scratch &S, const void *x, void *y, void *K, void *V,

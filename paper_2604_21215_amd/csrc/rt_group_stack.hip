@@ -130,6 +130,8 @@ bool group_stack_supported(const GroupStackState &T, const GroupState &P, const 
     //   d = 1024: up to 3.5 1.21 - 4.0, 4.4 - 5.2 0.99 - 1.16
     // (0.76: d = 768, B = 5, N = 4096, 12 layers, 208.6 / 275.3 ms; 4.0: one layer, B = 16, N = 2048, 101.9 / 25.4 ms.)
     if (!T.slab || !P.available || D.B > kGroups * kGroupRows || D.N >= (1 << 20) - 2) return false;
+    // one layer and one or two positions: 58 - 104 us as launches, 68 - 120 here at N = 1; B = 1, N = 2, d = 1024 129 / 131, but B = 16 187 / 148
+    if (L == 1 && D.N < (D.B <= kGroupRows ? 3 : 2)) return false;
     const int slots = kGroups / splits_for(D.B, L);
     const long long here = (long long)((L + slots - 1) / slots) * D.N, steps = D.N + 64LL * (L - 1);
     return 10 * here <= (D.d == 1024 ? 44 : 31) * steps;

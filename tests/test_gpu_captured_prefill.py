@@ -9,7 +9,7 @@ torch = pytest.importorskip("torch")
 
 
 @pytest.mark.parametrize("dtype,B,N,d,p_min,form", [
-    ("bf16", 2, 70, 256, 0, "groups"), ("bf16", 17, 40, 256, 0, "groups"), ("bf16", 3, 150, 256, 64, "one-launch"),
+    ("bf16", 2, 70, 256, 0, "groups"), ("bf16", 17, 40, 256, 0, "groups"), ("bf16", 2, 2, 1024, 0, "one-launch"), ("bf16", 3, 150, 256, 64, "one-launch"),
     ("f32", 2, 70, 256, 0, "groups"), ("f32", 2, 70, 256, 16, "launches")])
 def test_replays(dtype, B, N, d, p_min, form):
     from paper_2604_21215_amd import binding, torch_io as tio

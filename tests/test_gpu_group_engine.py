@@ -18,6 +18,11 @@ def test_rows_per_group(oracle, d, B, N, alibi):
               expect_engine="persistent", expect_form="groups")
 
 
+@pytest.mark.parametrize("B,N,d,form", [(2, 1, 256, "one-launch"), (2, 2, 256, "groups"), (9, 2, 1024, "one-launch"), (1, 3, 1024, "groups")])
+def test_first_positions(oracle, B, N, d, form):
+    _run_case(oracle, "bf16", B, N, d, d // 64, 4 * d, gains="random", scale=0.5, alpha=0.7, expect_engine="persistent", expect_form=form)
+
+
 @pytest.mark.parametrize("B,N,alibi", [(5, 1100, 0.0), (2, 1290, 8.0)])
 def test_blocks_of_up_to_1024_keys(oracle, B, N, alibi):
     _run_case(oracle, "bf16", B, N, 256, 4, 1024, gains="random", scale=0.125, alibi=alibi, expect_engine="persistent",
@@ -34,7 +39,7 @@ def test_windows_that_keep_the_other_form(oracle, B, N, d, p_min):
 
 @pytest.mark.parametrize("B,N,layers,d,alibi", [
     (1, 65, 1, 256, 0.0), (3, 64, 2, 512, 8.0), (4, 300, 5, 256, 0.0), (5, 129, 3, 768, 0.0), (8, 200, 4, 256, 8.0),
-    (9, 130, 2, 256, 0.0), (16, 70, 6, 256, 8.0), (12, 70, 7, 256, 0.0)])
+    (9, 130, 2, 256, 0.0), (16, 2, 1, 256, 0.0), (1, 3, 1, 256, 8.0), (3, 1, 5, 256, 0.0), (16, 70, 6, 256, 8.0), (12, 70, 7, 256, 0.0)])
 def test_stack(oracle, B, N, layers, d, alibi):
     """four, two or one layer at a time, more layers than run at once, chunks with a ragged last one"""
     wl = gen.Workload("stack_groups", "bf16", B, N, d, d // 64, 4 * d, layers=layers, vocab=300, decode_steps=2, seed=990 + B)
@@ -52,26 +57,26 @@ def test_stack_with_longer_chunks(oracle, monkeypatch, chunk, B, N, layers, alib
 
 
 @pytest.mark.parametrize("B,N,layers,d,F,p_min", [(17, 70, 2, 256, 1024, 0), (2, 70, 3, 256, 512, 0), (2, 150, 3, 256, 1024, 64),
-                                                  (9, 290, 8, 256, 1024, 0), (9, 100, 8, 256, 1024, 0)])
+                                                  (9, 290, 8, 256, 1024, 0), (9, 100, 8, 256, 1024, 0), (1, 2, 1, 256, 1024, 0), (16, 1, 1, 256, 1024, 0)])
 def test_stacks_that_keep_the_launches(oracle, B, N, layers, d, F, p_min):
     """more than sixteen sequences, another hidden width, a wider window, and on either side of where passes over the layers take
-    longer than launches that carry all of them: 8 * 290 > 3.1 (290 + 64 * 7), 8 * 100 < 3.1 (100 + 64 * 7)"""
+    longer than launches that carry all of them: 8 * 290 > 3.1 (290 + 64 * 7), 8 * 100 < 3.1 (100 + 64 * 7); one layer's first positions"""
     wl = gen.Workload("stack_launches", "bf16", B, N, d, d // 64, F, layers=layers, vocab=300, decode_steps=2, seed=970 + B)
     passes, steps = -(-layers // (4 if B <= 4 else 1)) * N, N + 64 * (layers - 1)
     deep = 10 * passes > 31 * steps
-    refused = B > 16 or F != 4 * d or p_min == 64
+    refused = B > 16 or F != 4 * d or p_min == 64 or layers == 1
     _run_elementwise(oracle, wl, B, N, 2, emb_scale=EMB_UNIT, wavefront=True, p_min=p_min,
                      expect_form="launches" if refused or deep else "groups")
 
 
-@pytest.mark.parametrize("B,N,d,alibi", [(1, 1, 128, 0.0), (2, 34, 256, 8.0), (3, 65, 384, 0.0), (8, 130, 128, 8.0), (9, 66, 256, 0.0),
+@pytest.mark.parametrize("B,N,d,alibi", [(1, 2, 128, 0.0), (2, 34, 256, 8.0), (3, 65, 384, 0.0), (8, 130, 128, 8.0), (9, 66, 256, 0.0),
                                          (16, 97, 384, 8.0), (4, 290, 256, 0.0), (1, 515, 128, 0.0), (32, 40, 128, 0.0)])
 def test_fp32(oracle, B, N, d, alibi):
     """fp32 storage: one sequence per group and several, widths whose share of a contraction ends inside a chunk, blocks of 32 to 512 keys"""
     _run_case(oracle, "f32", B, N, d, d // 64, 4 * d, gains="random", scale=0.5, alpha=0.7, alibi=alibi, kv_cap=N + 1, expect_form="groups")
 
 
-@pytest.mark.parametrize("B,N,d,F,p_min", [(33, 40, 128, 512, 32), (17, 40, 384, 1536, 32), (2, 40, 512, 2048, 32), (2, 40, 256, 512, 32), (2, 70, 256, 1024, 16)])
+@pytest.mark.parametrize("B,N,d,F,p_min", [(1, 1, 128, 512, 32), (2, 2, 384, 1536, 32), (33, 40, 128, 512, 32), (17, 40, 384, 1536, 32), (2, 40, 512, 2048, 32), (2, 40, 256, 512, 32), (2, 70, 256, 1024, 16)])
 def test_fp32_shapes_that_keep_the_launches(oracle, B, N, d, F, p_min):
     _run_case(oracle, "f32", B, N, d, d // 64, F, p_min=p_min, gains="random", scale=0.5, alpha=0.7, expect_engine="stepwise",
               expect_form="launches")
