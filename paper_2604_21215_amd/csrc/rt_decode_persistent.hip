@@ -687,15 +687,22 @@ rt_status decode_coop_step(DecodeCoopState &P, const LayerDims &D, const Weights
     A.pre_sleep = 2;   // units of 4 x 64 clocks
     A.trace = P.want_trace ? (unsigned long long *)(p + s.trace) : nullptr;
     // every word of the slab is written at most once per call and carries the call's number; when the numbers start
-    // over, no word of an earlier call may survive (the abort word at bar[8] is only ever set, never cleared here)
-    if (P.nonce == 0xFFFFFFFFu) {
+    // over, no word of an earlier call may survive (the abort word at bar[8] is only ever set, never cleared here).  A captured
+    // launch is replayed with the number it was captured with: it has the last one for its own and clears the words first.
+    hipStreamCaptureStatus capturing = hipStreamCaptureStatusNone;
+    if (st) {
+        const hipError_t ce = hipStreamIsCapturing(st, &capturing);
+        if (ce != hipSuccess) { err = std::string("hipStreamIsCapturing: ") + hipGetErrorString(ce); return RT_ERR_HIP; }
+    }
+    const bool captured = capturing != hipStreamCaptureStatusNone;
+    if (captured || P.nonce == 0xFFFFFFFEu) {
         hipLaunchKernelGGL(dec_clear_kernel, dim3(256), dim3(256), 0, st, (unsigned long long *)(p + s.qkv), (s.trace - s.qkv) / 8);
         hipError_t ce = hipGetLastError();
         if (ce != hipSuccess) { err = std::string("dec_clear_kernel: ") + hipGetErrorString(ce); return RT_ERR_HIP; }
-        P.nonce = 0;
+        if (!captured) P.nonce = 0;
     }
-    P.nonce += 1;
-    A.tag = P.nonce;
+    if (!captured) P.nonce += 1;
+    A.tag = captured ? 0xFFFFFFFFu : P.nonce;
     // An ordinary launch: one workgroup fills a compute unit (LDS), the grid is one workgroup per compute unit, so every
     // workgroup becomes resident as soon as the kernels before it on the stream have drained.  (A cooperative launch
     // guarantees the same, but goes through the device's cooperative queue, which measured 19 us per step between
