@@ -180,7 +180,7 @@ rt_status rt_decode_step_static(const rt_config *cfg, const rt_layer_weights *w,
  * units and up to sixteen sequences: four layers at a time (two, one for more than four, eight
  * sequences) with their weights on chip, one cooperative launch per step of a chunk whose length the call chooses (64 to 256
  * positions; `chunk` is checked and not used), on rt_config.stream alone.  Everything else, RT_FLAG_ENGINE_STEPWISE, and stacks so deep
- * that the layers one after the other take longer (where their passes times N exceed 3.1 (N + 64 (L - 1)), at d_model 1024 4.4 times), or one layer's first two positions:
+ * that the layers one after the other take longer (more than three, where their passes times N exceed 2.75 (N + 64 (L - 1)), at d_model 1024 4.4 times), or one layer's first two positions:
  * launches per position that carry all layers.  Both forms feed their products bf16 head and remainder of each vector, and the
  * weights as they are.
  * Unless rt_config.reserve_stack_layers reserved them at rt_create, the first call allocates one scratch set per layer

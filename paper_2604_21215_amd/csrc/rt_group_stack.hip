@@ -124,17 +124,19 @@ void group_stack_destroy(GroupStackState &T)
 bool group_stack_supported(const GroupStackState &T, const GroupState &P, const LayerDims &D, int L)
 {
     // ceil(L / slots) N positions here against N + 64 (L - 1) steps of the launches, which carry all layers: a position costs 9 to
-    // 12.5 us (d = 256 to 1024), a step 28 us and more, with d = 1024 from 50 us where the ratio of the two counts is large (twelve
-    // layers, or nine sequences and more).  Measured, launches / here, by that ratio (B = 1 .. 16, L = 1 .. 24, N = 128 .. 4096):
-    //   d < 1024: up to 2.9 1.22 - 3.2 times, 3.28 1.08 - 1.32, 3.4 - 3.7 0.93 - 1.24, 3.9 - 5.6 0.76 - 1.03
-    //   d = 1024: up to 3.5 1.21 - 4.0, 4.4 - 5.2 0.99 - 1.16
+    // 12.5 us (d = 256 to 1024), a step 25 us and more (34 with up to three layers), with d = 1024 from 50 us where the ratio of the
+    // two counts is large (twelve layers, or nine sequences and more).  Measured, launches / here, by that ratio (134 shapes, B = 1 .. 16,
+    // L = 1 .. 24, N = 128 .. 4096):
+    //   d < 1024: up to 2.5 1.13 - 3.1 times, 2.6 - 2.8 1.00 - 1.73, 2.8 - 3.1 0.89 - 1.40, 3.3 - 3.7 0.93 - 1.29, 3.9 - 5.6 0.76 - 1.03;
+    //             three layers at every ratio (up to 2.8) 1.26 - 2.1
+    //   d = 1024: up to 3.6 1.21 - 4.0, 4.4 - 5.2 0.99 - 1.30
     // (0.76: d = 768, B = 5, N = 4096, 12 layers, 208.6 / 275.3 ms; 4.0: one layer, B = 16, N = 2048, 101.9 / 25.4 ms.)
     if (!T.slab || !P.available || D.B > kGroups * kGroupRows || D.N >= (1 << 20) - 2) return false;
     // one layer and one or two positions: 58 - 104 us as launches, 68 - 120 here at N = 1; B = 1, N = 2, d = 1024 129 / 131, but B = 16 187 / 148
     if (L == 1 && D.N < (D.B <= kGroupRows ? 3 : 2)) return false;
     const int slots = kGroups / splits_for(D.B, L);
     const long long here = (long long)((L + slots - 1) / slots) * D.N, steps = D.N + 64LL * (L - 1);
-    return 10 * here <= (D.d == 1024 ? 44 : 31) * steps;
+    return L <= 3 || 100 * here <= (D.d == 1024 ? 440 : 275) * steps;
 }
 
 rt_status group_stack_prefill(GroupStackState &T, GroupState &P, const LayerDims &D, const WaveLayer *layers, int L, bool poison,
